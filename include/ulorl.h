@@ -124,9 +124,9 @@ typedef struct ulorl_launch {
                              others of its row before it leaves its part to the repair pass
                              (ULORL_STATUS_SYNC); 0: the default 2^24; a tiny value lets a test
                              exercise that pass                                                  */
-    int32_t gemm_tile;    /* lm_head variant: 0 = 256 x 256 x 64 block tile, eight waves, tiles
-                             copied global -> LDS directly (default); 1 = 128 x 128 x 64, four
-                             waves, for products with fewer than a few hundred large tiles      */
+    int32_t gemm_tile;    /* lm_head variant: 0 = 256 x 256 x 64 block tile, eight waves (default);
+                             1 = 128 x 128 x 64, four waves, for products with fewer than a few
+                             hundred large tiles                                                 */
     int32_t gemm_group_m; /* lm_head variant: block tiles along M that an XCD walks before it moves
                              along N (its L2 then re-serves their operand rows); 0 = default 4;
                              1..64                                                               */
@@ -313,10 +313,10 @@ int32_t ulorl_token_loss_fwd_bwd_static(
  * the stats-only pass selected by advantages == NULL (only lse, logp and entropy are written;
  * the workspace is still needed, sized with any R >= 1).
  *
- * The workspace (ulorl_lmhead_workspace_bytes, 256-byte aligned) holds W^T, hidden^T, two pairs of
- * dlogits chunk buffers (each chunk in both orientations; one chunk's gradient products read theirs
- * while the next chunk's are written: 4 x N x vocab_chunk x 2 bytes), an fp32 accumulator for
- * dHidden, the gathered live rows of hidden with their index maps and the token-loss workspace;
+ * The workspace (ulorl_lmhead_workspace_bytes, 256-byte aligned) holds two dlogits chunk buffers (one
+ * chunk's gradient products read theirs while the next chunk's are written: 2 x N x vocab_chunk x 2
+ * bytes), an fp32 accumulator for dHidden, the gathered live rows of hidden with their index maps, the
+ * token-loss workspace, and a zero-padded copy of W when Hd or V is no multiple of 64;
  * nothing in it needs to survive between the forward and the backward call.
  */
 size_t ulorl_lmhead_workspace_bytes(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk);

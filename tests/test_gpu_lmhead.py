@@ -57,6 +57,19 @@ def test_every_compiled_tile_shape(tile, group_m):
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS, tau=0.05), chunk=512, launch=launch)
 
 
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("n,V,hidden", [(256, 512, 64), (257, 520, 128), (63, 256, 192), (129, 264, 256), (1, 8, 8), (320, 1096, 72)])
+def test_tile_edges_of_every_product(tile, n, V, hidden):
+    """One to four K tiles (the peeled ends of the main loop), tiles one row or one vector past an
+    edge, and shapes whose weight is padded (hidden or vocabulary no multiple of 64); the tolerances
+    are those of every lm_head case."""
+    launch = ulorl.Launch(gemm_tile=tile)
+    w = ui.shrink(ui.config(5), [n], V=V, hidden=hidden, seg_len=64, name="lmhead_edges")
+    for dense in (False, True):
+        launch.dense_rows = dense
+        run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=320, launch=launch)
+
+
 def test_lmhead_small_ragged_chunks():
     w = ui.shrink(ui.config(5), [120, 83], V=2056, hidden=136, seg_len=32, name="lmhead_small")
     d = ui.generate(w, DEV)
