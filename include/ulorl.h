@@ -124,9 +124,9 @@ typedef struct ulorl_launch {
                              others of its row before it leaves its part to the repair pass
                              (ULORL_STATUS_SYNC); 0: the default 2^24; a tiny value lets a test
                              exercise that pass                                                  */
-    int32_t gemm_tile;    /* lm_head variant: 0 = 256 x 256 x 64 block tile, eight waves (default);
-                             1 = 128 x 128 x 64, four waves, for products with fewer than a few
-                             hundred large tiles                                                 */
+    int32_t gemm_tile;    /* lm_head variant: 0 = chosen by the shape (default): 256 x 256 x 64 block
+                             tiles, eight waves, or 128 x 128 x 64, four waves, for few rows or short
+                             rows of hidden; 1 = the small ones always.  ulorl_gemm_tn_bf16: 0 = large */
     int32_t gemm_group_m; /* lm_head variant: block tiles along M that an XCD walks before it moves
                              along N (its L2 then re-serves their operand rows); 0 = default 4;
                              1..64                                                               */
@@ -306,7 +306,8 @@ int32_t ulorl_token_loss_fwd_bwd_static(
  *   N             at most 2^22 - 256 token rows per call (N is a leading dimension of GEMM
  *                 operands in the backward pass; larger batches are split by the caller)
  *   vocab_chunk   multiple of 64, at most 2^22 - 256; the backward pass materialises dlogits one chunk of this many
- *                 vocabulary columns at a time ([N, vocab_chunk] bf16, twice) in the workspace
+ *                 vocabulary columns at a time ([N, vocab_chunk] bf16, twice) in the workspace, or
+ *                 of more where 256 MB hold more
  * Logits are formed tile by tile with bf16 MFMA and fp32 accumulation and consumed in registers.
  * Everything else (token ids, cu_seqlens, old_logp, advantages, parameters, per-token and
  * per-response outputs, counters, status bits) is exactly as in ulorl_token_loss_fwd, including
@@ -315,8 +316,9 @@ int32_t ulorl_token_loss_fwd_bwd_static(
  *
  * The workspace (ulorl_lmhead_workspace_bytes, 256-byte aligned) holds two dlogits chunk buffers (one
  * chunk's gradient products read theirs while the next chunk's are written: 2 x N x vocab_chunk x 2
- * bytes), an fp32 accumulator for dHidden, the gathered live rows of hidden with their index maps, the
- * token-loss workspace, and a zero-padded copy of W when Hd or V is no multiple of 64;
+ * bytes, or 2 x 64 to 256 MB where that is more), an fp32 accumulator for dHidden (up to eight where
+ * there are few rows), the gathered live rows of hidden with their index maps, the token-loss
+ * workspace, and a zero-padded copy of W when Hd or V is no multiple of 64;
  * nothing in it needs to survive between the forward and the backward call.
  */
 size_t ulorl_lmhead_workspace_bytes(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk);

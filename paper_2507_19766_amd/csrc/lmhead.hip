@@ -124,9 +124,10 @@ void gemm_tn_kernel(const GemmArgs g, int group_m)
     store_tile_f32<false>(T, g.C, g.ldc, g.b.count, g.a.count, m0, n0, g.wide != 0);
 }
 
-// d_hidden[t, :] = bf16(acc[pos[t], :]) (pos == NULL: acc[t, :]); rows without a live position are zero.
-// One thread converts 8 elements (Hd is a multiple of 8; both buffers 16-byte aligned).
-__global__ void dhidden_finish_kernel(const float* __restrict__ acc, const int* __restrict__ pos, int64_t N, int Hd,
+// d_hidden[t, :] = bf16(sum over slabs of acc[slab][pos[t], :]) (pos == NULL: row t itself); rows without a
+// live position are zero.  One thread converts 8 elements (Hd is a multiple of 8; both buffers
+// 16-byte aligned).
+__global__ void dhidden_finish_kernel(const float* __restrict__ acc, int slabs, const int* __restrict__ pos, int64_t N, int Hd,
                                       bf16_t* __restrict__ dst)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -137,12 +138,14 @@ __global__ void dhidden_finish_kernel(const float* __restrict__ acc, const int* 
     const int64_t j = pos != nullptr ? (int64_t)pos[t] : t;
     u32x4 out = {0u, 0u, 0u, 0u};
     if (j >= 0) {
-        const u32x4 lo = *reinterpret_cast<const u32x4*>(acc + j * Hd + c);
-        const u32x4 hi = *reinterpret_cast<const u32x4*>(acc + j * Hd + c + 4);
-        out[0] = pack_bf16x2(__builtin_bit_cast(float, (uint32_t)lo[0]), __builtin_bit_cast(float, (uint32_t)lo[1]));
-        out[1] = pack_bf16x2(__builtin_bit_cast(float, (uint32_t)lo[2]), __builtin_bit_cast(float, (uint32_t)lo[3]));
-        out[2] = pack_bf16x2(__builtin_bit_cast(float, (uint32_t)hi[0]), __builtin_bit_cast(float, (uint32_t)hi[1]));
-        out[3] = pack_bf16x2(__builtin_bit_cast(float, (uint32_t)hi[2]), __builtin_bit_cast(float, (uint32_t)hi[3]));
+        const float* q = acc + j * Hd + c;
+        f32x4 lo = *reinterpret_cast<const f32x4*>(q), hi = *reinterpret_cast<const f32x4*>(q + 4);
+        for (int s = 1; s < slabs; ++s) {
+            q += N * Hd;
+            lo += *reinterpret_cast<const f32x4*>(q);
+            hi += *reinterpret_cast<const f32x4*>(q + 4);
+        }
+        out = u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
     }
     *reinterpret_cast<u32x4*>(dst + t * Hd + c) = out;
 }
@@ -229,6 +232,35 @@ __global__ __launch_bounds__(kLiveBlock) void live_fill_kernel(const float* __re
         pos[t] = live ? p : -1;
         if (live) row_map[p] = (int)t;
     }
+}
+
+// The three kernels above in one launch, for up to kLiveRecountRows rows: every workgroup counts the rows
+// before its own itself (at most kLiveRecountRows / kLiveBlock independent loads per thread, from cache),
+// which is cheaper than two more launches of 4.5 us each: 32 x 1024 rows are recounted in about 7 us.
+constexpr int64_t kLiveRecountRows = 32768;
+__global__ __launch_bounds__(kLiveBlock) void live_rows_kernel(const float* __restrict__ gcoef, const float* __restrict__ lse,
+                                                               const int32_t* __restrict__ token_ids, float grad_out,
+                                                               int64_t N, int32_t V, int* __restrict__ pos,
+                                                               int* __restrict__ row_map, int* __restrict__ n_live)
+{
+    __shared__ int wave_tot[kLiveBlock / 64];
+    int before = 0;
+#pragma unroll 4
+    for (int b = 0; b < (int)blockIdx.x; ++b) {
+        const int64_t t = (int64_t)b * kLiveBlock + threadIdx.x;
+        before += row_has_gradient(gcoef[t] * grad_out, lse[t], token_ids[t], V) ? 1 : 0;
+    }
+    int base, total;
+    live_block_scan(before, wave_tot, &base);
+    const int64_t t = (int64_t)blockIdx.x * kLiveBlock + threadIdx.x;
+    const int live = t < N && row_has_gradient(gcoef[t] * grad_out, lse[t], token_ids[t], V);
+    const int incl = live_block_scan(live, wave_tot, &total);
+    if (t < N) {
+        const int p = base + incl - 1;
+        pos[t] = live ? p : -1;
+        if (live) row_map[p] = (int)t;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *n_live = base + total;
 }
 
 // dst[j, c] = src[row_map[j], c] (row_map == NULL: src[j, c]) for j < rows (*n_rows if given) and c < cols;
@@ -499,12 +531,14 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
 }
 
 // One launch of the backward pass over the vocabulary chunks: the two products of the PREVIOUS
-// chunk (d_W, then dHidden, from that chunk's dz) and the dz tiles of the NEXT chunk (into the other
+// chunk (d_W and dHidden, from that chunk's dz) and the dz tiles of the NEXT chunk (into the other
 // buffer) share the grid, longest tiles first.  Tile counts of the separate products rarely fill the
-// 256 compute units a whole number of times (dHidden has only rows/256 x Hd/256 tiles); as parts of
-// one launch the short dz tiles fill what the products leave idle.  Each part starts at a multiple of
-// 8 workgroups, so a workgroup's XCD is its part-local id modulo 8.  n_live (device, may be NULL):
-// the number of live rows, when rows were gathered.
+// 256 compute units a whole number of times; as parts of one launch the short dz tiles fill what the
+// products leave idle.  dHidden has only rows/256 x Hd/256 tiles, each over the whole chunk: where that
+// is too few, its contraction is cut into dh_splits parts that accumulate into slabs of their own (the
+// finish kernel adds them in order).  Each part starts at a multiple of 8 workgroups, so a workgroup's
+// XCD is its part-local id modulo 8.  n_live (device, may be NULL): the number of live rows, when rows
+// were gathered.
 struct BwdStepArgs {
     // d_W columns of the previous chunk: dW[k, vp + v] = sum_t dZ[t, v] H[t, k]
     Operand dw_z, dw_h;              // K_COLS both
@@ -512,8 +546,9 @@ struct BwdStepArgs {
     int64_t ld_w;
     // dHidden accumulator: acc[t, k] (+)= sum_v W[k, vp + v] dZ[t, v]
     Operand dh_w, dh_z;              // K_ROWS both; dh_z.count is replaced by the live count
-    int dh_K, dh_accumulate;
-    float* dh_acc;
+    int dh_K, dh_accumulate, dh_splits;
+    float* dh_acc;                   // [dh_splits][N][Hd]
+    int dh_first;                    // dHidden's tiles are the longer ones
     DzArgs dz;
     int have_products, have_dz;
     int N;                           // token rows (upper bound of the live count)
@@ -536,9 +571,32 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
     int tm, tn;
     if (a.have_products) {
         const int nk = (a.dw_h.count + B - 1) / B, nv = (a.dw_z.count + B - 1) / B;
+        const int nt = (rows + B - 1) / B, nh = (a.dh_w.count + B - 1) / B;
         const int g_dw = (int)tile_grid(nk, nv);
-        if (bid < g_dw) {
-            if (!tile_coords(bid, nk, nv, a.group_m, tn, tm)) return;
+        const int g_dh1 = rows > 0 ? (int)tile_grid(nt, nh) : 0;
+        const int g_dh = g_dh1 * a.dh_splits;
+        if (bid < g_dw + g_dh) {
+            const int dh_bid = a.dh_first ? bid : bid - g_dw;
+            if (dh_bid >= 0 && dh_bid < g_dh) {
+                if (!tile_coords(dh_bid % g_dh1, nt, nh, a.group_m, tn, tm)) return;
+                const int split = dh_bid / g_dh1;
+                const int per = (a.dh_K / kTileK + a.dh_splits - 1) / a.dh_splits * kTileK;
+                const int k0 = split * per, K = min(per, a.dh_K - k0);
+                if (K <= 0 && a.dh_accumulate) return;
+                TileDh T;
+                T.init(lds_raw);
+                Operand w = a.dh_w, z = a.dh_z;
+                w.p += k0;
+                z.p += k0;
+                z.count = rows;
+                if (K > 0) T.run(w, tm * B, z, tn * B, K);
+                else T.clear();
+                float* acc = a.dh_acc + (int64_t)split * a.N * a.dh_w.count;
+                if (a.dh_accumulate) store_tile_f32<true>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
+                else store_tile_f32<false>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
+                return;
+            }
+            if (!tile_coords(a.dh_first ? bid - g_dh : bid, nk, nv, a.group_m, tn, tm)) return;
             TileDw T;
             T.init(lds_raw);
             if (rows > 0) T.run(a.dw_z, tm * B, a.dw_h, tn * B, (rows + 63) / 64 * 64);
@@ -555,21 +613,7 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
                                      a.dw_z.count - tm * B);
             return;
         }
-        bid -= g_dw;
-        const int nt = (rows + B - 1) / B, nh = (a.dh_w.count + B - 1) / B;
-        const int g_dh = rows > 0 ? (int)tile_grid(nt, nh) : 0;
-        if (bid < g_dh) {
-            if (!tile_coords(bid, nt, nh, a.group_m, tn, tm)) return;
-            TileDh T;
-            T.init(lds_raw);
-            Operand z = a.dh_z;
-            z.count = rows;
-            T.run(a.dh_w, tm * B, z, tn * B, a.dh_K);
-            if (a.dh_accumulate) store_tile_f32<true>(T, a.dh_acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
-            else store_tile_f32<false>(T, a.dh_acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
-            return;
-        }
-        bid -= g_dh;
+        bid -= g_dw + g_dh;
     }
     if (a.have_dz && rows > 0) lmhead_dz_block<TileDz>(bid, a.dz, rows, a.group_m, lds_raw);
 }
@@ -580,47 +624,97 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t round_up64(int64_t x) { return (x + 63) / 64 * 64; }
 
-// ulorl_launch.gemm_tile: 0 = TileLarge, 1 = TileSmall (gemm_tile.hpp)
+// ulorl_launch.gemm_tile: 0 = by shape, 1 = TileSmall (gemm_tile.hpp).  Small tiles where large ones would be
+// mostly padding, too few, or too short a contraction to pay for their start and their store.  Measured,
+// large / small, us.  Forward statistics, 151936 columns: 64 x 512 112 / 106, 200 x 1024 165 / 161,
+// 512 x 512 115 / 124, 512 x 2048 301 / 406; 4096 x 256 x 5640 31 / 27.  Backward, 151936 columns:
+// 64 x 2048 584 / 453, 200 x 1024 529 / 390, 512 x 512 519 / 368, 777 x 512 533 / 579, 512 x 1024
+// 633 / 626, 512 x 2048 943 / 1213; 8192 x 256 x 5640 231 / 168.
+inline int forward_tile(const LaunchOpts& o, int64_t N, int64_t Hd) { return o.gemm_tile == 1 || N <= 256 || Hd <= 256 ? 1 : 0; }
+inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd) { return o.gemm_tile == 1 || N * Hd <= 3 * (1 << 17) || Hd <= 256 ? 1 : 0; }
+
 inline int tile_edge(int tile) { return tile == 1 ? TileSmall<K_ROWS, K_ROWS>::BM : TileLarge<K_ROWS, K_ROWS>::BM; }
 
 struct LmheadLayout {
     size_t wp, dz[2], dhacc, partial, token_ws, hc, pos, row_map, block_count, n_live, total;
     int64_t hd64, v64;   // padded hidden size and vocabulary
     bool pad_w;          // W is copied with padded rows and columns (Hd or V no multiple of 64)
-    int64_t ldc;         // padded chunk width (leading dimension of dZ)
+    int64_t chunk;       // vocabulary columns per backward launch, a multiple of 64 (leading dimension of dZ)
+    int dh_splits;
     int splits;
     int v_per_split;
 };
 
-LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t chunk, int tile)
+// Vocabulary slices of the forward statistics: a workgroup takes one tile of tokens and one slice.  Rounds
+// of the chip's tile slots times tiles per slice (plus about a third of a tile per workgroup for its
+// start and its merge) is what the launch costs; at least 8 slices, so that the workgroups of an XCD
+// (tile_coords) form a block of 4 token tiles by 8 slices and share both operands in its L2.
+int stats_splits(int64_t N, int64_t V, int edge, int slots)
+{
+    const int64_t ttiles = (N + edge - 1) / edge, vtiles = (V + edge - 1) / edge;
+    const int lo = (int)(vtiles < 8 ? vtiles : 8), hi = (int)(vtiles < 128 ? vtiles : 128);
+    int best = lo;
+    double best_cost = 0.0;
+    for (int s = lo; s <= hi; ++s) {
+        const double rounds = (double)((ttiles * s + slots - 1) / slots);
+        const double cost = rounds * ((double)((vtiles + s - 1) / s) + 0.35);
+        if (s == lo || cost < best_cost - 1e-9) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+constexpr int kComputeUnits = 256;
+
+LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk, int tile)
 {
     const int edge = tile_edge(tile);
     LmheadLayout L;
     L.hd64 = round_up64(Hd);
     L.v64 = round_up64(V);
     L.pad_w = L.hd64 != Hd || L.v64 != V;
-    L.ldc = round_up64(chunk);
     const int64_t n64 = round_up64(N);
-    const int64_t ttiles = (N + edge - 1) / edge;
-    constexpr int kMaxSplits = 16;                          // the partial-statistics buffer holds this many slices
-    int splits = (int)((1024 + ttiles - 1) / ttiles);       // aim at >= 1024 workgroups
+
+    // Columns per backward launch: the caller's vocab_chunk, or what a dz buffer of 64 to 256 MB (as W and
+    // hidden are larger) holds, where that is more: with few rows a chunk of 8192 columns is too little
+    // work for 256 compute units.  777 x 2048 x 151936: 20 steps of 8192 columns 3.3 ms, all columns in one
+    // chunk 1.4 ms.  With 16384 rows and more the width does not matter (8192, 16384, 32768: +-0.5 %).
+    const int64_t weights = (V + N) * Hd;                        // half the bytes of hidden and W
+    int64_t budget = weights < ((int64_t)64 << 20) ? ((int64_t)64 << 20) : weights > ((int64_t)256 << 20) ? ((int64_t)256 << 20) : weights;
+    int64_t chunk = round_up64(vocab_chunk);
+    const int64_t fits = budget / (2 * n64) / 256 * 256;
+    if (chunk < fits) chunk = fits;
+    if (chunk > kMaxLeadingDim - 256) chunk = (kMaxLeadingDim - 256) / 64 * 64;      // at least vocab_chunk: see check_lmhead
+    if (chunk > L.v64) chunk = L.v64;
+    L.chunk = chunk;
+    const int buffers = chunk < V ? 2 : 1;
+
+    // Parts of the dHidden contraction (see BwdStepArgs): enough tiles for every compute unit, at most 8
+    // (a slab is N x Hd fp32), none shorter than 16 K tiles.  The same for every tile shape.
+    const int64_t dh_tiles = ((N + 255) / 256) * ((Hd + 255) / 256);
+    int64_t dh_splits = kComputeUnits / dh_tiles;
+    if (dh_splits > 8) dh_splits = 8;
+    if (dh_splits > chunk / 1024) dh_splits = chunk / 1024;
+    L.dh_splits = dh_splits < 1 ? 1 : (int)dh_splits;
+
     const int64_t vtiles = (V + edge - 1) / edge;
-    if (splits > vtiles) splits = (int)vtiles;
-    if (splits > kMaxSplits) splits = kMaxSplits;
-    if (splits < 1) splits = 1;
-    const int64_t tiles_per_split = (vtiles + splits - 1) / splits;
-    L.v_per_split = (int)(tiles_per_split * edge);
-    L.splits = (int)((vtiles + tiles_per_split - 1) / tiles_per_split);
-    // sized for the largest split count any tile shape can ask for, so that the workspace
-    // requirement does not depend on the launch options
-    const size_t max_splits = kMaxSplits;
+    const int s_large = stats_splits(N, V, tile_edge(0), kComputeUnits), s_small = stats_splits(N, V, tile_edge(1), 2 * kComputeUnits);
+    const int64_t per_split = (vtiles + (tile == 1 ? s_small : s_large) - 1) / (tile == 1 ? s_small : s_large);
+    L.v_per_split = (int)(per_split * edge);
+    L.splits = (int)((vtiles + per_split - 1) / per_split);
+    // the workspace does not depend on the launch options: room for either tile shape's slices
+    const size_t max_splits = s_large > s_small ? s_large : s_small;
+
     size_t off = 0;
     L.wp = off;      off = align_up(off + (L.pad_w ? (size_t)L.hd64 * (size_t)L.v64 * 2 : 0), 256);
     // two dz buffers: one chunk's products read theirs while the next chunk's dz is written
-    for (int b = 0; b < 2; ++b) {
-        L.dz[b] = off;  off = align_up(off + (size_t)n64 * L.ldc * 2, 256);
+    for (int b = 0; b < buffers; ++b) {
+        L.dz[b] = off;  off = align_up(off + (size_t)n64 * L.chunk * 2, 256);
     }
-    L.dhacc = off;   off = align_up(off + (size_t)N * Hd * 4, 256);
+    if (buffers == 1) L.dz[1] = L.dz[0];
+    L.dhacc = off;   off = align_up(off + (size_t)L.dh_splits * N * Hd * 4, 256);
     L.partial = off; off = align_up(off + max_splits * (size_t)N * sizeof(StatQuad), 256);
     L.token_ws = off; off = align_up(off + workspace_layout(N, 0, R).total, 256);
     // backward over the live rows only: gathered hidden rows, row <-> position maps, scan scratch
@@ -707,7 +801,7 @@ bool launch_bwd_step(const BwdStepArgs& a, hipStream_t st)
     unsigned grid = 0;
     if (a.have_products) {
         grid += tile_grid((a.dw_h.count + B - 1) / B, (a.dw_z.count + B - 1) / B);
-        grid += tile_grid((a.N + B - 1) / B, (a.dh_w.count + B - 1) / B);
+        grid += tile_grid((a.N + B - 1) / B, (a.dh_w.count + B - 1) / B) * (unsigned)a.dh_splits;
     }
     if (a.have_dz) grid += tile_grid((a.dz.cw + B - 1) / B, (a.N + B - 1) / B);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Tile::NT), lds, st, a);
@@ -785,7 +879,8 @@ int32_t ulorl_lmhead_token_loss_fwd(const void* hidden, const void* W, int64_t N
     } else if (R <= 0) {
         R = 1;      // only sizes the workspace layout
     }
-    const LmheadLayout L = lmhead_layout(N, Hd, V, R, vocab_chunk, opts.gemm_tile);
+    const int tile = forward_tile(opts, N, Hd);
+    const LmheadLayout L = lmhead_layout(N, Hd, V, R, vocab_chunk, tile);
     if (!workspace || ((uintptr_t)workspace & 255u) != 0 || workspace_bytes < L.total) return ULORL_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
@@ -798,7 +893,7 @@ int32_t ulorl_lmhead_token_loss_fwd(const void* hidden, const void* W, int64_t N
         launch_copy_rows_padded((const bf16_t*)hidden, Hd, N, Hd, hc, L.hd64, st);
         Hop = Operand{hc, L.hd64, (int)N};
     }
-    const bool ok = opts.gemm_tile == 1
+    const bool ok = tile == 1
                         ? launch_stats<TileSmall>(Wop, Hop, (int)L.hd64, token_ids, L, partial, opts.gemm_group_m, st)
                         : launch_stats<TileLarge>(Wop, Hop, (int)L.hd64, token_ids, L, partial, opts.gemm_group_m, st);
     if (!ok) return ULORL_ERR_HIP;
@@ -827,7 +922,8 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
     if (rc != ULORL_OK) return rc;
     if (!token_ids || !lse || !gcoef || !d_hidden || !d_W) return ULORL_ERR_NULL;
     if (((uintptr_t)d_hidden & 15u) != 0 || ((uintptr_t)d_W & 15u) != 0) return ULORL_ERR_ALIGN;
-    const LmheadLayout L = lmhead_layout(N, Hd, V, 1, vocab_chunk, opts.gemm_tile);
+    const int tile = backward_tile(opts, N, Hd);
+    const LmheadLayout L = lmhead_layout(N, Hd, V, 1, vocab_chunk, tile);
     if (!workspace || ((uintptr_t)workspace & 255u) != 0 || workspace_bytes < L.total) return ULORL_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
@@ -848,11 +944,16 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
         int* cntw = (int*)(ws + L.block_count);
         int* nlw = (int*)(ws + L.n_live);
         const int nblk = (int)((N + kLiveBlock - 1) / kLiveBlock);
-        hipLaunchKernelGGL(live_count_kernel, dim3((unsigned)nblk), dim3(kLiveBlock), 0, st, gcoef, lse, token_ids, grad_out,
-                           N, (int32_t)V, cntw);
-        hipLaunchKernelGGL(live_scan_kernel, dim3(1), dim3(kLiveBlock), 0, st, cntw, nblk, nlw);
-        hipLaunchKernelGGL(live_fill_kernel, dim3((unsigned)nblk), dim3(kLiveBlock), 0, st, gcoef, lse, token_ids, grad_out, N,
-                           (int32_t)V, (const int*)cntw, posw, mapw);
+        if (N <= kLiveRecountRows) {
+            hipLaunchKernelGGL(live_rows_kernel, dim3((unsigned)nblk), dim3(kLiveBlock), 0, st, gcoef, lse, token_ids, grad_out, N,
+                               (int32_t)V, posw, mapw, nlw);
+        } else {
+            hipLaunchKernelGGL(live_count_kernel, dim3((unsigned)nblk), dim3(kLiveBlock), 0, st, gcoef, lse, token_ids, grad_out,
+                               N, (int32_t)V, cntw);
+            hipLaunchKernelGGL(live_scan_kernel, dim3(1), dim3(kLiveBlock), 0, st, cntw, nblk, nlw);
+            hipLaunchKernelGGL(live_fill_kernel, dim3((unsigned)nblk), dim3(kLiveBlock), 0, st, gcoef, lse, token_ids, grad_out, N,
+                               (int32_t)V, (const int*)cntw, posw, mapw);
+        }
         launch_copy_rows_padded(H, Hd, N, Hd, hc, L.hd64, st, mapw, nlw);
         row_map = mapw; pos = posw; n_live = nlw;
     } else if (L.hd64 != Hd || N % 64 != 0) {
@@ -863,43 +964,45 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
     if (hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
 
     // Chunk pipeline: launch c holds the dz tiles of chunk c and the two products of chunk c - 1.
-    const int64_t n_chunks = (V + vocab_chunk - 1) / vocab_chunk;
+    const int64_t n_chunks = (V + L.chunk - 1) / L.chunk;
+    auto width = [&](int64_t c) { return (int)(V - c * L.chunk < L.chunk ? V - c * L.chunk : L.chunk); };
     for (int64_t c = 0; c <= n_chunks; ++c) {
         BwdStepArgs a;
         memset(&a, 0, sizeof(a));
         a.N = (int)N;
         a.group_m = opts.gemm_group_m;
         a.n_live = n_live;
+        a.dh_splits = 1;
         if (c >= 1) {
-            const int64_t vp = (c - 1) * vocab_chunk;
-            const int cwp = (int)((V - vp < vocab_chunk) ? (V - vp) : vocab_chunk);
+            const int64_t vp = (c - 1) * L.chunk;
+            const int cwp = width(c - 1);
             const bf16_t* dZ = (const bf16_t*)(ws + L.dz[(c - 1) & 1]);
             a.have_products = 1;
-            a.dw_z = Operand{dZ, L.ldc, cwp};
+            a.dw_z = Operand{dZ, L.chunk, cwp};
             a.dw_h = Operand{Hop.p, L.hd64, (int)Hd};
             a.d_W = (bf16_t*)d_W + vp;
             a.ld_w = V;
             a.dh_w = Operand{Wop.p + vp, Wop.ld, (int)Hd};
-            a.dh_z = Operand{dZ, L.ldc, (int)N};
+            a.dh_z = Operand{dZ, L.chunk, (int)N};
             a.dh_K = (int)round_up64(cwp);
             a.dh_accumulate = c > 1;
+            a.dh_splits = L.dh_splits;
             a.dh_acc = dHacc;
+            a.dh_first = a.dh_K / L.dh_splits > N;      // contraction lengths of the two products' tiles
         }
         if (c < n_chunks) {
-            const int64_t vc0 = c * vocab_chunk;
-            const int cw = (int)((V - vc0 < vocab_chunk) ? (V - vc0) : vocab_chunk);
             a.have_dz = 1;
-            a.dz.W = Wop; a.dz.H = Hop; a.dz.K = (int)L.hd64; a.dz.vc0 = (int)vc0;
-            a.dz.cw = (int)round_up64(cw);               // dz of the padding columns is written as zero
+            a.dz.W = Wop; a.dz.H = Hop; a.dz.K = (int)L.hd64; a.dz.vc0 = (int)(c * L.chunk);
+            a.dz.cw = (int)round_up64(width(c));         // dz of the padding columns is written as zero
             a.dz.token_ids = token_ids; a.dz.lse = lse; a.dz.gcoef = gcoef; a.dz.grad_out = grad_out;
-            a.dz.dZ = (bf16_t*)(ws + L.dz[c & 1]); a.dz.ld = L.ldc;
+            a.dz.dZ = (bf16_t*)(ws + L.dz[c & 1]); a.dz.ld = L.chunk;
             a.dz.row_map = row_map;
         }
-        const bool ok = opts.gemm_tile == 1 ? launch_bwd_step<TileSmall>(a, st) : launch_bwd_step<TileLarge>(a, st);
+        const bool ok = tile == 1 ? launch_bwd_step<TileSmall>(a, st) : launch_bwd_step<TileLarge>(a, st);
         if (!ok || hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
     }
     const int64_t nh = N * Hd;
-    hipLaunchKernelGGL(dhidden_finish_kernel, dim3((unsigned)((nh / 8 + 255) / 256)), dim3(256), 0, st, (const float*)dHacc, pos,
+    hipLaunchKernelGGL(dhidden_finish_kernel, dim3((unsigned)((nh / 8 + 255) / 256)), dim3(256), 0, st, (const float*)dHacc, L.dh_splits, pos,
                        N, (int)Hd, (bf16_t*)d_hidden);
     return hipGetLastError() == hipSuccess ? ULORL_OK : ULORL_ERR_HIP;
 }

@@ -70,6 +70,18 @@ def test_tile_edges_of_every_product(tile, n, V, hidden):
         run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=320, launch=launch)
 
 
+@pytest.mark.parametrize("n,V,hidden", [(512, 65536 + 192, 64),     # two chunks, the second shorter than the parts of the dHidden contraction
+                                        (300, 9000, 320),             # one chunk, eight parts
+                                        (2049, 264, 64),              # live rows counted by three workgroups in one launch
+                                        (33000, 64, 64)])             # ... and by the three-launch scan
+def test_backward_partitions(n, V, hidden):
+    """Where the backward pass is cut: vocabulary chunks, parts of the dHidden contraction, and the two
+    ways the live rows are counted (clipped tokens are not live)."""
+    w = ui.shrink(ui.config(5), [n - 1, 1], V=V, hidden=hidden, seg_len=64, name="lmhead_parts")
+    res, tt = run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=64)
+    assert 0 < tt.n_clip_inactive < n
+
+
 def test_lmhead_small_ragged_chunks():
     w = ui.shrink(ui.config(5), [120, 83], V=2056, hidden=136, seg_len=32, name="lmhead_small")
     d = ui.generate(w, DEV)
