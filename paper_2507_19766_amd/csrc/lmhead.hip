@@ -905,8 +905,8 @@ int32_t ulorl_lmhead_token_loss_fwd(const void* hidden, const void* W, int64_t N
     const WorkspaceLayout wl = workspace_layout(N, 0, R);
     const TokenArgs a = make_token_args(N, V, token_ids, cu_seqlens, R, segment_ids, old_logp, advantages, p, logp,
                                         entropy, lse, gcoef, mpt_mask, ratio, segment_out, resp_entropy, resp_gate,
-                                        ws + L.token_ws, wl, seg);
-    launch_token_epilogue(a, wl, loss, counters, st);
+                                        loss, counters, ws + L.token_ws, wl, seg);
+    launch_token_epilogue(a, wl, st);
     return hipGetLastError() == hipSuccess ? ULORL_OK : ULORL_ERR_HIP;
 }
 

@@ -16,19 +16,10 @@ namespace {
 
 constexpr int kBlock = 1024;
 
-__device__ __forceinline__ double shfl_xor_f64(double x, int off)
-{
-    int lo = __double2loint(x), hi = __double2hiint(x);
-    lo = __shfl_xor(lo, off);
-    hi = __shfl_xor(hi, off);
-    return __hiloint2double(hi, lo);
-}
-
-// Fixed-shape reductions over the workgroup: lanes by xor-shuffle, waves through LDS in order.
+// Sum over the workgroup in a fixed order: lanes, then waves in index order.
 __device__ __forceinline__ double block_sum_f64(double x, double* scratch)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += shfl_xor_f64(x, off);
+    x = wave_sum_f64(x);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = x;
     __syncthreads();

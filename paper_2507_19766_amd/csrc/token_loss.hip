@@ -9,10 +9,12 @@
 //                         the same statistics from the pieces of cluster_row_kernel (below), used
 //                         by the forward call whenever it has a workspace: both paths then carry
 //                         the same bits.
-//   response_entropy_kernel, token_terms_kernel, loss_finalize_kernel
+//   response_entropy_kernel, token_terms_kernel
 //                         O(N) epilogue: per-response mean entropy and gate, SAIS/POIS ratio
 //                         (Sec. 3.1.2), clipped term (Eq. 7), MPT mask (Eq. MPTS / I_msk), the
-//                         token-mean loss and d loss / d logp.  Fixed-order fp64 sums.
+//                         token-mean loss and d loss / d logp.  Fixed-order fp64 sums.  The first also
+//                         finishes what a workgroup of cluster_row_kernel left undone because its
+//                         bounded wait expired (normally nothing).
 //   dlogits_chunk_kernel  the backward call: recomputes the softmax from the saved lse and writes
 //                         g_t * (onehot - p) with one 16-byte vector per thread; rows with
 //                         g_t == 0 are write-only.  Safe in place: each vector is read and then
@@ -21,12 +23,8 @@
 //                         piece keeps its piece in registers, the pieces exchange their partial
 //                         (max, sum, weighted sum) through memory and each writes its share of
 //                         the gradient: every logit is read once and written once.
-//   defer_compact_kernel, dlogits_rows_kernel
-//                         the rows the one-call path leaves until the entropy gate is known (the
-//                         members of the MPT set), collected into a list and finished from it.
-//   repair_rows_kernel, repair_pieces_kernel
-//                         finish what a workgroup of cluster_row_kernel left undone because its
-//                         bounded wait expired; they return at once when nothing was left.
+//   dlogits_rows_kernel   the rows the one-call path leaves until the entropy gate is known (the
+//                         members of the MPT set), from the list token_terms_kernel makes of them.
 //   fused_row_kernel      the same call by one workgroup per row, forward and backward back to
 //                         back (rows too long for the cooperative kernel, or on request).
 //
@@ -468,33 +466,9 @@ __global__ __launch_bounds__(256) void dlogits_rows_kernel(const typename Tr::el
                                lse, gcoef, grad_out, dlogits);
 }
 
-// Collects the rows flagged in `defer` into a list (order arbitrary: each row is processed exactly
-// once whatever its position).  *count must be zero before the launch.
-__global__ __launch_bounds__(256) void defer_compact_kernel(const uint8_t* __restrict__ defer, int64_t N,
-                                                            uint32_t* __restrict__ rows, uint32_t* __restrict__ count)
-{
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool flagged = t < N && defer[t] != 0;
-    const unsigned long long ballot = __ballot(flagged);
-    if (ballot == 0ull) return;
-    const int lane = threadIdx.x & 63;
-    uint32_t base = 0;
-    if (lane == 0) base = atomicAdd(count, (uint32_t)__popcll(ballot));
-    base = __shfl(base, 0);
-    if (flagged) rows[base + __popcll(ballot & ((1ull << lane) - 1ull))] = (uint32_t)t;
-}
-
 // ---------------------------------------------------------------------------------------------
 // O(N) epilogue of the forward call
 // ---------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ double shfl_xor_f64(double x, int off)
-{
-    int lo = __double2loint(x), hi = __double2hiint(x);
-    lo = __shfl_xor(lo, off);
-    hi = __shfl_xor(hi, off);
-    return __hiloint2double(hi, lo);
-}
 
 // Everything about one token that does not depend on the entropy gate (Sec. 3.1.2 ratio,
 // Eq. 7 clipped term, Eq. MPTS membership, coefficient assuming the token is not masked).
@@ -528,49 +502,18 @@ __device__ __forceinline__ TokenEval token_eval(float lpf, float advf, float old
 
 __device__ __forceinline__ bool not_finite(float x) { return !(fabsf(x) <= 3.0e38f); }
 
-// Fixed-shape tree: lanes by xor-shuffle, then waves through LDS in index order.
-template <int NT>
+// Sum over the workgroup in a fixed order: lanes, then waves in index order.
 __device__ __forceinline__ double block_sum_f64(double x, double* scratch)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += shfl_xor_f64(x, off);
+    x = wave_sum_f64(x);
     const int tid = threadIdx.x;
     __syncthreads();
     if ((tid & 63) == 0) scratch[tid >> 6] = x;
     __syncthreads();
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) s += scratch[w];
+    for (int w = 0; w < kTokWaves; ++w) s += scratch[w];
     return s;
-}
-
-template <int NT>
-__device__ __forceinline__ long long block_sum_i64(long long x, long long* scratch)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        int lo = (int)(x & 0xffffffffll), hi = (int)(x >> 32);
-        lo = __shfl_xor(lo, off);
-        hi = __shfl_xor(hi, off);
-        x += ((long long)hi << 32) | (unsigned int)lo;
-    }
-    const int tid = threadIdx.x;
-    __syncthreads();
-    if ((tid & 63) == 0) scratch[tid >> 6] = x;
-    __syncthreads();
-    long long s = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) s += scratch[w];
-    return s;
-}
-
-// Bitwise OR of the status bits over the workgroup (__syncthreads_or is a logical OR).
-__device__ __forceinline__ int block_or_bits(int flags)
-{
-    int r = 0;
-#pragma unroll
-    for (int bit = 1; bit <= 8; bit <<= 1) r |= __syncthreads_or(flags & bit) ? bit : 0;
-    return r;
 }
 
 __device__ __forceinline__ bool response_bounds_ok(const int32_t* cu, int i, int32_t R, int64_t N)
@@ -579,83 +522,144 @@ __device__ __forceinline__ bool response_bounds_ok(const int32_t* cu, int i, int
     return b >= 0 && e >= b && e <= N && (i != 0 || b == 0) && (i != R - 1 || e == N);
 }
 
-// Single workgroup: is cu_seqlens well formed?  (The fused kernel needs the answer before it
-// writes any gradient.)
-__global__ __launch_bounds__(kTokBlock) void cu_check_kernel(const int32_t* cu, int32_t R, int64_t N, uint32_t* badcu,
-                                                             uint32_t* defer_count)
+// Call-wide facts that every workgroup derives identically: whether cu_seqlens is malformed and, for the
+// GLOBAL gate, the token-mean entropy.  All kTokBlock threads call.
+__device__ __forceinline__ int batch_is_bad(const TokenArgs& a, double& hglobal, double* scratch)
 {
-    if (threadIdx.x == 0) *defer_count = 0u;       // the list of deferred rows starts empty
     int bad = 0;
-    for (int i = threadIdx.x; i < R; i += kTokBlock) bad |= response_bounds_ok(cu, i, R, N) ? 0 : 1;
-    bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) *badcu = bad ? 1u : 0u;
-}
-
-// One workgroup per response: sum of the token entropies (Sec. 3.2.2, H-bar_i numerator) and a
-// sanity check of the response's bounds.
-__global__ __launch_bounds__(kTokBlock) void response_entropy_kernel(TokenArgs a)
-{
-    __shared__ double scratch[kTokBlock / 64];
-    const int i = blockIdx.x;
-    const int64_t b = a.cu[i], e = a.cu[i + 1];
-    const bool ok = response_bounds_ok(a.cu, i, a.R, a.N);
-    double s = 0.0;
-    if (ok)
-        for (int64_t t = b + threadIdx.x; t < e; t += kTokBlock) s += (double)a.entropy[t];
-    s = block_sum_f64<kTokBlock>(s, scratch);
-    if (threadIdx.x == 0) {
-        a.hsum[i] = s;
-        a.rflags[i] = ok ? 0u : 1u;
-    }
-}
-
-__global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a)
-{
-    extern __shared__ double seg_table[];       // [K][7], only when the per-segment diagnostics are wanted
-    __shared__ double scratch[kTokBlock / 64];
-    __shared__ long long iscratch[kTokBlock / 64];
-    const int tid = threadIdx.x;
-
-    // call-wide facts every block derives identically: any malformed response, global entropy
-    int badcu = 0;
     double hall = 0.0;
-    for (int i = tid; i < a.R; i += kTokBlock) {
-        badcu |= (int)a.rflags[i];
-        hall += a.hsum[i];
+    for (int i = threadIdx.x; i < a.R; i += kTokBlock) bad |= (int)a.rflags[i];
+    bad = __syncthreads_or(bad);
+    hglobal = 0.0;
+    if (a.gate_mode == ULORL_GATE_GLOBAL) {
+        for (int i = threadIdx.x; i < a.R * a.slices; i += kTokBlock) hall += a.hsum[i];
+        hglobal = block_sum_f64(hall, scratch) / (double)a.N;
     }
-    badcu = __syncthreads_or(badcu);
-    double hglobal = 0.0;
-    if (a.gate_mode == ULORL_GATE_GLOBAL) hglobal = block_sum_f64<kTokBlock>(hall, scratch) / (double)a.N;
+    return bad;
+}
 
-    const int64_t t = (int64_t)blockIdx.x * kTokBlock + tid;
+// Mean entropy and gate of response i (Sec. 3.2.2).
+__device__ __forceinline__ int response_gate(const TokenArgs& a, int i, int64_t L, int badcu, double hglobal, double& hbar)
+{
+    hbar = 0.0;
+    if (!badcu && L > 0) {
+        double h = 0.0;
+        for (int s = 0; s < a.slices; ++s) h += a.hsum[(int64_t)i * a.slices + s];
+        hbar = h / (double)L;
+    }
+    switch (a.gate_mode) {
+    case ULORL_GATE_PER_RESPONSE: return (!badcu && L > 0) && (hbar < a.sigma);
+    case ULORL_GATE_GLOBAL: return hglobal < a.sigma;
+    case ULORL_GATE_ALWAYS: return 1;
+    default: return 0;
+    }
+}
+
+// Largest i in [lo, hi) with cu[i] <= t (lo if there is none).
+__device__ __forceinline__ int response_of(const int32_t* __restrict__ cu, int lo, int hi, int64_t t)
+{
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if ((int64_t)cu[mid] <= t) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// Final sums, per-response outputs and status bits, by the last workgroup of token_terms_kernel.
+template <bool SEG>
+__device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, int badcu, double hglobal, double* seg_scratch)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < a.R; i += kTokBlock) {
+        const int64_t L = badcu ? 0 : (int64_t)a.cu[i + 1] - (int64_t)a.cu[i];
+        double hbar;
+        const int gate = response_gate(a, i, L, badcu, hglobal, hbar);
+        if (a.resp_entropy) a.resp_entropy[i] = (float)hbar;
+        if (a.resp_gate) a.resp_gate[i] = badcu ? 0 : (uint8_t)gate;
+    }
+    // counts below 2^53 are exact as doubles, in any order
+    double s = 0.0, c0 = 0.0, c1 = 0.0, c2 = 0.0;
+    int fl = 0;
+    for (int64_t k = tid; k < nblk; k += kTokBlock) {
+        s += published(a.part_sum + k);
+        const int64_t w0 = published(a.part_cnt + 2 * k), w1 = published(a.part_cnt + 2 * k + 1);
+        c0 += (double)(int32_t)w0;
+        c1 += (double)(int32_t)(w0 >> 32);
+        c2 += (double)(int32_t)w1;
+        fl |= (int32_t)(w1 >> 32);
+    }
+    __shared__ double fin[kTokWaves][4];
+    __shared__ int fin_flags[kTokWaves];
+    s = wave_sum_f64(s);
+    c0 = wave_sum_f64(c0);
+    c1 = wave_sum_f64(c1);
+    c2 = wave_sum_f64(c2);
+    int wf = 0;
+#pragma unroll
+    for (int bit = 1; bit <= 8; bit <<= 1) wf |= __ballot(fl & bit) != 0ull ? bit : 0;
+    if (lane == 0) {
+        fin[wave][0] = s; fin[wave][1] = c0; fin[wave][2] = c1; fin[wave][3] = c2;
+        fin_flags[wave] = wf;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double t[4] = {0.0, 0.0, 0.0, 0.0};
+        int flags = 0;
+#pragma unroll
+        for (int w = 0; w < kTokWaves; ++w) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] += fin[w][q];
+            flags |= fin_flags[w];
+        }
+        if (a.sync_fail != nullptr && *a.sync_fail != 0u) flags |= ULORL_STATUS_SYNC;
+        *a.loss = (float)(-t[0] / a.D);
+        if (a.counters) {
+            a.counters[0] = (int64_t)t[1];
+            a.counters[1] = (int64_t)t[2];
+            a.counters[2] = (int64_t)t[3];
+            a.counters[3] = flags;
+        }
+    }
+    if constexpr (SEG) seg_finalize(a.seg, nblk, seg_scratch);
+}
+
+// Gate, ratio, clipped term, mask, coefficient and segment id of every token; block sums; the rows whose
+// gradient waited for the gate collected into a list; the last workgroup to deliver its sums forms the
+// call's results.  Latency bound (a few dependent loads, two barriers, the ticket): 131072 tokens took
+// 10 + 16 us as two launches with shuffle reductions, now 9.
+// SEG: the per-segment diagnostics are wanted.
+template <bool SEG>
+__global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int64_t nblk)
+{
+    extern __shared__ double seg_table[];       // SEG: [max(K * 7, kSegBlock)]
+    __shared__ double scratch[kTokWaves];
+    __shared__ double wave_s[kTokWaves];
+    __shared__ int wave_c[kTokWaves][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+    double hglobal;
+    const int badcu = batch_is_bad(a, hglobal, scratch);
+
+    const int64_t t0 = (int64_t)blockIdx.x * kTokBlock, t = t0 + tid;
     double contrib = 0.0;
-    long long n_mask = 0, n_clip = 0, n_pos = 0, flags = badcu ? ULORL_STATUS_BAD_CU : 0;
+    bool is_masked = false, is_clipped = false, is_positive = false;
+    int flags = badcu ? ULORL_STATUS_BAD_CU : 0;
     // what the per-segment diagnostics see of this token: exactly the values the call stores
     float g_out = 0.0f, r_out = 0.0f;
     uint8_t m_out = 0;
     int32_t sg_seg = 0;
     float sg_logp = 0.0f, sg_ent = 0.0f, sg_adv = 0.0f, sg_old = 0.0f;
+    bool listed = false;
 
+    // the responses this block's tokens lie in (uniform), then the token's own among them
+    const int first = response_of(a.cu, 0, a.R, t0);
+    const int last = response_of(a.cu, first, a.R, t0 + kTokBlock - 1);
     if (t < a.N) {
-        // response of token t: largest i with cu[i] <= t
-        int lo = 0, hi = a.R;  // invariant: cu[lo] <= t < cu[hi] for well-formed input
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if ((int64_t)a.cu[mid] <= t) lo = mid; else hi = mid;
-        }
-        const int i = lo;
+        const int i = response_of(a.cu, first, last + 1, t);
         const int64_t b = a.cu[i];
         const int64_t L = (int64_t)a.cu[i + 1] - b;
-
-        int gate;
-        double hbar = 0.0;
-        if (!badcu && L > 0) hbar = a.hsum[i] / (double)L;
-        switch (a.gate_mode) {
-        case ULORL_GATE_PER_RESPONSE: gate = (!badcu && L > 0) && (hbar < a.sigma); break;
-        case ULORL_GATE_GLOBAL: gate = hglobal < a.sigma; break;
-        case ULORL_GATE_ALWAYS: gate = 1; break;
-        default: gate = 0; break;
-        }
+        double hbar;
+        const int gate = response_gate(a, i, L, badcu, hglobal, hbar);
         const int32_t seg = a.segment_ids ? a.segment_ids[t]
                                           : (a.seg_len > 0 && !badcu ? (int32_t)((t - b) / a.seg_len) : 0);
         if (a.seg_out) a.seg_out[t] = seg;
@@ -665,115 +669,69 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a)
         const float lf = a.lse[t];
         const int32_t y = a.token_ids[t];
         const bool bad_tok = (y < 0 || y >= a.V);
-        const bool nonfinite = !(fabsf(lpf) <= 3.0e38f) || !(fabsf(hf) <= 3.0e38f) || !(fabsf(lf) <= 3.0e38f);
+        const bool nonfinite = not_finite(lpf) || not_finite(hf) || not_finite(lf);
         if (bad_tok) flags |= ULORL_STATUS_BAD_TOKEN;
         if (!bad_tok && nonfinite) flags |= ULORL_STATUS_NONFINITE;
 
         sg_seg = seg; sg_logp = lpf; sg_ent = hf; sg_adv = a.adv[t];
         sg_old = (a.old_logp != nullptr) ? a.old_logp[t] : 0.0f;
         if (!bad_tok && !nonfinite && !badcu) {
-            const TokenEval ev = token_eval(lpf, a.adv[t], a.is_mode == ULORL_IS_POIS ? 0.0f : a.old_logp[t],
-                                            a.is_mode, a.eps_low, a.eps_high, a.log_tau, a.inv_D);
-            const bool I = gate && ev.mpt;
-            contrib = I ? 0.0 : ev.s;
-            g_out = I ? 0.0f : ev.g;
+            const TokenEval ev = token_eval(lpf, sg_adv, a.is_mode == ULORL_IS_POIS ? 0.0f : sg_old, a.is_mode, a.eps_low,
+                                            a.eps_high, a.log_tau, a.inv_D);
+            is_masked = gate && ev.mpt;
+            contrib = is_masked ? 0.0 : ev.s;
+            g_out = is_masked ? 0.0f : ev.g;
             r_out = (float)ev.r;
-            m_out = I ? 1 : 0;
-            n_mask = I;
-            n_clip = !ev.active;
-            n_pos = ev.positive;
+            m_out = is_masked ? 1 : 0;
+            is_clipped = !ev.active;
+            is_positive = ev.positive;
         }
         a.gcoef[t] = g_out;
         if (a.ratio) a.ratio[t] = r_out;
         if (a.mask) a.mask[t] = m_out;
+        if (a.defer != nullptr) listed = a.defer[t] != 0;
+    }
+    // rows that waited for the gate (order arbitrary: each is finished once whatever its position)
+    const unsigned long long list_ballot = __ballot(listed);
+    if (list_ballot != 0ull) {
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(a.defer_count, (uint32_t)__popcll(list_ballot));
+        base = __shfl(base, 0);
+        if (listed) a.defer_list[base + __popcll(list_ballot & ((1ull << lane) - 1ull))] = (uint32_t)t;
     }
 
-    const double bs = block_sum_f64<kTokBlock>(contrib, scratch);
-    const long long c0 = block_sum_i64<kTokBlock>(n_mask, iscratch);
-    const long long c1 = block_sum_i64<kTokBlock>(n_clip, iscratch);
-    const long long c2 = block_sum_i64<kTokBlock>(n_pos, iscratch);
-    const int fl = block_or_bits((int)flags);
-    if (tid == 0) {
-        a.part_sum[blockIdx.x] = bs;
-        a.part_cnt[4 * (int64_t)blockIdx.x + 0] = c0;
-        a.part_cnt[4 * (int64_t)blockIdx.x + 1] = c1;
-        a.part_cnt[4 * (int64_t)blockIdx.x + 2] = c2;
-        a.part_cnt[4 * (int64_t)blockIdx.x + 3] = fl;
+    contrib = wave_sum_f64(contrib);
+    const int n_mask = __popcll(__ballot(is_masked)), n_clip = __popcll(__ballot(is_clipped)), n_pos = __popcll(__ballot(is_positive));
+    int wf = 0;
+#pragma unroll
+    for (int bit = 1; bit <= 4; bit <<= 1) wf |= __ballot(flags & bit) != 0ull ? bit : 0;
+    if (lane == 0) {
+        wave_s[wave] = contrib;
+        wave_c[wave][0] = n_mask; wave_c[wave][1] = n_clip; wave_c[wave][2] = n_pos; wave_c[wave][3] = wf;
     }
-    if (a.seg.K > 0) {      // uniform over the grid
+    __syncthreads();
+    if (tid == 0) {
+        double bs = 0.0;
+        int c0 = 0, c1 = 0, c2 = 0, fl = 0;
+#pragma unroll
+        for (int w = 0; w < kTokWaves; ++w) {
+            bs += wave_s[w];
+            c0 += wave_c[w][0]; c1 += wave_c[w][1]; c2 += wave_c[w][2]; fl |= wave_c[w][3];
+        }
+        publish(a.part_sum + blockIdx.x, bs);
+        publish(a.part_cnt + 2 * (int64_t)blockIdx.x, (int64_t)c0 | ((int64_t)c1 << 32));
+        publish(a.part_cnt + 2 * (int64_t)blockIdx.x + 1, (int64_t)c2 | ((int64_t)fl << 32));
+    }
+    if constexpr (SEG) {
         int k;
         double v[kSegStats], oor;
         seg_token_values(t < a.N, sg_seg, a.seg.K, r_out, sg_logp, a.old_logp != nullptr, sg_old, sg_ent, m_out, sg_adv,
                          a.eps_low, a.eps_high, k, v, oor);
         const double o = seg_block_partials(k, v, oor, a.seg.K, seg_table,
                                             a.seg.part + (int64_t)blockIdx.x * a.seg.K * kSegStats);
-        if (tid == 0) a.seg.part_oor[blockIdx.x] = o;
+        if (tid == 0) publish(a.seg.part_oor + blockIdx.x, o);
     }
-}
-
-__global__ __launch_bounds__(kTokBlock) void loss_finalize_kernel(TokenArgs a, int64_t nblk, float* loss,
-                                                                 int64_t* counters)
-{
-    __shared__ double scratch[kTokBlock / 64];
-    __shared__ long long iscratch[kTokBlock / 64];
-    const double* part_sum = a.part_sum;
-    const int64_t* part_cnt = a.part_cnt;
-    const double D = a.D;
-
-    // per-response outputs: mean entropy and gate (same call-wide reductions as token_terms_kernel)
-    {
-        int badcu = 0;
-        double hall = 0.0;
-        for (int i = threadIdx.x; i < a.R; i += kTokBlock) {
-            badcu |= (int)a.rflags[i];
-            hall += a.hsum[i];
-        }
-        badcu = __syncthreads_or(badcu);
-        double hglobal = 0.0;
-        if (a.gate_mode == ULORL_GATE_GLOBAL) hglobal = block_sum_f64<kTokBlock>(hall, scratch) / (double)a.N;
-        for (int i = threadIdx.x; i < a.R; i += kTokBlock) {
-            const int64_t L = badcu ? 0 : (int64_t)a.cu[i + 1] - (int64_t)a.cu[i];
-            const double hbar = L > 0 ? a.hsum[i] / (double)L : 0.0;
-            int gate;
-            switch (a.gate_mode) {
-            case ULORL_GATE_PER_RESPONSE: gate = L > 0 && hbar < a.sigma; break;
-            case ULORL_GATE_GLOBAL: gate = hglobal < a.sigma; break;
-            case ULORL_GATE_ALWAYS: gate = 1; break;
-            default: gate = 0; break;
-            }
-            if (a.resp_entropy) a.resp_entropy[i] = (float)hbar;
-            if (a.resp_gate) a.resp_gate[i] = badcu ? 0 : (uint8_t)gate;
-        }
-    }
-    double s = 0.0;
-    long long c0 = 0, c1 = 0, c2 = 0;
-    int fl = 0;
-    for (int64_t k = threadIdx.x; k < nblk; k += kTokBlock) {
-        s += part_sum[k];
-        c0 += part_cnt[4 * k + 0];
-        c1 += part_cnt[4 * k + 1];
-        c2 += part_cnt[4 * k + 2];
-        fl |= (int)part_cnt[4 * k + 3];
-    }
-    s = block_sum_f64<kTokBlock>(s, scratch);
-    c0 = block_sum_i64<kTokBlock>(c0, iscratch);
-    c1 = block_sum_i64<kTokBlock>(c1, iscratch);
-    c2 = block_sum_i64<kTokBlock>(c2, iscratch);
-    fl = block_or_bits(fl);
-    if (threadIdx.x == 0) {
-        if (a.sync_fail != nullptr && *a.sync_fail != 0u) fl |= ULORL_STATUS_SYNC;
-        *loss = (float)(-s / D);
-        if (counters) {
-            counters[0] = c0;
-            counters[1] = c1;
-            counters[2] = c2;
-            counters[3] = fl;
-        }
-    }
-    if (a.seg.K > 0) {
-        __shared__ double seg_scratch[kTokBlock];
-        seg_finalize(a.seg, nblk, seg_scratch);
-    }
+    if (last_workgroup(a.ticket, (uint32_t)nblk)) finalize_loss<SEG>(a, nblk, badcu, hglobal, seg_table);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1162,118 +1120,190 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_row_kernel(const type
     }
 }
 
-__global__ void fill_zero_u64_kernel(unsigned long long* p, int64_t n, uint32_t* flag)
+// First launch of the one-call path: the exchange slots (16 bytes per piece) and the call's flag words start
+// at zero, and workgroup 0 checks cu_seqlens (a malformed batch must not receive gradients).
+struct PrologueArgs {
+    u32x4* slots;
+    int64_t nslots;
+    uint32_t* sync_fail;
+    uint32_t* defer_count;
+    uint32_t* badcu;
+    const int32_t* cu;
+    int32_t R;
+    int64_t N;
+};
+__global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs p)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
-    if (i == 0) *flag = 0u;
-}
-
-// ---------------------------------------------------------------------------------------------
-// repair pass of the row-cooperative kernel
-// ---------------------------------------------------------------------------------------------
-// Both kernels have a small fixed grid and return at once unless a wait expired (sync_fail).  By
-// the time they run every piece of every row has published its statistics (a workgroup publishes
-// before it waits), so a row's statistics can be formed exactly as a workgroup would have formed
-// them; a pending piece's logits are intact because only its own workgroup writes them.
-constexpr int kRepairRowGrid = 256;      // workgroups of 4 waves, one wave per row at a time
-constexpr int kRepairPieceGrid = 2048;   // workgroups of kClusterThreads, one piece at a time
-
-// Rows with a pending piece: their statistics, per-row outputs and deferral flag, as piece 0 would
-// have written them (rewritten with the same bits if it did).
-__global__ __launch_bounds__(256) void repair_rows_kernel(ClusterArgs a, int32_t V)
-{
-    if (*a.sync_fail == 0u) return;
-    const int lane = threadIdx.x & 63;
-    const int C = a.C;
-    const uint32_t badcu = *a.f.badcu;
-    for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < a.N; row += (int64_t)gridDim.x * 4) {
-        float pm = kEmpty, pS = 0.0f, pT = 0.0f;
-        int pending = 0;
-        if (lane < C) {
-            const unsigned long long w0 = a.slots[(row * C + lane) * 2], w1 = a.slots[(row * C + lane) * 2 + 1];
-            pm = __uint_as_float((uint32_t)w0);
-            pS = __uint_as_float((uint32_t)(w0 >> 32));
-            pT = __uint_as_float((uint32_t)w1);
-            pending = (w1 >> 32) == kTagPending;
-        }
-        if (!__any(pending)) continue;
-        merge_pieces_tree(pm, pS, pT);
-        if (lane == 0) {
-            const int32_t y = a.f.token_ids[row];
-            float lse, lp, ent, g;
-            finish_pieces(pm, pS, pT, y >= 0 && y < V, a.f.zy_row[row], lse, lp, ent);
-            const int mode = row_decision(a.f, y, V, lse, lp, ent, a.f.adv[row],
-                                          a.f.is_mode == ULORL_IS_POIS ? 0.0f : a.f.old_logp[row], badcu, g);
-            a.f.lse[row] = lse;
-            a.f.logp[row] = lp;
-            a.f.entropy[row] = ent;
-            a.f.defer[row] = mode == 2 ? 1 : 0;
-        }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < p.nslots) p.slots[i] = u32x4{0u, 0u, 0u, 0u};
+    if (blockIdx.x != 0) return;
+    int bad = 0;
+    for (int r = threadIdx.x; r < p.R; r += 256) bad |= response_bounds_ok(p.cu, r, p.R, p.N) ? 0 : 1;
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) {
+        *p.badcu = bad ? 1u : 0u;
+        *p.sync_fail = 0u;
+        *p.defer_count = 0u;
     }
 }
 
-// Pending pieces of rows that were not deferred as a whole: their share of the gradient, with the
-// arithmetic of the backward call (the same bits the piece's own workgroup would have written).
-// Runs after the O(N) epilogue (gcoef) and after the filtered backward launch of the deferred rows.
+// ---------------------------------------------------------------------------------------------
+// per-response entropy sums, and the repair pass of the row-cooperative kernel
+// ---------------------------------------------------------------------------------------------
+// Repair: rows [r0, r1) by one workgroup, only when a wait expired (sync_fail).  By the time this runs every
+// piece of every row has published its statistics (a workgroup publishes before it waits), so a
+// row's statistics can be formed exactly as a workgroup would have formed them: its per-row outputs and
+// deferral flag are rewritten with the same bits, and the pending pieces' share of the gradient is
+// written with the arithmetic of the piece's own workgroup (a pending piece's logits are intact because
+// only its own workgroup writes them).  Deferred rows are left whole to the launch that follows the gate.
 template <class Tr>
-__global__ __launch_bounds__(kClusterThreads) void repair_pieces_kernel(const typename Tr::elem* logits, int64_t row_stride,
-                                                                        int32_t V, typename Tr::elem* dlogits,
-                                                                        ClusterArgs a, int32_t vpt,
-                                                                        const float* __restrict__ gcoef)
+struct RepairArgs {
+    ClusterArgs c;              // c.sync_fail == NULL: the row-cooperative kernel did not run
+    const typename Tr::elem* logits;
+    int64_t row_stride;
+    typename Tr::elem* dlogits;
+    int32_t vpt;
+};
+
+template <class Tr>
+__device__ void repair_rows(const RepairArgs<Tr>& q, int32_t V, int64_t r0, int64_t r1)
 {
-    if (*a.sync_fail == 0u) return;
+    __shared__ float sh_g, sh_lse;
+    __shared__ int sh_mode;
+    __shared__ unsigned long long sh_pending;
     constexpr int E = Tr::kPerVec;
-    constexpr int NT = kClusterThreads;
+    const ClusterArgs& a = q.c;
+    const int tid = threadIdx.x, NT = blockDim.x;
     const int C = a.C;
     const int nvec = V / E;
-    const int tid = threadIdx.x;
-    for (int64_t q = blockIdx.x; q < a.N * C; q += gridDim.x) {
-        const int64_t row = q / C;
-        const int c = (int)(q - row * C);
-        if ((a.slots[q * 2 + 1] >> 32) != kTagPending || a.f.defer[row] != 0) continue;   // uniform over the workgroup
-        const float g = gcoef[row] * a.f.grad_out;
-        const float l = a.f.lse[row];
+    const int piece = kClusterThreads * q.vpt;
+    const uint32_t badcu = *a.f.badcu;
+    for (int64_t row = r0; row < r1; ++row) {
+        if (tid < 64) {
+            float pm = kEmpty, pS = 0.0f, pT = 0.0f;
+            int pending = 0;
+            if (tid < C) {
+                const unsigned long long w0 = a.slots[(row * C + tid) * 2], w1 = a.slots[(row * C + tid) * 2 + 1];
+                pm = __uint_as_float((uint32_t)w0);
+                pS = __uint_as_float((uint32_t)(w0 >> 32));
+                pT = __uint_as_float((uint32_t)w1);
+                pending = (w1 >> 32) == kTagPending;
+            }
+            const unsigned long long mask = __ballot(pending);
+            merge_pieces_tree(pm, pS, pT);
+            if (tid == 0) {
+                sh_pending = mask;
+                if (mask != 0ull) {
+                    const int32_t y = a.f.token_ids[row];
+                    float lse, lp, ent, g;
+                    finish_pieces(pm, pS, pT, y >= 0 && y < V, a.f.zy_row[row], lse, lp, ent);
+                    const int mode = row_decision(a.f, y, V, lse, lp, ent, a.f.adv[row],
+                                                  a.f.is_mode == ULORL_IS_POIS ? 0.0f : a.f.old_logp[row], badcu, g);
+                    a.f.lse[row] = lse;
+                    a.f.logp[row] = lp;
+                    a.f.entropy[row] = ent;
+                    a.f.defer[row] = mode == 2 ? 1 : 0;
+                    sh_g = g;
+                    sh_lse = lse;
+                    sh_mode = mode;
+                }
+            }
+        }
+        __syncthreads();
+        if (sh_pending == 0ull) {
+            __syncthreads();
+            continue;
+        }
+        unsigned long long todo = sh_mode == 2 ? 0ull : sh_pending;
         const int32_t y = a.f.token_ids[row];
-        const bool live = row_is_live(g, l, y, V);
-        const typename Tr::elem* rowp = logits + row * row_stride;
-        typename Tr::elem* outp = dlogits + row * row_stride;
+        const float g = sh_g, l = sh_lse;
+        const bool live = sh_mode == 1;
         const float cexp = live ? fmaf(-l, kLog2e, log2f(fabsf(g))) : 0.0f;
         const bool negate = g > 0.0f;
         const float sgn = negate ? -1.0f : 1.0f;
         const float g_mag = negate ? -g : g;
         const int yvec = y / E;
-        const int first = c * NT * vpt;
-        for (int k = 0; k < vpt; ++k) {
-            const int i = first + k * NT + tid;
-            if (i >= nvec) break;
-            u32x4* op = reinterpret_cast<u32x4*>(outp) + i;
-            if (!live) {
-                store_stream(op, u32x4{0u, 0u, 0u, 0u});
-                continue;
-            }
-            float f[E];
-            Tr::unpack(load_stream(reinterpret_cast<const u32x4*>(rowp) + i), f);
-#pragma unroll
-            for (int e = 0; e < E; ++e) f[e] = fast_exp2(fmaf(f[e], kLog2e, cexp));
-            if (i == yvec) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) f[e] += (e == y - yvec * E) ? g_mag : 0.0f;
-            }
-            u32x4 o = Tr::pack(f);
-            if (negate) o ^= Tr::sign_bits();
-            store_stream(op, o);
-        }
-        if (c == C - 1 && tid == NT - 1) {      // ragged tail of the row
-            for (int j = nvec * E; j < V; ++j) {
-                float x = 0.0f;
-                if (live) {
-                    x = sgn * fast_exp2(fmaf(Tr::load1(rowp + j), kLog2e, cexp));
-                    if (j == y) x += g;
+        const typename Tr::elem* rowp = q.logits + row * q.row_stride;
+        typename Tr::elem* outp = q.dlogits + row * q.row_stride;
+        for (; todo != 0ull; todo &= todo - 1ull) {
+            const int c = __ffsll((long long)todo) - 1;
+            const int end = min(nvec, (c + 1) * piece);
+            for (int i = c * piece + tid; i < end; i += NT) {
+                u32x4* op = reinterpret_cast<u32x4*>(outp) + i;
+                if (!live) {
+                    store_stream(op, u32x4{0u, 0u, 0u, 0u});
+                    continue;
                 }
-                Tr::store1(outp + j, x);
+                float f[E];
+                Tr::unpack(load_stream(reinterpret_cast<const u32x4*>(rowp) + i), f);
+#pragma unroll
+                for (int e = 0; e < E; ++e) f[e] = fast_exp2(fmaf(f[e], kLog2e, cexp));
+                if (i == yvec) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) f[e] += (e == y - yvec * E) ? g_mag : 0.0f;
+                }
+                u32x4 o = Tr::pack(f);
+                if (negate) o ^= Tr::sign_bits();
+                store_stream(op, o);
+            }
+            if (c == C - 1 && tid == NT - 1) {      // ragged tail of the row
+                for (int j = nvec * E; j < V; ++j) {
+                    float x = 0.0f;
+                    if (live) {
+                        x = sgn * fast_exp2(fmaf(Tr::load1(rowp + j), kLog2e, cexp));
+                        if (j == y) x += g;
+                    }
+                    Tr::store1(outp + j, x);
+                }
             }
         }
+        __syncthreads();
+    }
+}
+
+// a.slices workgroups per response: the repair of their rows if any is needed, the sum of their token
+// entropies (Sec. 3.2.2, H-bar_i numerator) and a sanity check of the response's bounds.
+template <class Tr>
+__global__ __launch_bounds__(kTokBlock) void response_entropy_kernel(TokenArgs a, RepairArgs<Tr> rep)
+{
+    __shared__ double scratch[kTokWaves];
+    const int i = blockIdx.x / a.slices, s = blockIdx.x % a.slices;
+    const int64_t b = a.cu[i], e = a.cu[i + 1];
+    const bool ok = response_bounds_ok(a.cu, i, a.R, a.N);
+    const int64_t per = ok ? (e - b + a.slices - 1) / a.slices : 0;
+    const int64_t r0 = b + s * per, r1 = min(e, r0 + per);
+    if (rep.c.sync_fail != nullptr && *rep.c.sync_fail != 0u) {
+        if (*rep.c.f.badcu == 0u) {
+            repair_rows<Tr>(rep, a.V, r0, r1);
+        } else {                                    // no usable responses: an even share of all rows
+            const int64_t share = (a.N + gridDim.x - 1) / gridDim.x;
+            repair_rows<Tr>(rep, a.V, blockIdx.x * share, min(a.N, (int64_t)(blockIdx.x + 1) * share));
+        }
+        __syncthreads();
+    }
+    double h = 0.0;
+    if (ok) {
+#pragma unroll 4
+        for (int64_t t = r0 + threadIdx.x; t < r1; t += kTokBlock) h += (double)a.entropy[t];
+    }
+    h = block_sum_f64(h, scratch);
+    if (threadIdx.x == 0) {
+        a.hsum[blockIdx.x] = h;
+        if (s == 0) a.rflags[i] = ok ? 0u : 1u;
+        if (blockIdx.x == 0) *a.ticket = 0u;        // for token_terms_kernel
+    }
+}
+
+template <class Tr>
+void launch_epilogue(const TokenArgs& a, int64_t nblk, const RepairArgs<Tr>& rep, hipStream_t st)
+{
+    hipLaunchKernelGGL((response_entropy_kernel<Tr>), dim3((unsigned)a.R * (unsigned)a.slices), dim3(kTokBlock), 0, st, a, rep);
+    if (a.seg.K > 0) {
+        size_t lds = (size_t)a.seg.K * kSegStats * sizeof(double);
+        if (lds < kSegBlock * sizeof(double)) lds = kSegBlock * sizeof(double);      // scratch of seg_finalize
+        hipLaunchKernelGGL((token_terms_kernel<true>), dim3((unsigned)nblk), dim3(kTokBlock), lds, st, a, nblk);
+    } else {
+        hipLaunchKernelGGL((token_terms_kernel<false>), dim3((unsigned)nblk), dim3(kTokBlock), 0, st, a, nblk);
     }
 }
 
@@ -1392,17 +1422,16 @@ void launch_dlogits(const void* logits, int64_t N, int64_t V, int64_t stride, co
                        (typename Tr::elem*)dz);
 }
 
-// The gradient of the rows flagged in `defer`, through a compacted list.
+// The gradient of the rows that waited for the gate, from the list token_terms_kernel made.
 template <class Tr>
-void launch_dlogits_deferred(const void* logits, int64_t N, int64_t V, int64_t stride, const int32_t* y, const float* lse,
-                             const float* g, float grad_out, void* dz, const uint8_t* defer, uint32_t* list,
-                             uint32_t* count, hipStream_t st)
+void launch_dlogits_deferred(const void* logits, int64_t V, int64_t stride, const int32_t* y, const float* lse,
+                             const float* g, float grad_out, void* dz, const uint32_t* list, const uint32_t* count,
+                             hipStream_t st)
 {
     const int64_t nvec = V / Tr::kPerVec;
     const int64_t chunks = nvec > 0 ? (nvec + 255) / 256 : 1;
-    hipLaunchKernelGGL(defer_compact_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, defer, N, list, count);
     hipLaunchKernelGGL((dlogits_rows_kernel<Tr>), dim3((unsigned)chunks, kListRowSlots), dim3(256), 0, st,
-                       (const typename Tr::elem*)logits, stride, (int32_t)V, (const uint32_t*)list, (const uint32_t*)count, y,
+                       (const typename Tr::elem*)logits, stride, (int32_t)V, list, count, y,
                        lse, g, grad_out, (typename Tr::elem*)dz);
 }
 
@@ -1493,16 +1522,15 @@ WorkspaceLayout workspace_layout(int64_t N, int64_t V, int32_t R)
     const int pieces = V > 0 ? (a.pieces > b.pieces ? a.pieces : b.pieces) : 0;
     size_t off = 0;
     w.slots = off;    off = align_up(off + sizeof(unsigned long long) * 2 * (size_t)N * (size_t)pieces, 256);   // first: see ulorl_token_loss_fwd
-    w.syncfail = off; off = align_up(off + sizeof(uint32_t), 256);
-    w.hsum = off;     off = align_up(off + sizeof(double) * (size_t)R, 256);
+    w.syncfail = off; w.badcu = off + 4; w.defer_count = off + 8; w.ticket = off + 12;
+    off = align_up(off + 4 * sizeof(uint32_t), 256);
+    w.hsum = off;     off = align_up(off + sizeof(double) * (size_t)R * (size_t)entropy_slices(N, R), 256);
     w.rflags = off;   off = align_up(off + sizeof(uint32_t) * (size_t)R, 256);
     w.part_sum = off; off = align_up(off + sizeof(double) * (size_t)w.nblk, 256);
-    w.part_cnt = off; off = align_up(off + sizeof(int64_t) * 4 * (size_t)w.nblk, 256);
+    w.part_cnt = off; off = align_up(off + sizeof(int64_t) * 2 * (size_t)w.nblk, 256);
     w.defer = off;    off = align_up(off + (size_t)N, 256);
-    w.badcu = off;    off = align_up(off + sizeof(uint32_t), 256);
     w.zy = off;       off = align_up(off + (V > 0 ? sizeof(float) * (size_t)N : 0), 256);
     w.defer_list = off;  off = align_up(off + (V > 0 ? sizeof(uint32_t) * (size_t)N : 0), 256);
-    w.defer_count = off; off = align_up(off + sizeof(uint32_t), 256);
     w.total = off;
     return w;
 }
@@ -1564,7 +1592,8 @@ TokenArgs make_token_args(int64_t N, int64_t V, const int32_t* token_ids, const 
                           const int32_t* segment_ids, const float* old_logp, const float* advantages,
                           const ulorl_params* p, float* logp, float* entropy, float* lse, float* gcoef,
                           uint8_t* mpt_mask, float* ratio, int32_t* segment_out, float* resp_entropy,
-                          uint8_t* resp_gate, void* workspace, const WorkspaceLayout& wl, const SegStatsArgs& seg)
+                          uint8_t* resp_gate, float* loss, int64_t* counters, void* workspace, const WorkspaceLayout& wl,
+                          const SegStatsArgs& seg)
 {
     char* ws = (char*)workspace;
     TokenArgs a;
@@ -1573,8 +1602,11 @@ TokenArgs make_token_args(int64_t N, int64_t V, const int32_t* token_ids, const 
     a.gcoef = gcoef;
     a.mask = mpt_mask; a.ratio = ratio; a.seg_out = segment_out; a.resp_entropy = resp_entropy;
     a.resp_gate = resp_gate;
+    a.loss = loss; a.counters = counters;
     a.hsum = (double*)(ws + wl.hsum); a.rflags = (uint32_t*)(ws + wl.rflags);
-    a.sync_fail = nullptr;
+    a.slices = entropy_slices(N, R);
+    a.ticket = (uint32_t*)(ws + wl.ticket);
+    a.sync_fail = nullptr; a.defer = nullptr; a.defer_list = nullptr; a.defer_count = nullptr;
     a.part_sum = (double*)(ws + wl.part_sum); a.part_cnt = (int64_t*)(ws + wl.part_cnt);
     a.N = N; a.V = (int32_t)V; a.R = R;
     a.is_mode = p->is_mode; a.gate_mode = p->gate_mode; a.seg_len = p->seg_len;
@@ -1587,12 +1619,9 @@ TokenArgs make_token_args(int64_t N, int64_t V, const int32_t* token_ids, const 
     return a;
 }
 
-void launch_token_epilogue(const TokenArgs& a, const WorkspaceLayout& wl, float* loss, int64_t* counters, hipStream_t st)
+void launch_token_epilogue(const TokenArgs& a, const WorkspaceLayout& wl, hipStream_t st)
 {
-    const size_t seg_lds = (size_t)a.seg.K * kSegStats * sizeof(double);
-    hipLaunchKernelGGL(response_entropy_kernel, dim3((unsigned)a.R), dim3(kTokBlock), 0, st, a);
-    hipLaunchKernelGGL(token_terms_kernel, dim3((unsigned)wl.nblk), dim3(kTokBlock), seg_lds, st, a);
-    hipLaunchKernelGGL(loss_finalize_kernel, dim3(1), dim3(kTokBlock), 0, st, a, wl.nblk, loss, counters);
+    launch_epilogue<StoreF32>(a, wl.nblk, RepairArgs<StoreF32>{}, st);      // nothing to repair
 }
 
 }  // namespace ulorl_detail
@@ -1641,7 +1670,8 @@ int32_t fwd_bwd_enqueue(const void* logits, int32_t dt, int64_t N, int64_t V, in
     const bool bf16 = dt == ULORL_BF16;
 
     TokenArgs a = make_token_args(N, V, token_ids, cu_seqlens, R, segment_ids, old_logp, advantages, p, logp, entropy,
-                                  lse, gcoef, mpt_mask, ratio, segment_out, resp_entropy, resp_gate, workspace, wl, seg);
+                                  lse, gcoef, mpt_mask, ratio, segment_out, resp_entropy, resp_gate, loss, counters, workspace,
+                                  wl, seg);
     FusedArgs f;
     f.token_ids = token_ids; f.old_logp = old_logp; f.adv = advantages;
     f.lse = lse; f.logp = logp; f.entropy = entropy;
@@ -1650,56 +1680,54 @@ int32_t fwd_bwd_enqueue(const void* logits, int32_t dt, int64_t N, int64_t V, in
     f.eps_low = a.eps_low; f.eps_high = a.eps_high; f.log_tau = a.log_tau; f.inv_D = a.inv_D;
     f.grad_out = grad_out;
 
-    hipLaunchKernelGGL(cu_check_kernel, dim3(1), dim3(kTokBlock), 0, st, cu_seqlens, R, N, (uint32_t*)(ws + wl.badcu),
-                       (uint32_t*)(ws + wl.defer_count));
     const ClusterShape shape = cluster_shape(V, dt);
     const bool cooperative = !opts.per_row && shape.pieces > 0 && 2 * N * (int64_t)shape.pieces < (1LL << 38);
     ClusterArgs ca = {};
+    PrologueArgs pro = {};
+    pro.sync_fail = (uint32_t*)(ws + wl.syncfail);
+    pro.defer_count = (uint32_t*)(ws + wl.defer_count);
+    pro.badcu = (uint32_t*)(ws + wl.badcu);
+    pro.cu = cu_seqlens; pro.R = R; pro.N = N;
     if (cooperative) {
         ca.f = f;
         ca.slots = (unsigned long long*)(ws + wl.slots);
-        ca.sync_fail = (uint32_t*)(ws + wl.syncfail);
+        ca.sync_fail = pro.sync_fail;
         ca.N = N;
         ca.C = shape.pieces;
         ca.spin_limit = opts.sync_spins;
         a.sync_fail = ca.sync_fail;
-        const int64_t nslots = 2 * N * (int64_t)shape.pieces;
-        hipLaunchKernelGGL(fill_zero_u64_kernel, dim3((unsigned)((nslots + 255) / 256)), dim3(256), 0, st, ca.slots, nslots,
-                           ca.sync_fail);
-        const bool ok = bf16 ? launch_cluster<StoreBF16>(shape.vpt, logits, N, V, row_stride, dlogits, ca, st)
-                             : launch_cluster<StoreF32>(shape.vpt, logits, N, V, row_stride, dlogits, ca, st);
-        if (!ok) return ULORL_ERR_HIP;
-        hipLaunchKernelGGL(repair_rows_kernel, dim3(kRepairRowGrid), dim3(256), 0, st, ca, (int32_t)V);
-    } else if (bf16) {
-        launch_fused_rows<StoreBF16>(logits, N, V, row_stride, dlogits, f, st);
-    } else {
-        launch_fused_rows<StoreF32>(logits, N, V, row_stride, dlogits, f, st);
+        pro.slots = (u32x4*)ca.slots;
+        pro.nslots = N * (int64_t)shape.pieces;
     }
-    if (hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
-    launch_token_epilogue(a, wl, loss, counters, st);
-    if (hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
     if (a.gate_mode == ULORL_GATE_PER_RESPONSE || a.gate_mode == ULORL_GATE_GLOBAL) {
+        a.defer = f.defer;
+        a.defer_list = (uint32_t*)(ws + wl.defer_list);
+        a.defer_count = pro.defer_count;
+    }
+    const unsigned pro_blocks = (unsigned)((pro.nslots + 255) / 256);
+    hipLaunchKernelGGL(prologue_kernel, dim3(pro_blocks > 0 ? pro_blocks : 1), dim3(256), 0, st, pro);
+    auto rows = [&](auto tr) {
+        using Tr = decltype(tr);
+        RepairArgs<Tr> rep = {};
+        if (cooperative) {
+            if (!launch_cluster<Tr>(shape.vpt, logits, N, V, row_stride, dlogits, ca, st)) return false;
+            rep.c = ca;
+            rep.logits = (const typename Tr::elem*)logits;
+            rep.row_stride = row_stride;
+            rep.dlogits = (typename Tr::elem*)dlogits;
+            rep.vpt = shape.vpt;
+        } else {
+            launch_fused_rows<Tr>(logits, N, V, row_stride, dlogits, f, st);
+        }
+        if (hipGetLastError() != hipSuccess) return false;
+        launch_epilogue<Tr>(a, wl.nblk, rep, st);
+        if (hipGetLastError() != hipSuccess) return false;
         // MPT members waited for the gate: their rows are still logits (in place) or unwritten
-        uint32_t* list = (uint32_t*)(ws + wl.defer_list);
-        uint32_t* count = (uint32_t*)(ws + wl.defer_count);
-        if (bf16)
-            launch_dlogits_deferred<StoreBF16>(logits, N, V, row_stride, token_ids, lse, gcoef, grad_out, dlogits, f.defer, list,
-                                               count, st);
-        else
-            launch_dlogits_deferred<StoreF32>(logits, N, V, row_stride, token_ids, lse, gcoef, grad_out, dlogits, f.defer, list,
-                                              count, st);
-    }
-    if (cooperative) {
-        if (bf16)
-            hipLaunchKernelGGL((repair_pieces_kernel<StoreBF16>), dim3(kRepairPieceGrid), dim3(kClusterThreads), 0, st,
-                               (const uint16_t*)logits, row_stride, (int32_t)V, (uint16_t*)dlogits, ca, (int32_t)shape.vpt,
-                               (const float*)gcoef);
-        else
-            hipLaunchKernelGGL((repair_pieces_kernel<StoreF32>), dim3(kRepairPieceGrid), dim3(kClusterThreads), 0, st,
-                               (const float*)logits, row_stride, (int32_t)V, (float*)dlogits, ca, (int32_t)shape.vpt,
-                               (const float*)gcoef);
-    }
-    return hipGetLastError() == hipSuccess ? ULORL_OK : ULORL_ERR_HIP;
+        if (a.defer != nullptr)
+            launch_dlogits_deferred<Tr>(logits, V, row_stride, token_ids, lse, gcoef, grad_out, dlogits, a.defer_list, a.defer_count, st);
+        return hipGetLastError() == hipSuccess;
+    };
+    return (bf16 ? rows(StoreBF16{}) : rows(StoreF32{})) ? ULORL_OK : ULORL_ERR_HIP;
 }
 
 }  // namespace
@@ -1782,8 +1810,8 @@ int32_t ulorl_token_loss_fwd(const void* logits, int32_t dt, int64_t N, int64_t 
 
     const TokenArgs a = make_token_args(N, V, token_ids, cu_seqlens, R, segment_ids, old_logp, advantages, p, logp,
                                         entropy, lse, gcoef, mpt_mask, ratio, segment_out, resp_entropy, resp_gate,
-                                        workspace, wl, seg);
-    launch_token_epilogue(a, wl, loss, counters, st);
+                                        loss, counters, workspace, wl, seg);
+    launch_token_epilogue(a, wl, st);
     if (hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
     return ULORL_OK;
 }
