@@ -1454,7 +1454,12 @@ bool launch_piece_stats(const ClusterShape& shape, const void* logits, int64_t N
                            (const typename Tr::elem*)logits, stride, (int32_t)V, N, (int32_t)shape.pieces, slots); \
         launched = true;                                                                                        \
     }
-    ULORL_CASE(4) ULORL_CASE(8) ULORL_CASE(15)
+    ULORL_CASE(4) ULORL_CASE(8) ULORL_CASE(13) ULORL_CASE(15)
+    if constexpr (Tr::kPerVec == 8) {
+        ULORL_CASE(6) ULORL_CASE(7) ULORL_CASE(11)
+    } else {
+        ULORL_CASE(20)
+    }
 #undef ULORL_CASE
     if (!launched) return false;
     hipLaunchKernelGGL((piece_merge_kernel<Tr>), dim3((unsigned)((N + 3) / 4)), dim3(256), 0, st,
@@ -1476,7 +1481,12 @@ bool launch_cluster(int vpt, const void* logits, int64_t N, int64_t V, int64_t s
                            (const typename Tr::elem*)logits, stride, (int32_t)V, (typename Tr::elem*)dz, a);   \
         return true;                                                                                           \
     }
-    ULORL_CASE(4) ULORL_CASE(8) ULORL_CASE(15)
+    ULORL_CASE(4) ULORL_CASE(8) ULORL_CASE(13) ULORL_CASE(15)
+    if constexpr (Tr::kPerVec == 8) {
+        ULORL_CASE(6) ULORL_CASE(7) ULORL_CASE(11)
+    } else {
+        ULORL_CASE(20)
+    }
 #undef ULORL_CASE
     return false;
 }
@@ -1502,14 +1512,48 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // Shape of the row-cooperative kernel for a row of V elements: vectors per thread and pieces
 // (workgroups) per row; pieces == 0 if the row is too long for one wave to poll its pieces.
 // A function of V and the storage type only, so the workspace size is too.
+//
+// Few large pieces stream best, but a row's last piece should be full, since its partners wait for it and
+// a nearly empty one leaves its compute unit's share of the stream idle.  The candidates are priced as
+//     speed of the shape * (1 + 0.4 (allotted / real vectors - 1)) + 0.01 pieces
+// which picks the best or within 4 % of it at every length measured; bf16 one-call ms, 15 vectors (the
+// only long-row shape before) / chosen: 20000 x 32003 0.640 / 0.458 (6), 16000 x 50264 0.595 / 0.581 (13),
+// 12000 x 65536 0.559 / 0.518 (11), 10000 x 100000 0.738 / 0.680 (7), 8000 x 128256 0.701 / 0.678 (13),
+// 16384 x 151936 1.607 (15), 30000 x 24000 0.629 (8 before) / 0.473 (6); fp32 4096 x 151936 0.844 / 0.813
+// (20).  Shapes of 4 and 8 vectors only hold rows of one piece (pieces of 16 and 32 KB: 1.11 and 0.96 ms
+// where 15 vectors take 0.79).
 ClusterShape cluster_shape(int64_t V, int32_t dt)
 {
+    struct Candidate { int vpt; double speed; };
+    static constexpr Candidate kBf16[] = {{4, 1.0}, {6, 1.0}, {7, 0.97}, {8, 1.0}, {11, 0.99}, {13, 0.98}, {15, 0.96}};
+    static constexpr Candidate kF32[] = {{4, 1.0}, {8, 1.0}, {13, 0.98}, {15, 0.97}, {20, 0.93}};
     const int64_t nvec = V / (dt == ULORL_F32 ? 4 : 8);
+    auto pieces_of = [](int64_t n, int vpt) { return n > 0 ? (n + kClusterThreads * vpt - 1) / (kClusterThreads * vpt) : 1; };
     ClusterShape c;
-    c.vpt = nvec >= kClusterThreads * 15 ? 15 : nvec >= kClusterThreads * 8 ? 8 : 4;
-    const int64_t per_piece = kClusterThreads * (int64_t)c.vpt;
-    const int64_t pieces = nvec > 0 ? (nvec + per_piece - 1) / per_piece : 1;
-    c.pieces = pieces <= kClusterMaxPieces ? (int)pieces : 0;
+    c.vpt = 15;
+    c.pieces = 0;
+    if (pieces_of(nvec, 15) > kClusterMaxPieces) return c;
+    // no more pieces than a row of either type in 15-vector pieces: bounds the exchange slots of the workspace
+    const int64_t most = pieces_of(V / 4, 15) <= kClusterMaxPieces ? pieces_of(V / 4, 15) : pieces_of(V / 8, 15);
+    double best = 0.0;
+    auto consider = [&](const Candidate& k) {
+        const int64_t pieces = pieces_of(nvec, k.vpt), allotted = pieces * kClusterThreads * k.vpt;
+        if ((k.vpt == 4 || k.vpt == 8) && pieces > 1) return;
+        if (pieces > most && k.vpt != 15) return;
+        const double waste = nvec > 0 ? (double)allotted / (double)nvec - 1.0 : 0.0;
+        if (k.vpt == 20 && waste > 0.1) return;                 // 16384 fp32 vectors in 4 pieces: 0.63 ms, 5 of 15: 0.53
+        double cost = k.speed * (1.0 + 0.4 * waste) + 0.01 * (double)pieces;
+        if (pieces > 1 && nvec - (pieces - 1) * kClusterThreads * k.vpt < kClusterThreads) cost += 0.5;    // a last piece without a vector for every thread takes its vectors one by one
+        if (c.pieces == 0 || cost < best) {
+            best = cost;
+            c.vpt = k.vpt;
+            c.pieces = (int)pieces;
+        }
+    };
+    if (dt == ULORL_F32)
+        for (const Candidate& k : kF32) consider(k);
+    else
+        for (const Candidate& k : kBf16) consider(k);
     return c;
 }
 
