@@ -522,37 +522,71 @@ __device__ __forceinline__ bool response_bounds_ok(const int32_t* cu, int i, int
     return b >= 0 && e >= b && e <= N && (i != 0 || b == 0) && (i != R - 1 || e == N);
 }
 
-// Call-wide facts that every workgroup derives identically: whether cu_seqlens is malformed and, for the
-// GLOBAL gate, the token-mean entropy.  All kTokBlock threads call.
-__device__ __forceinline__ int batch_is_bad(const TokenArgs& a, double& hglobal, double* scratch)
+// Gate of a response with mean entropy hbar over L tokens (Sec. 3.2.2).
+__device__ __forceinline__ int gate_of(const TokenArgs& a, int64_t L, int badcu, double hglobal, double hbar)
 {
-    int bad = 0;
-    double hall = 0.0;
-    for (int i = threadIdx.x; i < a.R; i += kTokBlock) bad |= (int)a.rflags[i];
-    bad = __syncthreads_or(bad);
-    hglobal = 0.0;
-    if (a.gate_mode == ULORL_GATE_GLOBAL) {
-        for (int i = threadIdx.x; i < a.R * a.slices; i += kTokBlock) hall += a.hsum[i];
-        hglobal = block_sum_f64(hall, scratch) / (double)a.N;
-    }
-    return bad;
-}
-
-// Mean entropy and gate of response i (Sec. 3.2.2).
-__device__ __forceinline__ int response_gate(const TokenArgs& a, int i, int64_t L, int badcu, double hglobal, double& hbar)
-{
-    hbar = 0.0;
-    if (!badcu && L > 0) {
-        double h = 0.0;
-        for (int s = 0; s < a.slices; ++s) h += a.hsum[(int64_t)i * a.slices + s];
-        hbar = h / (double)L;
-    }
     switch (a.gate_mode) {
     case ULORL_GATE_PER_RESPONSE: return (!badcu && L > 0) && (hbar < a.sigma);
     case ULORL_GATE_GLOBAL: return hglobal < a.sigma;
     case ULORL_GATE_ALWAYS: return 1;
     default: return 0;
     }
+}
+__device__ __forceinline__ double entropy_sum(const TokenArgs& a, int i)
+{
+    double h = 0.0;
+    for (int s = 0; s < a.slices; ++s) h += a.hsum[(int64_t)i * a.slices + s];
+    return h;
+}
+
+// What a workgroup of token_terms_kernel knows of the batch: whether cu_seqlens is malformed, the token-mean entropy
+// (GLOBAL gate), and, for up to kTableResponses responses, their bounds, mean entropies and gates in LDS:
+// one round of loads instead of a chain of dependent ones per token.  (256 of them leave room for the
+// largest segment table, 1024 x 7 doubles, in the 64 KB a launch gets by default.)
+constexpr int kTableResponses = 256;
+struct BatchTable {
+    int32_t cu[kTableResponses + 1];
+    float hbar[kTableResponses];
+    uint8_t gate[kTableResponses];
+    double scratch[kTokWaves];
+};
+__device__ __forceinline__ int load_batch(const TokenArgs& a, BatchTable& b, double& hglobal)
+{
+    const int tid = threadIdx.x;
+    const bool table = a.R <= kTableResponses;
+    int bad = 0;
+    double h = 0.0;
+    int32_t c0 = 0, c1 = 0;
+    if (table) {
+        if (tid < a.R) {
+            c0 = a.cu[tid];
+            c1 = a.cu[tid + 1];
+            bad = (int)a.rflags[tid];
+            h = entropy_sum(a, tid);
+            b.cu[tid] = c0;
+            if (tid == a.R - 1) b.cu[a.R] = c1;
+        }
+    } else {
+        for (int i = tid; i < a.R; i += kTokBlock) bad |= (int)a.rflags[i];
+    }
+    bad = __syncthreads_or(bad);
+    hglobal = 0.0;
+    if (a.gate_mode == ULORL_GATE_GLOBAL) {
+        double hall = h;
+        if (!table)
+            for (int i = tid; i < a.R * a.slices; i += kTokBlock) hall += a.hsum[i];
+        hglobal = block_sum_f64(hall, b.scratch) / (double)a.N;
+    }
+    if (table) {
+        if (tid < a.R) {
+            const int64_t L = bad ? 0 : (int64_t)c1 - (int64_t)c0;
+            const double hbar = L > 0 ? h / (double)L : 0.0;
+            b.hbar[tid] = (float)hbar;
+            b.gate[tid] = (uint8_t)gate_of(a, L, bad, hglobal, hbar);
+        }
+        __syncthreads();
+    }
+    return bad;
 }
 
 // Largest i in [lo, hi) with cu[i] <= t (lo if there is none).
@@ -567,14 +601,23 @@ __device__ __forceinline__ int response_of(const int32_t* __restrict__ cu, int l
 
 // Final sums, per-response outputs and status bits, by the last workgroup of token_terms_kernel.
 template <bool SEG>
-__device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, int badcu, double hglobal, double* seg_scratch)
+__device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, int badcu, double hglobal, const BatchTable& batch,
+                                              double* seg_scratch)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < a.R; i += kTokBlock) {
-        const int64_t L = badcu ? 0 : (int64_t)a.cu[i + 1] - (int64_t)a.cu[i];
-        double hbar;
-        const int gate = response_gate(a, i, L, badcu, hglobal, hbar);
-        if (a.resp_entropy) a.resp_entropy[i] = (float)hbar;
+        float hbar;
+        int gate;
+        if (a.R <= kTableResponses) {
+            hbar = batch.hbar[i];
+            gate = batch.gate[i];
+        } else {
+            const int64_t L = badcu ? 0 : (int64_t)a.cu[i + 1] - (int64_t)a.cu[i];
+            const double h = L > 0 ? entropy_sum(a, i) / (double)L : 0.0;
+            hbar = (float)h;
+            gate = gate_of(a, L, badcu, hglobal, h);
+        }
+        if (a.resp_entropy) a.resp_entropy[i] = hbar;
         if (a.resp_gate) a.resp_gate[i] = badcu ? 0 : (uint8_t)gate;
     }
     // counts below 2^53 are exact as doubles, in any order
@@ -605,7 +648,7 @@ __device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, 
     if (tid == 0) {
         double t[4] = {0.0, 0.0, 0.0, 0.0};
         int flags = 0;
-#pragma unroll
+#pragma unroll 4
         for (int w = 0; w < kTokWaves; ++w) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) t[q] += fin[w][q];
@@ -625,22 +668,24 @@ __device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, 
 
 // Gate, ratio, clipped term, mask, coefficient and segment id of every token; block sums; the rows whose
 // gradient waited for the gate collected into a list; the last workgroup to deliver its sums forms the
-// call's results.  Latency bound (a few dependent loads, two barriers, the ticket): 131072 tokens took
-// 10 + 16 us as two launches with shuffle reductions, now 9.
+// call's results.  Latency bound (two rounds of loads, three barriers, the ticket):
+// 32768 tokens took 10 + 10 us as two launches with shuffle reductions, now 9.  (One workgroup for both
+// epilogue kernels was slower at every token count, 256 to 4096.)
 // SEG: the per-segment diagnostics are wanted.
 template <bool SEG>
 __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int64_t nblk)
 {
     extern __shared__ double seg_table[];       // SEG: [max(K * 7, kSegBlock)]
-    __shared__ double scratch[kTokWaves];
+    __shared__ BatchTable batch;
     __shared__ double wave_s[kTokWaves];
     __shared__ int wave_c[kTokWaves][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     double hglobal;
-    const int badcu = batch_is_bad(a, hglobal, scratch);
+    const int badcu = load_batch(a, batch, hglobal);
 
-    const int64_t t0 = (int64_t)blockIdx.x * kTokBlock, t = t0 + tid;
+    const int64_t blk = blockIdx.x;
+    const int64_t t0 = blk * kTokBlock, t = t0 + tid;
     double contrib = 0.0;
     bool is_masked = false, is_clipped = false, is_positive = false;
     int flags = badcu ? ULORL_STATUS_BAD_CU : 0;
@@ -651,30 +696,34 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
     float sg_logp = 0.0f, sg_ent = 0.0f, sg_adv = 0.0f, sg_old = 0.0f;
     bool listed = false;
 
-    // the responses this block's tokens lie in (uniform), then the token's own among them
-    const int first = response_of(a.cu, 0, a.R, t0);
-    const int last = response_of(a.cu, first, a.R, t0 + kTokBlock - 1);
     if (t < a.N) {
-        const int i = response_of(a.cu, first, last + 1, t);
-        const int64_t b = a.cu[i];
-        const int64_t L = (int64_t)a.cu[i + 1] - b;
-        double hbar;
-        const int gate = response_gate(a, i, L, badcu, hglobal, hbar);
-        const int32_t seg = a.segment_ids ? a.segment_ids[t]
-                                          : (a.seg_len > 0 && !badcu ? (int32_t)((t - b) / a.seg_len) : 0);
-        if (a.seg_out) a.seg_out[t] = seg;
-
-        const float lpf = a.logp[t];
-        const float hf = a.entropy[t];
-        const float lf = a.lse[t];
+        // all of the token's loads before the first store
+        const float lpf = a.logp[t], hf = a.entropy[t], lf = a.lse[t];
         const int32_t y = a.token_ids[t];
+        sg_adv = a.adv[t];
+        if (a.old_logp != nullptr) sg_old = a.old_logp[t];
+        if (a.segment_ids != nullptr) sg_seg = a.segment_ids[t];
+        if (a.defer != nullptr) listed = a.defer[t] != 0;
+
+        int32_t b;
+        int gate;
+        if (a.R <= kTableResponses) {
+            const int i = response_of(batch.cu, 0, a.R, t);
+            b = batch.cu[i];
+            gate = batch.gate[i];
+        } else {
+            const int i = response_of(a.cu, 0, a.R, t);
+            b = a.cu[i];
+            const int64_t L = (int64_t)a.cu[i + 1] - (int64_t)b;
+            gate = gate_of(a, L, badcu, hglobal, !badcu && L > 0 ? entropy_sum(a, i) / (double)L : 0.0);
+        }
+        if (a.segment_ids == nullptr) sg_seg = a.seg_len > 0 && !badcu ? (int32_t)((uint32_t)(t - b) / (uint32_t)a.seg_len) : 0;   // t < 2^31
+        sg_logp = lpf;
+        sg_ent = hf;
         const bool bad_tok = (y < 0 || y >= a.V);
         const bool nonfinite = not_finite(lpf) || not_finite(hf) || not_finite(lf);
         if (bad_tok) flags |= ULORL_STATUS_BAD_TOKEN;
         if (!bad_tok && nonfinite) flags |= ULORL_STATUS_NONFINITE;
-
-        sg_seg = seg; sg_logp = lpf; sg_ent = hf; sg_adv = a.adv[t];
-        sg_old = (a.old_logp != nullptr) ? a.old_logp[t] : 0.0f;
         if (!bad_tok && !nonfinite && !badcu) {
             const TokenEval ev = token_eval(lpf, sg_adv, a.is_mode == ULORL_IS_POIS ? 0.0f : sg_old, a.is_mode, a.eps_low,
                                             a.eps_high, a.log_tau, a.inv_D);
@@ -686,10 +735,10 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
             is_clipped = !ev.active;
             is_positive = ev.positive;
         }
+        if (a.seg_out) a.seg_out[t] = sg_seg;
         a.gcoef[t] = g_out;
         if (a.ratio) a.ratio[t] = r_out;
         if (a.mask) a.mask[t] = m_out;
-        if (a.defer != nullptr) listed = a.defer[t] != 0;
     }
     // rows that waited for the gate (order arbitrary: each is finished once whatever its position)
     const unsigned long long list_ballot = __ballot(listed);
@@ -713,14 +762,14 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
     if (tid == 0) {
         double bs = 0.0;
         int c0 = 0, c1 = 0, c2 = 0, fl = 0;
-#pragma unroll
+#pragma unroll 4
         for (int w = 0; w < kTokWaves; ++w) {
             bs += wave_s[w];
             c0 += wave_c[w][0]; c1 += wave_c[w][1]; c2 += wave_c[w][2]; fl |= wave_c[w][3];
         }
-        publish(a.part_sum + blockIdx.x, bs);
-        publish(a.part_cnt + 2 * (int64_t)blockIdx.x, (int64_t)c0 | ((int64_t)c1 << 32));
-        publish(a.part_cnt + 2 * (int64_t)blockIdx.x + 1, (int64_t)c2 | ((int64_t)fl << 32));
+        publish(a.part_sum + blk, bs);
+        publish(a.part_cnt + 2 * blk, (int64_t)c0 | ((int64_t)c1 << 32));
+        publish(a.part_cnt + 2 * blk + 1, (int64_t)c2 | ((int64_t)fl << 32));
     }
     if constexpr (SEG) {
         int k;
@@ -728,15 +777,15 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
         seg_token_values(t < a.N, sg_seg, a.seg.K, r_out, sg_logp, a.old_logp != nullptr, sg_old, sg_ent, m_out, sg_adv,
                          a.eps_low, a.eps_high, k, v, oor);
         const double o = seg_block_partials(k, v, oor, a.seg.K, seg_table,
-                                            a.seg.part + (int64_t)blockIdx.x * a.seg.K * kSegStats);
-        if (tid == 0) publish(a.seg.part_oor + blockIdx.x, o);
+                                            a.seg.part + blk * a.seg.K * kSegStats);
+        if (tid == 0) publish(a.seg.part_oor + blk, o);
     }
-    if (last_workgroup(a.ticket, (uint32_t)nblk)) finalize_loss<SEG>(a, nblk, badcu, hglobal, seg_table);
+    if (last_workgroup(a.ticket, (uint32_t)nblk)) finalize_loss<SEG>(a, nblk, badcu, hglobal, batch, seg_table);
 }
 
 // ---------------------------------------------------------------------------------------------
-// fused forward + backward, one looping workgroup per row (the older kernel of the one-call path,
-// selected with ULORL_TUNE_FUSED_CLUSTER = 0 and used for rows too long for the cooperative one)
+// fused forward + backward, one looping workgroup per row (on request, ULORL_LAUNCH_PER_ROW, and for rows
+// too long for the cooperative kernel)
 // ---------------------------------------------------------------------------------------------
 // One workgroup per row does both passes back to back: statistics with ordinary (cacheable)
 // loads, then the gradient with the row read a second time while it is still in the L2 /
@@ -1003,17 +1052,21 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_row_kernel(const type
     float m, S, T;
     piece_statistics<Tr, VPT>(vp, rowp, nvec, V, first, full, owns_tail, v, sm, sS, sT, m, S, T);
 
-    // ---- exchange (first wave)
+    // ---- exchange (first wave); a row of one piece has nobody to wait for
     if (tid < 64) {
         unsigned long long* slot = a.slots + (row * C) * 2;
-        if (tid == 0) {
+        if (tid == 0 && C > 1) {
             __builtin_amdgcn_s_waitcnt(0);      // every load of this thread, the chosen logit included, has returned
             __hip_atomic_store(slot + 2 * c, piece_word0(m, S), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(slot + 2 * c + 1, piece_word1(T), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        float pm = kEmpty, pS = 0.0f, pT = 0.0f;
+        float pm = m, pS = S, pT = T;
         int expired = 0;
-        if (tid < C) {
+        if (C > 1) {
+            pm = kEmpty;
+            pS = pT = 0.0f;
+        }
+        if (C > 1 && tid < C) {
             unsigned long long w0 = 0, w1 = 0;
             int spins = 0;
             for (;;) {
@@ -1030,7 +1083,7 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_row_kernel(const type
             }
         }
         expired = __any(expired);
-        merge_pieces_tree(pm, pS, pT);
+        if (C > 1) merge_pieces_tree(pm, pS, pT);
         if (tid == 0) {
             if (expired) {
                 // leave everything to the repair pass: nothing of this piece is written
@@ -1297,10 +1350,13 @@ __global__ __launch_bounds__(kTokBlock) void response_entropy_kernel(TokenArgs a
 template <class Tr>
 void launch_epilogue(const TokenArgs& a, int64_t nblk, const RepairArgs<Tr>& rep, hipStream_t st)
 {
+    size_t lds = 0;
+    if (a.seg.K > 0) {
+        lds = (size_t)a.seg.K * kSegStats * sizeof(double);
+        if (lds < kSegBlock * sizeof(double)) lds = kSegBlock * sizeof(double);      // scratch of seg_finalize
+    }
     hipLaunchKernelGGL((response_entropy_kernel<Tr>), dim3((unsigned)a.R * (unsigned)a.slices), dim3(kTokBlock), 0, st, a, rep);
     if (a.seg.K > 0) {
-        size_t lds = (size_t)a.seg.K * kSegStats * sizeof(double);
-        if (lds < kSegBlock * sizeof(double)) lds = kSegBlock * sizeof(double);      // scratch of seg_finalize
         hipLaunchKernelGGL((token_terms_kernel<true>), dim3((unsigned)nblk), dim3(kTokBlock), lds, st, a, nblk);
     } else {
         hipLaunchKernelGGL((token_terms_kernel<false>), dim3((unsigned)nblk), dim3(kTokBlock), 0, st, a, nblk);
@@ -1741,7 +1797,7 @@ int32_t fwd_bwd_enqueue(const void* logits, int32_t dt, int64_t N, int64_t V, in
         ca.spin_limit = opts.sync_spins;
         a.sync_fail = ca.sync_fail;
         pro.slots = (u32x4*)ca.slots;
-        pro.nslots = N * (int64_t)shape.pieces;
+        pro.nslots = shape.pieces > 1 ? N * (int64_t)shape.pieces : 0;
     }
     if (a.gate_mode == ULORL_GATE_PER_RESPONSE || a.gate_mode == ULORL_GATE_GLOBAL) {
         a.defer = f.defer;
