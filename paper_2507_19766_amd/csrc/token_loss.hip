@@ -1589,7 +1589,7 @@ ClusterShape cluster_shape(int64_t V, int32_t dt)
     c.vpt = 15;
     c.pieces = 0;
     if (pieces_of(nvec, 15) > kClusterMaxPieces) return c;
-    // no more pieces than a row of either type in 15-vector pieces: bounds the exchange slots of the workspace
+    // no more pieces than a row of either type in 15-vector pieces: within the exchange slots (slot_pieces)
     const int64_t most = pieces_of(V / 4, 15) <= kClusterMaxPieces ? pieces_of(V / 4, 15) : pieces_of(V / 8, 15);
     double best = 0.0;
     auto consider = [&](const Candidate& k) {
@@ -1613,24 +1613,36 @@ ClusterShape cluster_shape(int64_t V, int32_t dt)
     return c;
 }
 
+// Pieces the exchange slots are sized for: those of 15-vector pieces (8 and 4 for short rows) in the storage
+// type that needs more.  cluster_shape never takes more.
+static int64_t slot_pieces(int64_t V, int32_t dt)
+{
+    const int64_t nvec = V / (dt == ULORL_F32 ? 4 : 8);
+    const int64_t per_piece = kClusterThreads * (int64_t)(nvec >= kClusterThreads * 15 ? 15 : nvec >= kClusterThreads * 8 ? 8 : 4);
+    const int64_t pieces = nvec > 0 ? (nvec + per_piece - 1) / per_piece : 1;
+    return pieces <= kClusterMaxPieces ? pieces : 0;
+}
+
 WorkspaceLayout workspace_layout(int64_t N, int64_t V, int32_t R)
 {
     WorkspaceLayout w;
     w.nblk = (N + kTokBlock - 1) / kTokBlock;
-    // exchange slots of the row-cooperative kernel, sized for the storage type that needs more pieces
-    const ClusterShape a = cluster_shape(V, ULORL_F32), b = cluster_shape(V, ULORL_BF16);
-    const int pieces = V > 0 ? (a.pieces > b.pieces ? a.pieces : b.pieces) : 0;
+    const int64_t a = slot_pieces(V, ULORL_F32), b = slot_pieces(V, ULORL_BF16);
+    const int64_t pieces = V > 0 ? (a > b ? a : b) : 0;
     size_t off = 0;
     w.slots = off;    off = align_up(off + sizeof(unsigned long long) * 2 * (size_t)N * (size_t)pieces, 256);   // first: see ulorl_token_loss_fwd
-    w.syncfail = off; w.badcu = off + 4; w.defer_count = off + 8; w.ticket = off + 12;
-    off = align_up(off + 4 * sizeof(uint32_t), 256);
-    w.hsum = off;     off = align_up(off + sizeof(double) * (size_t)R * (size_t)entropy_slices(N, R), 256);
+    w.syncfail = off; w.ticket = off + 4; off = align_up(off + 2 * sizeof(uint32_t), 256);
+    w.hsum = off;     off = align_up(off + sizeof(double) * (size_t)R, 256);
     w.rflags = off;   off = align_up(off + sizeof(uint32_t) * (size_t)R, 256);
     w.part_sum = off; off = align_up(off + sizeof(double) * (size_t)w.nblk, 256);
-    w.part_cnt = off; off = align_up(off + sizeof(int64_t) * 2 * (size_t)w.nblk, 256);
+    // two words per block; behind them the entropy sums where a response has several (R * slices <= N / 4096)
+    w.part_cnt = off; off = align_up(off + sizeof(int64_t) * 4 * (size_t)w.nblk, 256);
+    if (entropy_slices(N, R) > 1) w.hsum = w.part_cnt + sizeof(int64_t) * 2 * (size_t)w.nblk;
     w.defer = off;    off = align_up(off + (size_t)N, 256);
+    w.badcu = off;    off = align_up(off + sizeof(uint32_t), 256);
     w.zy = off;       off = align_up(off + (V > 0 ? sizeof(float) * (size_t)N : 0), 256);
     w.defer_list = off;  off = align_up(off + (V > 0 ? sizeof(uint32_t) * (size_t)N : 0), 256);
+    w.defer_count = off; off = align_up(off + sizeof(uint32_t), 256);
     w.total = off;
     return w;
 }

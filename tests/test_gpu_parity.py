@@ -123,6 +123,33 @@ def test_ragged_vocab_and_launch_shapes(dtype, V, per_row):
     assert torch.isnan(buf[:, V:]).all()
 
 
+@pytest.mark.parametrize("dtype,V", [("bf16", v) for v in (12288, 12289, 14336, 16384, 16399, 24001, 32003, 50264, 65536, 67592, 100000, 128256)]
+                         + [("f32", v) for v in (8192, 8193, 13312, 32003, 40964, 81920, 83968, 151936)])
+def test_piece_shapes_by_row_length(dtype, V):
+    """Vocabularies that take each shape of the row-cooperative kernel (one piece, the last piece full, with a
+    remainder, one vector into it), both paths against the oracle and bit for bit with each other."""
+    base = ui.config(1) if dtype == "f32" else ui.config(2)
+    w = ui.shrink(base, [6, 3], V=V, seg_len=4, name="shapes_%s_%d" % (dtype, V))
+    d = ui.generate(w, DEV)
+    vec = 4 if dtype == "f32" else 8
+    stride = (V + vec - 1) // vec * vec
+    buf = torch.full((w.N, stride), float("nan"), dtype=w.torch_dtype(), device=DEV)
+    buf[:, :V] = d["logits"]
+    d["logits"] = buf[:, :V]
+    run_full_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS, tau=0.5), data=d)
+
+
+@pytest.mark.parametrize("lengths", [[20000], [9000, 1, 12000], [3] * 256, [3] * 257, [1, 0, 5] * 120])
+@pytest.mark.parametrize("gate", [ulorl.GATE_PER_RESPONSE, ulorl.GATE_GLOBAL])
+def test_epilogue_partitions(lengths, gate):
+    """Several workgroups per response (long ones), the largest batch whose responses fit the epilogue's table,
+    one more, and empty responses; every token and response against the oracle, with a gate that fires."""
+    w = ui.shrink(ui.config(1), lengths, V=64, seg_len=100, name="epilogue_%d" % len(lengths))
+    p = params_for(w, gate_mode=gate, sigma=1e9, tau=0.3)
+    res, tt, info = run_full_parity(w, p)
+    assert tt.n_masked > 0
+
+
 def test_single_row_single_token_and_empty_response():
     w = ui.shrink(ui.config(1), [1], V=512, seg_len=1, name="one_row")
     run_full_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS))
