@@ -663,17 +663,20 @@ struct LmheadLayout {
 // (tile_coords) form a block of 4 token tiles by 8 slices and share both operands in its L2.
 int stats_splits(int64_t N, int64_t V, int edge, int slots)
 {
-    const int64_t ttiles = (N + edge - 1) / edge, vtiles = (V + edge - 1) / edge;
-    const int lo = (int)(vtiles < 8 ? vtiles : 8), hi = (int)(vtiles < 128 ? vtiles : 128);
+    const int ttiles = (int)((N + edge - 1) / edge), vtiles = (int)((V + edge - 1) / edge);
+    const int lo = vtiles < 8 ? vtiles : 8, hi = vtiles < 128 ? vtiles : 128;
     int best = lo;
-    double best_cost = 0.0;
-    for (int s = lo; s <= hi; ++s) {
-        const double rounds = (double)((ttiles * s + slots - 1) / slots);
-        const double cost = rounds * ((double)((vtiles + s - 1) / s) + 0.35);
-        if (s == lo || cost < best_cost - 1e-9) {
+    double best_cost = (double)(((int64_t)ttiles * lo + slots - 1) / slots) * ((double)((vtiles + lo - 1) / lo) + 0.35);
+    for (int rounds = 1; rounds <= 8; ++rounds) {           // the most slices that fit that many rounds
+        int s = rounds * slots / ttiles;
+        if (s < lo) continue;
+        if (s > hi) s = hi;
+        const double cost = (double)rounds * ((double)((vtiles + s - 1) / s) + 0.35);
+        if (cost < best_cost - 1e-9) {
             best = s;
             best_cost = cost;
         }
+        if (s == hi) break;
     }
     return best;
 }

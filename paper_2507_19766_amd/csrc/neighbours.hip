@@ -31,44 +31,91 @@ __device__ __forceinline__ double block_sum_f64(double x, double* scratch)
 // ---------------------------------------------------------------------------------------------
 // advantage preparation (Eq. 4; dynamic-sampling constraint of Eq. 7; Sec. 3.5)
 // ---------------------------------------------------------------------------------------------
-// One workgroup walks all groups (a step has ~10^2..10^3 of them).
-__global__ __launch_bounds__(kBlock) void group_advantage_kernel(const float* __restrict__ rewards,
-                                                                 const uint8_t* __restrict__ truncated,
-                                                                 const int32_t* __restrict__ cu, int32_t R, int32_t G,
-                                                                 double eps, int unbiased, float* __restrict__ resp_adv,
-                                                                 uint8_t* __restrict__ group_keep,
-                                                                 int64_t* __restrict__ kept_tokens)
+// Statistics of one group: the mean and standard deviation of its rewards (truncated answers count 0), and
+// whether some but not all of its answers are correct.
+struct GroupStats {
+    double mean, sd;
+    bool keep;
+};
+__device__ __forceinline__ double reward_of(const float* __restrict__ rewards, const uint8_t* __restrict__ truncated, int i)
 {
-    __shared__ double scratch[kBlock / 64];
-    const int ngroups = R / G;
+    return (truncated && truncated[i]) ? 0.0 : (double)rewards[i];
+}
+__device__ __forceinline__ GroupStats group_stats(const float* __restrict__ rewards, const uint8_t* __restrict__ truncated, int g0,
+                                                  int G, int unbiased)
+{
+    GroupStats st;
+    double sum = 0.0;
+    int correct = 0;
+#pragma unroll 4
+    for (int i = g0; i < g0 + G; ++i) {
+        const double r = reward_of(rewards, truncated, i);
+        sum += r;
+        correct += r > 0.0;
+    }
+    st.mean = sum / G;
+    double ss = 0.0;
+#pragma unroll 4
+    for (int i = g0; i < g0 + G; ++i) {
+        const double r = reward_of(rewards, truncated, i);
+        ss += (r - st.mean) * (r - st.mean);
+    }
+    const double denom = unbiased ? (G > 1 ? G - 1 : 1) : G;
+    st.sd = sqrt(ss / denom);
+    st.keep = correct > 0 && correct < G;
+    return st;
+}
+__device__ __forceinline__ float advantage_of(const GroupStats& st, double r, double eps)
+{
+    return st.keep ? (float)((r - st.mean) / (st.sd + eps)) : 0.0f;
+}
+
+struct AdvantageArgs {
+    const float* rewards;
+    const uint8_t* truncated;
+    const int32_t* cu;
+    int32_t R, G;
+    int64_t N;
+    double eps;
+    int unbiased;
+    float* resp_adv;
+    uint8_t* group_keep;
+    float* token_adv;
+    int64_t* kept_tokens;
+};
+
+// One workgroup walks all groups (a step has ~10^2..10^3 of them): the per-response outputs.
+__device__ __forceinline__ void group_outputs(const AdvantageArgs& a, double* scratch)
+{
+    const int ngroups = a.R / a.G;
     double kept = 0.0;   // exact in fp64 for any token count below 2^53
     for (int g = threadIdx.x; g < ngroups; g += kBlock) {
-        const int g0 = g * G;
-        double sum = 0.0;
-        int correct = 0;
-        for (int i = g0; i < g0 + G; ++i) {
-            const double r = (truncated && truncated[i]) ? 0.0 : (double)rewards[i];
-            sum += r;
-            correct += r > 0.0;
-        }
-        const double mean = sum / G;
-        double ss = 0.0;
-        for (int i = g0; i < g0 + G; ++i) {
-            const double r = (truncated && truncated[i]) ? 0.0 : (double)rewards[i];
-            ss += (r - mean) * (r - mean);
-        }
-        const double denom = unbiased ? (G > 1 ? G - 1 : 1) : G;
-        const double sd = sqrt(ss / denom);
-        const bool keep = correct > 0 && correct < G;
-        if (group_keep) group_keep[g] = keep ? 1 : 0;
-        for (int i = g0; i < g0 + G; ++i) {
-            const double r = (truncated && truncated[i]) ? 0.0 : (double)rewards[i];
-            resp_adv[i] = keep ? (float)((r - mean) / (sd + eps)) : 0.0f;
-            if (keep) kept += (double)((int64_t)cu[i + 1] - (int64_t)cu[i]);
+        const int g0 = g * a.G;
+        const GroupStats st = group_stats(a.rewards, a.truncated, g0, a.G, a.unbiased);
+        if (a.group_keep) a.group_keep[g] = st.keep ? 1 : 0;
+        for (int i = g0; i < g0 + a.G; ++i) {
+            a.resp_adv[i] = advantage_of(st, reward_of(a.rewards, a.truncated, i), a.eps);
+            if (st.keep) kept += (double)((int64_t)a.cu[i + 1] - (int64_t)a.cu[i]);
         }
     }
     kept = block_sum_f64(kept, scratch);
-    if (threadIdx.x == 0 && kept_tokens) *kept_tokens = (int64_t)kept;
+    if (threadIdx.x == 0 && a.kept_tokens) *a.kept_tokens = (int64_t)kept;
+}
+
+__device__ __forceinline__ int response_at(const int32_t* __restrict__ cu, int32_t R, int64_t t)
+{
+    int lo = 0, hi = R;   // largest i with cu[i] <= t
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if ((int64_t)cu[mid] <= t) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kBlock) void group_advantage_kernel(AdvantageArgs a)
+{
+    __shared__ double scratch[kBlock / 64];
+    group_outputs(a, scratch);
 }
 
 __global__ __launch_bounds__(256) void broadcast_advantage_kernel(const float* __restrict__ resp_adv,
@@ -77,12 +124,25 @@ __global__ __launch_bounds__(256) void broadcast_advantage_kernel(const float* _
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= N) return;
-    int lo = 0, hi = R;   // largest i with cu[i] <= t
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if ((int64_t)cu[mid] <= t) lo = mid; else hi = mid;
+    token_adv[t] = resp_adv[response_at(cu, R, t)];
+}
+
+// Both in one launch: workgroup 0 writes the per-response outputs, the others form the advantage of each of
+// their tokens from its group's rewards again (2 G cached loads), which costs less than a second launch
+// of 4.5 us for groups of up to kGroupAgain answers.
+constexpr int kGroupAgain = 32;
+__global__ __launch_bounds__(kBlock) void advantage_kernel(AdvantageArgs a)
+{
+    __shared__ double scratch[kBlock / 64];
+    if (blockIdx.x == 0) {
+        group_outputs(a, scratch);
+        return;
     }
-    token_adv[t] = resp_adv[lo];
+    const int64_t t = (int64_t)(blockIdx.x - 1) * kBlock + threadIdx.x;
+    if (t >= a.N) return;
+    const int i = response_at(a.cu, a.R, t);
+    const GroupStats st = group_stats(a.rewards, a.truncated, i / a.G * a.G, a.G, a.unbiased);
+    a.token_adv[t] = advantage_of(st, reward_of(a.rewards, a.truncated, i), a.eps);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -220,10 +280,15 @@ int32_t ulorl_advantage_prep(const float* rewards, const uint8_t* truncated, con
     if (R <= 0 || group_size <= 0 || R % group_size != 0 || N <= 0 || N > 0x7fffffffLL) return ULORL_ERR_SHAPE;
     if (!(eps >= 0.0f)) return ULORL_ERR_PARAM;
     hipStream_t st = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(group_advantage_kernel, dim3(1), dim3(kBlock), 0, st, rewards, truncated, cu_seqlens, R, group_size,
-                       (double)eps, unbiased ? 1 : 0, resp_adv, group_keep, kept_tokens);
-    hipLaunchKernelGGL(broadcast_advantage_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, resp_adv, cu_seqlens,
-                       R, N, token_adv);
+    const AdvantageArgs a = {rewards, truncated, cu_seqlens, R, group_size, N, (double)eps, unbiased ? 1 : 0,
+                             resp_adv, group_keep, token_adv, kept_tokens};
+    if (group_size <= kGroupAgain) {
+        hipLaunchKernelGGL(advantage_kernel, dim3((unsigned)((N + kBlock - 1) / kBlock + 1)), dim3(kBlock), 0, st, a);
+    } else {
+        hipLaunchKernelGGL(group_advantage_kernel, dim3(1), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(broadcast_advantage_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, resp_adv, cu_seqlens,
+                           R, N, token_adv);
+    }
     return hipGetLastError() == hipSuccess ? ULORL_OK : ULORL_ERR_HIP;
 }
 

@@ -66,20 +66,22 @@ __device__ __forceinline__ void seg_token_values(bool valid, int32_t seg, int32_
 
 // Adds the workgroup's tokens to table (LDS, [K][7]) and hands it to `out` (global, [K][7], publish());
 // returns the workgroup's count of out-of-range tokens on every thread.  All kSegBlock threads must call.
-// Every wave forms the sums of up to kSegEntries distinct ids of its lanes at a time; one lane per
-// quantity then adds the waves' entries to the table in wave order.  (The waves used to take turns, each
-// with its reductions inside its turn: 55 us for 65536 tokens in 8 segments, now 12.)
+// Every wave forms the sums of up to kSegEntries distinct ids of its lanes at a time (counts by ballot); then
+// each slot of the table picks its entries up in wave order.  (The waves used to take turns, each with its
+// reductions inside its turn: 65536 tokens in 8 segments 55 + 11 us with the final sums, now 8 + 4.)
 constexpr int kSegEntries = 4;
 __device__ __forceinline__ double seg_block_partials(int k, const double (&v)[kSegStats], double oor, int32_t K,
                                                      double* table, double* __restrict__ out)
 {
     constexpr int NW = kSegBlock / 64;
-    __shared__ double entry[NW][kSegEntries][kSegStats];
-    __shared__ int entry_key[NW][kSegEntries];
+    constexpr int NE = NW * kSegEntries;
+    __shared__ double entry[kSegStats][NE];
+    __shared__ int entry_key[NE];
     __shared__ int oor_wave[NW];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < K * kSegStats; i += kSegBlock) table[i] = 0.0;
+    const int slots = K * kSegStats;
+    for (int i = tid; i < slots; i += kSegBlock) table[i] = 0.0;
     const int oor_count = __popcll(__ballot(oor != 0.0));
     if (lane == 0) oor_wave[wave] = oor_count;
     unsigned long long remaining = __ballot(k >= 0);
@@ -87,34 +89,42 @@ __device__ __forceinline__ double seg_block_partials(int k, const double (&v)[kS
     do {
 #pragma unroll 1
         for (int e = 0; e < kSegEntries; ++e) {
+            const int at = wave * kSegEntries + e;
             int key = -1;
             if (remaining != 0ull) {
                 key = __builtin_amdgcn_readlane(k, __ffsll((long long)remaining) - 1);
                 const bool mine = k == key;
-                remaining &= ~__ballot(mine);
-#pragma unroll
-                for (int s = 0; s < kSegStats; ++s) {
-                    const double x = mine ? v[s] : 0.0;
-                    const double sum = s == 2 ? wave_max_f64(x) : wave_sum_f64(x);
-                    if (lane == 0) entry[wave][e][s] = sum;
+                const unsigned long long members = __ballot(mine);
+                remaining &= ~members;
+                const double ratio = wave_sum_f64(mine ? v[1] : 0.0), top = wave_max_f64(mine ? v[2] : 0.0);
+                const double kl = wave_sum_f64(mine ? v[4] : 0.0), ent = wave_sum_f64(mine ? v[5] : 0.0);
+                const int clipped = __popcll(__ballot(mine && v[3] != 0.0)), masked = __popcll(__ballot(mine && v[6] != 0.0));
+                if (lane == 0) {
+                    entry[0][at] = (double)__popcll(members);
+                    entry[1][at] = ratio;
+                    entry[2][at] = top;
+                    entry[3][at] = (double)clipped;
+                    entry[4][at] = kl;
+                    entry[5][at] = ent;
+                    entry[6][at] = (double)masked;
                 }
             }
-            if (lane == 0) entry_key[wave][e] = key;
+            if (lane == 0) entry_key[at] = key;
         }
         more = __syncthreads_or(remaining != 0ull);
-        if (tid < kSegStats) {
-            for (int w = 0; w < NW; ++w)
-                for (int e = 0; e < kSegEntries; ++e) {
-                    const int key = entry_key[w][e];
-                    if (key < 0) break;
-                    double* t = table + key * kSegStats + tid;
-                    const double x = entry[w][e][tid];
-                    *t = tid == 2 ? fmax(*t, x) : *t + x;
-                }
+        for (int i = tid; i < slots; i += kSegBlock) {
+            const int key = i / kSegStats, q = i - key * kSegStats;
+            double t = table[i];
+#pragma unroll 8
+            for (int at = 0; at < NE; ++at) {           // no branch: the loads of several entries overlap
+                const double x = entry[q][at], with = q == 2 ? fmax(t, x) : t + x;
+                t = entry_key[at] == key ? with : t;
+            }
+            table[i] = t;
         }
         __syncthreads();
     } while (more);
-    for (int i = tid; i < K * kSegStats; i += kSegBlock) publish(out + i, table[i]);
+    for (int i = tid; i < slots; i += kSegBlock) publish(out + i, table[i]);      // each thread its own slots
     int total = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) total += oor_wave[w];
@@ -122,14 +132,14 @@ __device__ __forceinline__ double seg_block_partials(int k, const double (&v)[kS
 }
 
 // Final sums over the workgroups' tables, by ONE workgroup of kSegBlock threads.  Slot (k, s) is
-// summed by a group of T threads (T = the largest power of two with K * 7 * T <= kSegBlock, at
-// least 1), each over the blocks b = j, j + T, ... in order, then the T partial sums in order.
+// summed by a group of T threads (T = the largest power of two with K * 7 * T <= kSegBlock, between 1 and
+// 16), each over the blocks b = j, j + T, ... in order, then the T partial sums in order.
 __device__ __forceinline__ void seg_finalize(const SegStatsArgs& a, int64_t nblk, double* scratch /* [kSegBlock] */)
 {
     const int tid = threadIdx.x;
     const int slots = a.K * kSegStats;
     int T = 1;
-    while (slots * T * 2 <= kSegBlock) T *= 2;
+    while (T < 16 && slots * T * 2 <= kSegBlock) T *= 2;
     for (int base = 0; base < slots; base += kSegBlock / T) {
         const int slot = base + tid / T;
         const int j = tid % T;

@@ -37,6 +37,26 @@ def test_advantage_prep_matches_the_oracle(G, unbiased):
         assert 0 < o_keep.sum() < len(o_keep)
 
 
+@pytest.mark.parametrize("G", [31, 32, 33, 96])
+def test_advantage_prep_in_one_or_two_launches(G):
+    """Around the group size up to which the tokens' advantages are formed in the same launch as the
+    responses'; lengths that leave the last workgroup of tokens partly filled."""
+    rs = np.random.RandomState(G)
+    R = 3 * G
+    cu = np.concatenate([[0], np.cumsum(rs.randint(0, 40, size=R))]).astype(np.int32)
+    cu[-1] += 1                                              # at least one token
+    rewards = (rs.rand(R) < 0.4).astype(np.float32)
+    rewards[:G] = 1.0                                        # a dropped group
+    trunc = (rs.rand(R) < 0.1).astype(np.uint8)
+    trunc[:G] = 0
+    resp, keep, tok, kept = ulorl.advantage_prep(torch.from_numpy(rewards).to(DEV), torch.from_numpy(cu).to(DEV), G,
+                                                 truncated=torch.from_numpy(trunc).to(DEV))
+    ref = oracle.advantages(rewards, cu, G, truncated=trunc)
+    np.testing.assert_allclose(resp.cpu().numpy(), ref[0], rtol=1e-6, atol=1e-7)
+    assert torch.equal(tok.cpu(), resp.cpu()[torch.from_numpy(np.repeat(np.arange(R), np.diff(cu)))])
+    assert keep.cpu().tolist() == [0, 1, 1] and int(kept.item()) == ref[3]
+
+
 def test_prepared_advantages_feed_the_token_loss():
     """rewards -> advantages -> loss, all on the device, against the oracle chain."""
     w = ui.shrink(ui.config(2), [60, 45, 80, 30, 50, 50, 20, 70], V=4096, seg_len=32, name="chain")
