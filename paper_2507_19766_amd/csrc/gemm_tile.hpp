@@ -152,8 +152,8 @@ struct TileOperand {
         }
     }
 
-    // This wave's share of half h of the K tile at the cursor, into stage s.
-    __device__ __forceinline__ void copy(int h, int s) const
+    // This wave's share of half h of the K tile `back` tiles before the cursor, into stage s.
+    __device__ __forceinline__ void copy(int h, int s, int back = 0) const
     {
         bf16_t* dst = lds + (s * HALVES + h) * kHalfElems;
 #pragma unroll
@@ -161,10 +161,10 @@ struct TileOperand {
             if constexpr (LAYOUT == K_ROWS) {
                 const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, (int)extent, kRawBufferFlags);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
-                                                         voff[h * J + j], soff, 0, 0);
+                                                         voff[h * J + j], soff - back * kTileK * 2, 0, 0);
             } else {
                 const __amdgpu_buffer_rsrc_t rs =
-                    __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step), 0, (int)extent, kRawBufferFlags);
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step - back * step), 0, (int)extent, kRawBufferFlags);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
                                                          voff[h], 0, 0, 0);
             }
@@ -372,6 +372,59 @@ struct TileLarge {
         read_done<W1>();                   // half 0 of A
         bare_barrier();                    // the multiply phase that would follow
     }
+    // A tile with no column beyond the first 128: only half 0 of B exists, two phases per K tile,
+    //     phase   reads                   copies                     multiplies
+    //     1       B half 0, A half 0      A half 1 of k + 1          (0,0)
+    //     2       A half 1                B, A halves 0 of k + 2     (1,0)
+    // and by the same count of slots as above: what phase 1 reads was waited for at the end of phase 2 before
+    // (three halves are issued after it: six instructions), what phase 2 reads at the end of phase 1
+    // (likewise), and every copy goes where the phase before it read.
+    static __device__ __forceinline__ bool half_tile(const Operand& B, int n0) { return B.count - n0 <= kHalf; }
+    template <bool COPY1, bool COPY2, int W1, int W2>
+    __device__ __forceinline__ void tile_half(int s)
+    {
+        if constexpr (COPY1) a.copy(1, s ^ 1, 1);
+        b.read(0, s, fb[0]);
+        a.read(0, s, fa);
+        read_done<W1>();
+        multiply<0, 0>();
+        if constexpr (COPY2) {
+            b.copy(0, s);
+            a.copy(0, s);
+            a.advance();
+            b.advance();
+        }
+        a.read(1, s, fa);
+        read_done<W2>();
+        multiply<1, 0>();
+    }
+    __device__ __forceinline__ void run_half(int KT)
+    {
+        b.copy(0, 0);
+        a.copy(0, 0);
+        a.copy(1, 0);
+        a.advance();
+        b.advance();
+        if (KT > 1) {
+            b.copy(0, 1);
+            a.copy(0, 1);
+            a.advance();
+            b.advance();
+            ULORL_WAIT_VMEM(6);
+        } else {
+            ULORL_WAIT_VMEM(2);
+        }
+        bare_barrier();
+        if (wm == 1) bare_barrier();
+        int k = 0;
+        for (; k + 2 < KT; ++k) tile_half<true, true, 6, 6>(k & 1);
+        if (KT > 1) {
+            tile_half<true, false, 6, 2>(k & 1);
+            ++k;
+        }
+        tile_half<false, false, 0, -1>(k & 1);
+        if (wm == 0) bare_barrier();
+    }
     // acc = the product over K (a positive multiple of 64).  On return every wave is past its last LDS read.
     __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, int n0, int K)
     {
@@ -379,6 +432,10 @@ struct TileLarge {
         const int KT = K / kTileK;
         a.set_tile(A, m0, K);
         b.set_tile(B, n0, K);
+        if (half_tile(B, n0)) {
+            run_half(KT);
+            return;
+        }
         copy_tile(0);
         if (KT > 1) {
             copy_tile(1);
@@ -414,6 +471,7 @@ struct TileSmall {
     static __device__ __forceinline__ int row_off(int wave, int i) { return (wave >> 1) * 64 + i * 16; }
     static __device__ __forceinline__ int col_off(int wave, int j) { return (wave & 1) * 64 + j * 16; }
     static __device__ __forceinline__ int wave_m(int wave) { return wave >> 1; }
+    static __device__ __forceinline__ bool half_tile(const Operand&, int) { return false; }
 
     __device__ __forceinline__ void init(unsigned char* lds)
     {

@@ -318,6 +318,7 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
     const int t0 = t_tile * Tile::BN;
     const int vb = split * v_per_split;
     const int ve = min(V, vb + v_per_split);
+    const bool half = Tile::half_tile(H, t0);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int quad = lane >> 4;
     constexpr int MI = Tile::MI, NJ = Tile::NJ;
@@ -345,6 +346,7 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
             constexpr bool RAGGED = decltype(ragged_c)::value;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
+                if (half && j >= NJ / 2) break;               // columns without a token
                 float cm = kEmpty;
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
@@ -493,8 +495,10 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
     // padding) is zeroed on the packed pair; the chosen token's element is rewritten by the one lane that holds it.
     // Per element that leaves one FMA, one exponential and half a conversion in the common path.
     const bool ragged = v0 + Tile::BM > vend;     // uniform: the tile reaches past the end of the vocabulary
+    const int n_end = (Ntok + 63) / 64 * 64 - t0;
 #pragma unroll
     for (int j = 0; j < Tile::NJ; ++j) {
+        if (Tile::col_off(0, j) >= n_end) break;  // column blocks of the half that does not exist
         const int n = Tile::col_off(wave, j) + (lane & 15);
         const int t = t0 + n;
         float g_mag = 0.0f, c = 0.0f;
@@ -539,7 +543,7 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
         }
     }
     __syncthreads();
-    Image::store(lds_raw, a.dZ + (int64_t)t0 * a.ld + (v0 - a.vc0), a.ld, (Ntok + 63) / 64 * 64 - t0, a.vc0 + a.cw - v0);
+    Image::store(lds_raw, a.dZ + (int64_t)t0 * a.ld + (v0 - a.vc0), a.ld, n_end, a.vc0 + a.cw - v0);
 }
 
 // One launch of the backward pass over the vocabulary chunks: the two products of the PREVIOUS

@@ -82,6 +82,16 @@ def test_backward_partitions(n, V, hidden):
     assert 0 < tt.n_clip_inactive < n
 
 
+@pytest.mark.parametrize("n,V,hidden", [(1300, 64, 320), (1300, 136, 320), (1408, 264, 384), (1409, 1096, 392), (1537, 200, 512)])
+def test_large_tiles_with_half_empty_ones(n, V, hidden):
+    """Shapes that take the large tile, with a last token tile of 20, 128, 129 and 1 rows (up to 128: the
+    half that runs in two phases), hidden sizes whose last tile is half empty too, and contractions of one
+    to four K tiles in the dHidden product."""
+    w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_halves")
+    for dense in (False, True):
+        run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(dense_rows=dense))
+
+
 def test_lmhead_small_ragged_chunks():
     w = ui.shrink(ui.config(5), [120, 83], V=2056, hidden=136, seg_len=32, name="lmhead_small")
     d = ui.generate(w, DEV)
