@@ -161,8 +161,8 @@ const char *ulorl_status_string(int32_t status);
 /* Bytes of device workspace ulorl_token_loss_fwd / _fwd_bwd need for N rows of V logits
  * in R responses (0 if an argument is out of range).  The workspace holds per-response
  * entropy sums, per-block partial sums, nine bytes per row and 16 bytes per row and
- * per piece of the row (61440 bytes of a long row); its contents need not be preserved
- * between calls.  The size depends on N, V and R only.                              */
+ * per piece of the row (counted as 61440 bytes of a long row); its contents need not be
+ * preserved between calls.  The size depends on N, V and R only.                     */
 size_t ulorl_token_loss_workspace_bytes(int64_t N, int64_t V, int32_t R);
 
 /*
@@ -246,15 +246,15 @@ int32_t ulorl_token_loss_bwd(
  * so every logit is read once and every gradient written once: HBM sees one read and one write
  * per row instead of two reads and a write.  A row's gradient can be formed at once unless it
  * waits for the entropy gate of Sec. 3.2.2: under the PER_RESPONSE and GLOBAL gates the members
- * of the MPT set (A_t > 0, p_t >= tau) are finished by a second, filtered backward launch after
+ * of the MPT set (A_t > 0, p_t >= tau) are collected in a list, which a second launch walks once
  * the gate is known.  Results are bit-identical with ulorl_token_loss_fwd (given a workspace)
  * followed by ulorl_token_loss_bwd: both form a row's statistics from the same pieces in the same
  * order (under ULORL_LAUNCH_PER_ROW both calls take their one-workgroup-per-row kernels, again
  * bit-identical with each other).
  * The workgroups of a row wait for each other with a bounded wait.  One whose wait expires writes
- * nothing -- in place its part of the logits stays intact -- and marks its part; a repair pass at
- * the end of the call (two small launches that return at once when nothing is marked) forms the
- * row's statistics from the published pieces and writes the missing parts, so an expired wait
+ * nothing -- in place its part of the logits stays intact -- and marks its part; a repair pass (in the
+ * kernel that follows, skipped there when nothing is marked) forms the row's statistics from the
+ * published pieces and writes the missing parts, so an expired wait
  * costs time, never data: see ULORL_STATUS_SYNC.
  */
 int32_t ulorl_token_loss_fwd_bwd(

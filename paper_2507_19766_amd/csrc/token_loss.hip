@@ -809,7 +809,7 @@ struct FusedArgs {
 };
 
 // What the one-call path does with a row once its statistics are known: mode 0 = write zeros,
-// 1 = write the gradient with coefficient g, 2 = leave the row to the filtered backward launch that
+// 1 = write the gradient with coefficient g, 2 = leave the row to the listed backward launch that
 // follows the gate (a member of the MPT set under an entropy gate).
 __device__ __forceinline__ int row_decision(const FusedArgs& a, int32_t y, int32_t V, float lse, float lp, float ent,
                                             float adv, float old, uint32_t badcu, float& g)
