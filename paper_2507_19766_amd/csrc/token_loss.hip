@@ -873,7 +873,7 @@ __global__ __launch_bounds__(NT) void fused_row_kernel(const typename Tr::elem* 
 // line; the wait is nevertheless bounded (spin_limit polls, seconds by default).  A workgroup whose
 // wait expires writes NOTHING (in place, its piece of the logits stays intact), re-publishes its
 // second word with the tag kTagPending and raises the sync_fail word; after the kernel every piece's
-// statistics are in the slots, and the repair kernels below finish the row from them.  Every
+// statistics are in the slots, and the repair pass below finishes the row from them.  Every
 // workgroup of a row that completes its wait merges the same pieces in the same order and therefore
 // takes the same decisions; the repair pass merges them in that order too.
 constexpr int kClusterThreads = 256;
