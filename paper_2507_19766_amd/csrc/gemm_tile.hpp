@@ -152,23 +152,25 @@ struct TileOperand {
         }
     }
 
-    // This wave's share of half h of the K tile `back` tiles before the cursor, into stage s.
-    __device__ __forceinline__ void copy(int h, int s, int back = 0) const
+    // This wave's share of half h of the K tile `back` tiles before the cursor, into stage s; one of its J instructions.
+    __device__ __forceinline__ void copy_part(int j, int h, int s, int back = 0) const
     {
         bf16_t* dst = lds + (s * HALVES + h) * kHalfElems;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            if constexpr (LAYOUT == K_ROWS) {
-                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, (int)extent, kRawBufferFlags);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
-                                                         voff[h * J + j], soff - back * kTileK * 2, 0, 0);
-            } else {
-                const __amdgpu_buffer_rsrc_t rs =
-                    __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step - back * step), 0, (int)extent, kRawBufferFlags);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
-                                                         voff[h], 0, 0, 0);
-            }
+        if constexpr (LAYOUT == K_ROWS) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, (int)extent, kRawBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
+                                                     voff[h * J + j], soff - back * kTileK * 2, 0, 0);
+        } else {
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step - back * step), 0, (int)extent, kRawBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
+                                                     voff[h], 0, 0, 0);
         }
+    }
+    __device__ __forceinline__ void copy(int h, int s, int back = 0) const
+    {
+#pragma unroll
+        for (int j = 0; j < J; ++j) copy_part(j, h, s, back);
     }
     __device__ __forceinline__ void advance()
     {
@@ -248,8 +250,8 @@ struct TileOperand {
 // ---------------------------------------------------------------------------------------------
 // 256 x 256 tile, eight waves in two groups of four that take turns
 // ---------------------------------------------------------------------------------------------
-// A wave alternates read phases (fragments LDS -> registers, its share of a copy global -> LDS) and
-// multiply phases (16 MFMAs), with a barrier after each.  The second group runs one phase behind the
+// A wave alternates read phases (fragments LDS -> registers) and multiply phases (16 MFMAs), with a
+// barrier after each; its share of a copy global -> LDS is issued in one of the two, see below.  The second group runs one phase behind the
 // first, and each SIMD holds one wave of each group: while one multiplies, the other reads, so the
 // matrix pipe always has a wave with its operands in registers.  (With all eight waves in step, as
 // before, every wave waited for its fragments at the same time.)
@@ -268,18 +270,29 @@ struct TileOperand {
 //   * A half is read in the read phase after one that ended with a wait for it: each wave waits for its
 //     own share and then passes the barrier; group 1's wait lies in slot s + 1, the first read in s + 2.
 //     Copies complete in order, and six halves (twelve instructions of a wave) are issued after the one
-//     the next phase needs: so every read phase ends with "at most 12 outstanding".
+//     the next phase needs: so every read phase ends with "at most 12 outstanding" -- ten where the
+//     phase's own copy is issued after that wait, in the multiply phase (one slot later: also safe).
 // Both LDS stages are in flight all the time: a copy has six phase pairs (about 3000 clocks) to land.
 //
-// Measured, 2048 x 8192 x 32768 / 32768 x 2048 x 8192: 1500 / 1458 TFLOP/s against 1240 / 1340 for the
-// eight-waves-in-step loop it replaces (hipBLASLt: 1550 / 1570 on the same card).  Raising the
-// multiplying wave's priority (s_setprio) made it 3 % slower.
+// Where the copy goes: the read phase is the longer of the two (four waves take 32 KB out of LDS in about the
+// 256 clocks that 16 MFMAs last), and a copy instruction holds up the reads behind it.  With both operands
+// K_ROWS it is issued right after the reads and overlaps them; a K_COLS read returns only when its data
+// is there, so the copy goes between the MFMAs instead, its two instructions apart.  Products of
+// 8192 x 32768 x 2048, TFLOP/s, copy before the reads / after them / between the MFMAs: both K_ROWS 1493 /
+// 1570 / 1539 (contraction 8192, strided: 1461 / 1557 / 1513), A K_COLS 1425 / 1395 / 1434, both K_COLS
+// 1365 / 1363 / 1412.  (Copies out of L2 only would be 3 to 8 % faster still, no copies at all 22 %.)
+//
+// Against 1240 / 1340 for the eight-waves-in-step loop it replaces at 2048 x 8192 x 32768 / 32768 x 2048 x 8192
+// (hipBLASLt: 1550 / 1570 on the same card).  Raising the multiplying wave's priority (s_setprio) made it
+// 3 % slower.
 template <int LA, int LB>
 struct TileLarge {
     static constexpr int BM = 256, BN = 256, NW = 8, NT = 512;
     static constexpr int WAVES_PER_SIMD = 2;
     static constexpr int MI = 8, NJ = 4;                       // 16 x 16 blocks of a wave
     static constexpr int WAVES_M = 2;
+    static constexpr bool kCopyAfterReads = LA == K_ROWS && LB == K_ROWS;
+    static constexpr int kSteady = kCopyAfterReads ? 12 : 10;  // copy instructions outstanding at the end of a read phase
     static constexpr size_t LDS_BYTES = 8 * (size_t)kHalfElems * sizeof(bf16_t);
 
     TileOperand<LA, NW, 2, 4> a;
@@ -306,18 +319,27 @@ struct TileLarge {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    template <int H, int G>
-    __device__ __forceinline__ void multiply()
+    // 16 MFMAs; `copy(j)` issues instruction j (0, 1) of a copy between them.
+    template <int H, int G, class Copy>
+    __device__ __forceinline__ void multiply(Copy copy)
     {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
                     acc[H * 4 + i][G * 2 + j] =
                         __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ks][i], fb[G][ks][j], acc[H * 4 + i][G * 2 + j], 0, 0, 0);
+                if (ks == 0 && i == 1) copy(0);
+                if (ks == 1 && i == 0) copy(1);
+            }
         bare_barrier();
+    }
+    template <int H, int G>
+    __device__ __forceinline__ void multiply()
+    {
+        multiply<H, G>([](int) {});
     }
     // End of a read phase: the fragments are in registers, and at most VM of this wave's copies are outstanding.
     template <int VM>
@@ -331,26 +353,35 @@ struct TileLarge {
     template <bool COPY, bool NEXT, int W1, int W2, int W3, int W4>
     __device__ __forceinline__ void tile(int s)
     {
-        if constexpr (COPY) b.copy(0, s);
         a.read(0, s, fa);
-        read_done<W1>();
-        multiply<0, 0>();
-        if constexpr (COPY) a.copy(0, s);
+        phase<0, 0, COPY, W1>(b, 0, s);
         b.read(1, s, fb[1]);
-        read_done<W2>();
-        multiply<0, 1>();
-        if constexpr (COPY) b.copy(1, s);
+        phase<0, 1, COPY, W2>(a, 0, s);
         a.read(1, s, fa);
-        read_done<W3>();
-        multiply<1, 0>();
+        phase<1, 0, COPY, W3>(b, 1, s);
+        if constexpr (NEXT) b.read(0, s ^ 1, fb[0]);
+        phase<1, 1, COPY, W4>(a, 1, s);
         if constexpr (COPY) {
-            a.copy(1, s);
             a.advance();
             b.advance();
         }
-        if constexpr (NEXT) b.read(0, s ^ 1, fb[0]);
-        read_done<W4>();
-        multiply<1, 1>();
+    }
+    // The rest of a phase whose reads have been issued: the copy of half h of operand op, the waits, the MFMAs.
+    template <int H, int G, bool COPY, int W, class Op>
+    __device__ __forceinline__ void phase(const Op& op, int h, int s)
+    {
+        if constexpr (COPY && kCopyAfterReads) {
+            __builtin_amdgcn_sched_barrier(0);
+            op.copy(h, s);
+        }
+        read_done<W>();
+        multiply<H, G>([&](int j) {
+            if constexpr (COPY && !kCopyAfterReads) {
+                __builtin_amdgcn_sched_barrier(0);
+                op.copy_part(j, h, s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
     }
     __device__ __forceinline__ void copy_tile(int s)
     {
@@ -444,7 +475,7 @@ struct TileLarge {
             copy_tile(1);
             start<14, 12>();
             int k = 0;
-            for (; k + 2 < KT; ++k) tile<true, true, 12, 12, 12, 12>(k & 1);
+            for (; k + 2 < KT; ++k) tile<true, true, kSteady, kSteady, kSteady, kSteady>(k & 1);
             tile<false, true, 10, 8, 6, 4>(k & 1);
             ++k;
             tile<false, false, 2, 0, -1, -1>(k & 1);
