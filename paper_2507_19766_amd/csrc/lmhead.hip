@@ -32,6 +32,7 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kEmpty = -1.0e30f;
+constexpr float kWide = 536870912.0f;        // 2^29, see lmhead_stats_kernel
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -325,7 +326,9 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
 
     // Per token column of this lane: running max m, S + Sc = sum 2^(z log2e - fl(m log2e)), T = the same weighted
     // with its exponent (log2 units).  The exponents carry the rounding residual of fl(m log2e), the
-    // same for every term; it is taken out once at the end.
+    // same for every term; it is taken out once at the end.  The residual grows with m: from kWide on it
+    // exceeds 32 and soon the range of 2^x, so a workgroup that met such a maximum (S is 0 or not finite, or the last
+    // maximum is one) walks its tiles again and takes those columns' sums from exponents of z - m.
     float m[NJ], S[NJ], Sc[NJ], T[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -390,11 +393,49 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
         if (v0 + Tile::BM <= ve) absorb_tile(std::false_type{});
         else absorb_tile(std::true_type{});
     }
+    auto is_wide = [&](int j) { return !(S[j] > 0.0f && S[j] < 3.0e38f) || fabsf(m[j]) >= kWide; };
+    bool any_wide = false;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+        if (!half || j < NJ / 2) any_wide |= is_wide(j);
+    // The OR over the waves goes through token[], which is done with: __syncthreads_or brings LDS of its own, after
+    // which the stages no longer start at a multiple of 8 KB, and that costs 1.5 % of the kernel.
+    __syncthreads();
+    if (threadIdx.x < 64) token[threadIdx.x] = 0;
+    __syncthreads();
+    if (__any(any_wide) && lane == 0) token[wave] = 1;
+    __syncthreads();
+    const bool again = __any(token[lane]);
+    float S2[NJ], T2[NJ];
+    if (again) {                                              // rare: the maxima are known now
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) S2[j] = T2[j] = 0.0f;
+#pragma unroll 1
+        for (int v0 = vb; v0 < ve; v0 += Tile::BM) {
+            G.run(W, v0, H, t0, K);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float x = (G.acc[i][j][r] - m[j]) * kLog2e;
+                        const float e = fast_exp2(x);
+                        if (v0 + Tile::row_off(wave, i) + 4 * quad + r < ve) {
+                            S2[j] += e;
+                            T2[j] = fmaf(e, x, T2[j]);
+                        }
+                    }
+        }
+    }
 
     // four lanes (L, L ^ 16, L ^ 32, L ^ 48) share a token column; then the waves stacked along the vocabulary
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        const float delta = m[j] > 0.5f * kEmpty ? fmaf(m[j], kLog2e, -(m[j] * kLog2e)) : 0.0f;
+        float delta = m[j] > 0.5f * kEmpty ? fmaf(m[j], kLog2e, -(m[j] * kLog2e)) : 0.0f;
+        if (again && is_wide(j)) {
+            S[j] = S2[j]; Sc[j] = delta = 0.0f; T[j] = T2[j];
+        }
         const float un = fast_exp2(-delta);
         float mm = m[j], SS = un * (S[j] + Sc[j]), TT = un * fmaf(-delta, S[j], T[j]) * kLn2;
 #pragma unroll

@@ -228,3 +228,34 @@ def test_backward_with_few_or_no_live_rows(n_live):
     else:
         assert bool((dH[keep].float().abs().sum(dim=1) > 0).all())
         _assert_dw_same_up_to_rounding(dW, dW2)
+
+
+@pytest.mark.parametrize("n", [200, 300])        # the small and the large tile
+def test_forward_statistics_of_large_logits(n):
+    """Logits far beyond the range a model produces still have a log-sum-exp and an entropy: +-2^20 with
+    the maxima of one slice's tiles on both sides of it, 1.25 2^28 in steps of 32, 2^29 times small numbers
+    of either sign (maxima on both sides of the point where the statistics change their exponents; the
+    softmax is shared by the ties at the top) and 2^32 (all equal in fp32).  Two non-zero hidden dimensions keep every sum exact, so the reference is that of the
+    fp32 logits; what is left is the fp32 resolution of lse and of a difference of logits."""
+    V, Hd = 65536 + 8, 320                        # three tiles of 256 columns to a slice
+    g = torch.Generator(device=DEV).manual_seed(n)
+    w = torch.zeros(Hd, V, device=DEV)
+    w[0] = 1024.0
+    w[7] = torch.randint(-127, 128, (V,), generator=g, device=DEV) / 8.0
+    first = (torch.arange(V, device=DEV) // 256) % 3 == 0
+    w[7] -= torch.where(first, 16.0, 0.0)         # multiples of 1/8 up to 32: 8 bits
+    h = torch.zeros(n, Hd, device=DEV)
+    kind = torch.arange(n, device=DEV) % 6
+    h[:, 0] = torch.tensor([1024.0, -1024.0, 0.0, 2.0 ** 22, 0.0, 1.25 * 2.0 ** 18], device=DEV)[kind]
+    h[:, 7] = torch.tensor([1.0, 1.0, 2.0 ** 29, 1.0, -2.0 ** 29, 256.0], device=DEV)[kind]
+    h, w = h.bfloat16(), w.bfloat16()
+    y = torch.randint(0, V, (n,), generator=g, device=DEV, dtype=torch.int32)
+    res = ulorl.lmhead_token_loss_fwd(h, w, y, None, None)
+    z = (h[:, :8].double() @ w[:8].double()).float().double()
+    lse = torch.logsumexp(z, 1)
+    logp = z - lse[:, None]
+    ent = -(logp.exp() * torch.where(logp > -700, logp, 0.0)).sum(1)
+    at = logp.gather(1, y[:, None].long())[:, 0]
+    assert torch.all((res.lse.double() - lse).abs() <= 2.0 ** -23 * lse.abs() + 2e-6)
+    assert torch.all((res.entropy.double() - ent).abs() <= 2e-5 * ent + 2e-5), float((res.entropy.double() - ent).abs().max())
+    assert torch.all((res.logp.double() - at).abs() <= 1e-6 * at.abs() + 2e-6 + 2e-6 * ent)
