@@ -307,7 +307,7 @@ int32_t ulorl_token_loss_fwd_bwd_static(
  *                 operands in the backward pass; larger batches are split by the caller)
  *   vocab_chunk   multiple of 64, at most 2^22 - 256; the backward pass materialises dlogits one chunk of this many
  *                 vocabulary columns at a time ([N, vocab_chunk] bf16, twice) in the workspace, or
- *                 of more where 256 MB hold more
+ *                 of more where the workspace has room for more
  * Logits are formed tile by tile with bf16 MFMA and fp32 accumulation and consumed in registers.
  * Everything else (token ids, cu_seqlens, old_logp, advantages, parameters, per-token and
  * per-response outputs, counters, status bits) is exactly as in ulorl_token_loss_fwd, including
@@ -315,11 +315,14 @@ int32_t ulorl_token_loss_fwd_bwd_static(
  * the workspace is still needed, sized with any R >= 1).
  *
  * The workspace (ulorl_lmhead_workspace_bytes, 256-byte aligned) holds two dlogits chunk buffers (one
- * chunk's gradient products read theirs while the next chunk's are written: 2 x N x vocab_chunk x 2
- * bytes, or 2 x 64 to 256 MB where that is more), an fp32 accumulator for dHidden (up to eight where
- * there are few rows), the gathered live rows of hidden with their index maps, the token-loss
- * workspace, and a zero-padded copy of W when Hd or V is no multiple of 64;
- * nothing in it needs to survive between the forward and the backward call.
+ * chunk's gradient products read theirs while the next chunk's are written), one to eight fp32
+ * accumulators for dHidden, the gathered live rows of hidden with their index maps and the
+ * token-loss workspace; with Hd no multiple of 64 (or V no multiple of 64 and below 2 N), a zero-padded
+ * copy of W as well.  Its size does not fall as N, R or vocab_chunk grow, so one sized for the longest
+ * batch serves every shorter one.  Beyond what one chunk of vocab_chunk columns needs, a call takes at
+ * most 16 KB per column of vocab_chunk, or twice hidden and W plus four chunks if that is more (never
+ * more than it can use): chunks are widened within that, up to 256 MB a buffer.  Nothing in it needs
+ * to survive between the forward and the backward call.
  */
 size_t ulorl_lmhead_workspace_bytes(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk);
 

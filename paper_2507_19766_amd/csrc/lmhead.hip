@@ -603,8 +603,9 @@ struct BwdStepArgs {
     int64_t ld_w;
     // dHidden accumulator: acc[t, k] (+)= sum_v W[k, vp + v] dZ[t, v]
     Operand dh_w, dh_z;              // K_ROWS both; dh_z.count is replaced by the live count
+    const bf16_t* dh_tail;           // W's columns from vp + dh_K to V, padded to [Hd][64] with zeros (may be NULL)
     int dh_K, dh_accumulate, dh_splits;
-    float* dh_acc;                   // [dh_splits][N][Hd]
+    float* dh_acc;                   // [dh_splits, + 1 with a tail][N][Hd]
     int dh_first;                    // dHidden's tiles are the longer ones
     DzArgs dz;
     int have_products, have_dz;
@@ -631,25 +632,28 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
         const int nt = (rows + B - 1) / B, nh = (a.dh_w.count + B - 1) / B;
         const int g_dw = (int)tile_grid(nk, nv);
         const int g_dh1 = rows > 0 ? (int)tile_grid(nt, nh) : 0;
-        const int g_dh = g_dh1 * a.dh_splits;
+        const int g_dh = g_dh1 * (a.dh_splits + (a.dh_tail != nullptr ? 1 : 0));
         if (bid < g_dw + g_dh) {
             const int dh_bid = a.dh_first ? bid : bid - g_dw;
             if (dh_bid >= 0 && dh_bid < g_dh) {
                 if (!tile_coords(dh_bid % g_dh1, nt, nh, a.group_m, tn, tm)) return;
                 const int split = dh_bid / g_dh1;
+                const bool tail = split == a.dh_splits;           // W's last columns, once, into a slab of their own
                 const int per = (a.dh_K / kTileK + a.dh_splits - 1) / a.dh_splits * kTileK;
-                const int k0 = split * per, K = min(per, a.dh_K - k0);
-                if (K <= 0 && a.dh_accumulate) return;
+                const int k0 = tail ? a.dh_K : split * per, K = tail ? kTileK : min(per, a.dh_K - k0);
+                const bool add = a.dh_accumulate && !tail;
+                if (K <= 0 && add) return;
                 TileDh T;
                 T.init(lds_raw);
                 Operand w = a.dh_w, z = a.dh_z;
-                w.p += k0;
+                w.p = tail ? a.dh_tail : w.p + k0;
+                w.ld = tail ? kTileK : w.ld;
                 z.p += k0;
                 z.count = rows;
                 if (K > 0) T.run(w, tm * B, z, tn * B, K);
                 else T.clear();
                 float* acc = a.dh_acc + (int64_t)split * a.N * a.dh_w.count;
-                if (a.dh_accumulate) store_tile_f32<true>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
+                if (add) store_tile_f32<true>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
                 else store_tile_f32<false>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
                 return;
             }
@@ -692,12 +696,23 @@ inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd) { return o.
 
 inline int tile_edge(int tile) { return tile == 1 ? TileSmall<K_ROWS, K_ROWS>::BM : TileLarge<K_ROWS, K_ROWS>::BM; }
 
+constexpr int kComputeUnits = 256;
+
+// Workspace of one call.  The forward and the backward call lay the same bytes out differently.
 struct LmheadLayout {
-    size_t wp, dz[2], dhacc, partial, token_ws, hc, pos, row_map, block_count, n_live, total;
+    size_t total;
+    size_t wp;                                                            // both calls
+    size_t hp, token_ws, partial;                                         // forward
+    size_t dz[2], dhacc, tail, rows, pos, row_map, block_count, n_live;   // backward
     int64_t hd64, v64;   // padded hidden size and vocabulary
-    bool pad_w;          // W is copied with padded rows and columns (Hd or V no multiple of 64)
+    bool pad_k;          // the products read copies of hidden and W with zeros up to hd64 (Hd no multiple of 64)
+    // V no multiple of 64: the dHidden product, which contracts over the vocabulary, reads a copy of W with zeros up to
+    // v64 (pad_v) or takes W's last columns from a small copy of theirs, into an accumulator of their own (tail_v).
+    // The first moves 4 V Hd bytes, the second 8 N Hd.  Backward, 1000 columns: 20000 x 2048 570 / 650 us, x 5120 905 / 1110;
+    // 50264 columns: 150 x 128 96 / 93, 100008 columns: 3000 x 1024 1860 / 1725.
+    bool pad_v, tail_v;
     int64_t chunk;       // vocabulary columns per backward launch, a multiple of 64 (leading dimension of dZ)
-    int dh_splits;
+    int dh_splits, dh_slabs;
     int splits;
     int v_per_split;
 };
@@ -706,10 +721,10 @@ struct LmheadLayout {
 // of the chip's tile slots times tiles per slice (plus about a third of a tile per workgroup for its
 // start and its merge) is what the launch costs; at least 8 slices, so that the workgroups of an XCD
 // (tile_coords) form a block of 4 token tiles by 8 slices and share both operands in its L2.
-int stats_splits(int64_t N, int64_t V, int edge, int slots)
+int stats_splits(int64_t N, int64_t V, int edge, int slots, int most)
 {
     const int ttiles = (int)((N + edge - 1) / edge), vtiles = (int)((V + edge - 1) / edge);
-    const int lo = vtiles < 8 ? vtiles : 8, hi = vtiles < 128 ? vtiles : 128;
+    const int lo = vtiles < 8 ? vtiles : 8, hi = vtiles < most ? vtiles : most;
     int best = lo;
     double best_cost = (double)(((int64_t)ttiles * lo + slots - 1) / slots) * ((double)((vtiles + lo - 1) / lo) + 0.35);
     for (int rounds = 1; rounds <= 8; ++rounds) {           // the most slices that fit that many rounds
@@ -726,64 +741,121 @@ int stats_splits(int64_t N, int64_t V, int edge, int slots)
     return best;
 }
 
-constexpr int kComputeUnits = 256;
-
-LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk, int tile)
+LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk, int fwd_tile)
 {
-    const int edge = tile_edge(tile);
     LmheadLayout L;
     L.hd64 = round_up64(Hd);
     L.v64 = round_up64(V);
-    L.pad_w = L.hd64 != Hd || L.v64 != V;
+    L.pad_k = L.hd64 != Hd;
+    L.pad_v = L.v64 != V && (L.pad_k || V < 2 * N);
+    L.tail_v = L.v64 != V && !L.pad_v;
     const int64_t n64 = round_up64(N);
+    const size_t padded_w = (size_t)L.hd64 * (size_t)L.v64 * 2;
+    const size_t token_ws = workspace_layout(N, 0, R).total;
+    const size_t count_blocks = (size_t)((N + kLiveBlock - 1) / kLiveBlock) * sizeof(int);
+    const size_t slice = (size_t)N * sizeof(StatQuad), slab = (size_t)N * Hd * 4, column = (size_t)n64 * 2;
+    size_t off;
+    auto place = [&](size_t bytes) {
+        const size_t at = off;
+        off = align_up(off + bytes, 256);
+        return at;
+    };
+    auto larger = [](size_t x, size_t y) { return x > y ? x : y; };
+    auto smaller = [](size_t x, size_t y) { return x < y ? x : y; };
+    auto forward = [&](size_t slices) {
+        off = 0;
+        L.wp = place(L.pad_k ? padded_w : 0);
+        L.hp = place(L.pad_k ? (size_t)n64 * L.hd64 * 2 : 0);
+        L.token_ws = place(token_ws);
+        L.partial = place(slices * slice);
+        return off;
+    };
+    // The dZ chunks in front: 5.55 ms where they began at any multiple of 256 bytes 5.88 (20000 x 128 x 151936).
+    auto backward = [&](size_t dz_bytes, int buffers, size_t slab_bytes) {
+        off = 0;
+        L.wp = place(L.pad_k || L.pad_v ? padded_w : 0);
+        L.dz[0] = place(dz_bytes);
+        L.dz[1] = buffers == 2 ? place(dz_bytes) : L.dz[0];
+        L.dhacc = place(slab_bytes);
+        L.tail = place(L.v64 != V && !L.pad_k ? (size_t)Hd * kTileK * 2 : 0);
+        L.rows = place((size_t)n64 * L.hd64 * 2);
+        L.pos = place((size_t)N * sizeof(int));
+        L.row_map = place((size_t)n64 * sizeof(int));
+        L.block_count = place(count_blocks);
+        L.n_live = place(sizeof(int));
+        return off;
+    };
 
-    // Columns per backward launch: the caller's vocab_chunk, or what a dz buffer of 64 to 256 MB (as W and
-    // hidden are larger) holds, where that is more: with few rows a chunk of 8192 columns is too little
-    // work for 256 compute units.  777 x 2048 x 151936: 20 steps of 8192 columns 3.3 ms, all columns in one
-    // chunk 1.4 ms.  With 16384 rows and more the width does not matter (8192, 16384, 32768: +-0.5 %).
+    // What more room than the least is used for.  Statistics: 8 to 128 slices.  dHidden (see BwdStepArgs): enough tiles for
+    // every compute unit, at most 8 parts.  dZ: vocab_chunk columns, or what a buffer of 64 to 256 MB (as W and
+    // hidden are larger) holds: with few rows a chunk of 8192 columns is too little work for 256 compute
+    // units.  777 x 2048 x 151936: 20 steps of 8192 columns 3.3 ms, all columns in one chunk 1.4 ms.  With 16384 rows
+    // and more the width does not matter (8192, 16384, 32768: +-0.5 %).
+    const int tail_slab = L.tail_v ? 1 : 0;
     const int64_t weights = (V + N) * Hd;                        // half the bytes of hidden and W
-    int64_t budget = weights < ((int64_t)64 << 20) ? ((int64_t)64 << 20) : weights > ((int64_t)256 << 20) ? ((int64_t)256 << 20) : weights;
-    int64_t chunk = round_up64(vocab_chunk);
-    const int64_t fits = budget / (2 * n64) / 256 * 256;
-    if (chunk < fits) chunk = fits;
-    if (chunk > kMaxLeadingDim - 256) chunk = (kMaxLeadingDim - 256) / 64 * 64;      // at least vocab_chunk: see check_lmhead
-    if (chunk > L.v64) chunk = L.v64;
-    L.chunk = chunk;
-    const int buffers = chunk < V ? 2 : 1;
+    const size_t budget = weights < ((int64_t)64 << 20) ? (size_t)64 << 20 : weights > ((int64_t)256 << 20) ? (size_t)256 << 20 : (size_t)weights;
+    const int64_t least = vocab_chunk < L.v64 ? vocab_chunk : L.v64;
+    const size_t dz_least = align_up(column * least, 256), dz_all = align_up(column * L.v64, 256);
+    constexpr size_t kTileRound = (size_t)kComputeUnits * 256 * 256 * 4;
+    const size_t slabs_most = larger(slab, smaller(8 * slab, kTileRound)) + tail_slab * slab;
 
-    // Parts of the dHidden contraction (see BwdStepArgs): enough tiles for every compute unit, at most 8
-    // (a slab is N x Hd fp32), none shorter than 16 K tiles.  The same for every tile shape.
-    const int64_t dh_tiles = ((N + 255) / 256) * ((Hd + 255) / 256);
-    int64_t dh_splits = kComputeUnits / dh_tiles;
-    if (dh_splits > 8) dh_splits = 8;
-    if (dh_splits > chunk / 1024) dh_splits = chunk / 1024;
-    L.dh_splits = dh_splits < 1 ? 1 : (int)dh_splits;
+    // What a call asks for grows with N, R and vocab_chunk, so that a workspace sized for the largest batch serves the
+    // smaller ones, and has a bound that vocab_chunk sets: the larger of 16 KB a column beyond the least, and twice hidden
+    // and W, four dZ chunks, one dHidden accumulator, 16 statistics a row and the token loss.
+    const size_t need = larger(forward(8), backward(dz_least, 2, (1 + tail_slab) * slab));
+    const size_t dz_most = dz_all <= budget ? larger(2 * dz_least, dz_all) : 2 * larger(dz_least, budget);
+    const size_t use = larger(forward(128), backward(dz_most, 1, slabs_most));
+    off = 0;
+    if (L.pad_k) place(padded_w);
+    place((size_t)V * Hd * 2);
+    place((size_t)Hd * n64 * 2);
+    for (int b = 0; b < 2; ++b) {
+        place((size_t)N * vocab_chunk * 2);
+        place((size_t)vocab_chunk * n64 * 2);
+    }
+    place(slab);
+    place(16 * slice);
+    place(token_ws);
+    place((size_t)N * Hd * 2);
+    place((size_t)N * sizeof(int));
+    place((size_t)n64 * sizeof(int));
+    place(count_blocks);
+    place(sizeof(int));
+    L.total = larger(need, smaller(use, larger(off, need + (size_t)vocab_chunk * 16384)));
 
+    const size_t room_slices = (L.total - forward(0)) / slice;
+    const int edge = tile_edge(fwd_tile);
     const int64_t vtiles = (V + edge - 1) / edge;
-    const int s_large = stats_splits(N, V, tile_edge(0), kComputeUnits), s_small = stats_splits(N, V, tile_edge(1), 2 * kComputeUnits);
-    const int64_t per_split = (vtiles + (tile == 1 ? s_small : s_large) - 1) / (tile == 1 ? s_small : s_large);
+    const int64_t slices = stats_splits(N, V, edge, fwd_tile == 1 ? 2 * kComputeUnits : kComputeUnits, (int)smaller(room_slices, 128));
+    const int64_t per_split = (vtiles + slices - 1) / slices;
     L.v_per_split = (int)(per_split * edge);
     L.splits = (int)((vtiles + per_split - 1) / per_split);
-    // the workspace does not depend on the launch options: room for either tile shape's slices
-    const size_t max_splits = s_large > s_small ? s_large : s_small;
 
-    size_t off = 0;
-    L.wp = off;      off = align_up(off + (L.pad_w ? (size_t)L.hd64 * (size_t)L.v64 * 2 : 0), 256);
-    // two dz buffers: one chunk's products read theirs while the next chunk's dz is written
-    for (int b = 0; b < buffers; ++b) {
-        L.dz[b] = off;  off = align_up(off + (size_t)n64 * L.chunk * 2, 256);
+    // Every column in one dZ buffer if that and one accumulator fit, else up to a quarter of the room for the accumulators.
+    const size_t room = L.total - backward(0, 1, 0);
+    auto slabs = [&](int64_t n) { return align_up((size_t)(n + tail_slab) * slab, 256); };
+    int64_t dh_splits = kComputeUnits / (((N + 255) / 256) * ((Hd + 255) / 256));
+    if (dh_splits > 8) dh_splits = 8;
+    int64_t chunk = L.v64;
+    if (chunk <= kMaxLeadingDim - 256 && slabs(1) + dz_all <= room) {
+        while (dh_splits > 1 && slabs(dh_splits) + dz_all > room) --dh_splits;
+    } else {
+        while (dh_splits > 1 && (slabs(dh_splits) + 2 * dz_least > room || slabs(dh_splits) > room / 4)) --dh_splits;
+        const size_t half = (room - slabs(dh_splits < 1 ? 1 : dh_splits)) / 2 / 256 * 256;
+        chunk = (int64_t)(smaller(budget, half) / column / 64 * 64);
+        if (chunk >= 256) chunk = chunk / 256 * 256;
+        if (chunk < vocab_chunk) chunk = vocab_chunk;
+        if (chunk > kMaxLeadingDim - 256) chunk = (kMaxLeadingDim - 256) / 64 * 64;      // at least vocab_chunk: see check_lmhead
+        if (chunk > L.v64) chunk = L.v64;
     }
-    if (buffers == 1) L.dz[1] = L.dz[0];
-    L.dhacc = off;   off = align_up(off + (size_t)L.dh_splits * N * Hd * 4, 256);
-    L.partial = off; off = align_up(off + max_splits * (size_t)N * sizeof(StatQuad), 256);
-    L.token_ws = off; off = align_up(off + workspace_layout(N, 0, R).total, 256);
-    // backward over the live rows only: gathered hidden rows, row <-> position maps, scan scratch
-    L.hc = off;          off = align_up(off + (size_t)n64 * L.hd64 * 2, 256);
-    L.pos = off;         off = align_up(off + (size_t)N * sizeof(int), 256);
-    L.row_map = off;     off = align_up(off + (size_t)n64 * sizeof(int), 256);
-    L.block_count = off; off = align_up(off + (size_t)((N + kLiveBlock - 1) / kLiveBlock) * sizeof(int), 256);
-    L.n_live = off;      off = align_up(off + sizeof(int), 256);
-    L.total = off;
+    if (dh_splits > chunk / 1024) dh_splits = chunk / 1024;      // no part shorter than 16 K tiles
+    if (dh_splits < 1) dh_splits = 1;
+    L.chunk = chunk;
+    L.dh_splits = (int)dh_splits;
+    L.dh_slabs = L.dh_splits + tail_slab;
+    forward(L.splits);
+    // two dz buffers: one chunk's products read theirs while the next chunk's dz is written
+    backward(column * chunk, chunk < V ? 2 : 1, (size_t)L.dh_slabs * slab);
     return L;
 }
 
@@ -861,7 +933,7 @@ bool launch_bwd_step(const BwdStepArgs& a, hipStream_t st)
     unsigned grid = 0;
     if (a.have_products) {
         grid += tile_grid((a.dw_h.count + B - 1) / B, (a.dw_z.count + B - 1) / B);
-        grid += tile_grid((a.N + B - 1) / B, (a.dh_w.count + B - 1) / B) * (unsigned)a.dh_splits;
+        grid += tile_grid((a.N + B - 1) / B, (a.dh_w.count + B - 1) / B) * (unsigned)(a.dh_splits + (a.dh_tail != nullptr ? 1 : 0));
     }
     if (a.have_dz) grid += tile_grid((a.dz.cw + B - 1) / B, (a.N + B - 1) / B);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Tile::NT), lds, st, a);
@@ -946,12 +1018,12 @@ int32_t ulorl_lmhead_token_loss_fwd(const void* hidden, const void* W, int64_t N
     char* ws = (char*)workspace;
     StatQuad* partial = (StatQuad*)(ws + L.partial);
 
-    const Operand Wop = weight_operand((const bf16_t*)W, Hd, V, L, ws, L.hd64 != Hd, st);
+    const Operand Wop = weight_operand((const bf16_t*)W, Hd, V, L, ws, L.pad_k, st);
     Operand Hop = {(const bf16_t*)hidden, Hd, (int)N};
-    if (L.hd64 != Hd) {
-        bf16_t* hc = (bf16_t*)(ws + L.hc);
-        launch_copy_rows_padded((const bf16_t*)hidden, Hd, N, Hd, hc, L.hd64, st);
-        Hop = Operand{hc, L.hd64, (int)N};
+    if (L.pad_k) {
+        bf16_t* hp = (bf16_t*)(ws + L.hp);
+        launch_copy_rows_padded((const bf16_t*)hidden, Hd, N, Hd, hp, L.hd64, st);
+        Hop = Operand{hp, L.hd64, (int)N};
     }
     const bool ok = tile == 1
                         ? launch_stats<TileSmall>(Wop, Hop, (int)L.hd64, token_ids, L, partial, opts.gemm_group_m, st)
@@ -988,9 +1060,15 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     float* dHacc = (float*)(ws + L.dhacc);
-    bf16_t* hc = (bf16_t*)(ws + L.hc);
+    bf16_t* hc = (bf16_t*)(ws + L.rows);
     const bf16_t* H = (const bf16_t*)hidden;
-    const Operand Wop = weight_operand((const bf16_t*)W, Hd, V, L, ws, L.pad_w, st);
+    const Operand Wop = weight_operand((const bf16_t*)W, Hd, V, L, ws, L.pad_k || L.pad_v, st);
+    const int64_t v_whole = L.tail_v ? V / kTileK * kTileK : L.v64;      // columns that whole K tiles of the dHidden product cover
+    bf16_t* w_tail = nullptr;
+    if (L.tail_v) {
+        w_tail = (bf16_t*)(ws + L.tail);
+        launch_copy_rows_padded((const bf16_t*)W + v_whole, V, Hd, V - v_whole, w_tail, kTileK, st);
+    }
 
     // Live rows (those with a non-zero coefficient): positions in order and gathered hidden rows.
     // ULORL_LAUNCH_DENSE_ROWS runs every row through the products instead.
@@ -1016,7 +1094,7 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
         }
         launch_copy_rows_padded(H, Hd, N, Hd, hc, L.hd64, st, mapw, nlw);
         row_map = mapw; pos = posw; n_live = nlw;
-    } else if (L.hd64 != Hd || N % 64 != 0) {
+    } else if (L.pad_k || N % 64 != 0) {
         launch_copy_rows_padded(H, Hd, N, Hd, hc, L.hd64, st);
     } else {
         Hop.p = H;
@@ -1044,7 +1122,8 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
             a.ld_w = V;
             a.dh_w = Operand{Wop.p + vp, Wop.ld, (int)Hd};
             a.dh_z = Operand{dZ, L.chunk, (int)N};
-            a.dh_K = (int)round_up64(cwp);
+            a.dh_K = (int)(vp + L.chunk < v_whole ? L.chunk : v_whole - vp);
+            a.dh_tail = c == n_chunks ? w_tail : nullptr;
             a.dh_accumulate = c > 1;
             a.dh_splits = L.dh_splits;
             a.dh_acc = dHacc;
@@ -1062,7 +1141,7 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
         if (!ok || hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
     }
     const int64_t nh = N * Hd;
-    hipLaunchKernelGGL(dhidden_finish_kernel, dim3((unsigned)((nh / 8 + 255) / 256)), dim3(256), 0, st, (const float*)dHacc, L.dh_splits, pos,
+    hipLaunchKernelGGL(dhidden_finish_kernel, dim3((unsigned)((nh / 8 + 255) / 256)), dim3(256), 0, st, (const float*)dHacc, L.dh_slabs, pos,
                        N, (int)Hd, (bf16_t*)d_hidden);
     return hipGetLastError() == hipSuccess ? ULORL_OK : ULORL_ERR_HIP;
 }

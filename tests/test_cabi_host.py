@@ -178,3 +178,25 @@ def test_lmhead_workspace_query_rejects_bad_shapes():
     assert ulorl.lmhead_workspace_bytes(1024, 256, 4096, 2, 1024) > 0
     assert ulorl.lmhead_workspace_bytes(0, 256, 4096, 2, 1024) == 0
     assert ulorl.lmhead_workspace_bytes(1024, 256, 4096, 2, 1000) == 0     # chunk not a multiple of 64
+
+
+@pytest.mark.parametrize("hidden,V", [(2048, 151936), (256, 32000), (1024, 50264), (72, 1000), (8, 8), (5120, 32008)])
+@pytest.mark.parametrize("chunk", [64, 1024, 8192])
+def test_lmhead_workspace_of_a_batch_serves_every_smaller_one(hidden, V, chunk):
+    """A caller sizes one workspace for its longest batch: the size must not fall as N, R or vocab_chunk
+    grow, and vocab_chunk must bound it: twice hidden and W, four chunks of dlogits, the rest per
+    row, or 16 KB per column of a chunk beyond the least a call can do with; a hidden size that is no
+    multiple of 64 brings a padded copy of W."""
+    rows = sorted({1, 2, 63, 64, 65, 127, 255, 256, 257, 511, 777, 1000, 2000, 4095, 4096, 4097, 4288, 9000, 16384, 20000, 40000}
+                  | {int(1.07 ** k) for k in range(150)})
+    rows = [n for n in rows if n <= 65536]
+    sizes = [ulorl.lmhead_workspace_bytes(n, hidden, V, 3, chunk) for n in rows]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    for n, size in zip(rows, sizes):
+        assert ulorl.lmhead_workspace_bytes(n, hidden, V, 1, chunk) <= size <= ulorl.lmhead_workspace_bytes(n, hidden, V, 300, chunk)
+        assert size <= ulorl.lmhead_workspace_bytes(n, hidden, V, 3, chunk + 64)
+        n64, h64, v64 = (n + 63) // 64 * 64, (hidden + 63) // 64 * 64, (V + 63) // 64 * 64
+        padded = 2 * h64 * v64 if hidden % 64 else 0
+        wide = padded + 2 * hidden * V + 4 * n64 * (2 * chunk + h64) + 4 * n * (2 * chunk + hidden) + 400 * n64 + 65536
+        least = 2 * h64 * (v64 if V < 2 * n or padded else 64) + 2 * n64 * h64 + 8 * n * hidden + 4 * n64 * min(chunk, v64) + 512 * n64 + 65536
+        assert size <= max(wide, least + 16384 * chunk), (n, size)

@@ -259,3 +259,31 @@ def test_forward_statistics_of_large_logits(n):
     assert torch.all((res.lse.double() - lse).abs() <= 2.0 ** -23 * lse.abs() + 2e-6)
     assert torch.all((res.entropy.double() - ent).abs() <= 2e-5 * ent + 2e-5), float((res.entropy.double() - ent).abs().max())
     assert torch.all((res.logp.double() - at).abs() <= 1e-6 * at.abs() + 2e-6 + 2e-6 * ent)
+
+
+# The vocabulary in several chunks (vocab_chunk = 64 and more rows than hidden columns, so that the workspace
+# has no room for wide ones), the last one narrower and no multiple of 64; W with its last columns apart
+# (hidden a multiple of 64), padded for having few columns (V < 2 n) and padded along hidden.
+@pytest.mark.parametrize("n,V,hidden", [(700, 8392, 64), (1501, 3000, 64), (900, 6000, 72), (90, 56, 64),      # small tile
+                                        (1300, 5000, 320), (1400, 2760, 320), (1300, 5000, 328)])      # large tile
+@pytest.mark.parametrize("dense", [False, True])
+def test_backward_over_several_ragged_chunks(n, V, hidden, dense):
+    w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_chunks")
+    run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=64, launch=ulorl.Launch(dense_rows=dense))
+
+
+@pytest.mark.parametrize("n,most,V,hidden", [(300, 400, 2056, 128), (1300, 1313, 5000, 320), (1300, 4288, 5000, 72)])
+def test_workspace_of_a_larger_batch(n, most, V, hidden):
+    """A workspace sized for the longest batch takes a shorter one, with the bits of its own workspace."""
+    w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_reuse")
+    d = ui.generate(w, DEV)
+    p = ulorl.Params(gate_mode=ulorl.GATE_ALWAYS, seg_len=w.seg_len)
+    got = []
+    for rows in (n, most):
+        ws = torch.full((ulorl.lmhead_workspace_bytes(rows, hidden, V, 2, 512),), 0xA5, dtype=torch.uint8, device=DEV)
+        f = ulorl.lmhead_token_loss_fwd(d["hidden"], d["weight"], d["token_ids"], d["cu_seqlens"], d["advantages"], d["old_logp"], p,
+                                        vocab_chunk=512, workspace=ws)
+        got.append((f.loss, f.lse, f.entropy) + ulorl.lmhead_token_loss_bwd(d["hidden"], d["weight"], d["token_ids"], f.lse, f.gcoef, 1.0,
+                                                                            vocab_chunk=512, workspace=ws))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
