@@ -398,16 +398,16 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
         if (!half || j < NJ / 2) any_wide |= is_wide(j);
-    // The OR over the waves goes through token[], which is done with: __syncthreads_or brings LDS of its own, after
+    // The OR over the waves goes through a stage, which no wave reads any more: __syncthreads_or brings LDS of its own, after
     // which the stages no longer start at a multiple of 8 KB, and that costs 1.5 % of the kernel.
+    const int wave_wide = __any(any_wide);
+    int* flags = reinterpret_cast<int*>(lds_raw);
+    if (lane == 0) flags[wave] = wave_wide;
     __syncthreads();
-    if (threadIdx.x < 64) token[threadIdx.x] = 0;
-    __syncthreads();
-    if (__any(any_wide) && lane == 0) token[wave] = 1;
-    __syncthreads();
-    const bool again = __any(token[lane]);
+    const bool again = __any(lane < Tile::NW && flags[lane] != 0);
     float S2[NJ], T2[NJ];
     if (again) {                                              // rare: the maxima are known now
+        __syncthreads();
 #pragma unroll
         for (int j = 0; j < NJ; ++j) S2[j] = T2[j] = 0.0f;
 #pragma unroll 1
