@@ -302,7 +302,8 @@ int32_t ulorl_token_loss_fwd_bwd_static(
  *
  *   hidden        [N, Hd] bf16 row-major (Hd contiguous), 16-byte aligned
  *   W             [Hd, V] bf16 row-major (V contiguous), 16-byte aligned: output projection
- *   Hd, V         multiples of 8 (16-byte rows); Hd <= 2^20
+ *   Hd, V         multiples of 8 (16-byte rows); Hd <= 2^20, V <= 2^29 in the forward and 2^23 in the backward
+ *                 call (W's rows are addressed by 32-bit offsets inside a tile): ULORL_ERR_SHAPE beyond
  *   N             at most 2^22 - 256 token rows per call (N is a leading dimension of GEMM
  *                 operands in the backward pass; larger batches are split by the caller)
  *   vocab_chunk   multiple of 64, at most 2^22 - 256; the backward pass materialises dlogits one chunk of this many

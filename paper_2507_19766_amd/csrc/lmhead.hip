@@ -862,9 +862,9 @@ LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t 
 int32_t check_lmhead(const void* hidden, const void* W, int64_t N, int64_t Hd, int64_t V, int32_t chunk)
 {
     if (!hidden || !W) return ULORL_ERR_NULL;
-    // N and the chunk width become leading dimensions of GEMM operands (see kMaxLeadingDim)
-    if (N <= 0 || N > kMaxLeadingDim - 256 || V <= 0 || V > 0x7fffffffLL || Hd <= 0 || Hd > (1 << 20)) return ULORL_ERR_SHAPE;
-    if (Hd % 8 != 0 || V % 8 != 0) return ULORL_ERR_SHAPE;     // 16-byte rows of hidden, W and their transposes
+    // N, the chunk width and V become leading dimensions of GEMM operands (see kMaxLeadingDim)
+    if (N <= 0 || N > kMaxLeadingDim - 256 || V <= 0 || V > kMaxColsLeadingDim || Hd <= 0 || Hd > (1 << 20)) return ULORL_ERR_SHAPE;
+    if (Hd % 8 != 0 || V % 8 != 0) return ULORL_ERR_SHAPE;     // 16-byte rows of hidden and W
     if (chunk <= 0 || chunk % 64 != 0 || chunk > kMaxLeadingDim - 256) return ULORL_ERR_SHAPE;
     if (((uintptr_t)hidden & 15u) != 0 || ((uintptr_t)W & 15u) != 0) return ULORL_ERR_ALIGN;
     return ULORL_OK;
@@ -981,7 +981,7 @@ int32_t ulorl_gemm_tn_bf16(const void* A, int64_t lda, const void* B, int64_t ld
 
 size_t ulorl_lmhead_workspace_bytes(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t vocab_chunk)
 {
-    if (N <= 0 || N > 0x7fffffffLL || Hd <= 0 || V <= 0 || R <= 0 || vocab_chunk <= 0 || vocab_chunk % 64 != 0) return 0;
+    if (N <= 0 || N > 0x7fffffffLL || Hd <= 0 || V <= 0 || V > kMaxColsLeadingDim || R <= 0 || vocab_chunk <= 0 || vocab_chunk % 64 != 0) return 0;
     return lmhead_layout(N, Hd, V, R, vocab_chunk, 0).total;      // the same for every tile shape
 }
 
@@ -1056,6 +1056,7 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
     if (((uintptr_t)d_hidden & 15u) != 0 || ((uintptr_t)d_W & 15u) != 0) return ULORL_ERR_ALIGN;
     const int tile = backward_tile(opts, N, Hd);
     const LmheadLayout L = lmhead_layout(N, Hd, V, 1, vocab_chunk, tile);
+    if (!k_rows_fit(tile_edge(tile), L.v64, L.chunk)) return ULORL_ERR_SHAPE;     // W as an operand of the dHidden product
     if (!workspace || ((uintptr_t)workspace & 255u) != 0 || workspace_bytes < L.total) return ULORL_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;

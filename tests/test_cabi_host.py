@@ -200,3 +200,26 @@ def test_lmhead_workspace_of_a_batch_serves_every_smaller_one(hidden, V, chunk):
         wide = padded + 2 * hidden * V + 4 * n64 * (2 * chunk + h64) + 4 * n * (2 * chunk + hidden) + 400 * n64 + 65536
         least = 2 * h64 * (v64 if V < 2 * n or padded else 64) + 2 * n64 * h64 + 8 * n * hidden + 4 * n64 * min(chunk, v64) + 512 * n64 + 65536
         assert size <= max(wide, least + 16384 * chunk), (n, size)
+
+
+def test_lmhead_rejects_vocabularies_its_offsets_cannot_address():
+    """W has V as its leading dimension: the products address up to 256 of its rows (dHidden) or four of
+    them (logits) by 32-bit offsets.  A larger vocabulary is refused instead of read at wrapped offsets."""
+    lib = ulorl.load_library()
+    vp = ctypes.c_void_p
+    p = binding.Params().to_c()
+
+    def fwd(V, N=2000, Hd=512):
+        return lib.ulorl_lmhead_token_loss_fwd(vp(0x1000), vp(0x2000), N, Hd, V, 64, vp(0x3000), vp(0x4000), 1, None, vp(0x5000),
+                                               vp(0x6000), ctypes.byref(p), vp(0x7000), vp(0x8000), vp(0x9000), vp(0xa000), vp(0xb000),
+                                               None, None, None, None, None, None, None, None, 0, None, None)
+
+    def bwd(V, N=2000, Hd=512):
+        return lib.ulorl_lmhead_token_loss_bwd(vp(0x1000), vp(0x2000), N, Hd, V, 64, vp(0x3000), vp(0x4000), vp(0x5000), 1.0,
+                                               vp(0x6000), vp(0x7000), None, 0, None, None)
+    assert fwd(151936) == -6 and fwd(1 << 29) == -6                   # accepted: the next check, the workspace, fails
+    assert fwd((1 << 29) + 8) == -2 and bwd((1 << 29) + 8) == -2
+    assert bwd(1 << 23) == -6 and bwd((1 << 23) + (1 << 16)) == -2    # 256 rows of W in a tile
+    assert bwd(1 << 24, N=100) == -6 and bwd((1 << 24) + (1 << 18), N=100) == -2     # 128 rows
+    assert ulorl.lmhead_workspace_bytes(2000, 512, (1 << 29) + 8, 1, 64) == 0
+    assert ulorl.lmhead_workspace_bytes(2000, 512, 1 << 29, 1, 64) > 0
