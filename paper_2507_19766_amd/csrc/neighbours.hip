@@ -128,9 +128,12 @@ __global__ __launch_bounds__(256) void broadcast_advantage_kernel(const float* _
 }
 
 // Both in one launch: workgroup 0 writes the per-response outputs, the others form the advantage of each of
-// their tokens from its group's rewards again (2 G cached loads), which costs less than a second launch
-// of 4.5 us for groups of up to kGroupAgain answers.
+// their tokens from its group's rewards again (2 G cached loads), which costs less than a second launch for groups of up
+// to kGroupAgain answers and up to kTokensAgain tokens: beside workgroup 0 they are free only while they fit the
+// chip in about one round.  One launch / two, us, groups of 8: 65536 tokens 5.8 / 8.4, 524288 9.5 / 9.6, 1048576 14 / 11.5,
+// 4194304 43 / 22; of 32: 16.8 / 20.4, 19.8 / 21.3, 30 / 23.6, 95 / 36.
 constexpr int kGroupAgain = 32;
+constexpr int64_t kTokensAgain = 1 << 19;
 __global__ __launch_bounds__(kBlock) void advantage_kernel(AdvantageArgs a)
 {
     __shared__ double scratch[kBlock / 64];
@@ -282,7 +285,7 @@ int32_t ulorl_advantage_prep(const float* rewards, const uint8_t* truncated, con
     hipStream_t st = (hipStream_t)hip_stream;
     const AdvantageArgs a = {rewards, truncated, cu_seqlens, R, group_size, N, (double)eps, unbiased ? 1 : 0,
                              resp_adv, group_keep, token_adv, kept_tokens};
-    if (group_size <= kGroupAgain) {
+    if (group_size <= kGroupAgain && N <= kTokensAgain) {
         hipLaunchKernelGGL(advantage_kernel, dim3((unsigned)((N + kBlock - 1) / kBlock + 1)), dim3(kBlock), 0, st, a);
     } else {
         hipLaunchKernelGGL(group_advantage_kernel, dim3(1), dim3(kBlock), 0, st, a);

@@ -57,6 +57,21 @@ def test_advantage_prep_in_one_or_two_launches(G):
     assert keep.cpu().tolist() == [0, 1, 1] and int(kept.item()) == ref[3]
 
 
+@pytest.mark.parametrize("N", [(1 << 19) - 1, 1 << 19, (1 << 19) + 1, 3 << 19])
+def test_advantage_prep_around_the_token_count_of_one_launch(N):
+    """Up to 2^19 tokens their advantages are formed in the launch of the responses', beyond by a second one."""
+    G, R = 8, 64
+    rs = np.random.RandomState(N % 1000)
+    cu = np.sort(np.concatenate([[0, N], rs.randint(0, N, size=R - 1)])).astype(np.int32)
+    rewards = (rs.rand(R) < 0.4).astype(np.float32)
+    rewards[:G] = 1.0
+    resp, keep, tok, kept = ulorl.advantage_prep(torch.from_numpy(rewards).to(DEV), torch.from_numpy(cu).to(DEV), G)
+    ref = oracle.advantages(rewards, cu, G)
+    np.testing.assert_allclose(resp.cpu().numpy(), ref[0], rtol=1e-6, atol=1e-7)
+    assert torch.equal(tok.cpu(), resp.cpu()[torch.from_numpy(np.repeat(np.arange(R), np.diff(cu)))])
+    assert int(kept.item()) == ref[3]
+
+
 def test_prepared_advantages_feed_the_token_loss():
     """rewards -> advantages -> loss, all on the device, against the oracle chain."""
     w = ui.shrink(ui.config(2), [60, 45, 80, 30, 50, 50, 20, 70], V=4096, seg_len=32, name="chain")
