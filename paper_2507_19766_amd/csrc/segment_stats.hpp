@@ -6,7 +6,7 @@
 //
 // Per workgroup of kSegBlock consecutive tokens: a table [K][7] in LDS; each wave walks the distinct
 // segment ids of its lanes (in order of the first lane holding one) and the waves' fixed-tree sums are
-// added to the table in wave order.  One workgroup then sums the tables.  No floating-point
+// added to the table in a fixed order.  One workgroup then sums the tables.  No floating-point
 // atomics: the result depends on the inputs only.
 #ifndef ULORL_SEGMENT_STATS_HPP
 #define ULORL_SEGMENT_STATS_HPP
@@ -66,20 +66,23 @@ __device__ __forceinline__ void seg_token_values(bool valid, int32_t seg, int32_
 
 // Adds the workgroup's tokens to table (LDS, [K][7]) and hands it to `out` (global, [K][7], publish());
 // returns the workgroup's count of out-of-range tokens on every thread.  All kSegBlock threads must call.
-// Every wave forms the sums of up to kSegEntries distinct ids of its lanes at a time (counts by ballot); then
-// each slot of the table picks its entries up in wave order.  (The waves used to take turns, each with its
-// reductions inside its turn: 65536 tokens in 8 segments 55 + 11 us with the final sums, now 8 + 4.)
+// Every wave forms the sums of up to kSegEntries distinct ids of its lanes at a time (counts by ballot); then the
+// wave that holds the first entry of an id adds all entries of that id to the table, in the entries' order.  A pass
+// costs what the ids present cost, not the size of the table.  The call on 65536 tokens, the waves taking turns /
+// every slot of the table scanning all entries / this, us: 8 ids in runs 26 / 11.1 / 10.6, in no order 103 / 20.4 / 19.2;
+// 1024 ids in runs 165 / 196 / 73, in no order 837 / 993 / 165.
 constexpr int kSegEntries = 4;
 __device__ __forceinline__ double seg_block_partials(int k, const double (&v)[kSegStats], double oor, int32_t K,
                                                      double* table, double* __restrict__ out)
 {
     constexpr int NW = kSegBlock / 64;
     constexpr int NE = NW * kSegEntries;
-    __shared__ double entry[kSegStats][NE];
+    static_assert(NE == 64, "a ballot covers the entries");
+    __shared__ double entry[NE][8];                  // a row per entry: a wave reads or writes one at a time
     __shared__ int entry_key[NE];
     __shared__ int oor_wave[NW];
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slots = K * kSegStats;
     for (int i = tid; i < slots; i += kSegBlock) table[i] = 0.0;
     const int oor_count = __popcll(__ballot(oor != 0.0));
@@ -89,7 +92,7 @@ __device__ __forceinline__ double seg_block_partials(int k, const double (&v)[kS
     do {
 #pragma unroll 1
         for (int e = 0; e < kSegEntries; ++e) {
-            const int at = wave * kSegEntries + e;
+            const int at = e * NW + wave;          // the waves' first ids, then their second ones, ...: an id's sums then fall to different waves
             int key = -1;
             if (remaining != 0ull) {
                 key = __builtin_amdgcn_readlane(k, __ffsll((long long)remaining) - 1);
@@ -100,31 +103,43 @@ __device__ __forceinline__ double seg_block_partials(int k, const double (&v)[kS
                 const double kl = wave_sum_f64(mine ? v[4] : 0.0), ent = wave_sum_f64(mine ? v[5] : 0.0);
                 const int clipped = __popcll(__ballot(mine && v[3] != 0.0)), masked = __popcll(__ballot(mine && v[6] != 0.0));
                 if (lane == 0) {
-                    entry[0][at] = (double)__popcll(members);
-                    entry[1][at] = ratio;
-                    entry[2][at] = top;
-                    entry[3][at] = (double)clipped;
-                    entry[4][at] = kl;
-                    entry[5][at] = ent;
-                    entry[6][at] = (double)masked;
+                    entry[at][0] = (double)__popcll(members);
+                    entry[at][1] = ratio;
+                    entry[at][2] = top;
+                    entry[at][3] = (double)clipped;
+                    entry[at][4] = kl;
+                    entry[at][5] = ent;
+                    entry[at][6] = (double)masked;
                 }
             }
             if (lane == 0) entry_key[at] = key;
         }
         more = __syncthreads_or(remaining != 0ull);
-        for (int i = tid; i < slots; i += kSegBlock) {
-            const int key = i / kSegStats, q = i - key * kSegStats;
-            double t = table[i];
-#pragma unroll 8
-            for (int at = 0; at < NE; ++at) {           // no branch: the loads of several entries overlap
-                const double x = entry[q][at], with = q == 2 ? fmax(t, x) : t + x;
-                t = entry_key[at] == key ? with : t;
+        const int key_of_lane = entry_key[lane];
+#pragma unroll 1
+        for (int e = 0; e < kSegEntries; ++e) {
+            const int at = e * NW + wave;
+            const int key = __builtin_amdgcn_readlane(key_of_lane, at);
+            unsigned long long same = __ballot(key_of_lane == key);
+            if (key < 0 || __ffsll((long long)same) - 1 != at) continue;      // uniform: no entry, or not the id's first
+            if (lane < kSegStats) {
+                double t = table[key * kSegStats + lane];
+                while (same != 0ull) {                                        // four reads in flight; 0 changes neither sums nor maxima
+                    double x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        x[u] = same != 0ull ? entry[__ffsll((long long)same) - 1][lane] : 0.0;
+                        same &= same - 1ull;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) t = lane == 2 ? fmax(t, x[u]) : t + x[u];
+                }
+                table[key * kSegStats + lane] = t;
             }
-            table[i] = t;
         }
         __syncthreads();
     } while (more);
-    for (int i = tid; i < slots; i += kSegBlock) publish(out + i, table[i]);      // each thread its own slots
+    for (int i = tid; i < slots; i += kSegBlock) publish(out + i, table[i]);
     int total = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) total += oor_wave[w];
@@ -146,9 +161,23 @@ __device__ __forceinline__ void seg_finalize(const SegStatsArgs& a, int64_t nblk
         double acc = 0.0;
         const bool is_max = (slot % kSegStats) == 2;
         if (slot < slots && tid / T < kSegBlock / T) {
-            for (int64_t b = j; b < nblk; b += T) {
-                const double p = published(a.part + b * slots + slot);
-                acc = is_max ? fmax(acc, p) : acc + p;
+            const double* p = a.part + (int64_t)j * slots + slot;
+            const int64_t step = (int64_t)T * slots;
+            int64_t b = j;
+            for (; b + 7 * T < nblk; b += 8 * T) {              // eight loads in flight
+                double x[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    x[q] = published(p);
+                    p += step;
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc = is_max ? fmax(acc, x[q]) : acc + x[q];
+            }
+            for (; b < nblk; b += T) {
+                const double x = published(p);
+                p += step;
+                acc = is_max ? fmax(acc, x) : acc + x;
             }
         }
         __syncthreads();

@@ -243,3 +243,31 @@ def test_pool_step_feeds_advantages_and_token_loss():
     seg_ids = res.segment_out.cpu().numpy()
     cu_h = cu.cpu().numpy()
     assert seg_ids[cu_h[1]:cu_h[2]].max() == 3 and seg_ids[cu_h[0]:cu_h[1]].max() == 0
+
+
+@pytest.mark.parametrize("N,K", [(1, 1), (65, 3), (1024, 64), (5000, 5), (5000, 70), (9000, 1024), (70000, 9)])
+def test_segment_diagnostics_of_ids_in_any_order(N, K):
+    """Ids without order: up to 64 distinct ones in a wave (several passes of four), shared by all waves or by
+    none, some out of range; sums against 64 bits, and again with the same bits."""
+    g = torch.Generator(device=DEV).manual_seed(N + K)
+    seg = torch.randint(-1, K + 1, (N,), generator=g, device=DEV, dtype=torch.int32)
+    ratio, logp, old, ent = (torch.rand(N, generator=g, device=DEV) * 1.5 for _ in range(4))
+    mask = (torch.rand(N, generator=g, device=DEV) < 0.3).to(torch.uint8)
+    adv = torch.where(torch.rand(N, generator=g, device=DEV) < 0.5, 1.5, -0.65).float()
+    res = ulorl.FwdResult(None, logp, ent, logp, mpt_mask=mask, ratio=ratio, segment_out=seg)
+    got, again = (ulorl.segment_diagnostics(res, adv, old, K) for _ in range(2))
+    ok = (seg >= 0) & (seg < K)
+    at = seg[ok].long()
+    zero = torch.zeros(K, dtype=torch.float64, device=DEV)
+    r = ratio.double()
+    lo, hi = 1.0 - float(np.float32(0.2)), 1.0 + float(np.float32(0.2))
+    clipped = r * adv.double() > r.clamp(lo, hi) * adv.double()
+    ref = dict(count=zero.index_add(0, at, torch.ones_like(r)[ok]), ratio_sum=zero.index_add(0, at, r[ok]),
+               ratio_max=zero.scatter_reduce(0, at, r[ok], "amax"), clipped=zero.index_add(0, at, clipped.double()[ok]),
+               kl_sum=zero.index_add(0, at, (old.double() - logp.double())[ok]), ent_sum=zero.index_add(0, at, ent.double()[ok]),
+               masked=zero.index_add(0, at, mask.double()[ok]))
+    for name, want in ref.items():
+        assert torch.equal(got[name], again[name]), name
+        # sums of up to N doubles below 1.5 in another order
+        assert torch.all((got[name].double() - want).abs() <= 1.5 * N * N * 2.0 ** -53), name
+    assert int(got["out_of_range"]) == int((~ok).sum())
