@@ -1203,12 +1203,16 @@ __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs p)
 // ---------------------------------------------------------------------------------------------
 // per-response entropy sums, and the repair pass of the row-cooperative kernel
 // ---------------------------------------------------------------------------------------------
-// Repair: rows [r0, r1) by one workgroup, only when a wait expired (sync_fail).  By the time this runs every
-// piece of every row has published its statistics (a workgroup publishes before it waits), so a
-// row's statistics can be formed exactly as a workgroup would have formed them: its per-row outputs and
-// deferral flag are rewritten with the same bits, and the pending pieces' share of the gradient is
-// written with the arithmetic of the piece's own workgroup (a pending piece's logits are intact because
-// only its own workgroup writes them).  Deferred rows are left whole to the launch that follows the gate.
+// Repair, only when a wait expired (sync_fail).  By the time this runs every piece of every row has published its
+// statistics (a workgroup publishes before it waits), so a row's statistics can be formed exactly as a
+// workgroup would have formed them: its per-row outputs and deferral flag are rewritten with the same bits
+// (repair_row_outputs, by the workgroups that sum the row's response), and the pending pieces' share of the gradient is
+// written with the arithmetic of the piece's own workgroup (repair_gradient, by workgroups of the same launch that
+// have nothing else to do, whatever the responses' lengths; a pending piece's logits are intact because only its own
+// workgroup writes them).  Deferred rows are left whole to the launch that follows the gate.
+// Every wait expired: 8191 rows x 151936 in one response 1.7 ms, by the response's workgroup alone 65 (undisturbed 0.82).  The idle
+// workgroups cost an undisturbed call 0.2 to 0.4 us.
+constexpr int kRepairGroups = 256;
 template <class Tr>
 struct RepairArgs {
     ClusterArgs c;              // c.sync_fail == NULL: the row-cooperative kernel did not run
@@ -1218,8 +1222,51 @@ struct RepairArgs {
     int32_t vpt;
 };
 
+// One wave: the pending pieces of a row, and if there are any the row's statistics and what is to be done with it
+// (mode, see row_decision) in lane 0.
+__device__ __forceinline__ unsigned long long pending_pieces(const ClusterArgs& a, int32_t V, int64_t row, int lane, uint32_t badcu,
+                                                             float& lse, float& lp, float& ent, float& g, int& mode)
+{
+    float pm = kEmpty, pS = 0.0f, pT = 0.0f;
+    int pending = 0;
+    if (lane < a.C) {
+        const unsigned long long w0 = a.slots[(row * a.C + lane) * 2], w1 = a.slots[(row * a.C + lane) * 2 + 1];
+        pm = __uint_as_float((uint32_t)w0);
+        pS = __uint_as_float((uint32_t)(w0 >> 32));
+        pT = __uint_as_float((uint32_t)w1);
+        pending = (w1 >> 32) == kTagPending;
+    }
+    const unsigned long long mask = __ballot(pending);
+    if (mask == 0ull) return mask;
+    merge_pieces_tree(pm, pS, pT);
+    if (lane == 0) {
+        const int32_t y = a.f.token_ids[row];
+        finish_pieces(pm, pS, pT, y >= 0 && y < V, a.f.zy_row[row], lse, lp, ent);
+        mode = row_decision(a.f, y, V, lse, lp, ent, a.f.adv[row], a.f.is_mode == ULORL_IS_POIS ? 0.0f : a.f.old_logp[row], badcu, g);
+    }
+    return mask;
+}
+
+// Rows [r0, r1) by one workgroup, a wave per row.
+__device__ void repair_row_outputs(const ClusterArgs& a, int32_t V, int64_t r0, int64_t r1)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t badcu = *a.f.badcu;
+    for (int64_t row = r0 + (threadIdx.x >> 6); row < r1; row += kTokWaves) {
+        float lse, lp, ent, g;
+        int mode;
+        if (pending_pieces(a, V, row, lane, badcu, lse, lp, ent, g, mode) != 0ull && lane == 0) {
+            a.f.lse[row] = lse;
+            a.f.logp[row] = lp;
+            a.f.entropy[row] = ent;
+            a.f.defer[row] = mode == 2 ? 1 : 0;
+        }
+    }
+}
+
+// Every step-th row from r0 on by one workgroup.
 template <class Tr>
-__device__ void repair_rows(const RepairArgs<Tr>& q, int32_t V, int64_t r0, int64_t r1)
+__device__ void repair_gradient(const RepairArgs<Tr>& q, int32_t V, int64_t r0, int64_t step)
 {
     __shared__ float sh_g, sh_lse;
     __shared__ int sh_mode;
@@ -1231,32 +1278,15 @@ __device__ void repair_rows(const RepairArgs<Tr>& q, int32_t V, int64_t r0, int6
     const int nvec = V / E;
     const int piece = kClusterThreads * q.vpt;
     const uint32_t badcu = *a.f.badcu;
-    for (int64_t row = r0; row < r1; ++row) {
+    for (int64_t row = r0; row < a.N; row += step) {
         if (tid < 64) {
-            float pm = kEmpty, pS = 0.0f, pT = 0.0f;
-            int pending = 0;
-            if (tid < C) {
-                const unsigned long long w0 = a.slots[(row * C + tid) * 2], w1 = a.slots[(row * C + tid) * 2 + 1];
-                pm = __uint_as_float((uint32_t)w0);
-                pS = __uint_as_float((uint32_t)(w0 >> 32));
-                pT = __uint_as_float((uint32_t)w1);
-                pending = (w1 >> 32) == kTagPending;
-            }
-            const unsigned long long mask = __ballot(pending);
-            merge_pieces_tree(pm, pS, pT);
+            float lse, lp, ent, gr;
+            int mode;
+            const unsigned long long mask = pending_pieces(a, V, row, tid, badcu, lse, lp, ent, gr, mode);
             if (tid == 0) {
                 sh_pending = mask;
                 if (mask != 0ull) {
-                    const int32_t y = a.f.token_ids[row];
-                    float lse, lp, ent, g;
-                    finish_pieces(pm, pS, pT, y >= 0 && y < V, a.f.zy_row[row], lse, lp, ent);
-                    const int mode = row_decision(a.f, y, V, lse, lp, ent, a.f.adv[row],
-                                                  a.f.is_mode == ULORL_IS_POIS ? 0.0f : a.f.old_logp[row], badcu, g);
-                    a.f.lse[row] = lse;
-                    a.f.logp[row] = lp;
-                    a.f.entropy[row] = ent;
-                    a.f.defer[row] = mode == 2 ? 1 : 0;
-                    sh_g = g;
+                    sh_g = gr;
                     sh_lse = lse;
                     sh_mode = mode;
                 }
@@ -1314,25 +1344,33 @@ __device__ void repair_rows(const RepairArgs<Tr>& q, int32_t V, int64_t r0, int6
     }
 }
 
-// a.slices workgroups per response: the repair of their rows if any is needed, the sum of their token
-// entropies (Sec. 3.2.2, H-bar_i numerator) and a sanity check of the response's bounds.
+// a.slices workgroups per response: the repair of their rows' outputs if any is needed, the sum of their token
+// entropies (Sec. 3.2.2, H-bar_i numerator) and a sanity check of the response's bounds.  Behind them, where the
+// row-cooperative kernel ran, kRepairGroups workgroups for the repair of gradients, which normally end at once.
 template <class Tr>
 __global__ __launch_bounds__(kTokBlock) void response_entropy_kernel(TokenArgs a, RepairArgs<Tr> rep)
 {
     __shared__ double scratch[kTokWaves];
+    const bool repair = rep.c.sync_fail != nullptr && *rep.c.sync_fail != 0u;
+    const int64_t groups = (int64_t)a.R * a.slices;
+    if (blockIdx.x >= groups) {
+        if (repair) repair_gradient<Tr>(rep, a.V, blockIdx.x - groups, gridDim.x - groups);
+        return;
+    }
     const int i = blockIdx.x / a.slices, s = blockIdx.x % a.slices;
     const int64_t b = a.cu[i], e = a.cu[i + 1];
     const bool ok = response_bounds_ok(a.cu, i, a.R, a.N);
     const int64_t per = ok ? (e - b + a.slices - 1) / a.slices : 0;
     const int64_t r0 = b + s * per, r1 = min(e, r0 + per);
-    if (rep.c.sync_fail != nullptr && *rep.c.sync_fail != 0u) {
+    if (repair) {
         if (*rep.c.f.badcu == 0u) {
-            repair_rows<Tr>(rep, a.V, r0, r1);
+            repair_row_outputs(rep.c, a.V, r0, r1);
         } else {                                    // no usable responses: an even share of all rows
-            const int64_t share = (a.N + gridDim.x - 1) / gridDim.x;
-            repair_rows<Tr>(rep, a.V, blockIdx.x * share, min(a.N, (int64_t)(blockIdx.x + 1) * share));
+            const int64_t share = (a.N + groups - 1) / groups;
+            repair_row_outputs(rep.c, a.V, blockIdx.x * share, min(a.N, (int64_t)(blockIdx.x + 1) * share));
         }
         __syncthreads();
+        if (gridDim.x == groups) repair_gradient<Tr>(rep, a.V, blockIdx.x, groups);      // too many responses for workgroups of its own
     }
     double h = 0.0;
     if (ok) {
@@ -1355,7 +1393,9 @@ void launch_epilogue(const TokenArgs& a, int64_t nblk, const RepairArgs<Tr>& rep
         lds = (size_t)a.seg.K * kSegStats * sizeof(double);
         if (lds < kSegBlock * sizeof(double)) lds = kSegBlock * sizeof(double);      // scratch of seg_finalize
     }
-    hipLaunchKernelGGL((response_entropy_kernel<Tr>), dim3((unsigned)a.R * (unsigned)a.slices), dim3(kTokBlock), 0, st, a, rep);
+    unsigned groups = (unsigned)a.R * (unsigned)a.slices;
+    if (rep.c.sync_fail != nullptr && groups + kRepairGroups <= 0xffffffffu / kTokBlock) groups += kRepairGroups;     // within a launch's threads
+    hipLaunchKernelGGL((response_entropy_kernel<Tr>), dim3(groups), dim3(kTokBlock), 0, st, a, rep);
     if (a.seg.K > 0) {
         hipLaunchKernelGGL((token_terms_kernel<true>), dim3((unsigned)nblk), dim3(kTokBlock), lds, st, a, nblk);
     } else {

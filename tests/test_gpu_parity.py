@@ -415,6 +415,35 @@ def test_an_expired_wait_costs_time_not_data(gate, inplace):
     assert seen, "no wait expired in four calls with a single poll: the repair pass was not exercised"
 
 
+@pytest.mark.parametrize("lengths,cu_ok", [([16500], True), ([1, 9000, 15, 0, 3], True), ([3000, 1500], False)])
+def test_expired_waits_in_long_and_uneven_responses(lengths, cu_ok):
+    """Rows of several pieces whose waits are given up after one poll, in a response whose entropy several
+    workgroups sum, in a batch with one long response, and in one whose cu_seqlens are malformed (no row
+    gets a gradient): the bits of an undisturbed call."""
+    V, n = 40000, sum(lengths)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    z = (torch.randn(n, V, generator=g, device=DEV) * 3).to(torch.bfloat16)
+    y = torch.randint(0, V, (n,), generator=g, device=DEV, dtype=torch.int32)
+    cu = torch.tensor([0] + lengths).cumsum(0).to(torch.int32).to(DEV)
+    if not cu_ok:
+        cu[1] = cu[2] + 1
+    adv = torch.where(torch.rand(n, generator=g, device=DEV) < 0.7, 1.0, -0.5)
+    old = -torch.rand(n, generator=g, device=DEV) - 9.0
+    p = ulorl.Params(gate_mode=ulorl.GATE_GLOBAL, sigma=100.0, tau=1e-4, eps_low=0.5, eps_high=0.5, seg_len=512)
+    good, dz_good = ulorl.token_loss_fwd_bwd(z, y, cu, adv, old, p)
+    seen = 0
+    for attempt in range(4):
+        res, dz = ulorl.token_loss_fwd_bwd(z, y, cu, adv, old, p, launch=ulorl.Launch(sync_spins=1))
+        seen += int(res.counters[3]) & ulorl.STATUS_SYNC != 0
+        for name in ("loss", "logp", "entropy", "lse", "gcoef", "mpt_mask", "ratio", "resp_entropy", "resp_gate"):
+            assert torch.equal(getattr(res, name), getattr(good, name)), name
+        assert torch.equal(res.counters[:3], good.counters[:3])
+        assert torch.equal(dz.view(torch.int16), dz_good.view(torch.int16))
+        if seen:
+            break
+    assert seen
+
+
 def test_rows_too_long_for_the_cooperative_kernel_fall_back():
     """A row of more than 64 pieces (1.97 M bf16 logits) is handled by one looping workgroup per
     row; a row of exactly 64 pieces still takes the cooperative kernel.  Both against the oracle."""
