@@ -42,8 +42,9 @@ def test_gemm_tn_bf16_against_fp64(M, N, K):
 
 @pytest.mark.parametrize("tile,group_m", [(0, 0), (1, 0), (0, 1), (0, 7), (1, 64)])
 def test_every_compiled_tile_shape(tile, group_m):
-    """Both tile shapes / both main loops (direct-to-LDS and register-staged) and other walks of the
-    tile grid give the same answers."""
+    """Every tile of the plain product (large, small, and the one for a ragged K) and other walks of the tile
+    grid give the same answers; the lm_head case is one of few rows and a short hidden size, which takes the
+    small tile whatever is asked for (its large tiles: test_walks_of_large_tiles)."""
     launch = ulorl.Launch(gemm_tile=tile, gemm_group_m=group_m)
     g = torch.Generator(device=DEV).manual_seed(tile)
     for (M, N, K) in ((300, 520, 192), (256, 256, 72), (1300, 700, 128)):     # K = 72 exercises the ragged-K fallback
@@ -60,9 +61,10 @@ def test_every_compiled_tile_shape(tile, group_m):
 @pytest.mark.parametrize("tile", [0, 1])
 @pytest.mark.parametrize("n,V,hidden", [(256, 512, 64), (257, 520, 128), (63, 256, 192), (129, 264, 256), (1, 8, 8), (320, 1096, 72)])
 def test_tile_edges_of_every_product(tile, n, V, hidden):
-    """One to four K tiles (the peeled ends of the main loop), tiles one row or one vector past an
-    edge, and shapes whose weight is padded (hidden or vocabulary no multiple of 64); the tolerances
-    are those of every lm_head case."""
+    """One to four K tiles of the small tile (all of these shapes take it, by their size or by request), tiles
+    one row or one vector past an edge, and shapes whose weight is padded or whose last columns are taken apart
+    (hidden or vocabulary no multiple of 64); the tolerances are those of every lm_head case.  The large
+    tile: test_large_tiles_with_half_empty_ones, test_large_tiles_with_few_live_rows."""
     launch = ulorl.Launch(gemm_tile=tile)
     w = ui.shrink(ui.config(5), [n], V=V, hidden=hidden, seg_len=64, name="lmhead_edges")
     for dense in (False, True):
@@ -70,8 +72,8 @@ def test_tile_edges_of_every_product(tile, n, V, hidden):
         run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=320, launch=launch)
 
 
-@pytest.mark.parametrize("n,V,hidden", [(512, 65536 + 192, 64),     # two chunks, the second shorter than the parts of the dHidden contraction
-                                        (300, 9000, 320),             # one chunk, eight parts
+@pytest.mark.parametrize("n,V,hidden", [(512, 65536 + 192, 64),     # eighteen chunks, the last shorter than the three parts of the dHidden contraction
+                                        (300, 9000, 320),             # three chunks of three parts
                                         (2049, 264, 64),              # live rows counted by three workgroups in one launch
                                         (33000, 64, 64)])             # ... and by the three-launch scan
 def test_backward_partitions(n, V, hidden):
@@ -90,6 +92,43 @@ def test_large_tiles_with_half_empty_ones(n, V, hidden):
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_halves")
     for dense in (False, True):
         run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(dense_rows=dense))
+
+
+@pytest.mark.parametrize("n", [300, 1300])        # small and large tile
+def test_backward_in_one_chunk_of_eight_parts(n):
+    w = ui.shrink(ui.config(5), [n - 1, 1], V=9000, hidden=320, seg_len=64, name="lmhead_eight_parts")
+    run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192)
+
+
+def _few_live(w, n_live):
+    """The workload's inputs with an advantage in n_live rows only, and parameters that neither clip nor mask."""
+    d = ui.generate(w, DEV)
+    keep = torch.zeros(w.N, dtype=torch.bool, device=DEV)
+    keep[torch.randperm(w.N, generator=torch.Generator().manual_seed(n_live))[:n_live].to(DEV)] = True
+    d["advantages"] = torch.where(keep, torch.full_like(d["advantages"], 0.75), torch.zeros_like(d["advantages"]))
+    return d, keep
+
+
+@pytest.mark.parametrize("n_live", [0, 1, 64, 65, 128, 129, 257])
+@pytest.mark.parametrize("hidden,V", [(320, 328), (512, 256), (392, 1096)])
+def test_large_tiles_with_few_live_rows(n_live, hidden, V):
+    """A large batch (which takes the large tile) with few rows that carry a gradient: the d_W product, both
+    operands transposed, contracts over none, one, two, three and five K tiles (first and last tiles of the
+    loop peeled), in whole and half tiles; against the oracle."""
+    w = ui.shrink(ui.config(5), [1290, 10], V=V, hidden=hidden, seg_len=64, name="lmhead_large_few")
+    d, keep = _few_live(w, n_live)
+    p = params_for(w, gate_mode=ulorl.GATE_NEVER, eps_low=10.0, eps_high=10.0)
+    res, _ = run_lmhead_parity(w, p, chunk=8192, data=d)
+    assert int((res.gcoef != 0).sum()) == n_live
+    assert bool((res.d_hidden[~keep] == 0).all())
+    if n_live == 0:
+        assert bool((res.d_weight == 0).all())
+
+
+@pytest.mark.parametrize("group_m", [1, 7, 64])
+def test_walks_of_large_tiles(group_m):
+    w = ui.shrink(ui.config(5), [1200, 120], V=1544, hidden=320, seg_len=64, name="lmhead_large_walk")
+    run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS, tau=0.05), chunk=512, launch=ulorl.Launch(gemm_group_m=group_m))
 
 
 def test_lmhead_small_ragged_chunks():
@@ -138,7 +177,10 @@ def test_lmhead_mpt_mask_fires():
 
 
 @pytest.mark.parametrize("lengths,V,hidden,chunk", [([300, 212], 4096 + 1544, 256, 1024), ([64], 8192 + 8, 64, 64),
-                                                    ([1000, 24], 1544, 128, 2048)])
+                                                    ([1000, 24], 1544, 128, 2048),
+                                                    # several chunks: last columns apart, W padded for V < 2 n, padded along hidden; the last two large tiles
+                                                    ([693, 7], 8392, 64, 64), ([1500, 1], 3000, 64, 64), ([893, 7], 6000, 72, 64),
+                                                    ([1299, 1], 5000, 320, 64), ([1400], 2760, 328, 64)])
 def test_workspace_is_never_overrun(lengths, V, hidden, chunk):
     """Guard bytes behind the workspace stay untouched by the forward and the backward call (shapes
     with few token tiles and many vocabulary tiles ask for the most vocabulary slices)."""

@@ -114,3 +114,28 @@ def test_random_lmhead_case(c):
     res, tt = run_lmhead_parity(w, p, chunk=c["chunk"], data=d, grad_out=c["grad_out"], launch=launch)
     if c["dead_frac"] > 0.0:
         assert bool((res.gcoef[dead] == 0).all()) and bool((res.d_hidden[dead] == 0).all())
+
+
+def _lmhead_large_cases():
+    """Shapes that take the large tile in both passes (more than 256 rows and hidden columns, more than 3 * 2^17
+    elements of hidden), with small chunks and more rows than hidden columns, so that most run over several chunks."""
+    rs = np.random.RandomState(20250729)
+    out = []
+    for i in range(8):
+        hidden = 8 * int(rs.randint(33, 80)) if i % 2 else 64 * int(rs.randint(5, 10))
+        n = int(rs.randint(1 + 3 * 2 ** 17 // hidden, 3000))
+        out.append(dict(idx=i, hidden=hidden, V=8 * int(rs.randint(8, 900)), lengths=[n - 9, 9], chunk=64 * int(rs.randint(1, 5)),
+                        group=int(rs.choice([0, 1, 3])), dead_frac=float(rs.choice([0.0, 0.5, 0.98])), dense_rows=bool(i % 3 == 2)))
+    return out
+
+
+@pytest.mark.parametrize("c", _lmhead_large_cases(), ids=lambda c: "%02d_N%d_Hd%d_V%d_c%d" % (c["idx"], sum(c["lengths"]), c["hidden"], c["V"], c["chunk"]))
+def test_random_lmhead_case_of_large_tiles(c):
+    from parity import run_lmhead_parity
+    w = ui.shrink(ui.config(5), c["lengths"], V=c["V"], hidden=c["hidden"], seg_len=64, name="lmhead_large_%02d" % c["idx"])
+    d = ui.generate(w, DEV)
+    dead = (torch.rand(w.N, generator=torch.Generator().manual_seed(c["idx"])) < c["dead_frac"]).to(DEV)
+    d["advantages"] = torch.where(dead, torch.zeros_like(d["advantages"]), d["advantages"])
+    res, _ = run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=c["chunk"], data=d,
+                               launch=ulorl.Launch(gemm_group_m=c["group"], dense_rows=c["dense_rows"]))
+    assert bool((res.gcoef[dead] == 0).all()) and bool((res.d_hidden[dead] == 0).all())
