@@ -4,8 +4,9 @@ a training script where a log-softmax / gather / clipped-ratio chain would other
     loss = ulorl.autograd.token_loss(logits, token_ids, cu_seqlens, advantages, old_logp, params)
     loss.backward()                     # logits.grad holds dlogits
 
-Nothing here computes: every function forwards tensors to the library calls of ``binding`` and
-hands their results to autograd.  There is no CPU path.
+Every function forwards tensors to the library calls of ``binding`` and hands their results to autograd;
+the one thing computed here is the product of the saved coefficients and the upstream gradient.  There
+is no CPU path.
 
 Two ways to run the logits path:
   * ``fused=False`` (default): ``ulorl_token_loss_fwd`` in forward, ``ulorl_token_loss_bwd`` in

@@ -2,7 +2,7 @@
 
 Every function here has the name of the C entry point it wraps (minus the ``ulorl_`` prefix)
 and does nothing but check tensors (device, dtype, contiguity), allocate outputs with torch
-and pass raw pointers plus the current HIP stream.  All arithmetic runs in the HIP kernels.
+and pass raw pointers plus the current HIP stream.  All arithmetic of these calls runs in the HIP kernels.
 """
 from __future__ import annotations
 

@@ -792,7 +792,7 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
 // memory-side cache, so HBM sees one read and one write per row.  This is possible whenever the
 // row's coefficient does not depend on other rows: always for the ALWAYS / NEVER gates, and for
 // every token outside the MPT set under the entropy gates.  MPT members under an entropy gate
-// are left untouched and flagged in `defer`; dlogits_kernel finishes them once the gate is known.
+// are left untouched and flagged in `defer`; dlogits_rows_kernel finishes them once the gate is known.
 struct FusedArgs {
     const int32_t* token_ids;
     const float* old_logp;
@@ -1409,7 +1409,7 @@ void launch_epilogue(const TokenArgs& a, int64_t nblk, const RepairArgs<Tr>& rep
 // The same pieces, the same per-piece arithmetic and the same merge tree as cluster_row_kernel, so
 // lse, log-prob and entropy (and every decision taken from them) carry the same bits on both paths.
 // No waiting here: a second kernel merges the pieces.  Consecutive workgroups read consecutive
-// 61 KB pieces, the access pattern HBM serves best.
+// pieces of VPT * 4 KB, the access pattern HBM serves best.
 template <class Tr, int VPT>
 __global__ __launch_bounds__(kClusterThreads) void piece_stats_kernel(const typename Tr::elem* logits, int64_t row_stride,
                                                                       int32_t V, int64_t N, int32_t C,
