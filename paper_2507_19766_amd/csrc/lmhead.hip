@@ -237,8 +237,7 @@ __global__ __launch_bounds__(kLiveBlock) void live_fill_kernel(const float* __re
 
 // The three kernels above in one launch, for up to kLiveRecountRows rows: every workgroup counts the rows
 // before its own itself (three independent loads from cache per row, at most 3 * kLiveRecountRows / kLiveBlock
-// per thread),
-// which is cheaper than two more launches of 4.5 us each: 32 x 1024 rows are recounted in about 7 us.
+// per thread), which is cheaper than two more launches of 4.5 us each: 32 x 1024 rows are recounted in about 7 us.
 constexpr int64_t kLiveRecountRows = 32768;
 __global__ __launch_bounds__(kLiveBlock) void live_rows_kernel(const float* __restrict__ gcoef, const float* __restrict__ lse,
                                                                const int32_t* __restrict__ token_ids, float grad_out,
