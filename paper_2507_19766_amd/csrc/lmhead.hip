@@ -690,9 +690,15 @@ inline int64_t round_up64(int64_t x) { return (x + 63) / 64 * 64; }
 // large / small, us.  Forward statistics, 151936 columns: 64 x 512 112 / 106, 200 x 1024 165 / 161,
 // 512 x 512 115 / 124, 512 x 2048 301 / 406; 4096 x 256 x 5640 31 / 27.  Backward, 151936 columns:
 // 64 x 2048 584 / 453, 200 x 1024 529 / 390, 512 x 512 519 / 368, 777 x 512 533 / 579, 512 x 1024
-// 633 / 626, 512 x 2048 943 / 1213; 8192 x 256 x 5640 231 / 168.
+// 633 / 626, 512 x 2048 943 / 1213; 8192 x 256 x 5640 231 / 168.  Many rows and a d_W of few large tiles, which then
+// contract over all rows on a few compute units (rows x hidden x columns): 20000 x 512 x 1000 433 / 263, x 2000 458 / 297,
+// x 4096 507 / 373, x 8192 645 / 662; 20000 x 2048 x 1000 563 / 395.
 inline int forward_tile(const LaunchOpts& o, int64_t N, int64_t Hd) { return o.gemm_tile == 1 || N <= 256 || Hd <= 256 ? 1 : 0; }
-inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd) { return o.gemm_tile == 1 || N * Hd <= 3 * (1 << 17) || Hd <= 256 ? 1 : 0; }
+inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
+{
+    const int64_t dw_tiles = ((V + 255) / 256) * ((Hd + 255) / 256);
+    return o.gemm_tile == 1 || N * Hd <= 3 * (1 << 17) || Hd <= 256 || (N >= 8192 && dw_tiles <= 32) ? 1 : 0;
+}
 
 inline int tile_edge(int tile) { return tile == 1 ? TileSmall<K_ROWS, K_ROWS>::BM : TileLarge<K_ROWS, K_ROWS>::BM; }
 
@@ -1054,7 +1060,7 @@ int32_t ulorl_lmhead_token_loss_bwd(const void* hidden, const void* W, int64_t N
     if (rc != ULORL_OK) return rc;
     if (!token_ids || !lse || !gcoef || !d_hidden || !d_W) return ULORL_ERR_NULL;
     if (((uintptr_t)d_hidden & 15u) != 0 || ((uintptr_t)d_W & 15u) != 0) return ULORL_ERR_ALIGN;
-    const int tile = backward_tile(opts, N, Hd);
+    const int tile = backward_tile(opts, N, Hd, V);
     const LmheadLayout L = lmhead_layout(N, Hd, V, 1, vocab_chunk, tile);
     if (!k_rows_fit(tile_edge(tile), L.v64, L.chunk)) return ULORL_ERR_SHAPE;     // W as an operand of the dHidden product
     if (!workspace || ((uintptr_t)workspace & 255u) != 0 || workspace_bytes < L.total) return ULORL_ERR_WORKSPACE;

@@ -100,6 +100,13 @@ def test_backward_in_one_chunk_of_eight_parts(n):
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192)
 
 
+@pytest.mark.parametrize("n,V", [(8191, 264), (8192, 264), (8200, 4096), (8200, 4104)])
+def test_backward_of_many_rows_and_few_columns(n, V):
+    """Around the line from which a d_W of few tiles (at most 32 of 256 x 256) is cut into small ones."""
+    w = ui.shrink(ui.config(5), [n - 1, 1], V=V, hidden=320, seg_len=64, name="lmhead_many_rows")
+    run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192)
+
+
 def _few_live(w, n_live):
     """The workload's inputs with an advantage in n_live rows only, and parameters that neither clip nor mask."""
     d = ui.generate(w, DEV)
