@@ -47,18 +47,19 @@ METRIC = "token-rows/sec fused fwd+bwd RL token loss (V=151936 bf16) + % HBM roo
 # expressed as measured / algorithmic ratios per row.  They hold for the kernel source they were taken
 # on: the digest below is checked at run time and `traffic` is null once the kernels changed.
 PMC = {
-    "source_sha256": "615e0ad7b59bd9704f9e50bf98daee7f91878eaa233293782a5014092bed9ad0",
+    "source_sha256": "ab0ea78ae88eb9e8332cbc2075c4298fd8f4433f65d1f964819d28329da31d32",
     "fused_read": 1.0078, "fused_write": 1.0015,      # cluster_row_kernel: every row once, plus the polling of the exchange slots
     "bwd_read": 1.0007, "bwd_write": 1.0000,          # dlogits_chunk_kernel
 }
 
 # HBM bytes of one lm_head backward / forward call at configuration 5 (vocabulary chunk 8192), from two
 # rocprofv3 --pmc runs of this script (FETCH_SIZE, then WRITE_SIZE, summed over the call's kernels and
-# scaled as above); valid for the lm_head source with this digest and for that workload only.
+# scaled as above; profiles/lmhead_cfg5_kernel_trace.txt); valid for the lm_head source with this digest and for
+# that workload only.
 PMC_LMHEAD = {
-    "source_sha256": "9f1e03bb04fbc79ed15b08a2832e08111ee79ddabe0d31adf5d400a8d8f934f2",
-    "bwd_bytes": 131621665 * 1024,     # 20 x lmhead_bwd_step_kernel + live-row gather, transposes, accumulator fill, final conversion
-    "fwd_bytes": 35197904 * 1024,      # lmhead_stats_kernel + transpose of W + the small kernels
+    "source_sha256": "3eb243c8737e0895a0b76b8288cb73b08a758aec59aad64dc9466c25fea74a00",
+    "bwd_bytes": 119064759 * 1024,     # 20 x lmhead_bwd_step_kernel + live rows and their gather, final conversion
+    "fwd_bytes": 34917635 * 1024,      # lmhead_stats_kernel + the small kernels
 }
 
 
