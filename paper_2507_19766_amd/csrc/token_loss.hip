@@ -1211,7 +1211,7 @@ __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs p)
 // have nothing else to do, whatever the responses' lengths; a pending piece's logits are intact because only its own
 // workgroup writes them).  Deferred rows are left whole to the launch that follows the gate.
 // Every wait expired: 8191 rows x 151936 in one response 1.7 ms, by the response's workgroup alone 65 (undisturbed 0.82).  The idle
-// workgroups cost an undisturbed call 0.2 to 0.4 us.
+// workgroups and the code cost an undisturbed call 0.2 to 0.3 us.
 constexpr int kRepairGroups = 256;
 template <class Tr>
 struct RepairArgs {
@@ -1351,14 +1351,14 @@ template <class Tr>
 __global__ __launch_bounds__(kTokBlock) void response_entropy_kernel(TokenArgs a, RepairArgs<Tr> rep)
 {
     __shared__ double scratch[kTokWaves];
-    const bool repair = rep.c.sync_fail != nullptr && *rep.c.sync_fail != 0u;
-    const int64_t groups = (int64_t)a.R * a.slices;
+    const unsigned groups = (unsigned)a.R * (unsigned)a.slices;
     if (blockIdx.x >= groups) {
-        if (repair) repair_gradient<Tr>(rep, a.V, blockIdx.x - groups, gridDim.x - groups);
+        if (*rep.c.sync_fail != 0u) repair_gradient<Tr>(rep, a.V, blockIdx.x - groups, gridDim.x - groups);
         return;
     }
     const int i = blockIdx.x / a.slices, s = blockIdx.x % a.slices;
     const int64_t b = a.cu[i], e = a.cu[i + 1];
+    const bool repair = rep.c.sync_fail != nullptr && *rep.c.sync_fail != 0u;      // loaded beside the bounds
     const bool ok = response_bounds_ok(a.cu, i, a.R, a.N);
     const int64_t per = ok ? (e - b + a.slices - 1) / a.slices : 0;
     const int64_t r0 = b + s * per, r1 = min(e, r0 + per);
@@ -1366,7 +1366,7 @@ __global__ __launch_bounds__(kTokBlock) void response_entropy_kernel(TokenArgs a
         if (*rep.c.f.badcu == 0u) {
             repair_row_outputs(rep.c, a.V, r0, r1);
         } else {                                    // no usable responses: an even share of all rows
-            const int64_t share = (a.N + groups - 1) / groups;
+            const int64_t share = (a.N + groups - 1) / (int64_t)groups;
             repair_row_outputs(rep.c, a.V, blockIdx.x * share, min(a.N, (int64_t)(blockIdx.x + 1) * share));
         }
         __syncthreads();
