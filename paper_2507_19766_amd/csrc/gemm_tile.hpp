@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_loop.hpp"
+
 namespace ulorl_detail {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -24,6 +26,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x32 __attribute__((ext_vector_type(32)));
 typedef uint16_t bf16_t;  // raw storage
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
@@ -50,10 +53,11 @@ constexpr int kHalfElems = kHalf * kTileK;       // 16 KB
 // Word 3 of a raw (unstructured, stride 0) buffer descriptor on gfx9-family parts: 32-bit data format.
 constexpr int kRawBufferFlags = 0x00020000;
 // Operands are addressed by 32-bit byte offsets: K_ROWS from a tile's first row (up to 256 rows of ld elements), K_COLS from the
-// first of four rows.  With at most kMaxLeadingDim elements either stays below 2^31 bytes; larger ones are
-// checked by the caller (k_rows_fit, kMaxColsLeadingDim).
+// first of four rows (small tile) or of 52 (large tile).  With at most kMaxLeadingDim elements any stays below 2^31 bytes;
+// larger ones are checked by the caller (k_rows_fit, kMaxColsLeadingDim, kMaxLargeColsLeadingDim).
 constexpr int64_t kMaxLeadingDim = 1 << 22;
 constexpr int64_t kMaxColsLeadingDim = 1 << 29;
+constexpr int64_t kMaxLargeColsLeadingDim = 1 << 25;
 inline bool k_rows_fit(int64_t tile_rows, int64_t ld, int64_t K) { return ((tile_rows - 1) * ld + K) * 2 <= 0xffffffffLL; }
 
 // s_waitcnt immediates: at most n vector memory operations (LDS operations) still outstanding.
@@ -86,60 +90,65 @@ __device__ __forceinline__ void bare_barrier()
 template <int LAYOUT, int NW, int HALVES, int BLOCKS>
 struct TileOperand {
     static constexpr int J = 16 / NW;            // copy instructions per wave and half tile
-    static constexpr int NV = LAYOUT == K_ROWS ? HALVES * J : HALVES;
+    static constexpr int NV = HALVES == 2 && LAYOUT == K_ROWS ? 1 : LAYOUT == K_ROWS ? J : HALVES;
     static constexpr int NR = LAYOUT == K_ROWS ? 2 : BLOCKS;
     const char* src;          // this wave's rows of the K tile at the copy cursor (uniform)
     int64_t step;             // bytes from one K tile to the next
-    int64_t row_step;         // K_COLS: bytes from copy instruction j to j + 1
+    int64_t row_step;         // K_COLS, and K_ROWS of the large tile: bytes from copy instruction j to j + 1
     int soff;                 // K_ROWS: byte offset of the copy cursor along k
     uint32_t extent;
     uint32_t voff[NV];        // this lane's byte offset
     int roff[NR];             // this lane's LDS read offset, in bytes inside a half
     bf16_t* lds;              // [stage][half]
+    int64_t ld;
+    int count;                // rows (columns) of this tile
     int wave;
 
-    // first: first row (column) of the tile; the copy cursor is at k = 0.  Rows past op.count are
-    // taken from the last one (their results are ignored).
-    __device__ __forceinline__ void set_tile(const Operand& op, int first, int64_t K)
+    // first: first row (column) of the tile, `most` of them at most; the copy cursor is at k = 0.  K_ROWS rows past the last
+    // lie outside the buffer and arrive as zeros, without memory traffic; K_COLS columns past it repeat earlier ones (their
+    // results are ignored).
+    __device__ __forceinline__ void set_tile(const Operand& op, int first, int64_t K, int wave_, int most = HALVES * kHalf)
     {
-        const int lane = threadIdx.x & 63;
+        wave = wave_;
+        ld = op.ld;
+        count = min(most, op.count - first);
         if constexpr (LAYOUT == K_ROWS) {
-            src = reinterpret_cast<const char*>(op.p + (int64_t)first * op.ld);
+            src = reinterpret_cast<const char*>(op.p + (int64_t)first * ld);
             soff = 0;
-            const int rows = min(HALVES * kHalf, op.count - first);
-            const uint64_t ext = ((uint64_t)(rows - 1) * (uint64_t)op.ld + (uint64_t)K) * 2;
+            row_step = (int64_t)NW * 8 * ld * 2;
+            const uint64_t ext = ((uint64_t)(count - 1) * (uint64_t)ld + (uint64_t)K) * 2;
             extent = (uint32_t)min(ext, (uint64_t)0xffffffffu);
-#pragma unroll
-            for (int h = 0; h < HALVES; ++h)
-#pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    const int row = (j * NW + wave) * 8 + lane / 8;
-                    const int vec = (lane % 8) ^ ((row >> 1) & 7);
-                    const int r = min(h * kHalf + row, rows - 1);
-                    voff[h * J + j] = (uint32_t)(((int64_t)r * op.ld + vec * 8) * 2);
-                }
         } else {
-            const int cols = min(HALVES * kHalf, op.count - first);
-            src = reinterpret_cast<const char*>(op.p + (int64_t)(wave * 4) * op.ld + first);
-            step = (int64_t)kTileK * op.ld * 2;
-            row_step = (int64_t)NW * 4 * op.ld * 2;
-            const uint64_t ext = ((uint64_t)3 * (uint64_t)op.ld + (uint64_t)cols) * 2;
+            src = reinterpret_cast<const char*>(op.p + (int64_t)(wave * 4) * ld + first);
+            step = (int64_t)kTileK * ld * 2;
+            row_step = (int64_t)NW * 4 * ld * 2;
+            // rows of k reached from src: 4 (each copy instruction has its own base) or, with the large tile's offsets, 48 more
+            const uint64_t ext = ((uint64_t)(HALVES == 2 ? 51 : 3) * (uint64_t)ld + (uint64_t)count) * 2;
             extent = (uint32_t)min(ext, (uint64_t)0xffffffffu);
+        }
+    }
+    __device__ __forceinline__ void set_copies(int lane)
+    {
+        if constexpr (LAYOUT == K_ROWS) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const int row = (j * NW + wave) * 8 + lane / 8;
+                const int vec = (lane % 8) ^ ((row >> 1) & 7);
+                voff[j] = (uint32_t)(((int64_t)row * ld + vec * 8) * 2);
+            }
+        } else {
             const int k = wave * 4 + lane / 16;
             const int vec = (lane % 16) ^ (((k & 3) << 2) | (((k >> 3) & 1) << 1));
 #pragma unroll
             for (int h = 0; h < HALVES; ++h) {
-                const int col = min(h * kHalf + vec * 8, cols - 8);      // counts are multiples of 8
-                voff[h] = (uint32_t)(((int64_t)(lane / 16) * op.ld + col) * 2);
+                const int col = min(h * kHalf + vec * 8, count - 8);     // counts are multiples of 8
+                voff[h] = (uint32_t)(((int64_t)(lane / 16) * ld + col) * 2);
             }
         }
     }
-
-    __device__ __forceinline__ void set_reads(bf16_t* lds_, int wave_, int wave_row)
+    __device__ __forceinline__ void set_reads(bf16_t* lds_, int wave_row, int lane)
     {
         lds = lds_;
-        wave = wave_;
-        const int lane = threadIdx.x & 63;
         if constexpr (LAYOUT == K_ROWS) {
             const int row = wave_row + (lane & 15);
 #pragma unroll
@@ -155,25 +164,25 @@ struct TileOperand {
         }
     }
 
-    // This wave's share of half h of the K tile `back` tiles before the cursor, into stage s; one of its J instructions.
-    __device__ __forceinline__ void copy_part(int j, int h, int s, int back = 0) const
+    // This wave's share of half h of the K tile at the cursor, into stage s; one of its J instructions.
+    __device__ __forceinline__ void copy_part(int j, int h, int s) const
     {
         bf16_t* dst = lds + (s * HALVES + h) * kHalfElems;
         if constexpr (LAYOUT == K_ROWS) {
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, (int)extent, kRawBufferFlags);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
-                                                     voff[h * J + j], soff - back * kTileK * 2, 0, 0);
+                                                     voff[j], soff, 0, 0);
         } else {
             const __amdgpu_buffer_rsrc_t rs =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step - back * step), 0, (int)extent, kRawBufferFlags);
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step), 0, (int)extent, kRawBufferFlags);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
                                                      voff[h], 0, 0, 0);
         }
     }
-    __device__ __forceinline__ void copy(int h, int s, int back = 0) const
+    __device__ __forceinline__ void copy(int h, int s) const
     {
 #pragma unroll
-        for (int j = 0; j < J; ++j) copy_part(j, h, s, back);
+        for (int j = 0; j < J; ++j) copy_part(j, h, s);
     }
     __device__ __forceinline__ void advance()
     {
@@ -250,70 +259,65 @@ struct TileOperand {
     }
 };
 
+// Columns [first, first + width) of the result.
+struct ColumnTile {
+    int first, width;
+};
+
 // ---------------------------------------------------------------------------------------------
-// 256 x 256 tile, eight waves in two groups of four that take turns
+// 256 x 256 tile, four waves (gemm_loop.hpp)
 // ---------------------------------------------------------------------------------------------
-// A wave alternates read phases (fragments LDS -> registers) and multiply phases (16 MFMAs), with a
-// barrier after each; its share of a copy global -> LDS is issued in one of the two, see below.  The second group runs one phase behind the
-// first, and each SIMD holds one wave of each group: while one multiplies, the other reads, so the
-// matrix pipe always has a wave with its operands in registers.  (With all eight waves in step, as
-// before, every wave waited for its fragments at the same time.)
+// Wave (wm, wn) owns the 64-row pieces at rows 128 h + 64 wm, h = 0, 1, and the columns 64 wn ..+63 of half 0 and
+// 16 j1 wn ..+16 j1 - 1 of half 1, where j1 = 1..4 is a quarter of the width of half 1: with B K_ROWS the tile may be 160,
+// 192, 224 or 256 columns wide.  The tiles of a product share its columns evenly, in units of 32 (columns()), so
+// that a last tile of a few columns does not cost a whole one: the parts that multiply half 1 leave after j1 of four blocks.
 //
-// Wave (wm, wn), wm = group, owns the four 64 x 32 pieces at rows 128 h + 64 wm, columns 128 g + 32 wn;
-// per K tile it multiplies them in the order (0,0) (0,1) (1,0) (1,1):
-//     phase   reads                 copies (tile k + 2)     multiplies
-//     1       A half 0              B half 0                (0,0)
-//     2       B half 1              A half 0                (0,1)
-//     3       A half 1              B half 1                (1,0)
-//     4       B half 0 of k + 1     A half 1                (1,1)
-// Count barriers as time slots; in slot s group 0 runs segment s of its sequence [read, multiply, read,
-// ...] and group 1 segment s - 1.
-//   * A half may be overwritten by a copy issued one read phase after the phase that read it: group 0
-//     issues it in slot s + 2, group 1 finished its reads (waited for before its barrier) in slot s + 1.
-//   * A half is read in the read phase after one that ended with a wait for it: each wave waits for its
-//     own share and then passes the barrier; group 1's wait lies in slot s + 1, the first read in s + 2.
-//     Copies complete in order, and six halves (twelve instructions of a wave) are issued after the one
-//     the next phase needs: so every read phase ends with "at most 12 outstanding" -- ten where the
-//     phase's own copy is issued after that wait, in the multiply phase (one slot later: also safe).
-// Both LDS stages are in flight all the time: a copy has six phase pairs (about 3000 clocks) to land.
-//
-// Where the copy goes: the read phase is the longer of the two (four waves take 32 KB out of LDS in about the
-// 256 clocks that 16 MFMAs last), and a copy instruction holds up the reads behind it.  With both operands
-// K_ROWS it is issued right after the reads and overlaps them; a K_COLS read returns only when its data
-// is there, so the copy goes between the MFMAs instead, its two instructions apart.  Products of
-// 8192 x 32768 x 2048, TFLOP/s, copy before the reads / after them / between the MFMAs: both K_ROWS 1493 /
-// 1570 / 1539 (contraction 8192, strided: 1461 / 1557 / 1513), A K_COLS 1425 / 1395 / 1434, both K_COLS
-// 1365 / 1363 / 1412.  (Copies out of L2 only would be 3 to 8 % faster still, no copies at all 22 %.)
-//
-// Against 1240 / 1340 for the eight-waves-in-step loop it replaces at 2048 x 8192 x 32768 / 32768 x 2048 x 8192
-// (hipBLASLt: 1550 / 1570 on the same card).  Raising the multiplying wave's priority (s_setprio) made it
-// 3 % slower.
+// begin() issues the first copies, finish() does the rest: a kernel that walks several tiles begins the next one
+// before it works on the results of the last.
 template <int LA, int LB>
 struct TileLarge {
-    static constexpr int BM = 256, BN = 256, NW = 8, NT = 512;
-    static constexpr int WAVES_PER_SIMD = 2;
-    static constexpr int MI = 8, NJ = 4;                       // 16 x 16 blocks of a wave
+    static constexpr int BM = 256, BN = 256, NW = 4, NT = 256;
+    static constexpr int WAVES_PER_SIMD = 1;
+    static constexpr int MI = 8, NJ = 8;                       // 16 x 16 blocks of a wave
     static constexpr int WAVES_M = 2;
-    static constexpr bool kCopyAfterReads = LA == K_ROWS && LB == K_ROWS;
-    static constexpr int kSteady = kCopyAfterReads ? 12 : 10;  // copy instructions outstanding at the end of a read phase
     static constexpr size_t LDS_BYTES = 8 * (size_t)kHalfElems * sizeof(bf16_t);
 
     TileOperand<LA, NW, 2, 4> a;
-    TileOperand<LB, NW, 2, 2> b;
+    TileOperand<LB, NW, 2, 4> b;
     f32x4 acc[MI][NJ];
-    bf16x8 fa[2][4], fb[2][2][2];
-    int wm;
+    uint32_t lds_base;
+    uint32_t y_shift;         // K_ROWS B: bytes from a half 0 read address to that of half 1
+    int wave, j1, kt;
 
-    static __device__ __forceinline__ int row_off(int wave, int i) { return (i >> 2) * 128 + (wave >> 2) * 64 + (i & 3) * 16; }
-    static __device__ __forceinline__ int col_off(int wave, int j) { return (j >> 1) * 128 + (wave & 3) * 32 + (j & 1) * 16; }
-    static __device__ __forceinline__ int wave_m(int wave) { return wave >> 2; }
+    static __device__ __forceinline__ int row_off(int wave, int i) { return (i >> 2) * 128 + (wave >> 1) * 64 + (i & 3) * 16; }
+    __device__ __forceinline__ int col_off(int wave, int j) const
+    {
+        return j < 4 ? (wave & 1) * 64 + j * 16 : 128 + (wave & 1) * 16 * j1 + (j - 4) * 16;
+    }
+    static __device__ __forceinline__ int wave_m(int wave) { return wave >> 1; }
+    __device__ __forceinline__ int blocks() const { return 4 + j1; }          // column blocks that hold results
+
+    // Tile t of ceil(count / 256).
+    static __device__ __forceinline__ ColumnTile columns(int count, int t)
+    {
+        if constexpr (LB == K_COLS) return ColumnTile{t * BN, BN};
+        const int tiles = (count + BN - 1) / BN, units = (count + 31) / 32;
+        const int each = units / tiles, more = units - each * tiles;
+        return ColumnTile{32 * (t * each + min(t, more)), 32 * (each + (t < more ? 1 : 0))};
+    }
 
     __device__ __forceinline__ void init(unsigned char* lds)
     {
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        wm = wave >> 2;
-        a.set_reads(reinterpret_cast<bf16_t*>(lds), wave, (wave >> 2) * 64);
-        b.set_reads(reinterpret_cast<bf16_t*>(lds) + 4 * kHalfElems, wave, (wave & 3) * 32);
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+    }
+    // A lane's addresses are formed anew for each of the two blocks of assembly: kept over the main loop they are
+    // spilled, and their reloads wait for the copies in flight.
+    static __device__ __forceinline__ int fresh_lane()
+    {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        return lane;
     }
     __device__ __forceinline__ void clear()
     {
@@ -321,172 +325,92 @@ struct TileLarge {
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        j1 = 4;
     }
-    // 16 MFMAs; `copy(j)` issues instruction j (0, 1) of a copy between them.
-    template <int H, int G, class Copy>
-    __device__ __forceinline__ void multiply(Copy copy)
+    // K a positive multiple of 64, or 0: nothing is copied but zeros, and finish() may not follow.  No wave may still read from LDS.
+    __device__ __forceinline__ void begin(const Operand& A, int m0, const Operand& B, ColumnTile c, int K)
     {
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[H * 4 + i][G * 2 + j] =
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ks][i], fb[G][ks][j], acc[H * 4 + i][G * 2 + j], 0, 0, 0);
-                if (ks == 0 && i == 1) copy(0);
-                if (ks == 1 && i == 0) copy(1);
-            }
-        bare_barrier();
+        const int lane = fresh_lane();
+        a.set_tile(A, m0, K, wave);
+        b.set_tile(B, c.first, K, wave, c.width);
+        a.set_copies(lane);
+        b.set_copies(lane);
+        const int width = min(c.width, B.count - c.first);
+        j1 = LB == K_COLS ? (width > kHalf ? 4 : 1) : max((width + 31) / 32 - 4, 1);
+        y_shift = (uint32_t)((wave & 1) * (16 * j1 - 64) * 128);
+        kt = K / kTileK;
+        const uint64_t pa = (uint64_t)(uintptr_t)a.src, pb = (uint64_t)(uintptr_t)b.src;
+#define UL_POINTERS [pa] "s"(pa), [pb] "s"(pb)
+        if constexpr (LA == K_ROWS && LB == K_ROWS)
+            asm volatile(UL_BEGIN(ROWS, ROWS) : : UL_IN, UL_POINTERS, UL_IN_COPY_ROWS_A, UL_IN_COPY_ROWS_B : UL_CLOBBERS);
+        else if constexpr (LA == K_COLS && LB == K_ROWS)
+            asm volatile(UL_BEGIN(COLS, ROWS) : : UL_IN, UL_POINTERS, UL_IN_COPY_COLS_A, UL_IN_COPY_ROWS_B : UL_CLOBBERS);
+        else
+            asm volatile(UL_BEGIN(COLS, COLS) : : UL_IN, UL_POINTERS, UL_IN_COPY_COLS_A, UL_IN_COPY_COLS_B : UL_CLOBBERS);
     }
-    template <int H, int G>
-    __device__ __forceinline__ void multiply()
+    // acc = the product over K.  On return no wave reads from LDS any more.
+    __device__ __forceinline__ void finish()
     {
-        multiply<H, G>([](int) {});
+        static_assert(LA == K_COLS || LB == K_ROWS, "not written out");
+        const int lane = fresh_lane();
+        a.set_copies(lane);
+        b.set_copies(lane);
+        a.set_reads(nullptr, (wave >> 1) * 64, lane);
+        b.set_reads(nullptr, (wave & 1) * 64, lane);
+        uint64_t pa, pb;
+        cursors(pa, pb);
+        f32x32 f0, f1, f2, f3;
+#define UL_FRAGMENTS "=&{v[128:159]}"(f0), "=&{v[160:191]}"(f1), "=&{v[192:223]}"(f2), "=&{v[224:255]}"(f3)
+#define UL_MAIN_IN UL_IN, UL_POINTERS, [j1] "s"(j1)
+        if constexpr (LA == K_ROWS && LB == K_ROWS)
+            asm volatile(UL_MAIN(ROWS, ROWS) : UL_BLOCKS(UL_OUT) UL_FRAGMENTS
+                         : UL_MAIN_IN, UL_IN_COPY_ROWS_A, UL_IN_COPY_ROWS_B, UL_IN_READ_ROWS_A, UL_IN_READ_ROWS_B : UL_CLOBBERS);
+        else if constexpr (LA == K_COLS && LB == K_ROWS)
+            asm volatile(UL_MAIN(COLS, ROWS) : UL_BLOCKS(UL_OUT) UL_FRAGMENTS
+                         : UL_MAIN_IN, UL_IN_COPY_COLS_A, UL_IN_COPY_ROWS_B, UL_IN_READ_COLS_A, UL_IN_READ_ROWS_B : UL_CLOBBERS);
+        else
+            asm volatile(UL_MAIN(COLS, COLS) : UL_BLOCKS(UL_OUT) UL_FRAGMENTS
+                         : UL_MAIN_IN, UL_IN_COPY_COLS_A, UL_IN_COPY_COLS_B, UL_IN_READ_COLS_A, UL_IN_READ_COLS_B : UL_CLOBBERS);
     }
-    // End of a read phase: the fragments are in registers, and at most VM of this wave's copies are outstanding.
-    template <int VM>
-    __device__ __forceinline__ void read_done()
+    // The same with the caller's 32 running values given to the block, which leaves them alone, in registers of their own: the
+    // compiler would keep some of them in scratch memory around it, and a reload waits for every copy in flight.
+    __device__ __forceinline__ void finish_keep(float (&m)[NJ], float (&S)[NJ], float (&C)[NJ], float (&T)[NJ])
     {
-        ULORL_WAIT_LDS(0);
-        if constexpr (VM >= 0) ULORL_WAIT_VMEM(VM);
-        bare_barrier();
+        const int lane = fresh_lane();
+        a.set_copies(lane);
+        b.set_copies(lane);
+        a.set_reads(nullptr, (wave >> 1) * 64, lane);
+        b.set_reads(nullptr, (wave & 1) * 64, lane);
+        uint64_t pa, pb;
+        cursors(pa, pb);
+        f32x32 f0, f1, f2, f3;
+        asm volatile(UL_MAIN(COLS, ROWS) : UL_BLOCKS(UL_OUT) UL_FRAGMENTS
+                         : UL_MAIN_IN, UL_IN_COPY_COLS_A, UL_IN_COPY_ROWS_B, UL_IN_READ_COLS_A, UL_IN_READ_ROWS_B, "{v96}"(m[0]), "{v97}"(m[1]), "{v98}"(m[2]), "{v99}"(m[3]), "{v100}"(m[4]), "{v101}"(m[5]), "{v102}"(m[6]), "{v103}"(m[7]), "{v104}"(S[0]), "{v105}"(S[1]), "{v106}"(S[2]), "{v107}"(S[3]), "{v108}"(S[4]), "{v109}"(S[5]), "{v110}"(S[6]), "{v111}"(S[7]), "{v112}"(C[0]), "{v113}"(C[1]), "{v114}"(C[2]), "{v115}"(C[3]), "{v116}"(C[4]), "{v117}"(C[5]), "{v118}"(C[6]), "{v119}"(C[7]), "{v120}"(T[0]), "{v121}"(T[1]), "{v122}"(T[2]), "{v123}"(T[3]), "{v124}"(T[4]), "{v125}"(T[5]), "{v126}"(T[6]), "{v127}"(T[7]) : UL_CLOBBERS);
     }
-    // One K tile out of stage s.  COPY: the copies of tile k + 2 go along; NEXT: there is a tile k + 1.
-    template <bool COPY, bool NEXT, int W1, int W2, int W3, int W4>
-    __device__ __forceinline__ void tile(int s)
+    // x = block (I, J) of the result, taken when it is needed.
+    template <int I, int J>
+    __device__ __forceinline__ void take(float (&x)[4]) const
     {
-        a.read(0, s, fa);
-        phase<0, 0, COPY, W1>(b, 0, s);
-        b.read(1, s, fb[1]);
-        phase<0, 1, COPY, W2>(a, 0, s);
-        a.read(1, s, fa);
-        phase<1, 0, COPY, W3>(b, 1, s);
-        if constexpr (NEXT) b.read(0, s ^ 1, fb[0]);
-        phase<1, 1, COPY, W4>(a, 1, s);
-        if constexpr (COPY) {
-            a.advance();
-            b.advance();
-        }
+        UL_BLOCKS(UL_TAKE)
     }
-    // The rest of a phase whose reads have been issued: the copy of half h of operand op, the waits, the MFMAs.
-    template <int H, int G, bool COPY, int W, class Op>
-    __device__ __forceinline__ void phase(const Op& op, int h, int s)
+    // Value p (4 i + r; -1: none, the result is then anything) of this lane in column block J.
+    template <int J>
+    __device__ __forceinline__ float pick(int p) const
     {
-        if constexpr (COPY && kCopyAfterReads) {
-            __builtin_amdgcn_sched_barrier(0);
-            op.copy(h, s);
-        }
-        read_done<W>();
-        multiply<H, G>([&](int j) {
-            if constexpr (COPY && !kCopyAfterReads) {
-                __builtin_amdgcn_sched_barrier(0);
-                op.copy_part(j, h, s);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        });
+        float z = 0.0f, t;
+        UL_COLUMNS(UL_PICK)
+        return z;
     }
-    __device__ __forceinline__ void copy_tile(int s)
+    // Where begin() left the copy cursors, B's one K tile further (a K_ROWS operand's offsets count from k = 0).
+    __device__ __forceinline__ void cursors(uint64_t& pa, uint64_t& pb) const
     {
-        b.copy(0, s);
-        a.copy(0, s);
-        b.copy(1, s);
-        a.copy(1, s);
-        a.advance();
-        b.advance();
+        pa = (uint64_t)(uintptr_t)a.src + (LA == K_COLS ? a.step : 0);
+        pb = (uint64_t)(uintptr_t)b.src + (LB == K_COLS ? 2 * b.step : 0);
     }
-    // First copies and the first read; the second group falls one phase behind.
-    template <int W0, int W1>
-    __device__ __forceinline__ void start()
+    __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, ColumnTile c, int K)
     {
-        ULORL_WAIT_VMEM(W0);               // half 0 of B has landed (this wave's share) ...
-        bare_barrier();                    // ... and everybody's
-        if (wm == 1) bare_barrier();
-        b.read(0, 0, fb[0]);
-        read_done<W1>();                   // half 0 of A
-        bare_barrier();                    // the multiply phase that would follow
-    }
-    // A tile with no column beyond the first 128: only half 0 of B exists, two phases per K tile,
-    //     phase   reads                   copies                     multiplies
-    //     1       B half 0, A half 0      A half 1 of k + 1          (0,0)
-    //     2       A half 1                B, A halves 0 of k + 2     (1,0)
-    // and by the same count of slots as above: what phase 1 reads was waited for at the end of phase 2 before
-    // (three halves are issued after it: six instructions), what phase 2 reads at the end of phase 1
-    // (likewise), and every copy goes where the phase before it read.
-    // It takes about three quarters of a whole tile's time (three quarters of the copies, the same start and
-    // store).  Backward call, 2048 x 151936, whole / half last tile: 300 rows 819 / 800 us, 520 1145 / 1105,
-    // 777 1513 / 1489, 2100 3327 / 3234.
-    static __device__ __forceinline__ bool half_tile(const Operand& B, int n0) { return B.count - n0 <= kHalf; }
-    template <bool COPY1, bool COPY2, int W1, int W2>
-    __device__ __forceinline__ void tile_half(int s)
-    {
-        if constexpr (COPY1) a.copy(1, s ^ 1, 1);
-        b.read(0, s, fb[0]);
-        a.read(0, s, fa);
-        read_done<W1>();
-        multiply<0, 0>();
-        if constexpr (COPY2) {
-            b.copy(0, s);
-            a.copy(0, s);
-            a.advance();
-            b.advance();
-        }
-        a.read(1, s, fa);
-        read_done<W2>();
-        multiply<1, 0>();
-    }
-    __device__ __forceinline__ void run_half(int KT)
-    {
-        b.copy(0, 0);
-        a.copy(0, 0);
-        a.copy(1, 0);
-        a.advance();
-        b.advance();
-        if (KT > 1) {
-            b.copy(0, 1);
-            a.copy(0, 1);
-            a.advance();
-            b.advance();
-            ULORL_WAIT_VMEM(6);
-        } else {
-            ULORL_WAIT_VMEM(2);
-        }
-        bare_barrier();
-        if (wm == 1) bare_barrier();
-        int k = 0;
-        for (; k + 2 < KT; ++k) tile_half<true, true, 6, 6>(k & 1);
-        if (KT > 1) {
-            tile_half<true, false, 6, 2>(k & 1);
-            ++k;
-        }
-        tile_half<false, false, 0, -1>(k & 1);
-        if (wm == 0) bare_barrier();
-    }
-    // acc = the product over K (a positive multiple of 64).  On return every wave is past its last LDS read.
-    __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, int n0, int K)
-    {
-        clear();
-        const int KT = K / kTileK;
-        a.set_tile(A, m0, K);
-        b.set_tile(B, n0, K);
-        if (half_tile(B, n0)) {
-            run_half(KT);
-            return;
-        }
-        copy_tile(0);
-        if (KT > 1) {
-            copy_tile(1);
-            start<14, 12>();
-            int k = 0;
-            for (; k + 2 < KT; ++k) tile<true, true, kSteady, kSteady, kSteady, kSteady>(k & 1);
-            tile<false, true, 10, 8, 6, 4>(k & 1);
-            ++k;
-            tile<false, false, 2, 0, -1, -1>(k & 1);
-        } else {
-            start<6, 4>();
-            tile<false, false, 2, 0, -1, -1>(0);
-        }
-        if (wm == 0) bare_barrier();       // the groups are in step again
+        begin(A, m0, B, c, K);
+        finish();
     }
 };
 
@@ -504,17 +428,19 @@ struct TileSmall {
     TileOperand<LA, NW, 1, 4> a;
     TileOperand<LB, NW, 1, 4> b;
     f32x4 acc[MI][NJ];
+    int wave;
 
     static __device__ __forceinline__ int row_off(int wave, int i) { return (wave >> 1) * 64 + i * 16; }
     static __device__ __forceinline__ int col_off(int wave, int j) { return (wave & 1) * 64 + j * 16; }
     static __device__ __forceinline__ int wave_m(int wave) { return wave >> 1; }
-    static __device__ __forceinline__ bool half_tile(const Operand&, int) { return false; }
+    static __device__ __forceinline__ int blocks() { return NJ; }
+    static __device__ __forceinline__ ColumnTile columns(int, int t) { return ColumnTile{t * BN, BN}; }
 
     __device__ __forceinline__ void init(unsigned char* lds)
     {
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        a.set_reads(reinterpret_cast<bf16_t*>(lds), wave, (wave >> 1) * 64);
-        b.set_reads(reinterpret_cast<bf16_t*>(lds) + 2 * kHalfElems, wave, (wave & 1) * 64);
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        a.set_reads(reinterpret_cast<bf16_t*>(lds), (wave >> 1) * 64, threadIdx.x & 63);
+        b.set_reads(reinterpret_cast<bf16_t*>(lds) + 2 * kHalfElems, (wave & 1) * 64, threadIdx.x & 63);
     }
     __device__ __forceinline__ void clear()
     {
@@ -533,12 +459,40 @@ struct TileSmall {
     // Tile k is in stage k & 1.  It is read once this wave's share has landed (the eight copies of tile
     // k + 1 may be outstanding) and everybody has passed a barrier; after the second barrier every wave
     // has its fragments in registers and tile k + 2 may overwrite the stage.
-    __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, int n0, int K)
+    template <int I, int J>
+    __device__ __forceinline__ void take(float (&x)[4]) const
+    {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = acc[I][J][r];
+    }
+    template <int J>
+    __device__ __forceinline__ float pick(int p) const
+    {
+        float z = 0.0f;
+        if (__any(p >= 0)) {
+#pragma unroll
+            for (int n = 0; n < 4 * MI; ++n) z = p == n ? acc[n / 4][J][n % 4] : z;
+        }
+        return z;
+    }
+    // The two workgroups of a compute unit cover each other's start: nothing is begun early.
+    const Operand* next_a;
+    const Operand* next_b;
+    int next_m, next_n, next_k;
+    __device__ __forceinline__ void begin(const Operand& A, int m0, const Operand& B, ColumnTile c, int K)
+    {
+        next_a = &A; next_b = &B; next_m = m0; next_n = c.first; next_k = K;
+    }
+    __device__ __forceinline__ void finish_keep(float (&m)[NJ], float (&S)[NJ], float (&C)[NJ], float (&T)[NJ]) { finish(); }
+    __device__ __forceinline__ void finish() { run(*next_a, next_m, *next_b, ColumnTile{next_n, BN}, next_k); }
+    __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, ColumnTile c, int K)
     {
         clear();
         const int KT = K / kTileK;
-        a.set_tile(A, m0, K);
-        b.set_tile(B, n0, K);
+        a.set_tile(A, m0, K, wave);
+        b.set_tile(B, c.first, K, wave);
+        a.set_copies(threadIdx.x & 63);
+        b.set_copies(threadIdx.x & 63);
         copy_tile(0);
         if (KT > 1) copy_tile(1);
         for (int k = 0; k < KT; ++k) {
@@ -582,8 +536,11 @@ struct TileRagged {
     static __device__ __forceinline__ int col_off(int wave, int j) { return (wave & 1) * 64 + j * 16; }
 
     __device__ __forceinline__ void init(unsigned char* p) { lds = reinterpret_cast<bf16_t*>(p); }
-    __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, int n0, int K)
+    static __device__ __forceinline__ int blocks() { return NJ; }
+    static __device__ __forceinline__ ColumnTile columns(int, int t) { return ColumnTile{t * BN, BN}; }
+    __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, ColumnTile c, int K)
     {
+        const int n0 = c.first;
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
         for (int i = 0; i < MI; ++i)

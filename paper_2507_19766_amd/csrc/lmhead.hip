@@ -50,7 +50,8 @@ __device__ __forceinline__ void store_tile_f32(const Tile& T, float* __restrict_
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int j = 0; j < Tile::NJ; ++j) {
-        const int n = n0 + Tile::col_off(wave, j) + (lane & 15);
+        if (j >= T.blocks()) continue;
+        const int n = n0 + T.col_off(wave, j) + (lane & 15);
         if (n >= N) continue;
 #pragma unroll
         for (int i = 0; i < Tile::MI; ++i) {
@@ -118,11 +119,12 @@ void gemm_tn_kernel(const GemmArgs g, int group_m)
     if (!tile_coords((int)blockIdx.x, (g.a.count + Tile::BN - 1) / Tile::BN, (g.b.count + Tile::BM - 1) / Tile::BM, group_m, tile_m, tile_n))
         return;
     // C has n contiguous: B takes the engine's m side
-    const int m0 = tile_n * Tile::BM, n0 = tile_m * Tile::BN;
+    const int m0 = tile_n * Tile::BM;
+    const ColumnTile c = Tile::columns(g.a.count, tile_m);
     Tile T;
     T.init(lds_raw);
-    T.run(g.b, m0, g.a, n0, g.K);
-    store_tile_f32<false>(T, g.C, g.ldc, g.b.count, g.a.count, m0, n0, g.wide != 0);
+    T.run(g.b, m0, g.a, c, g.K);
+    store_tile_f32<false>(T, g.C, g.ldc, g.b.count, g.a.count, m0, c.first, g.wide != 0);
 }
 
 // d_hidden[t, :] = bf16(sum over slabs of acc[slab][pos[t], :]) (pos == NULL: row t itself); rows without a
@@ -303,6 +305,14 @@ struct StatQuad {
     float m, S, T, zy;
 };
 
+// f(integral_constant i) for i = 0 .. N - 1.
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void each_index(F f)
+{
+    f(std::integral_constant<int, I>{});
+    if constexpr (I + 1 < N) each_index<N, I + 1>(f);
+}
+
 // One workgroup: the statistics of one tile of tokens over one slice of the vocabulary.
 template <class Tile>
 ULORL_TILE_KERNEL(Tile::NT, Tile::WAVES_PER_SIMD)
@@ -316,10 +326,10 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
     const int V = W.count, Ntok = H.count;
     int t_tile, split;
     if (!tile_coords((int)blockIdx.x, (Ntok + Tile::BN - 1) / Tile::BN, splits, group_m, t_tile, split)) return;
-    const int t0 = t_tile * Tile::BN;
+    const ColumnTile cols = Tile::columns(Ntok, t_tile);
+    const int t0 = cols.first;
     const int vb = split * v_per_split;
     const int ve = min(V, vb + v_per_split);
-    const bool half = Tile::half_tile(H, t0);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int quad = lane >> 4;
     constexpr int MI = Tile::MI, NJ = Tile::NJ;
@@ -328,133 +338,166 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
     // with its exponent (log2 units).  The exponents carry the rounding residual of fl(m log2e), the
     // same for every term; it is taken out once at the end.  The residual grows with m: from kWide on it
     // exceeds 32 and soon the range of 2^x, so a workgroup that met such a maximum (S is 0 or not finite, or the last
-    // maximum is one) walks its tiles again and takes those columns' sums from exponents of z - m.
+    // maximum is one; its S is handed on as NaN) walks its tiles again and takes those columns' sums from exponents of z - m.
     float m[NJ], S[NJ], Sc[NJ], T[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         m[j] = kEmpty; S[j] = 0.0f; Sc[j] = 0.0f; T[j] = 0.0f;
     }
+    Tile G;
+    G.init(lds_raw);
+    G.begin(W, vb, H, cols, K);
     for (int c = threadIdx.x; c < Tile::BN; c += Tile::NT) {
         chosen[c] = kEmpty;
         token[c] = t0 + c < Ntok ? token_ids[t0 + c] : -1;
     }
     __syncthreads();
 
-    Tile G;
-    G.init(lds_raw);
-    for (int v0 = vb; v0 < ve; v0 += Tile::BM) {
-        G.run(W, v0, H, t0, K);
-        // RAGGED: the tile reaches past the end of this workgroup's vocabulary range
-        auto absorb_tile = [&](auto ragged_c) {
-            constexpr bool RAGGED = decltype(ragged_c)::value;
+    // One tile, finished, and the next one begun: its first copies go along with the work on this one's results.  That work has no
+    // branch in it: the accumulators of TileLarge lie in registers that only moves can read, and what a second block
+    // uses is moved at once, all 256.  RAGGED: the tile reaches past the end of this workgroup's vocabulary range.
+    auto absorb_tile = [&](int v0, auto ragged_c) {
+        constexpr bool RAGGED = decltype(ragged_c)::value;
+        G.finish_keep(m, S, Sc, T);
+        int col0 = lane & 15, my_rows = Tile::wave_m(wave) * 64 + quad * 4;      // my rows of a tile: bits 2, 3 and 6 are these
+        asm volatile("" : "+v"(col0), "+v"(my_rows));         // nothing formed from them is kept over the loop, in registers it needs
+        const bool last = v0 + Tile::BM >= ve;
+        G.begin(W, last ? v0 : v0 + Tile::BM, H, cols, last ? 0 : K);
+        each_index<NJ>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            // the chosen token's logit, if it is one of this lane's (rare); otherwise the store goes nowhere
+            const int col = G.col_off(wave, j) + col0;
+            const int dy = token[col] - v0;
+            const int rows = j < G.blocks() ? min(Tile::BM, ve - v0) : 0;
+            const bool mine = ((uint32_t)dy < (uint32_t)rows) & ((dy & 0x4c) == my_rows);
+            const float zy = G.template pick<j>(mine ? ((dy >> 3) & 16) | ((dy >> 2) & 12) | (dy & 3) : -1);
+            *(mine ? &chosen[col] : &red[0][0][0]) = zy;
+            float z[MI][4];
+            each_index<MI>([&](auto ic) { G.template take<decltype(ic)::value, j>(z[decltype(ic)::value]); });
+            float cm = kEmpty;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if (half && j >= NJ / 2) break;               // columns without a token
-                float cm = kEmpty;
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
+                for (int r = 0; r < 4; ++r)
+                    if (!RAGGED || v0 + Tile::row_off(wave, i) + 4 * quad + r < ve) cm = fmaxf(cm, z[i][r]);
+            const float mn = fmaxf(m[j], cm);
+            const float mL = mn * kLog2e;
+            const float d = m[j] * kLog2e - mL;               // <= 0
+            const float sc = fast_exp2(d);
+            const float Tn = sc * fmaf(d, S[j], T[j]);
+            const float Sn = sc * S[j];
+            const float Scn = sc * Sc[j];
+            float ps[4] = {0.0f, 0.0f, 0.0f, 0.0f}, pt[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // this tile's terms first, then one TwoSum
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (!RAGGED || v0 + Tile::row_off(wave, i) + 4 * quad + r < ve) cm = fmaxf(cm, G.acc[i][j][r]);
-                const float mn = fmaxf(m[j], cm);
-                const float mL = mn * kLog2e;
-                const float d = m[j] * kLog2e - mL;           // <= 0
-                const float sc = fast_exp2(d);
-                const float Tn = sc * fmaf(d, S[j], T[j]);
-                const float Sn = sc * S[j];
-                const float Scn = sc * Sc[j];
-                float ps[4] = {0.0f, 0.0f, 0.0f, 0.0f}, pt[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // this tile's terms first, then one TwoSum
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float x = fmaf(G.acc[i][j][r], kLog2e, -mL);
-                        float e = fast_exp2(x);
-                        if (RAGGED && v0 + Tile::row_off(wave, i) + 4 * quad + r >= ve) { x = 0.0f; e = 0.0f; }
-                        ps[r] += e;
-                        pt[r] = fmaf(e, x, pt[r]);
-                    }
-                const float part = (ps[0] + ps[1]) + (ps[2] + ps[3]);
-                const float tsum = Sn + part;
-                const float bv = tsum - Sn;
-                const float err = (Sn - (tsum - bv)) + (part - bv);
-                S[j] = tsum; Sc[j] = Scn + err; T[j] = Tn + ((pt[0] + pt[1]) + (pt[2] + pt[3])); m[j] = mn;
-                // the chosen token's logit, if its row is one of this lane's in this tile (rare)
-                const int dy = token[Tile::col_off(wave, j) + (lane & 15)] - v0;
-                if (dy >= 0 && dy < Tile::BM && ((dy >> 6) & 1) == Tile::wave_m(wave) && ((dy >> 2) & 3) == quad && v0 + dy < ve) {
-#pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (Tile::row_off(wave, i) + 4 * quad + r == dy) chosen[Tile::col_off(wave, j) + (lane & 15)] = G.acc[i][j][r];
+                for (int r = 0; r < 4; ++r) {
+                    float x = fmaf(z[i][r], kLog2e, -mL);
+                    float e = fast_exp2(x);
+                    if (RAGGED && v0 + Tile::row_off(wave, i) + 4 * quad + r >= ve) { x = 0.0f; e = 0.0f; }
+                    ps[r] += e;
+                    pt[r] = fmaf(e, x, pt[r]);
                 }
-            }
-        };
-        if (v0 + Tile::BM <= ve) absorb_tile(std::false_type{});
-        else absorb_tile(std::true_type{});
-    }
-    auto is_wide = [&](int j) { return !(S[j] > 0.0f && S[j] < 3.0e38f) || fabsf(m[j]) >= kWide; };
-    bool any_wide = false;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-        if (!half || j < NJ / 2) any_wide |= is_wide(j);
-    // The OR over the waves goes through a stage, which no wave reads any more: __syncthreads_or brings LDS of its own, after
-    // which the stages no longer start at a multiple of 8 KB, and that costs 1.5 % of the kernel.
-    const int wave_wide = __any(any_wide);
-    int* flags = reinterpret_cast<int*>(lds_raw);
-    if (lane == 0) flags[wave] = wave_wide;
+            const float part = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+            const float tsum = Sn + part;
+            const float bv = tsum - Sn;
+            const float err = (Sn - (tsum - bv)) + (part - bv);
+            S[j] = tsum; Sc[j] = Scn + err; T[j] = Tn + ((pt[0] + pt[1]) + (pt[2] + pt[3])); m[j] = mn;
+            __builtin_amdgcn_sched_barrier(0);                // no column's values are taken before the last one's are used up
+        });
+    };
+    int v0 = vb;
+    for (; v0 + Tile::BM <= ve; v0 += Tile::BM) absorb_tile(v0, std::false_type{});
+    if (v0 < ve) absorb_tile(v0, std::true_type{});
+    ULORL_WAIT_VMEM(0);                                       // the zeros that the last begin() copied
     __syncthreads();
-    const bool again = __any(lane < Tile::NW && flags[lane] != 0);
-    float S2[NJ], T2[NJ];
-    if (again) {                                              // rare: the maxima are known now
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) S2[j] = T2[j] = 0.0f;
-#pragma unroll 1
-        for (int v0 = vb; v0 < ve; v0 += Tile::BM) {
-            G.run(W, v0, H, t0, K);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float x = (G.acc[i][j][r] - m[j]) * kLog2e;
-                        const float e = fast_exp2(x);
-                        if (v0 + Tile::row_off(wave, i) + 4 * quad + r < ve) {
-                            S2[j] += e;
-                            T2[j] = fmaf(e, x, T2[j]);
-                        }
-                    }
-        }
-    }
-
     // four lanes (L, L ^ 16, L ^ 32, L ^ 48) share a token column; then the waves stacked along the vocabulary
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        float delta = m[j] > 0.5f * kEmpty ? fmaf(m[j], kLog2e, -(m[j] * kLog2e)) : 0.0f;
-        if (again && is_wide(j)) {
-            S[j] = S2[j]; Sc[j] = delta = 0.0f; T[j] = T2[j];
-        }
+        if (j >= G.blocks()) continue;
+        const float delta = m[j] > 0.5f * kEmpty ? fmaf(m[j], kLog2e, -(m[j] * kLog2e)) : 0.0f;
         const float un = fast_exp2(-delta);
-        float mm = m[j], SS = un * (S[j] + Sc[j]), TT = un * fmaf(-delta, S[j], T[j]) * kLn2;
+        const bool wide = !(S[j] > 0.0f && S[j] < 3.0e38f) || fabsf(m[j]) >= kWide;
+        float mm = m[j], SS = wide ? __builtin_nanf("") : un * (S[j] + Sc[j]), TT = un * fmaf(-delta, S[j], T[j]) * kLn2;
 #pragma unroll
         for (int off = 16; off <= 32; off <<= 1) {
             const float m2 = __shfl_xor(mm, off), S2 = __shfl_xor(SS, off), T2 = __shfl_xor(TT, off);
             merge_nat(mm, SS, TT, m2, S2, T2);
         }
         if (lane < 16) {
-            float* q = red[Tile::wave_m(wave)][Tile::col_off(wave, j) + lane];
+            float* q = red[Tile::wave_m(wave)][G.col_off(wave, j) + lane];
             q[0] = mm; q[1] = SS; q[2] = TT;
         }
     }
     __syncthreads();
+    bool any_wide = false;
     for (int c = threadIdx.x; c < Tile::BN; c += Tile::NT) {
         float mm = red[0][c][0], SS = red[0][c][1], TT = red[0][c][2];
 #pragma unroll
         for (int w = 1; w < Tile::WAVES_M; ++w) merge_nat(mm, SS, TT, red[w][c][0], red[w][c][1], red[w][c][2]);
         const int t = t0 + c;
-        if (t < Ntok) partial[(int64_t)split * Ntok + t] = StatQuad{mm, SS, TT, chosen[c]};
+        const bool mine = c < cols.width && t < Ntok;
+        if (mine) partial[(int64_t)split * Ntok + t] = StatQuad{mm, SS, TT, chosen[c]};
+        chosen[c] = mm;
+        token[c] = mine && !(SS > 0.0f && SS < 3.0e38f);
+        any_wide |= token[c] != 0;
+    }
+    // The OR over the waves goes through a stage, which no wave reads any more: __syncthreads_or brings LDS of its own, after
+    // which the stages no longer start at a multiple of 8 KB, and that costs 1.5 % of the kernel.
+    const int wave_wide = __any(any_wide);
+    int* flags = reinterpret_cast<int*>(lds_raw);
+    if (lane == 0) flags[wave] = wave_wide;
+    __syncthreads();
+    if (!__any(lane < Tile::NW && flags[lane] != 0)) return;
+    // Rare: the tiles once more, for the columns marked in token[], whose maxima (in chosen[]) are known now.
+    __syncthreads();
+    float S2[NJ], T2[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) S2[j] = T2[j] = 0.0f;
+#pragma unroll 1
+    for (v0 = vb; v0 < ve; v0 += Tile::BM) {
+        G.run(W, v0, H, cols, K);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const float top = chosen[G.col_off(wave, j) + (lane & 15)];
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float x = (G.acc[i][j][r] - top) * kLog2e;
+                    const float e = fast_exp2(x);
+                    if (v0 + Tile::row_off(wave, i) + 4 * quad + r < ve) {
+                        S2[j] += e;
+                        T2[j] = fmaf(e, x, T2[j]);
+                    }
+                }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if (j >= G.blocks()) continue;
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            S2[j] += __shfl_xor(S2[j], off);
+            T2[j] += __shfl_xor(T2[j], off);
+        }
+        if (lane < 16) {
+            float* q = red[Tile::wave_m(wave)][G.col_off(wave, j) + lane];
+            q[1] = S2[j]; q[2] = T2[j];
+        }
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < Tile::BN; c += Tile::NT) {
+        if (token[c] == 0) continue;
+        float SS = 0.0f, TT = 0.0f;
+#pragma unroll
+        for (int w = 0; w < Tile::WAVES_M; ++w) {
+            SS += red[w][c][1];
+            TT += red[w][c][2];
+        }
+        StatQuad& q = partial[(int64_t)split * Ntok + t0 + c];
+        q.S = SS;
+        q.T = TT * kLn2;
     }
 }
 
@@ -516,7 +559,8 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
     int v_tile, t_tile;
     if (!tile_coords(bid, (a.cw + Tile::BM - 1) / Tile::BM, (Ntok + Tile::BN - 1) / Tile::BN, group_m, v_tile, t_tile)) return;
     const int v0 = a.vc0 + v_tile * Tile::BM;
-    const int t0 = t_tile * Tile::BN;
+    const ColumnTile cols = Tile::columns(Ntok, t_tile);
+    const int t0 = cols.first;
     const int V = a.W.count;
     const int vend = min(V, a.vc0 + a.cw);
     Tile G;
@@ -524,7 +568,7 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
     {
         Operand H = a.H;
         H.count = Ntok;
-        G.run(a.W, v0, H, t0, a.K);          // v0 < V: the padding columns of a chunk never fill a tile
+        G.run(a.W, v0, H, cols, a.K);          // v0 < V: the padding columns of a chunk never fill a tile
     }
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -536,11 +580,11 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
     // padding) is zeroed on the packed pair; the chosen token's element is rewritten by the one lane that holds it.
     // Per element that leaves one FMA, one exponential and half a conversion in the common path.
     const bool ragged = v0 + Tile::BM > vend;     // uniform: the tile reaches past the end of the vocabulary
-    const int n_end = (Ntok + 63) / 64 * 64 - t0;
+    const int n_end = min(cols.width, (Ntok + 63) / 64 * 64 - t0);
 #pragma unroll
     for (int j = 0; j < Tile::NJ; ++j) {
-        if (Tile::col_off(0, j) >= n_end) break;  // column blocks of the half that does not exist
-        const int n = Tile::col_off(wave, j) + (lane & 15);
+        if (j >= G.blocks()) continue;
+        const int n = G.col_off(wave, j) + (lane & 15);
         const int t = t0 + n;
         float g_mag = 0.0f, c = 0.0f;
         uint32_t flip = 0u, keep = 0u;
@@ -584,7 +628,14 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
         }
     }
     __syncthreads();
-    Image::store(lds_raw, a.dZ + (int64_t)t0 * a.ld + (v0 - a.vc0), a.ld, n_end, a.vc0 + a.cw - v0);
+    bf16_t* dst = a.dZ + (int64_t)t0 * a.ld + (v0 - a.vc0);
+    const int m_end = a.vc0 + a.cw - v0;
+    Image::store(lds_raw, dst, a.ld, n_end, m_end);
+    if (t0 + cols.width >= Ntok) {                // the last tile: zeros up to the next multiple of 64 rows
+        constexpr int VPR = Tile::BM / 8;
+        for (int q = threadIdx.x + n_end * VPR; q < ((Ntok + 63) / 64 * 64 - t0) * VPR; q += Tile::NT)
+            if (q % VPR * 8 < m_end) *reinterpret_cast<u32x4*>(dst + (int64_t)(q / VPR) * a.ld + q % VPR * 8) = u32x4{0u, 0u, 0u, 0u};
+    }
 }
 
 // One launch of the backward pass over the vocabulary chunks: the two products of the PREVIOUS
@@ -650,25 +701,28 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
                 w.ld = tail ? kTileK : w.ld;
                 z.p += k0;
                 z.count = rows;
-                if (K > 0) T.run(w, tm * B, z, tn * B, K);
+                const ColumnTile c = TileDh::columns(rows, tn);
+                if (K > 0) T.run(w, tm * B, z, c, K);
                 else T.clear();
                 float* acc = a.dh_acc + (int64_t)split * a.N * a.dh_w.count;
-                if (add) store_tile_f32<true>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
-                else store_tile_f32<false>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, tn * B, true);
+                if (add) store_tile_f32<true>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, c.first, true);
+                else store_tile_f32<false>(T, acc, a.dh_w.count, a.dh_w.count, rows, tm * B, c.first, true);
                 return;
             }
             if (!tile_coords(a.dh_first ? bid - g_dh : bid, nk, nv, a.group_m, tn, tm)) return;
             TileDw T;
             T.init(lds_raw);
-            if (rows > 0) T.run(a.dw_z, tm * B, a.dw_h, tn * B, (rows + 63) / 64 * 64);
+            if (rows > 0) T.run(a.dw_z, tm * B, a.dw_h, TileDw::columns(a.dw_h.count, tn), (rows + 63) / 64 * 64);
             else T.clear();                       // no live row: the product is zero
             const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-            for (int j = 0; j < TileDw::NJ; ++j)
+            for (int j = 0; j < TileDw::NJ; ++j) {
+                if (j >= T.blocks()) continue;
 #pragma unroll
                 for (int i = 0; i < TileDw::MI; ++i)
-                    TileImage<TileDw>::put(lds_raw, TileDw::col_off(wave, j) + (lane & 15), TileDw::row_off(wave, i) + 4 * (lane >> 4),
+                    TileImage<TileDw>::put(lds_raw, T.col_off(wave, j) + (lane & 15), TileDw::row_off(wave, i) + 4 * (lane >> 4),
                                            u32x2{pack_bf16x2(T.acc[i][j][0], T.acc[i][j][1]), pack_bf16x2(T.acc[i][j][2], T.acc[i][j][3])});
+            }
             __syncthreads();
             TileImage<TileDw>::store(lds_raw, a.d_W + (int64_t)(tn * B) * a.ld_w + tm * B, a.ld_w, a.dw_h.count - tn * B,
                                      a.dw_z.count - tm * B);
@@ -693,7 +747,11 @@ inline int64_t round_up64(int64_t x) { return (x + 63) / 64 * 64; }
 // 633 / 626, 512 x 2048 943 / 1213; 8192 x 256 x 5640 231 / 168.  Many rows and a d_W of few large tiles, which then
 // contract over all rows on a few compute units (rows x hidden x columns): 20000 x 512 x 1000 433 / 263, x 2000 458 / 297,
 // x 4096 507 / 373, x 8192 645 / 662; 20000 x 2048 x 1000 563 / 395.
-inline int forward_tile(const LaunchOpts& o, int64_t N, int64_t Hd) { return o.gemm_tile == 1 || N <= 256 || Hd <= 256 ? 1 : 0; }
+// The large tile adds 48 rows of W to a lane's 32-bit offset (kMaxLargeColsLeadingDim).
+inline int forward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
+{
+    return o.gemm_tile == 1 || N <= 256 || Hd <= 256 || V > kMaxLargeColsLeadingDim ? 1 : 0;
+}
 inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
 {
     const int64_t dw_tiles = ((V + 255) / 256) * ((Hd + 255) / 256);
@@ -1017,7 +1075,7 @@ int32_t ulorl_lmhead_token_loss_fwd(const void* hidden, const void* W, int64_t N
     } else if (R <= 0) {
         R = 1;      // only sizes the workspace layout
     }
-    const int tile = forward_tile(opts, N, Hd);
+    const int tile = forward_tile(opts, N, Hd, V);
     const LmheadLayout L = lmhead_layout(N, Hd, V, R, vocab_chunk, tile);
     if (!workspace || ((uintptr_t)workspace & 255u) != 0 || workspace_bytes < L.total) return ULORL_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;

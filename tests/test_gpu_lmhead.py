@@ -86,10 +86,19 @@ def test_backward_partitions(n, V, hidden):
 
 @pytest.mark.parametrize("n,V,hidden", [(1300, 64, 320), (1300, 136, 320), (1408, 264, 384), (1409, 1096, 392), (1537, 200, 512)])
 def test_large_tiles_with_half_empty_ones(n, V, hidden):
-    """Shapes that take the large tile, with a last token tile of 20, 128, 129 and 1 rows (up to 128: the
-    half that runs in two phases), hidden sizes whose last tile is half empty too, and contractions of one
+    """Shapes that take the large tile, with a last token tile of 20, 128, 129 and 1 rows (last tiles share
+    their columns with the others), hidden sizes whose last tile is half empty too, and contractions of one
     to four K tiles in the dHidden product."""
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_halves")
+    for dense in (False, True):
+        run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(dense_rows=dense))
+
+
+@pytest.mark.parametrize("n", [257, 290, 353, 450, 513, 545])
+def test_large_tiles_of_every_width(n):
+    """Large tiles share the tokens evenly, in units of 32 columns: two of 160 (the second with one row or empty
+    columns), of 192, of 256 and 224, three of 192 and 160; seven K tiles and a rest of the vocabulary."""
+    w = ui.shrink(ui.config(5), [n - 7, 7], V=456, hidden=1536, seg_len=64, name="lmhead_widths")
     for dense in (False, True):
         run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(dense_rows=dense))
 
@@ -313,6 +322,26 @@ def test_forward_statistics_of_large_logits(n):
 # The vocabulary in several chunks (vocab_chunk = 64 and more rows than hidden columns, so that the workspace
 # has no room for wide ones), the last one narrower and no multiple of 64; W with its last columns apart
 # (hidden a multiple of 64), padded for having few columns (V < 2 n) and padded along hidden.
+@pytest.mark.parametrize("V", [1 << 25, (1 << 25) + 8])        # the widest weight of the large tile, and the small tile beyond
+def test_forward_of_a_very_wide_vocabulary(V):
+    """Offsets into the weight of more than 2^31 bytes.  All columns are zero but for blocks at the start, in the
+    middle and at the end; the logits reach 100, whose fp32 products
+    and sums are good to 1e-5."""
+    n, Hd = 260, 264
+    g = torch.Generator(device=DEV).manual_seed(7)
+    w = torch.zeros(Hd, V, dtype=torch.bfloat16, device=DEV)
+    cols = torch.cat([torch.arange(0, 300), torch.arange(V // 2 - 200, V // 2 + 100), torch.arange(V - 300, V)]).to(DEV)
+    w[:, cols] = torch.randn(Hd, 900, generator=g, device=DEV).bfloat16()
+    h = torch.randn(n, Hd, generator=g, device=DEV).bfloat16()
+    y = cols[torch.randint(0, 900, (n,), generator=g, device=DEV)].int()
+    res = ulorl.lmhead_token_loss_fwd(h, w, y, None, None)
+    z = h.double() @ w[:, cols].double()
+    lse = torch.logsumexp(torch.cat([z, torch.full((n, 1), float(np.log(V - 900)), dtype=torch.float64, device=DEV)], 1), 1)
+    at = (h.double() * w[:, y.long()].double().T).sum(1)
+    assert float((res.lse - lse).abs().max()) <= 2e-5
+    assert float((res.logp - (at - lse)).abs().max()) <= 4e-5
+
+
 @pytest.mark.parametrize("n,V,hidden", [(700, 8392, 64), (1501, 3000, 64), (900, 6000, 72), (90, 56, 64),      # small tile
                                         (1300, 5000, 320), (1400, 2760, 320), (1300, 5000, 328)])      # large tile
 @pytest.mark.parametrize("dense", [False, True])
