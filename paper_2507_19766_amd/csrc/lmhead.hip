@@ -70,33 +70,18 @@ __device__ __forceinline__ void store_tile_f32(const Tile& T, float* __restrict_
     }
 }
 
-// bf16 tiles leave through LDS (the pipeline stages, free by now): image [n][m] with padded rows, read
-// back as 16-byte vectors so that a row of the tile goes out in one contiguous run.
-template <class Tile>
-struct TileImage {
-    static constexpr int PITCH = Tile::BM * 2 + 16;            // bytes
-    static constexpr size_t BYTES = (size_t)Tile::BN * PITCH;
-    static __device__ __forceinline__ void put(unsigned char* img, int n, int m, u32x2 four)
-    {
-        *reinterpret_cast<u32x2*>(img + n * PITCH + m * 2) = four;
-    }
-    // Rows n < n_end and columns m < m_end (both relative to the tile, m_end a multiple of 8) to C.
-    static __device__ __forceinline__ void store(const unsigned char* img, bf16_t* __restrict__ C, int64_t ldc, int n_end, int m_end)
-    {
-        constexpr int VPR = Tile::BM / 8;
-#pragma unroll 4
-        for (int q = threadIdx.x; q < Tile::BN * VPR; q += Tile::NT) {
-            const int n = q / VPR, vec = q % VPR;
-            const u32x4 x = *reinterpret_cast<const u32x4*>(img + n * PITCH + vec * 16);
-            if (n < n_end && vec * 8 < m_end) *reinterpret_cast<u32x4*>(C + (int64_t)n * ldc + vec * 8) = x;
-        }
-    }
-};
-
-template <class Tile>
-constexpr size_t tile_lds_bytes()
+// bf16 tiles, straight from the registers too.  A lane of a result block holds four rows m of a column n, packed 8 bytes; of
+// two blocks below each other (x: rows m .. m + 15, y: the next 16) lanes trade halves so that each has eight rows in
+// one 16-byte vector and four lanes 64 contiguous bytes.  A dz tile's work after its product took 20400 clocks with its
+// terms fetched column by column and its values stored through an image in LDS (5300 of them), and takes 10000 now;
+// 32768 x 8192 x 2048 dz alone 924 us before, 826 now.
+__device__ __forceinline__ void store_bf16_pair(bf16_t* __restrict__ column, int m, int m_end, bool valid, u32x2 x, u32x2 y)
 {
-    return Tile::LDS_BYTES > TileImage<Tile>::BYTES ? Tile::LDS_BYTES : TileImage<Tile>::BYTES;
+    const auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+    const int row = ((int)threadIdx.x >> 4) & 3;
+    m += (row & 1) * 16 + (row >> 1) * 8;
+    if (valid && m < m_end) *reinterpret_cast<u32x4*>(column + m) = u32x4{lo[0], hi[0], lo[1], hi[1]};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -551,6 +536,12 @@ struct DzArgs {
     const int* row_map;
 };
 
+struct DzTerm {
+    float g_mag, c;                  // -|g| (0: no gradient), log2|g| - lse log2e
+    uint32_t flip;                   // sign bits of a packed pair, set for g > 0
+    int dy;                          // row of the chosen token in the tile, or -1
+};
+
 // The tile of workgroup `bid`.  Ntok: the number of token rows; rows up to the next multiple of 64 are
 // written as zeros (the d_W product contracts over whole K tiles of 64 tokens).
 template <class Tile>
@@ -563,74 +554,74 @@ __device__ __forceinline__ void lmhead_dz_block(int bid, const DzArgs& a, int Nt
     const int t0 = cols.first;
     const int V = a.W.count;
     const int vend = min(V, a.vc0 + a.cw);
-    Tile G;
-    G.init(lds_raw);
-    {
-        Operand H = a.H;
-        H.count = Ntok;
-        G.run(a.W, v0, H, cols, a.K);          // v0 < V: the padding columns of a chunk never fill a tile
-    }
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int quad = lane >> 4;
-    using Image = TileImage<Tile>;
-    // Per token column of this lane:  dz = g (onehot - e^(z - lse)) = s (2^(z log2e + c) - |g| onehot)  with s = -sign(g),
+    // Per token column:  dz = g (onehot - e^(z - lse)) = s (2^(z log2e + c) - |g| onehot)  with s = -sign(g),
     // c = log2|g| - lse log2e.  The magnitudes are computed and rounded; a negative s is applied to the packed pair by
     // flipping sign bits (rounding to nearest even is symmetric); a column without a gradient (zero coefficient, flagged row,
     // padding) is zeroed on the packed pair; the chosen token's element is rewritten by the one lane that holds it.
     // Per element that leaves one FMA, one exponential and half a conversion in the common path.
-    const bool ragged = v0 + Tile::BM > vend;     // uniform: the tile reaches past the end of the vocabulary
-    const int n_end = min(cols.width, (Ntok + 63) / 64 * 64 - t0);
-#pragma unroll
-    for (int j = 0; j < Tile::NJ; ++j) {
-        if (j >= G.blocks()) continue;
-        const int n = G.col_off(wave, j) + (lane & 15);
+    // The terms of the tile's columns are fetched while its first copies are in flight: fetched by each lane for its eight columns
+    // after the product, two loads deep, they took 6 us of a tile's 58 (one wave per SIMD covers no wait).
+    DzTerm* terms = reinterpret_cast<DzTerm*>(lds_raw + Tile::LDS_BYTES);
+    Tile G;
+    G.init(lds_raw);
+    Operand H = a.H;
+    H.count = Ntok;
+    G.begin(a.W, v0, H, cols, a.K);          // v0 < V: the padding columns of a chunk never fill a tile
+    for (int n = threadIdx.x; n < Tile::BN; n += Tile::NT) {
+        DzTerm q = {0.0f, 0.0f, 0u, -1};
         const int t = t0 + n;
-        float g_mag = 0.0f, c = 0.0f;
-        uint32_t flip = 0u, keep = 0u;
-        int dy = -1;                              // row of the chosen token inside the tile, -1 if not this lane's
         if (t < Ntok) {
             const int tt = a.row_map != nullptr ? a.row_map[t] : t;
             const float gg = a.gcoef[tt] * a.grad_out;
             const float l = a.lse[tt];
             const int32_t yy = a.token_ids[tt];
             if (row_has_gradient(gg, l, yy, V)) {
-                const bool negate = gg > 0.0f;
-                g_mag = negate ? -gg : gg;        // -|g|
-                c = fmaf(-l, kLog2e, log2f(fabsf(gg)));
-                flip = negate ? 0x80008000u : 0u;
-                keep = 0xffffffffu;
-                const int d = yy - v0;
-                if (d >= 0 && d < Tile::BM && yy < vend && ((d >> 6) & 1) == Tile::wave_m(wave) && ((d >> 2) & 3) == quad) dy = d;
+                q.g_mag = -fabsf(gg);
+                q.c = fmaf(-l, kLog2e, log2f(fabsf(gg)));
+                q.flip = gg > 0.0f ? 0x80008000u : 0u;
+                if (yy >= v0 && yy < min(vend, v0 + Tile::BM)) q.dy = yy - v0;
             }
         }
-#pragma unroll
-        for (int i = 0; i < Tile::MI; ++i) {
-            const int mrow = Tile::row_off(wave, i) + 4 * quad;
-            float e[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) e[r] = fast_exp2(fmaf(G.acc[i][j][r], kLog2e, c));
-            if (ragged) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) e[r] = v0 + mrow + r < vend ? e[r] : 0.0f;
-            }
-            Image::put(lds_raw, n, mrow, u32x2{(pack_bf16x2(e[0], e[1]) ^ flip) & keep, (pack_bf16x2(e[2], e[3]) ^ flip) & keep});
-        }
-        if (dy >= 0) {                            // rare
-#pragma unroll
-            for (int i = 0; i < Tile::MI; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (Tile::row_off(wave, i) + 4 * quad + r == dy) {
-                        const float e = fast_exp2(fmaf(G.acc[i][j][r], kLog2e, c)) + g_mag;
-                        *reinterpret_cast<bf16_t*>(lds_raw + n * Image::PITCH + dy * 2) = (bf16_t)(to_bf16(e) ^ (bf16_t)flip);
-                    }
-        }
+        terms[n] = q;
     }
-    __syncthreads();
-    bf16_t* dst = a.dZ + (int64_t)t0 * a.ld + (v0 - a.vc0);
-    const int m_end = a.vc0 + a.cw - v0;
-    Image::store(lds_raw, dst, a.ld, n_end, m_end);
+    G.finish();                              // its barriers stand between the terms' stores and their use
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int quad = lane >> 4;
+    const int my_rows = Tile::wave_m(wave) * 64 + quad * 4;       // of the tile: those whose bits 2, 3 and 6 are these
+    const bool ragged = v0 + Tile::BM > vend;     // uniform: the tile reaches past the end of the vocabulary
+    const int n_end = min(cols.width, (Ntok + 63) / 64 * 64 - t0), m_end = a.vc0 + a.cw - v0;
+    bf16_t* const dst = a.dZ + (int64_t)t0 * a.ld + (v0 - a.vc0);
+#pragma unroll
+    for (int j = 0; j < Tile::NJ; ++j) {
+        if (j >= G.blocks()) continue;
+        const int n = G.col_off(wave, j) + (lane & 15);
+        const DzTerm q = terms[n];
+        const uint32_t keep = q.g_mag != 0.0f ? 0xffffffffu : 0u;
+        const bool mine = q.dy >= 0 && (q.dy & 0x4c) == my_rows;
+        // CARE: with columns beyond the vocabulary, or the chosen token of one of the wave's columns (one block of 40)
+        auto column = [&](auto care_c) {
+            constexpr bool CARE = decltype(care_c)::value;
+            u32x2 packed[Tile::MI];
+#pragma unroll
+            for (int i = 0; i < Tile::MI; ++i) {
+                const int mrow = Tile::row_off(wave, i) + 4 * quad;
+                float e[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    e[r] = fast_exp2(fmaf(G.acc[i][j][r], kLog2e, q.c));
+                    if (CARE && mine && mrow + r == q.dy) e[r] += q.g_mag;
+                    if (CARE && v0 + mrow + r >= vend) e[r] = 0.0f;
+                }
+                packed[i] = u32x2{(pack_bf16x2(e[0], e[1]) ^ q.flip) & keep, (pack_bf16x2(e[2], e[3]) ^ q.flip) & keep};
+            }
+#pragma unroll
+            for (int i = 0; i < Tile::MI; i += 2)
+                store_bf16_pair(dst + (int64_t)n * a.ld, Tile::row_off(wave, i), m_end, n < n_end, packed[i], packed[i + 1]);
+        };
+        if (ragged || __any(mine)) column(std::true_type{});
+        else column(std::false_type{});
+    }
     if (t0 + cols.width >= Ntok) {                // the last tile: zeros up to the next multiple of 64 rows
         constexpr int VPR = Tile::BM / 8;
         for (int q = threadIdx.x + n_end * VPR; q < ((Ntok + 63) / 64 * 64 - t0) * VPR; q += Tile::NT)
@@ -715,17 +706,19 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
             if (rows > 0) T.run(a.dw_z, tm * B, a.dw_h, TileDw::columns(a.dw_h.count, tn), (rows + 63) / 64 * 64);
             else T.clear();                       // no live row: the product is zero
             const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+            const int n_end = a.dw_h.count - tn * B, m_end = a.dw_z.count - tm * B;
 #pragma unroll
             for (int j = 0; j < TileDw::NJ; ++j) {
                 if (j >= T.blocks()) continue;
+                const int n = T.col_off(wave, j) + (lane & 15);
+                bf16_t* column = a.d_W + (int64_t)(tn * B + n) * a.ld_w + tm * B;
+                auto packed = [&](int i) {
+                    return u32x2{pack_bf16x2(T.acc[i][j][0], T.acc[i][j][1]), pack_bf16x2(T.acc[i][j][2], T.acc[i][j][3])};
+                };
 #pragma unroll
-                for (int i = 0; i < TileDw::MI; ++i)
-                    TileImage<TileDw>::put(lds_raw, T.col_off(wave, j) + (lane & 15), TileDw::row_off(wave, i) + 4 * (lane >> 4),
-                                           u32x2{pack_bf16x2(T.acc[i][j][0], T.acc[i][j][1]), pack_bf16x2(T.acc[i][j][2], T.acc[i][j][3])});
+                for (int i = 0; i < TileDw::MI; i += 2)
+                    store_bf16_pair(column, TileDw::row_off(wave, i), m_end, n < n_end, packed(i), packed(i + 1));
             }
-            __syncthreads();
-            TileImage<TileDw>::store(lds_raw, a.d_W + (int64_t)(tn * B) * a.ld_w + tm * B, a.ld_w, a.dw_h.count - tn * B,
-                                     a.dw_z.count - tm * B);
             return;
         }
         bid -= g_dw + g_dh;
@@ -990,7 +983,7 @@ bool launch_bwd_step(const BwdStepArgs& a, hipStream_t st)
 {
     using Tile = TileT<K_COLS, K_COLS>;
     auto kern = lmhead_bwd_step_kernel<TileT>;
-    constexpr size_t lds = tile_lds_bytes<Tile>();
+    constexpr size_t lds = Tile::LDS_BYTES + Tile::BN * sizeof(DzTerm);
     if (!allow_lds(kern, lds)) return false;
     // the largest grid the live count allows; workgroups beyond the actual tiles return at once
     constexpr int B = Tile::BM;
