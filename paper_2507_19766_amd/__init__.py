@@ -1,6 +1,6 @@
 """MI355X-native fused token loss of the UloRL objective (arxiv 2507.19766).
 
-The package is a thin ctypes binding over ``lib/libulorl.so`` (hand-written HIP for gfx950,
+The package is a thin binding over ``lib/libulorl.so`` (hand-written HIP for gfx950,
 C ABI declared in ``include/ulorl.h``).  PyTorch is used for device memory and streams only;
 there is no CPU or eager fallback: without the built library, or without a GPU, calls fail.
 """

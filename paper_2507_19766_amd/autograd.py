@@ -4,9 +4,10 @@ a training script where a log-softmax / gather / clipped-ratio chain would other
     loss = ulorl.autograd.token_loss(logits, token_ids, cu_seqlens, advantages, old_logp, params)
     loss.backward()                     # logits.grad holds dlogits
 
-Every function forwards tensors to the library calls of ``binding`` and hands their results to autograd;
-the one thing computed here is the product of the saved coefficients and the upstream gradient.  There
-is no CPU path.
+Every function forwards tensors to the library calls and hands their results to autograd (the two-call nodes are
+native, in ``csrc/torch_marshal.cpp``: backward runs on autograd's device thread, where Python cost 50 us a
+call); the one thing computed there is the product of the saved coefficients and the upstream gradient.
+There is no CPU path.
 
 Two ways to run the logits path:
   * ``fused=False`` (default): ``ulorl_token_loss_fwd`` in forward, ``ulorl_token_loss_bwd`` in
@@ -28,39 +29,25 @@ from . import binding
 from .binding import FwdResult, Launch, Params
 
 
-class _TokenLoss(torch.autograd.Function):
+class _FusedTokenLoss(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, logits, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids, fused, in_place,
-                launch, sink):
-        ctx.fused = bool(fused)
-        if fused:
-            res, dlogits = binding.token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, params,
+    def forward(ctx, logits, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids, in_place, launch, sink):
+        res, ctx.dlogits = binding.token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, params,
                                                       segment_ids=segment_ids, grad_out=1.0, inplace=bool(in_place),
                                                       launch=launch)
-            ctx.dlogits = dlogits
-        else:
-            if in_place:
-                raise ValueError("in_place needs fused=True (the two-call path reads the logits again in backward)")
-            res = binding.token_loss_fwd(logits, token_ids, cu_seqlens, advantages, old_logp, params,
-                                         segment_ids=segment_ids, launch=launch)
-            ctx.save_for_backward(logits, token_ids, res.lse, res.gcoef)
         if sink is not None:
             sink.append(res)
         return res.loss.reshape(())
 
     @staticmethod
     def backward(ctx, grad_loss):
-        if ctx.fused:
-            g = float(grad_loss)
-            if g != 1.0:
-                raise RuntimeError("token_loss(fused=True) computed the gradient of an upstream 1 in its forward pass; "
-                                   "got an upstream gradient of %r: scale through Params.denominator or use fused=False" % g)
-            d = ctx.dlogits
-            ctx.dlogits = None
-        else:
-            logits, token_ids, lse, gcoef = ctx.saved_tensors
-            d = binding.token_loss_bwd(logits, token_ids, lse, gcoef * grad_loss)
-        return (d,) + (None,) * 10
+        g = float(grad_loss)
+        if g != 1.0:
+            raise RuntimeError("token_loss(fused=True) computed the gradient of an upstream 1 in its forward pass; "
+                               "got an upstream gradient of %r: scale through Params.denominator or use fused=False" % g)
+        d = ctx.dlogits
+        ctx.dlogits = None
+        return (d,) + (None,) * 9
 
 
 def token_loss(logits: torch.Tensor, token_ids, cu_seqlens, advantages, old_logp=None, params: Optional[Params] = None,
@@ -69,29 +56,17 @@ def token_loss(logits: torch.Tensor, token_ids, cu_seqlens, advantages, old_logp
     """The masked, clipped policy-gradient loss of Sec. 3.2.2 as a differentiable 0-dim tensor (gradient
     to ``logits`` only).  ``results``: a list that receives the call's ``FwdResult`` (per-token
     log-probs, entropies, mask, ratio, counters)."""
-    return _TokenLoss.apply(logits, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids, fused, in_place,
-                            launch, results)
-
-
-class _LmheadTokenLoss(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, hidden, weight, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids, vocab_chunk,
-                launch, sink):
-        res = binding.lmhead_token_loss_fwd(hidden, weight, token_ids, cu_seqlens, advantages, old_logp, params,
-                                            segment_ids=segment_ids, vocab_chunk=vocab_chunk, launch=launch)
-        ctx.save_for_backward(hidden, weight, token_ids, res.lse, res.gcoef)
-        ctx.vocab_chunk = vocab_chunk
-        ctx.launch = launch
-        if sink is not None:
-            sink.append(res)
-        return res.loss.reshape(())
-
-    @staticmethod
-    def backward(ctx, grad_loss):
-        hidden, weight, token_ids, lse, gcoef = ctx.saved_tensors
-        d_hidden, d_weight = binding.lmhead_token_loss_bwd(hidden, weight, token_ids, lse, gcoef * grad_loss,
-                                                           vocab_chunk=ctx.vocab_chunk, launch=ctx.launch)
-        return (d_hidden, d_weight) + (None,) * 9
+    if fused:
+        return _FusedTokenLoss.apply(logits, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids, in_place, launch,
+                                     results)
+    if in_place:
+        raise ValueError("in_place needs fused=True (the two-call path reads the logits again in backward)")
+    with_params, with_launch = binding._structs(params, launch)
+    loss, fields = binding.native().autograd_token_loss(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids,
+                                                        binding._addr(with_params), binding._addr(with_launch), results is not None)
+    if results is not None:
+        results.append(FwdResult(*fields))
+    return loss
 
 
 def lmhead_token_loss(hidden: torch.Tensor, weight: torch.Tensor, token_ids, cu_seqlens, advantages, old_logp=None,
@@ -99,8 +74,13 @@ def lmhead_token_loss(hidden: torch.Tensor, weight: torch.Tensor, token_ids, cu_
                       launch: Optional[Launch] = None, results: Optional[list] = None) -> torch.Tensor:
     """The same loss from the last hidden states and the lm_head weight [hidden, vocabulary], the
     logits never materialised; gradients to ``hidden`` and ``weight`` (both computed, bf16)."""
-    return _LmheadTokenLoss.apply(hidden, weight, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids,
-                                  vocab_chunk, launch, results)
+    with_params, with_launch = binding._structs(params, launch)
+    loss, fields = binding.native().autograd_lmhead(hidden, weight, token_ids, cu_seqlens, advantages, old_logp, segment_ids,
+                                                    binding._addr(with_params), binding._addr(with_launch), vocab_chunk,
+                                                    results is not None)
+    if results is not None:
+        results.append(FwdResult(*fields))
+    return loss
 
 
 __all__ = ["token_loss", "lmhead_token_loss", "FwdResult"]

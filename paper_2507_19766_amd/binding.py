@@ -1,12 +1,14 @@
-"""ctypes binding of libulorl: argument marshalling only.
+"""Binding of libulorl: argument marshalling only.
 
 Every function here has the name of the C entry point it wraps (minus the ``ulorl_`` prefix)
 and does nothing but check tensors (device, dtype, contiguity), allocate outputs with torch
-and pass raw pointers plus the current HIP stream.  All arithmetic of these calls runs in the HIP kernels.
+and pass raw pointers plus the current HIP stream; the calls of a training step do that in an extension module
+(``csrc/torch_marshal.cpp``), the rest through ctypes.  All arithmetic of these calls runs in the HIP kernels.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -87,6 +89,14 @@ class Params:
     def to_c(self) -> _CParams:
         return _CParams(self.eps_low, self.eps_high, self.tau, self.sigma, self.is_mode,
                         self.gate_mode, self.seg_len, 0, self.denominator)
+
+
+def _structs(params: Optional["Params"], launch: Optional["Launch"]):
+    return (params or Params()).to_c(), launch.to_c() if launch is not None else None
+
+
+def _addr(struct) -> int:
+    return ctypes.addressof(struct) if struct is not None else 0
 
 
 def lib_path() -> str:
@@ -187,28 +197,24 @@ def token_loss_workspace_bytes(N: int, V: int, R: int) -> int:
 
 # ------------------------------------------------------------------------------------ helpers
 
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError("logits must be float32 or bfloat16, got %s" % t.dtype)
+_marshal = None
 
 
-def _check_logits(logits: torch.Tensor):
-    if not logits.is_cuda:
-        raise RuntimeError("libulorl runs on the GPU only: logits must be a device tensor")
-    if logits.dim() != 2 or logits.stride(1) != 1:
-        raise ValueError("logits must be [N, V] with unit stride along V")
-    return _dtype_code(logits), logits.shape[0], logits.shape[1], logits.stride(0)
-
-
-def _vec(t: Optional[torch.Tensor], dtype, n: int, name: str, dev):
-    if t is None:
-        return None
-    if t.device != dev or t.dtype != dtype or t.dim() != 1 or t.shape[0] != n or not t.is_contiguous():
-        raise ValueError("%s must be a contiguous %s[%d] tensor on %s" % (name, dtype, n, dev))
-    return t
+def native():
+    """The extension module that turns tensors into arguments (lib/_marshal.so, built with the library if it is absent)."""
+    global _marshal
+    if _marshal is None:
+        load_library()
+        path = os.path.join(_HERE, "lib", "_marshal.so")
+        if not os.path.exists(path):
+            from . import build as _build
+            _build.build()
+        spec = importlib.util.spec_from_file_location("_marshal", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.set_status_error(UlorlError)
+        _marshal = module
+    return _marshal
 
 
 def _p(t: Optional[torch.Tensor]):
@@ -234,53 +240,24 @@ class FwdResult:
     counters: Optional[torch.Tensor] = None
     segment_stats: Optional[dict] = None      # per-segment diagnostics, when asked for (segments=K)
 
-
-def _segment_stats_buffers(K: int, N: int, dev):
-    """Output tensors and workspace of the per-segment diagnostics -> (dict, ulorl_segment_stats)."""
-    i64 = dict(dtype=torch.int64, device=dev)
-    f64 = dict(dtype=torch.float64, device=dev)
-    out = {"count": torch.empty(K, **i64), "ratio_sum": torch.empty(K, **f64),
-           "ratio_max": torch.empty(K, dtype=torch.float32, device=dev), "clipped": torch.empty(K, **i64),
-           "kl_sum": torch.empty(K, **f64), "ent_sum": torch.empty(K, **f64), "masked": torch.empty(K, **i64),
-           "out_of_range": torch.empty(1, **i64)}
-    need = int(load_library().ulorl_segment_diagnostics_workspace_bytes(N, K))
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    out["_workspace"] = ws
-    c = _CSegStats(K, 0, out["count"].data_ptr(), out["ratio_sum"].data_ptr(), out["ratio_max"].data_ptr(),
-                   out["clipped"].data_ptr(), out["kl_sum"].data_ptr(), out["ent_sum"].data_ptr(),
-                   out["masked"].data_ptr(), out["out_of_range"].data_ptr(), ws.data_ptr(), ws.numel())
-    return out, c
+    def _fields(self):
+        return [self.loss, self.logp, self.entropy, self.lse, self.gcoef, self.mpt_mask, self.ratio, self.segment_out,
+                self.resp_entropy, self.resp_gate, self.counters]
 
 
-def _prepare_objective(logits, token_ids, cu_seqlens, advantages, old_logp, params, segment_ids, out, workspace):
-    """Shared marshalling of the objective's inputs/outputs for the fwd and fwd_bwd calls."""
-    dt, N, V, stride = _check_logits(logits)
-    dev = logits.device
-    f32 = dict(dtype=torch.float32, device=dev)
-    token_ids = _vec(token_ids, torch.int32, N, "token_ids", dev)
+SEGMENT_FIELDS = ("count", "ratio_sum", "ratio_max", "clipped", "kl_sum", "ent_sum", "masked", "out_of_range", "_workspace")
+
+
+def _result(out: Optional[FwdResult], fields, segments) -> FwdResult:
+    """The call's tensors as a FwdResult: a new one, or the caller's with what was missing filled in."""
     if out is None:
-        out = FwdResult(None, torch.empty(N, **f32), torch.empty(N, **f32), torch.empty(N, **f32))
-    params = params or Params()
-    if cu_seqlens.device != dev or cu_seqlens.dtype != torch.int32 or not cu_seqlens.is_contiguous():
-        raise ValueError("cu_seqlens must be a contiguous int32 device tensor")
-    R = cu_seqlens.shape[0] - 1
-    advantages = _vec(advantages, torch.float32, N, "advantages", dev)
-    old_logp = _vec(old_logp, torch.float32, N, "old_logp", dev)
-    segment_ids = _vec(segment_ids, torch.int32, N, "segment_ids", dev)
-    if out.loss is None:
-        out.loss = torch.empty(1, **f32)
-        out.gcoef = torch.empty(N, **f32)
-        out.mpt_mask = torch.empty(N, dtype=torch.uint8, device=dev)
-        out.ratio = torch.empty(N, **f32)
-        out.segment_out = torch.empty(N, dtype=torch.int32, device=dev)
-        out.resp_entropy = torch.empty(max(R, 1), **f32)[:R]
-        out.resp_gate = torch.empty(max(R, 1), dtype=torch.uint8, device=dev)[:R]
-        out.counters = torch.empty(4, dtype=torch.int64, device=dev)
-    if workspace is None:
-        workspace = torch.empty(max(token_loss_workspace_bytes(N, V, R), 256), dtype=torch.uint8, device=dev)
-    ws_bytes = workspace.numel() * workspace.element_size()
-    return (dt, N, V, stride, dev, token_ids, R, advantages, old_logp, segment_ids, params.to_c(), out,
-            workspace, ws_bytes)
+        out = FwdResult(*fields)
+    else:
+        (out.loss, out.logp, out.entropy, out.lse, out.gcoef, out.mpt_mask, out.ratio, out.segment_out, out.resp_entropy,
+         out.resp_gate, out.counters) = fields
+    if segments:
+        out.segment_stats = dict(zip(SEGMENT_FIELDS, segments))
+    return out
 
 
 def token_loss_fwd(logits, token_ids, cu_seqlens, advantages, old_logp=None, params: Params = None,
@@ -290,41 +267,10 @@ def token_loss_fwd(logits, token_ids, cu_seqlens, advantages, old_logp=None, par
     """ulorl_token_loss_fwd.  ``advantages=None`` selects the stats-only pass.
     ``out``/``workspace`` let a caller reuse buffers (nothing is allocated then).
     ``segments=K`` asks for the per-segment diagnostics of ids 0..K-1 (``out.segment_stats``)."""
-    lib = load_library()
-    lref, _keep = _launch_ref(launch)
-    if advantages is None:                       # stats-only: lse, logp, entropy
-        dt, N, V, stride = _check_logits(logits)
-        dev = logits.device
-        token_ids = _vec(token_ids, torch.int32, N, "token_ids", dev)
-        f32 = dict(dtype=torch.float32, device=dev)
-        if out is None:
-            out = FwdResult(None, torch.empty(N, **f32), torch.empty(N, **f32), torch.empty(N, **f32))
-        if workspace is None:                    # optional here; with it the statistics are formed by pieces
-            workspace = torch.empty(token_loss_workspace_bytes(N, V, 1), dtype=torch.uint8, device=dev)
-        ws_bytes = workspace.numel() * workspace.element_size()
-        rc = lib.ulorl_token_loss_fwd(
-            _p(logits), dt, N, V, stride, _p(token_ids), None, 0, None, None, None, None,
-            None, _p(out.logp), _p(out.entropy), _p(out.lse), None, None, None, None, None, None, None, None,
-            _p(workspace), ws_bytes, lref, _stream(dev))
-        if rc != 0:
-            raise UlorlError(rc, "ulorl_token_loss_fwd")
-        return out
-    (dt, N, V, stride, dev, token_ids, R, advantages, old_logp, segment_ids, cparams, out, workspace,
-     ws_bytes) = _prepare_objective(logits, token_ids, cu_seqlens, advantages, old_logp, params,
-                                    segment_ids, out, workspace)
-    sref = None
-    if segments > 0:
-        out.segment_stats, cseg = _segment_stats_buffers(segments, N, dev)
-        sref = ctypes.byref(cseg)
-    rc = lib.ulorl_token_loss_fwd(
-        _p(logits), dt, N, V, stride, _p(token_ids), _p(cu_seqlens), R, _p(segment_ids), _p(old_logp),
-        _p(advantages), ctypes.byref(cparams),
-        _p(out.loss), _p(out.logp), _p(out.entropy), _p(out.lse), _p(out.gcoef),
-        _p(out.mpt_mask), _p(out.ratio), _p(out.segment_out), _p(out.resp_entropy),
-        _p(out.resp_gate), _p(out.counters), sref, _p(workspace), ws_bytes, lref, _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_token_loss_fwd")
-    return out
+    with_params, with_launch = _structs(params, launch)
+    fields, seg = native().token_loss_fwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
+                                          _addr(with_launch), out._fields() if out is not None else None, workspace, segments)
+    return _result(out, fields, seg)
 
 
 def token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp=None, params: Params = None,
@@ -333,33 +279,11 @@ def token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp=None,
                        workspace: Optional[torch.Tensor] = None, launch: Optional[Launch] = None,
                        segments: int = 0):
     """ulorl_token_loss_fwd_bwd -> (FwdResult, dlogits).  ``inplace=True`` overwrites ``logits``."""
-    lib = load_library()
-    lref, _keep = _launch_ref(launch)
-    (dt, N, V, stride, dev, token_ids, R, advantages, old_logp, segment_ids, cparams, out, workspace,
-     ws_bytes) = _prepare_objective(logits, token_ids, cu_seqlens, advantages, old_logp, params,
-                                    segment_ids, out, workspace)
-    if advantages is None:
-        raise ValueError("token_loss_fwd_bwd needs advantages")
-    if inplace:
-        dlogits = logits
-    elif dlogits is None:
-        dlogits = torch.empty_strided((N, V), (stride, 1), dtype=logits.dtype, device=dev)
-    if (dlogits.shape != logits.shape or dlogits.dtype != logits.dtype or dlogits.device != dev
-            or dlogits.stride() != logits.stride()):
-        raise ValueError("dlogits must match logits in shape, dtype, strides and device")
-    sref = None
-    if segments > 0:
-        out.segment_stats, cseg = _segment_stats_buffers(segments, N, dev)
-        sref = ctypes.byref(cseg)
-    rc = lib.ulorl_token_loss_fwd_bwd(
-        _p(logits), dt, N, V, stride, _p(token_ids), _p(cu_seqlens), R, _p(segment_ids), _p(old_logp),
-        _p(advantages), ctypes.byref(cparams), float(grad_out),
-        _p(out.loss), _p(out.logp), _p(out.entropy), _p(out.lse), _p(out.gcoef),
-        _p(out.mpt_mask), _p(out.ratio), _p(out.segment_out), _p(out.resp_entropy),
-        _p(out.resp_gate), _p(out.counters), sref, _p(dlogits), _p(workspace), ws_bytes, lref, _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_token_loss_fwd_bwd")
-    return out, dlogits
+    with_params, with_launch = _structs(params, launch)
+    fields, seg, d = native().token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
+                                                 _addr(with_launch), grad_out, dlogits, inplace, False,
+                                                 out._fields() if out is not None else None, workspace, segments)
+    return _result(out, fields, seg), d
 
 
 def init() -> None:
@@ -380,43 +304,11 @@ def token_loss_fwd_bwd_static(logits, token_ids, cu_seqlens, advantages, old_log
     """ulorl_token_loss_fwd_bwd_static -> (FwdResult, dlogits): the one-call path on the library's
     static scratch array (the C call allocates nothing; pass ``out`` and ``dlogits`` to keep this
     wrapper from allocating outputs either)."""
-    lib = load_library()
-    dt, N, V, stride = _check_logits(logits)
-    dev = logits.device
-    f32 = dict(dtype=torch.float32, device=dev)
-    token_ids = _vec(token_ids, torch.int32, N, "token_ids", dev)
-    if cu_seqlens.device != dev or cu_seqlens.dtype != torch.int32 or not cu_seqlens.is_contiguous():
-        raise ValueError("cu_seqlens must be a contiguous int32 device tensor")
-    R = cu_seqlens.shape[0] - 1
-    advantages = _vec(advantages, torch.float32, N, "advantages", dev)
-    old_logp = _vec(old_logp, torch.float32, N, "old_logp", dev)
-    segment_ids = _vec(segment_ids, torch.int32, N, "segment_ids", dev)
-    if advantages is None:
-        raise ValueError("token_loss_fwd_bwd_static needs advantages")
-    lref, _keep = _launch_ref(launch)
-    cparams = (params or Params()).to_c()
-    if out is None:
-        out = FwdResult(torch.empty(1, **f32), torch.empty(N, **f32), torch.empty(N, **f32), torch.empty(N, **f32),
-                        torch.empty(N, **f32), torch.empty(N, dtype=torch.uint8, device=dev), torch.empty(N, **f32),
-                        torch.empty(N, dtype=torch.int32, device=dev), torch.empty(max(R, 1), **f32)[:R],
-                        torch.empty(max(R, 1), dtype=torch.uint8, device=dev)[:R],
-                        torch.empty(4, dtype=torch.int64, device=dev))
-    if inplace:
-        dlogits = logits
-    elif dlogits is None:
-        dlogits = torch.empty_strided((N, V), (stride, 1), dtype=logits.dtype, device=dev)
-    if (dlogits.shape != logits.shape or dlogits.dtype != logits.dtype or dlogits.device != dev
-            or dlogits.stride() != logits.stride()):
-        raise ValueError("dlogits must match logits in shape, dtype, strides and device")
-    rc = lib.ulorl_token_loss_fwd_bwd_static(
-        _p(logits), dt, N, V, stride, _p(token_ids), _p(cu_seqlens), R, _p(segment_ids), _p(old_logp),
-        _p(advantages), ctypes.byref(cparams), float(grad_out),
-        _p(out.loss), _p(out.logp), _p(out.entropy), _p(out.lse), _p(out.gcoef),
-        _p(out.mpt_mask), _p(out.ratio), _p(out.segment_out), _p(out.resp_entropy),
-        _p(out.resp_gate), _p(out.counters), None, _p(dlogits), lref, _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_token_loss_fwd_bwd_static")
-    return out, dlogits
+    with_params, with_launch = _structs(params, launch)
+    fields, _, d = native().token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
+                                               _addr(with_launch), grad_out, dlogits, inplace, True,
+                                               out._fields() if out is not None else None, None, 0)
+    return _result(out, fields, None), d
 
 
 def row_stats(logits, token_ids, out: Optional[FwdResult] = None, launch: Optional[Launch] = None) -> FwdResult:
@@ -427,24 +319,7 @@ def row_stats(logits, token_ids, out: Optional[FwdResult] = None, launch: Option
 def token_loss_bwd(logits, token_ids, lse, gcoef, grad_out: float = 1.0,
                    dlogits: Optional[torch.Tensor] = None, inplace: bool = False) -> torch.Tensor:
     """ulorl_token_loss_bwd.  ``inplace=True`` overwrites ``logits`` with the gradient."""
-    lib = load_library()
-    dt, N, V, stride = _check_logits(logits)
-    dev = logits.device
-    token_ids = _vec(token_ids, torch.int32, N, "token_ids", dev)
-    lse = _vec(lse, torch.float32, N, "lse", dev)
-    gcoef = _vec(gcoef, torch.float32, N, "gcoef", dev)
-    if inplace:
-        dlogits = logits
-    elif dlogits is None:
-        dlogits = torch.empty_strided((N, V), (stride, 1), dtype=logits.dtype, device=dev)
-    if (dlogits.shape != logits.shape or dlogits.dtype != logits.dtype or dlogits.device != dev
-            or dlogits.stride() != logits.stride()):
-        raise ValueError("dlogits must match logits in shape, dtype, strides and device")
-    rc = lib.ulorl_token_loss_bwd(_p(logits), dt, N, V, stride, _p(token_ids), _p(lse), _p(gcoef),
-                                  float(grad_out), _p(dlogits), _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_token_loss_bwd")
-    return dlogits
+    return native().token_loss_bwd(logits, token_ids, lse, gcoef, grad_out, dlogits, inplace)
 
 
 # ------------------------------------------------------------------------------------ lm_head variant
@@ -453,95 +328,24 @@ def lmhead_workspace_bytes(N: int, Hd: int, V: int, R: int, vocab_chunk: int) ->
     return int(load_library().ulorl_lmhead_workspace_bytes(N, Hd, V, R, vocab_chunk))
 
 
-def _check_lmhead(hidden, weight):
-    if not hidden.is_cuda or not weight.is_cuda:
-        raise RuntimeError("libulorl runs on the GPU only")
-    if hidden.dtype != torch.bfloat16 or weight.dtype != torch.bfloat16:
-        raise TypeError("hidden and weight must be bfloat16")
-    if hidden.dim() != 2 or weight.dim() != 2 or not hidden.is_contiguous() or not weight.is_contiguous():
-        raise ValueError("hidden [N, Hd] and weight [Hd, V] must be contiguous")
-    if hidden.shape[1] != weight.shape[0]:
-        raise ValueError("hidden is [N, Hd], weight is [Hd, V]")
-    return hidden.shape[0], hidden.shape[1], weight.shape[1]
-
-
 def lmhead_token_loss_fwd(hidden, weight, token_ids, cu_seqlens, advantages, old_logp=None,
                           params: Params = None, segment_ids=None, vocab_chunk: int = 8192,
                           out: Optional[FwdResult] = None, workspace: Optional[torch.Tensor] = None,
                           launch: Optional[Launch] = None, segments: int = 0) -> FwdResult:
     """ulorl_lmhead_token_loss_fwd."""
-    lib = load_library()
-    lref, _keep = _launch_ref(launch)
-    N, Hd, V = _check_lmhead(hidden, weight)
-    dev = hidden.device
-    f32 = dict(dtype=torch.float32, device=dev)
-    token_ids = _vec(token_ids, torch.int32, N, "token_ids", dev)
-    params = params or Params()
-    cparams = params.to_c()
-    R = cu_seqlens.shape[0] - 1 if cu_seqlens is not None else 1
-    advantages = _vec(advantages, torch.float32, N, "advantages", dev)
-    old_logp = _vec(old_logp, torch.float32, N, "old_logp", dev)
-    segment_ids = _vec(segment_ids, torch.int32, N, "segment_ids", dev)
-    if advantages is None:          # stats-only pass
-        if out is None:
-            out = FwdResult(None, torch.empty(N, **f32), torch.empty(N, **f32), torch.empty(N, **f32),
-                            None, None, None, None, None, None, None)
-        if workspace is None:
-            workspace = torch.empty(max(lmhead_workspace_bytes(N, Hd, V, R, vocab_chunk), 256), dtype=torch.uint8,
-                                    device=dev)
-        rc = lib.ulorl_lmhead_token_loss_fwd(
-            _p(hidden), _p(weight), N, Hd, V, vocab_chunk, _p(token_ids), _p(cu_seqlens), R, None, None, None,
-            ctypes.byref(cparams), None, _p(out.logp), _p(out.entropy), _p(out.lse), None, None, None, None, None,
-            None, None, None, _p(workspace), workspace.numel(), lref, _stream(dev))
-        if rc != 0:
-            raise UlorlError(rc, "ulorl_lmhead_token_loss_fwd")
-        return out
-    if out is None:
-        out = FwdResult(torch.empty(1, **f32), torch.empty(N, **f32), torch.empty(N, **f32), torch.empty(N, **f32),
-                        torch.empty(N, **f32), torch.empty(N, dtype=torch.uint8, device=dev), torch.empty(N, **f32),
-                        torch.empty(N, dtype=torch.int32, device=dev), torch.empty(max(R, 1), **f32)[:R],
-                        torch.empty(max(R, 1), dtype=torch.uint8, device=dev)[:R],
-                        torch.empty(4, dtype=torch.int64, device=dev))
-    if workspace is None:
-        workspace = torch.empty(max(lmhead_workspace_bytes(N, Hd, V, R, vocab_chunk), 256), dtype=torch.uint8, device=dev)
-    sref = None
-    if segments > 0:
-        out.segment_stats, cseg = _segment_stats_buffers(segments, N, dev)
-        sref = ctypes.byref(cseg)
-    rc = lib.ulorl_lmhead_token_loss_fwd(
-        _p(hidden), _p(weight), N, Hd, V, vocab_chunk, _p(token_ids), _p(cu_seqlens), R, _p(segment_ids),
-        _p(old_logp), _p(advantages), ctypes.byref(cparams),
-        _p(out.loss), _p(out.logp), _p(out.entropy), _p(out.lse), _p(out.gcoef), _p(out.mpt_mask), _p(out.ratio),
-        _p(out.segment_out), _p(out.resp_entropy), _p(out.resp_gate), _p(out.counters), sref,
-        _p(workspace), workspace.numel(), lref, _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_lmhead_token_loss_fwd")
-    return out
+    with_params, with_launch = _structs(params, launch)
+    fields, seg = native().lmhead_fwd(hidden, weight, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
+                                      _addr(with_launch), vocab_chunk, out._fields() if out is not None else None, workspace, segments)
+    return _result(out, fields, seg)
 
 
 def lmhead_token_loss_bwd(hidden, weight, token_ids, lse, gcoef, grad_out: float = 1.0, vocab_chunk: int = 8192,
                           d_hidden: Optional[torch.Tensor] = None, d_weight: Optional[torch.Tensor] = None,
                           workspace: Optional[torch.Tensor] = None, launch: Optional[Launch] = None):
     """ulorl_lmhead_token_loss_bwd -> (d_hidden [N, Hd] bf16, d_weight [Hd, V] bf16)."""
-    lib = load_library()
-    N, Hd, V = _check_lmhead(hidden, weight)
-    dev = hidden.device
-    token_ids = _vec(token_ids, torch.int32, N, "token_ids", dev)
-    lse = _vec(lse, torch.float32, N, "lse", dev)
-    gcoef = _vec(gcoef, torch.float32, N, "gcoef", dev)
-    if d_hidden is None:
-        d_hidden = torch.empty_like(hidden)
-    if d_weight is None:
-        d_weight = torch.empty_like(weight)
-    if workspace is None:
-        workspace = torch.empty(max(lmhead_workspace_bytes(N, Hd, V, 1, vocab_chunk), 256), dtype=torch.uint8, device=dev)
-    lref, _keep = _launch_ref(launch)
-    rc = lib.ulorl_lmhead_token_loss_bwd(
-        _p(hidden), _p(weight), N, Hd, V, vocab_chunk, _p(token_ids), _p(lse), _p(gcoef), float(grad_out),
-        _p(d_hidden), _p(d_weight), _p(workspace), workspace.numel(), lref, _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_lmhead_token_loss_bwd")
-    return d_hidden, d_weight
+    with_launch = launch.to_c() if launch is not None else None
+    return native().lmhead_bwd(hidden, weight, token_ids, lse, gcoef, grad_out, vocab_chunk, d_hidden, d_weight, workspace,
+                               _addr(with_launch))
 
 
 def gemm_tn_bf16(a: torch.Tensor, b: torch.Tensor, out: Optional[torch.Tensor] = None,
@@ -568,73 +372,20 @@ def gemm_tn_bf16(a: torch.Tensor, b: torch.Tensor, out: Optional[torch.Tensor] =
 
 def advantage_prep(rewards, cu_seqlens, group_size: int, truncated=None, eps: float = 1e-6, unbiased: bool = False):
     """ulorl_advantage_prep -> (resp_adv [R], group_keep [R/G], token_adv [N], kept_tokens [1] int64)."""
-    lib = load_library()
-    dev = rewards.device
-    if not rewards.is_cuda:
-        raise RuntimeError("libulorl runs on the GPU only")
-    R = rewards.shape[0]
-    rewards = _vec(rewards, torch.float32, R, "rewards", dev)
-    truncated = _vec(truncated, torch.uint8, R, "truncated", dev)
-    if cu_seqlens.device != dev or cu_seqlens.dtype != torch.int32 or cu_seqlens.shape[0] != R + 1:
-        raise ValueError("cu_seqlens must be int32 [R+1] on the same device")
-    N = int(cu_seqlens[-1].item())
-    resp = torch.empty(R, dtype=torch.float32, device=dev)
-    keep = torch.empty(max(R // max(group_size, 1), 1), dtype=torch.uint8, device=dev)
-    tok = torch.empty(N, dtype=torch.float32, device=dev)
-    kept = torch.empty(1, dtype=torch.int64, device=dev)
-    rc = lib.ulorl_advantage_prep(_p(rewards), _p(truncated), _p(cu_seqlens), R, group_size, N, float(eps),
-                                  1 if unbiased else 0, _p(resp), _p(keep), _p(tok), _p(kept), _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_advantage_prep")
-    return resp, keep[:R // group_size], tok, kept
+    return native().advantage_prep(rewards, truncated, cu_seqlens, group_size, eps, unbiased)
 
 
 def segment_diagnostics(res: FwdResult, advantages, old_logp, K: int, eps_low: float = 0.2, eps_high: float = 0.2,
                         segment_ids=None):
     """ulorl_segment_diagnostics on the outputs of a forward call -> dict of per-segment tensors."""
-    lib = load_library()
     seg = res.segment_out if segment_ids is None else segment_ids
-    dev = seg.device
-    N = seg.shape[0]
-    i64 = dict(dtype=torch.int64, device=dev)
-    f64 = dict(dtype=torch.float64, device=dev)
-    out = {"count": torch.empty(K, **i64), "ratio_sum": torch.empty(K, **f64),
-           "ratio_max": torch.empty(K, dtype=torch.float32, device=dev), "clipped": torch.empty(K, **i64),
-           "kl_sum": torch.empty(K, **f64), "ent_sum": torch.empty(K, **f64), "masked": torch.empty(K, **i64),
-           "out_of_range": torch.empty(1, **i64)}
-    ws = torch.empty(max(int(lib.ulorl_segment_diagnostics_workspace_bytes(N, K)), 256), dtype=torch.uint8, device=dev)
-    rc = lib.ulorl_segment_diagnostics(
-        N, K, _p(seg), _p(res.ratio), _p(res.logp), _p(old_logp), _p(res.entropy), _p(res.mpt_mask), _p(advantages),
-        float(eps_low), float(eps_high), _p(out["count"]), _p(out["ratio_sum"]), _p(out["ratio_max"]),
-        _p(out["clipped"]), _p(out["kl_sum"]), _p(out["ent_sum"]), _p(out["masked"]), _p(out["out_of_range"]),
-        _p(ws), ws.numel(), _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_segment_diagnostics")
-    return out
+    return dict(zip(SEGMENT_FIELDS[:-1], native().segment_diagnostics(K, seg, res.ratio, res.logp, old_logp, res.entropy, res.mpt_mask,
+                                                                      advantages, eps_low, eps_high)))
 
 
 def segment_pool_step(prev_len, new_len, hit_eos, seg_len: int, max_len: int):
     """ulorl_segment_pool_step -> dict of device tensors: state, total_len, segments [B];
     unfinished_idx, experience_idx, exp_truncated [B] and exp_cu_seqlens [B+1] (only the leading
     counts[0] / counts[1] (+1) entries are meaningful); counts [5] int64."""
-    lib = load_library()
-    if not prev_len.is_cuda:
-        raise RuntimeError("libulorl runs on the GPU only")
-    dev = prev_len.device
-    B = prev_len.shape[0]
-    prev_len = _vec(prev_len, torch.int32, B, "prev_len", dev)
-    new_len = _vec(new_len, torch.int32, B, "new_len", dev)
-    hit_eos = _vec(hit_eos, torch.uint8, B, "hit_eos", dev)
-    i32 = dict(dtype=torch.int32, device=dev)
-    u8 = dict(dtype=torch.uint8, device=dev)
-    out = {"state": torch.empty(B, **u8), "total_len": torch.empty(B, **i32), "segments": torch.empty(B, **i32),
-           "unfinished_idx": torch.empty(B, **i32), "experience_idx": torch.empty(B, **i32),
-           "exp_cu_seqlens": torch.empty(B + 1, **i32), "exp_truncated": torch.empty(B, **u8),
-           "counts": torch.empty(5, dtype=torch.int64, device=dev)}
-    rc = lib.ulorl_segment_pool_step(
-        B, _p(prev_len), _p(new_len), _p(hit_eos), int(seg_len), int(max_len), _p(out["state"]), _p(out["total_len"]),
-        _p(out["segments"]), _p(out["unfinished_idx"]), _p(out["experience_idx"]), _p(out["exp_cu_seqlens"]),
-        _p(out["exp_truncated"]), _p(out["counts"]), _stream(dev))
-    if rc != 0:
-        raise UlorlError(rc, "ulorl_segment_pool_step")
-    return out
+    return dict(zip(("state", "total_len", "segments", "unfinished_idx", "experience_idx", "exp_cu_seqlens", "exp_truncated", "counts"),
+                    native().segment_pool_step(prev_len, new_len, hit_eos, seg_len, max_len)))

@@ -1,10 +1,11 @@
-"""Builds libulorl.so (gfx950) in-tree with hipcc.  No JIT cache: the built library lives next
-to the sources so that it travels with the tree."""
+"""Builds libulorl.so (gfx950) in-tree with hipcc, and _marshal.so, the extension module between torch and it, with
+the host compiler.  No JIT cache: what is built lives next to the sources so that it travels with the tree."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
@@ -12,6 +13,7 @@ CSRC = os.path.join(_HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_DIR = os.path.join(_HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libulorl.so")
+MARSHAL_PATH = os.path.join(LIB_DIR, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -45,9 +47,32 @@ def _hipcc(args, out_path, verbose):
     return out_path
 
 
+def _marshal(verbose):
+    """lib/_marshal.so: torch tensors to C arguments; finds libulorl.so beside itself."""
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
+    system = include_paths() + [sysconfig.get_paths()["include"], os.path.join(rocm, "include"), "/opt/rocm/include"]
+    tmp = MARSHAL_PATH + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-DTORCH_EXTENSION_NAME=_marshal", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + INCLUDE]
+    for d in system:
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "torch_marshal.cpp"), "-o", tmp, LIB_PATH, "-Wl,-rpath,$ORIGIN"]
+    cmd += ["-L" + d for d in library_paths()]
+    cmd += ["-ltorch", "-ltorch_cpu", "-ltorch_python", "-lc10", "-ltorch_hip", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + proc.stdout)
+    os.replace(tmp, MARSHAL_PATH)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every HIP source (one object each, in parallel) and link lib/libulorl.so; always
-    recompiles."""
+    """Compile every HIP source (one object each, in parallel), link lib/libulorl.so and build the extension
+    module over it; always recompiles."""
     from concurrent.futures import ThreadPoolExecutor
 
     os.makedirs(LIB_DIR, exist_ok=True)
@@ -60,7 +85,8 @@ def build(verbose: bool = False) -> str:
 
     with ThreadPoolExecutor(max_workers=4) as pool:
         objs = list(pool.map(compile_one, sources()))
-    _hipcc(["-shared"] + objs, LIB_PATH, verbose)
+    _hipcc(["-shared", "-Wl,-soname,libulorl.so"] + objs, LIB_PATH, verbose)
+    _marshal(verbose)
     return LIB_PATH
 
 

@@ -64,3 +64,57 @@ def test_lmhead_token_loss_gradients_to_hidden_and_weight():
     (loss * -1.5).backward()
     assert torch.equal(loss.detach().reshape(1), ref.loss)
     assert torch.equal(_bits(hidden.grad), _bits(rH)) and torch.equal(_bits(weight.grad), _bits(rW))
+
+
+@pytest.mark.parametrize("change,error", [
+    (dict(logits=lambda t: t.half()), TypeError), (dict(logits=lambda t: t[0]), ValueError), (dict(logits=lambda t: t.t()), ValueError),
+    (dict(logits=lambda t: t.cpu()), RuntimeError), (dict(token_ids=lambda t: t.long()), ValueError),
+    (dict(token_ids=lambda t: t[:-1]), ValueError), (dict(token_ids=lambda t: t.repeat(2)[::2]), ValueError),
+    (dict(advantages=lambda t: t.double()), ValueError), (dict(old_logp=lambda t: t.cpu()), ValueError),
+    (dict(old_logp=lambda t: None), ulorl.UlorlError), (dict(token_ids=lambda t: None), ulorl.UlorlError),
+    (dict(cu_seqlens=lambda t: t.long()), ValueError), (dict(logits=lambda t: t[:, 1:]), ulorl.UlorlError)])
+def test_refusals(change, error):
+    """What the marshalling and the library refuse, and how, in the call and under autograd."""
+    w = ui.shrink(ui.config(2), [20, 13], V=520, seg_len=16, name="marshal_refusals")
+    d = ui.generate(w, DEV)
+    d.update({k: f(d[k]) for k, f in change.items()})
+    p = params_for(w, gate_mode=ulorl.GATE_NEVER)
+    args = (d["logits"], d["token_ids"], d["cu_seqlens"], d["advantages"], d["old_logp"], p)
+    for call in (ulorl.token_loss_fwd, ulorl.token_loss_fwd_bwd, ulorl.autograd.token_loss):
+        with pytest.raises(error) as e:
+            call(*args)
+        assert type(e.value) is error
+        if error is ulorl.UlorlError:
+            assert e.value.status < 0
+
+
+@pytest.mark.parametrize("lmhead", [False, True])
+def test_native_nodes_are_autograd_nodes(lmhead):
+    """Saved tensors pass through saved-tensor hooks, a kept graph runs twice, a changed input is noticed, and no
+    graph is kept without grad; on a stream of its own."""
+    w = ui.shrink(ui.config(5) if lmhead else ui.config(2), [20, 13], V=520, seg_len=16, name="marshal_nodes", **({"hidden": 64} if lmhead else {}))
+    d = ui.generate(w, DEV)
+    p = params_for(w, gate_mode=ulorl.GATE_NEVER)
+    rest = (d["token_ids"], d["cu_seqlens"], d["advantages"], d["old_logp"], p)
+    leaves = [d[k].requires_grad_(True) for k in (("hidden", "weight") if lmhead else ("logits",))]
+    call = ulorl.autograd.lmhead_token_loss if lmhead else ulorl.autograd.token_loss
+    seen = []
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side), torch.autograd.graph.saved_tensors_hooks(lambda t: (seen.append(t.shape), t)[1], lambda t: t):
+        loss = call(*leaves, *rest)
+    torch.cuda.current_stream().wait_stream(side)
+    assert len(seen) == (5 if lmhead else 4)
+    first = torch.autograd.grad(loss, leaves, retain_graph=True)
+    again = torch.autograd.grad(loss, leaves)
+    assert all(torch.equal(_bits(a), _bits(b)) for a, b in zip(first, again))
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(loss, leaves)
+    loss = call(*leaves, *rest)
+    with torch.no_grad():
+        leaves[0].add_(1.0)
+    with pytest.raises(RuntimeError, match="inplace"):
+        loss.backward()
+    with torch.no_grad():
+        got = []
+        assert call(*leaves, *rest, results=got).grad_fn is None and got[0].lse.shape == (w.N,)
