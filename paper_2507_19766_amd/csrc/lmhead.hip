@@ -402,7 +402,8 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
         if (j >= G.blocks()) continue;
         const float delta = m[j] > 0.5f * kEmpty ? fmaf(m[j], kLog2e, -(m[j] * kLog2e)) : 0.0f;
         const float un = fast_exp2(-delta);
-        const bool wide = !(S[j] > 0.0f && S[j] < 3.0e38f) || fabsf(m[j]) >= kWide;
+        // a lane without a row inside the vocabulary has met nothing: m is kEmpty and S 0
+        const bool wide = m[j] > kEmpty && (!(S[j] > 0.0f && S[j] < 3.0e38f) || fabsf(m[j]) >= kWide);
         float mm = m[j], SS = wide ? __builtin_nanf("") : un * (S[j] + Sc[j]), TT = un * fmaf(-delta, S[j], T[j]) * kLn2;
 #pragma unroll
         for (int off = 16; off <= 32; off <<= 1) {
@@ -486,25 +487,26 @@ void lmhead_stats_kernel(const Operand W, const Operand H, int K, const int32_t*
     }
 }
 
-// Eight lanes per token: each merges every eighth slice in order, then a fixed shuffle tree.  (One thread
-// per token walked up to 128 slices one dependent load after the other: 22 us at 64 slices, now 5.)
+// LANES lanes per token: each merges every LANES-th slice in order, then a fixed shuffle tree.  (One thread per token walked up
+// to 128 slices one dependent load after the other: 22 us at 64 slices, 5 with eight lanes.)  32 lanes beyond 64 slices.
+template <int LANES>
 __global__ __launch_bounds__(256) void lmhead_stats_merge_kernel(const StatQuad* __restrict__ partial, int splits, int Ntok, int V,
                                                                  const int32_t* __restrict__ token_ids, float* __restrict__ lse,
                                                                  float* __restrict__ logp, float* __restrict__ entropy)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int t = (int)(i >> 3), part = (int)(i & 7);
+    const int t = (int)(i / LANES), part = (int)(i % LANES);
     StatQuad q = {kEmpty, 0.0f, 0.0f, kEmpty};
     if (t < Ntok) {
 #pragma unroll 4
-        for (int s = part; s < splits; s += 8) {
+        for (int s = part; s < splits; s += LANES) {
             const StatQuad p = partial[(int64_t)s * Ntok + t];
             merge_nat(q.m, q.S, q.T, p.m, p.S, p.T);
             q.zy = fmaxf(q.zy, p.zy);
         }
     }
 #pragma unroll
-    for (int off = 1; off <= 4; off <<= 1) {
+    for (int off = 1; off < LANES; off <<= 1) {
         const float m2 = __shfl_xor(q.m, off), S2 = __shfl_xor(q.S, off), T2 = __shfl_xor(q.T, off), z2 = __shfl_xor(q.zy, off);
         merge_nat(q.m, q.S, q.T, m2, S2, T2);
         q.zy = fmaxf(q.zy, z2);
@@ -732,19 +734,33 @@ void lmhead_bwd_step_kernel(const BwdStepArgs a)
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t round_up64(int64_t x) { return (x + 63) / 64 * 64; }
 
-// ulorl_launch.gemm_tile: 0 = by shape, 1 = TileSmall (gemm_tile.hpp).  Small tiles where large ones would be
-// mostly padding, too few, or too short a contraction to pay for their start and their store.  Measured,
-// large / small, us.  Forward statistics, 151936 columns: 64 x 512 112 / 106, 200 x 1024 165 / 161,
-// 512 x 512 115 / 124, 512 x 2048 301 / 406; 4096 x 256 x 5640 31 / 27.  Backward, 151936 columns:
-// 64 x 2048 584 / 453, 200 x 1024 529 / 390, 512 x 512 519 / 368, 777 x 512 533 / 579, 512 x 1024
-// 633 / 626, 512 x 2048 943 / 1213; 8192 x 256 x 5640 231 / 168.  Many rows and a d_W of few large tiles, which then
-// contract over all rows on a few compute units (rows x hidden x columns): 20000 x 512 x 1000 433 / 263, x 2000 458 / 297,
-// x 4096 507 / 373, x 8192 645 / 662; 20000 x 2048 x 1000 563 / 395.
+constexpr int kComputeUnits = 256;
+
+// ulorl_launch.gemm_tile: 0 = by shape, 1 = TileSmall (gemm_tile.hpp).
+//
+// Forward: what either tile's launch costs, in us, from a sweep of 64 to 4096 rows, hidden sizes of 512 to 2048 and
+// vocabularies of 4096 to 151936 (both tiles at 96 shapes; the choice costs 0.3 % on average, 9 % at most 2 shapes, against
+// the better of the two; "more than 256 rows and hidden size" cost 7.7 %).  A round of large tiles takes 8 us to start and
+// to finish and 17 per 1024 of the hidden size, a little less when they are narrow; small tiles 1.5 us and 15.5 per 1024 for
+// two on every compute unit, 9.3 for one.  us, large / small: 512 x 2048 x 4096 46 / 28, 512 x 2048 x 32008 64 / 75, 2048 x 2048 x
+// 5000 53 / 63, 512 x 1024 x 20000 37 / 33, 128 x 1024 x 151936 85 / 77, 256 x 2048 x 151936 159 / 220, 4096 x 1024 x 4096 39 / 41.
 // The large tile adds 48 rows of W to a lane's 32-bit offset (kMaxLargeColsLeadingDim).
 inline int forward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
 {
-    return o.gemm_tile == 1 || N <= 256 || Hd <= 256 || V > kMaxLargeColsLeadingDim ? 1 : 0;
+    if (o.gemm_tile == 1 || Hd <= 256 || V > kMaxLargeColsLeadingDim) return 1;
+    const int64_t ttiles = (N + 255) / 256, width = (N + 31) / 32 * 32 / ttiles;
+    const double depth = Hd / 1024.0, narrow = 0.4 + 0.6 * (width > 160 ? (double)width : 160.0) / 256;
+    const int64_t large = ttiles * ((V + 255) / 256), small = ((N + 127) / 128) * ((V + 127) / 128);
+    const int64_t last = small % (2 * kComputeUnits);
+    const double cost_large = (double)((large + kComputeUnits - 1) / kComputeUnits) * (8.0 + 17.0 * depth * narrow);
+    const double cost_small = (double)(small / (2 * kComputeUnits)) * (1.5 + 15.5 * depth) +
+                              (last == 0 ? 0.0 : last <= kComputeUnits ? 1.5 + 9.3 * depth : 1.5 + 15.5 * depth);
+    return cost_small <= cost_large ? 1 : 0;
 }
+// Backward: small tiles where large ones would be mostly padding, too few, or too short a contraction to pay for their start and
+// their store.  151936 columns, us, large / small: 64 x 2048 584 / 453, 200 x 1024 529 / 390, 512 x 512 519 / 368, 777 x 512 533 / 579;
+// 8192 x 256 x 5640 231 / 168.  Many rows and a d_W of few large tiles (rows x hidden x columns): 20000 x 512 x 1000 433 / 263, x 4096
+// 507 / 373, x 8192 645 / 662; 20000 x 2048 x 1000 563 / 395.
 inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
 {
     const int64_t dw_tiles = ((V + 255) / 256) * ((Hd + 255) / 256);
@@ -752,8 +768,6 @@ inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
 }
 
 inline int tile_edge(int tile) { return tile == 1 ? TileSmall<K_ROWS, K_ROWS>::BM : TileLarge<K_ROWS, K_ROWS>::BM; }
-
-constexpr int kComputeUnits = 256;
 
 // Workspace of one call.  The forward and the backward call lay the same bytes out differently.
 struct LmheadLayout {
@@ -883,7 +897,7 @@ LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t 
     const size_t room_slices = (L.total - forward(0)) / slice;
     const int edge = tile_edge(fwd_tile);
     const int64_t vtiles = (V + edge - 1) / edge;
-    const int64_t slices = stats_splits(N, V, edge, fwd_tile == 1 ? 2 * kComputeUnits : kComputeUnits, (int)smaller(room_slices, 128));
+    const int64_t slices = stats_splits(N, V, edge, fwd_tile == 1 ? 2 * kComputeUnits : kComputeUnits, (int)smaller(room_slices, 512));
     const int64_t per_split = (vtiles + slices - 1) / slices;
     L.v_per_split = (int)(per_split * edge);
     L.splits = (int)((vtiles + per_split - 1) / per_split);
@@ -892,13 +906,13 @@ LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t 
     const size_t room = L.total - backward(0, 1, 0);
     auto slabs = [&](int64_t n) { return align_up((size_t)(n + tail_slab) * slab, 256); };
     int64_t dh_splits = kComputeUnits / (((N + 255) / 256) * ((Hd + 255) / 256));
-    if (dh_splits > 8) dh_splits = 8;
+    dh_splits = dh_splits > 8 ? 8 : dh_splits < 1 ? 1 : dh_splits;
     int64_t chunk = L.v64;
     if (chunk <= kMaxLeadingDim - 256 && slabs(1) + dz_all <= room) {
         while (dh_splits > 1 && slabs(dh_splits) + dz_all > room) --dh_splits;
     } else {
         while (dh_splits > 1 && (slabs(dh_splits) + 2 * dz_least > room || slabs(dh_splits) > room / 4)) --dh_splits;
-        const size_t half = (room - slabs(dh_splits < 1 ? 1 : dh_splits)) / 2 / 256 * 256;
+        const size_t half = (room - slabs(dh_splits)) / 2 / 256 * 256;
         chunk = (int64_t)(smaller(budget, half) / column / 64 * 64);
         if (chunk >= 256) chunk = chunk / 256 * 256;
         if (chunk < vocab_chunk) chunk = vocab_chunk;
@@ -1086,8 +1100,9 @@ int32_t ulorl_lmhead_token_loss_fwd(const void* hidden, const void* W, int64_t N
                         ? launch_stats<TileSmall>(Wop, Hop, (int)L.hd64, token_ids, L, partial, opts.gemm_group_m, st)
                         : launch_stats<TileLarge>(Wop, Hop, (int)L.hd64, token_ids, L, partial, opts.gemm_group_m, st);
     if (!ok) return ULORL_ERR_HIP;
-    hipLaunchKernelGGL(lmhead_stats_merge_kernel, dim3((unsigned)((N * 8 + 255) / 256)), dim3(256), 0, st, partial, L.splits,
-                       (int)N, (int)V, token_ids, lse, logp, entropy);
+    const int lanes = L.splits > 64 ? 32 : 8;
+    hipLaunchKernelGGL(lanes == 32 ? lmhead_stats_merge_kernel<32> : lmhead_stats_merge_kernel<8>, dim3((unsigned)((N * lanes + 255) / 256)),
+                       dim3(256), 0, st, partial, L.splits, (int)N, (int)V, token_ids, lse, logp, entropy);
     if (hipGetLastError() != hipSuccess) return ULORL_ERR_HIP;
     if (stats_only) return ULORL_OK;
 
