@@ -757,14 +757,16 @@ inline int forward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
                               (last == 0 ? 0.0 : last <= kComputeUnits ? 1.5 + 9.3 * depth : 1.5 + 15.5 * depth);
     return cost_small <= cost_large ? 1 : 0;
 }
-// Backward: small tiles where large ones would be mostly padding, too few, or too short a contraction to pay for their start and
-// their store.  151936 columns, us, large / small: 64 x 2048 584 / 453, 200 x 1024 529 / 390, 512 x 512 519 / 368, 777 x 512 533 / 579;
-// 8192 x 256 x 5640 231 / 168.  Many rows and a d_W of few large tiles (rows x hidden x columns): 20000 x 512 x 1000 433 / 263, x 4096
-// 507 / 373, x 8192 645 / 662; 20000 x 2048 x 1000 563 / 395.
+// Backward: small tiles where large ones would be mostly padding, too few for the chip, too short a contraction to pay for their
+// start and their store, or a d_W of few tiles that contract over many rows.  us, large / small, rows x hidden x columns:
+// 64 x 2048 x 151936 556 / 458, 512 x 512 x 151936 526 / 382, 777 x 512 534 / 557; 200 x 2048 x 20000 113 / 101, 256 x 2048 x 50000
+// 276 / 256, 400 x 1024 x 100000 445 / 389, 300 x 2048 x 20000 112 / 116; few tiles: 1024 x 2048 x 4096 91 / 79, 2048 x 2048 x
+// 4096 124 / 124, 2048 x 1024 x 4096 84 / 74, 1500 x 1024 x 5640 89 / 97, 4096 x 512 x 5000 126 / 102; 20000 x 512 x 4096 507 / 373, x 8192 645 / 662.
 inline int backward_tile(const LaunchOpts& o, int64_t N, int64_t Hd, int64_t V)
 {
-    const int64_t dw_tiles = ((V + 255) / 256) * ((Hd + 255) / 256);
-    return o.gemm_tile == 1 || N * Hd <= 3 * (1 << 17) || Hd <= 256 || (N >= 8192 && dw_tiles <= 32) ? 1 : 0;
+    const int64_t vtiles = (V + 255) / 256, dz_tiles = vtiles * ((N + 255) / 256), dw_tiles = vtiles * ((Hd + 255) / 256);
+    const bool shallow = Hd <= 256 || N * Hd <= 3 * (1 << 17) || (Hd >= 1024 && N * Hd <= 1 << 19);
+    return o.gemm_tile == 1 || shallow || dz_tiles < 112 || dw_tiles < 64 || dz_tiles + dw_tiles < 224 ? 1 : 0;
 }
 
 inline int tile_edge(int tile) { return tile == 1 ? TileSmall<K_ROWS, K_ROWS>::BM : TileLarge<K_ROWS, K_ROWS>::BM; }
@@ -902,14 +904,17 @@ LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t 
     L.v_per_split = (int)(per_split * edge);
     L.splits = (int)((vtiles + per_split - 1) / per_split);
 
-    // Every column in one dZ buffer if that and one accumulator fit, else up to a quarter of the room for the accumulators.
+    // Every column in one dZ buffer if that and half of the accumulators fit, else up to a quarter of the room for the accumulators.
     const size_t room = L.total - backward(0, 1, 0);
     auto slabs = [&](int64_t n) { return align_up((size_t)(n + tail_slab) * slab, 256); };
     int64_t dh_splits = kComputeUnits / (((N + 255) / 256) * ((Hd + 255) / 256));
     dh_splits = dh_splits > 8 ? 8 : dh_splits < 1 ? 1 : dh_splits;
     int64_t chunk = L.v64;
-    if (chunk <= kMaxLeadingDim - 256 && slabs(1) + dz_all <= room) {
-        while (dh_splits > 1 && slabs(dh_splits) + dz_all > room) --dh_splits;
+    int64_t fitting = dh_splits;                 // accumulators beside a dZ of all columns
+    while (fitting > 0 && slabs(fitting) + dz_all > room) --fitting;
+    // With few of them a handful of workgroups contract over all columns: 1500 x 512 x 50000, two of eight, 858 us; in three chunks 320.
+    if (chunk <= kMaxLeadingDim - 256 && fitting > 0 && 2 * fitting >= dh_splits) {
+        dh_splits = fitting;
     } else {
         while (dh_splits > 1 && (slabs(dh_splits) + 2 * dz_least > room || slabs(dh_splits) > room / 4)) --dh_splits;
         const size_t half = (room - slabs(dh_splits)) / 2 / 256 * 256;

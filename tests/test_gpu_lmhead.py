@@ -126,6 +126,22 @@ def test_large_tiles_of_the_backward_with_few_live_rows(n_live, hidden, V):
     assert bool((res.d_hidden[~keep] == 0).all())
 
 
+@pytest.mark.parametrize("n,V,hidden", [(1500, 50000, 512), (400, 151936, 256)])
+def test_chunks_where_the_accumulators_do_not_fit_beside_all_columns(n, V, hidden):
+    """Shapes whose workspace holds dZ of all columns but few of the dHidden accumulators: in chunks (large and
+    small tile); d_hidden and d_weight against products of the library's own dlogits."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    h, w = torch.randn(n, hidden, generator=g, device=DEV).bfloat16(), (torch.randn(hidden, V, generator=g, device=DEV) * 0.05).bfloat16()
+    y = torch.randint(0, V, (n,), generator=g, device=DEV, dtype=torch.int32)
+    lse = ulorl.lmhead_token_loss_fwd(h, w, y, None, None).lse
+    coef = torch.randn(n, generator=g, device=DEV) / n
+    dh, dw = ulorl.lmhead_token_loss_bwd(h, w, y, lse, coef)
+    dz = -coef[:, None].double() * torch.exp(h.double() @ w.double() - lse[:, None].double())
+    dz[torch.arange(n, device=DEV), y.long()] += coef.double()
+    for got, ref in ((dh, dz @ w.double().T), (dw, h.double().T @ dz)):
+        assert float((got.double() - ref).norm() / ref.norm()) <= 4e-3          # bf16 roundings of dz and of the result: 2^-9 each
+
+
 @pytest.mark.parametrize("n", [300, 1300])        # small and large tile
 def test_backward_in_one_chunk_of_eight_parts(n):
     w = ui.shrink(ui.config(5), [n - 1, 1], V=9000, hidden=320, seg_len=64, name="lmhead_eight_parts")
