@@ -97,9 +97,9 @@
     UL_COPY_ONE(LDS, "3", "buffer_load_dwordx4 " UL_ROW_##X ", " UL_RSRC_##X UL_KOFF_##X)
 #define UL_COPY_COLS(XS, X, H, LDS)                                                                            \
     UL_COPY_ONE(LDS, "0", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X "0")                                  \
-    UL_COPY_ONE(LDS, "1", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X "%[s" XS "1]")                        \
-    UL_COPY_ONE(LDS, "2", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X "%[s" XS "2]")                        \
-    UL_COPY_ONE(LDS, "3", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X "%[s" XS "3]")
+    UL_COPY_ONE(LDS, "1", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X UL_COFF_##X##1)                        \
+    UL_COPY_ONE(LDS, "2", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X UL_COFF_##X##2)                        \
+    UL_COPY_ONE(LDS, "3", "buffer_load_dwordx4 %[v" XS #H "], " UL_RSRC_##X UL_COFF_##X##3)
 // The copy cursor of one operand to the next K tile.
 #define UL_NEXT_ROWS_a "s_add_u32 s52, s52, 128\n"
 #define UL_NEXT_ROWS_b "s_add_u32 s53, s53, 128\n"
