@@ -599,10 +599,17 @@ __device__ __forceinline__ int response_of(const int32_t* __restrict__ cu, int l
     return lo;
 }
 
-// Final sums, per-response outputs and status bits, by the last workgroup of token_terms_kernel.
+// Sums over tokens: of their terms, of the masked, clipped and positive ones; status bits.
+struct TokenSums {
+    double terms, masked, clipped, positive;
+    int flags;
+};
+
+// Final sums, per-response outputs and status bits, by the last workgroup of token_terms_kernel.  own (thread 0):
+// the sums of this workgroup, which are the final ones where it is the only one.
 template <bool SEG>
 __device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, int badcu, double hglobal, const BatchTable& batch,
-                                              double* seg_scratch)
+                                              double* seg_scratch, TokenSums own, bool sync_failed)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < a.R; i += kTokBlock) {
@@ -620,47 +627,46 @@ __device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, 
         if (a.resp_entropy) a.resp_entropy[i] = hbar;
         if (a.resp_gate) a.resp_gate[i] = badcu ? 0 : (uint8_t)gate;
     }
-    // counts below 2^53 are exact as doubles, in any order
-    double s = 0.0, c0 = 0.0, c1 = 0.0, c2 = 0.0;
-    int fl = 0;
-    for (int64_t k = tid; k < nblk; k += kTokBlock) {
-        s += published(a.part_sum + k);
-        const int64_t w0 = published(a.part_cnt + 2 * k), w1 = published(a.part_cnt + 2 * k + 1);
-        c0 += (double)(int32_t)w0;
-        c1 += (double)(int32_t)(w0 >> 32);
-        c2 += (double)(int32_t)w1;
-        fl |= (int32_t)(w1 >> 32);
-    }
-    __shared__ double fin[kTokWaves][4];
-    __shared__ int fin_flags[kTokWaves];
-    s = wave_sum_f64(s);
-    c0 = wave_sum_f64(c0);
-    c1 = wave_sum_f64(c1);
-    c2 = wave_sum_f64(c2);
-    int wf = 0;
-#pragma unroll
-    for (int bit = 1; bit <= 8; bit <<= 1) wf |= __ballot(fl & bit) != 0ull ? bit : 0;
-    if (lane == 0) {
-        fin[wave][0] = s; fin[wave][1] = c0; fin[wave][2] = c1; fin[wave][3] = c2;
-        fin_flags[wave] = wf;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double t[4] = {0.0, 0.0, 0.0, 0.0};
-        int flags = 0;
-#pragma unroll 4
-        for (int w = 0; w < kTokWaves; ++w) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) t[q] += fin[w][q];
-            flags |= fin_flags[w];
+    if (nblk > 1) {                             // uniform.  Counts below 2^53 are exact as doubles, in any order
+        TokenSums q = {0.0, 0.0, 0.0, 0.0, 0};
+        for (int64_t k = tid; k < nblk; k += kTokBlock) {
+            q.terms += published(a.part_sum + k);
+            const int64_t w0 = published(a.part_cnt + 2 * k), w1 = published(a.part_cnt + 2 * k + 1);
+            q.masked += (double)(int32_t)w0;
+            q.clipped += (double)(int32_t)(w0 >> 32);
+            q.positive += (double)(int32_t)w1;
+            q.flags |= (int32_t)(w1 >> 32);
         }
-        if (a.sync_fail != nullptr && *a.sync_fail != 0u) flags |= ULORL_STATUS_SYNC;
-        *a.loss = (float)(-t[0] / a.D);
+        __shared__ TokenSums fin[kTokWaves];
+        q.terms = wave_sum_f64(q.terms);
+        q.masked = wave_sum_f64(q.masked);
+        q.clipped = wave_sum_f64(q.clipped);
+        q.positive = wave_sum_f64(q.positive);
+        int wf = 0;
+#pragma unroll
+        for (int bit = 1; bit <= 8; bit <<= 1) wf |= __ballot(q.flags & bit) != 0ull ? bit : 0;
+        q.flags = wf;
+        if (lane == 0) fin[wave] = q;
+        __syncthreads();
+        if (tid == 0) {
+            own = TokenSums{0.0, 0.0, 0.0, 0.0, 0};
+#pragma unroll 4
+            for (int w = 0; w < kTokWaves; ++w) {
+                own.terms += fin[w].terms;
+                own.masked += fin[w].masked;
+                own.clipped += fin[w].clipped;
+                own.positive += fin[w].positive;
+                own.flags |= fin[w].flags;
+            }
+        }
+    }
+    if (tid == 0) {
+        *a.loss = (float)(-own.terms / a.D);
         if (a.counters) {
-            a.counters[0] = (int64_t)t[1];
-            a.counters[1] = (int64_t)t[2];
-            a.counters[2] = (int64_t)t[3];
-            a.counters[3] = flags;
+            a.counters[0] = (int64_t)own.masked;
+            a.counters[1] = (int64_t)own.clipped;
+            a.counters[2] = (int64_t)own.positive;
+            a.counters[3] = own.flags | (sync_failed ? ULORL_STATUS_SYNC : 0);
         }
     }
     if constexpr (SEG) seg_finalize(a.seg, nblk, seg_scratch);
@@ -668,8 +674,9 @@ __device__ __forceinline__ void finalize_loss(const TokenArgs& a, int64_t nblk, 
 
 // Gate, ratio, clipped term, mask, coefficient and segment id of every token; block sums; the rows whose
 // gradient waited for the gate collected into a list; the last workgroup to deliver its sums forms the
-// call's results.  Latency bound (two rounds of loads, three barriers, the ticket):
-// 32768 tokens took 10 + 10 us as two launches with shuffle reductions, now 9.  (One workgroup for both
+// call's results.  Latency bound (a round of loads, three barriers, the ticket and a second round):
+// 32768 tokens took 10 + 10 us as two launches with shuffle reductions, now 9.  A workgroup that is the only one keeps its sums
+// instead of reading them back: 512 tokens 5.5 -> 3.7 us, 2048 (two of them) 7.6 -> 7.2.  (One workgroup for both
 // epilogue kernels was slower at every token count, 256 to 4096.)
 // SEG: the per-segment diagnostics are wanted.
 template <bool SEG>
@@ -681,30 +688,38 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
     __shared__ int wave_c[kTokWaves][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
+    // all of the token's loads go with those of the batch (after them: one more round trip, and the last workgroup's read of
+    // the flag another)
+    const int64_t blk = blockIdx.x;
+    const int64_t t0 = blk * kTokBlock, t = t0 + tid;
+    float lpf = 0.0f, hf = 0.0f, lf = 0.0f;
+    int32_t y = 0;
+    int32_t sg_seg = 0;
+    float sg_adv = 0.0f, sg_old = 0.0f;
+    bool listed = false;
+    if (t < a.N) {
+        lpf = a.logp[t];
+        hf = a.entropy[t];
+        lf = a.lse[t];
+        y = a.token_ids[t];
+        sg_adv = a.adv[t];
+        if (a.old_logp != nullptr) sg_old = a.old_logp[t];
+        if (a.segment_ids != nullptr) sg_seg = a.segment_ids[t];
+        if (a.defer != nullptr) listed = a.defer[t] != 0;
+    }
+    const bool sync_failed = a.sync_fail != nullptr && *a.sync_fail != 0u;
+
     double hglobal;
     const int badcu = load_batch(a, batch, hglobal);
 
-    const int64_t blk = blockIdx.x;
-    const int64_t t0 = blk * kTokBlock, t = t0 + tid;
     double contrib = 0.0;
     bool is_masked = false, is_clipped = false, is_positive = false;
     int flags = badcu ? ULORL_STATUS_BAD_CU : 0;
     // what the per-segment diagnostics see of this token: exactly the values the call stores
     float g_out = 0.0f, r_out = 0.0f;
     uint8_t m_out = 0;
-    int32_t sg_seg = 0;
-    float sg_logp = 0.0f, sg_ent = 0.0f, sg_adv = 0.0f, sg_old = 0.0f;
-    bool listed = false;
 
     if (t < a.N) {
-        // all of the token's loads before the first store
-        const float lpf = a.logp[t], hf = a.entropy[t], lf = a.lse[t];
-        const int32_t y = a.token_ids[t];
-        sg_adv = a.adv[t];
-        if (a.old_logp != nullptr) sg_old = a.old_logp[t];
-        if (a.segment_ids != nullptr) sg_seg = a.segment_ids[t];
-        if (a.defer != nullptr) listed = a.defer[t] != 0;
-
         int32_t b;
         int gate;
         if (a.R <= kTableResponses) {
@@ -718,8 +733,6 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
             gate = gate_of(a, L, badcu, hglobal, !badcu && L > 0 ? entropy_sum(a, i) / (double)L : 0.0);
         }
         if (a.segment_ids == nullptr) sg_seg = a.seg_len > 0 && !badcu ? (int32_t)((uint32_t)(t - b) / (uint32_t)a.seg_len) : 0;   // t < 2^31
-        sg_logp = lpf;
-        sg_ent = hf;
         const bool bad_tok = (y < 0 || y >= a.V);
         const bool nonfinite = not_finite(lpf) || not_finite(hf) || not_finite(lf);
         if (bad_tok) flags |= ULORL_STATUS_BAD_TOKEN;
@@ -759,28 +772,33 @@ __global__ __launch_bounds__(kTokBlock) void token_terms_kernel(TokenArgs a, int
         wave_c[wave][0] = n_mask; wave_c[wave][1] = n_clip; wave_c[wave][2] = n_pos; wave_c[wave][3] = wf;
     }
     __syncthreads();
+    TokenSums own = {0.0, 0.0, 0.0, 0.0, 0};
     if (tid == 0) {
-        double bs = 0.0;
-        int c0 = 0, c1 = 0, c2 = 0, fl = 0;
+        int c0 = 0, c1 = 0, c2 = 0;
 #pragma unroll 4
         for (int w = 0; w < kTokWaves; ++w) {
-            bs += wave_s[w];
-            c0 += wave_c[w][0]; c1 += wave_c[w][1]; c2 += wave_c[w][2]; fl |= wave_c[w][3];
+            own.terms += wave_s[w];
+            c0 += wave_c[w][0]; c1 += wave_c[w][1]; c2 += wave_c[w][2]; own.flags |= wave_c[w][3];
         }
-        publish(a.part_sum + blk, bs);
-        publish(a.part_cnt + 2 * blk, (int64_t)c0 | ((int64_t)c1 << 32));
-        publish(a.part_cnt + 2 * blk + 1, (int64_t)c2 | ((int64_t)fl << 32));
+        if (nblk > 1) {
+            publish(a.part_sum + blk, own.terms);
+            publish(a.part_cnt + 2 * blk, (int64_t)c0 | ((int64_t)c1 << 32));
+            publish(a.part_cnt + 2 * blk + 1, (int64_t)c2 | ((int64_t)own.flags << 32));
+        }
+        own.masked = c0;
+        own.clipped = c1;
+        own.positive = c2;
     }
     if constexpr (SEG) {
         int k;
         double v[kSegStats], oor;
-        seg_token_values(t < a.N, sg_seg, a.seg.K, r_out, sg_logp, a.old_logp != nullptr, sg_old, sg_ent, m_out, sg_adv,
+        seg_token_values(t < a.N, sg_seg, a.seg.K, r_out, lpf, a.old_logp != nullptr, sg_old, hf, m_out, sg_adv,
                          a.eps_low, a.eps_high, k, v, oor);
         const double o = seg_block_partials(k, v, oor, a.seg.K, seg_table,
                                             a.seg.part + blk * a.seg.K * kSegStats);
         if (tid == 0) publish(a.seg.part_oor + blk, o);
     }
-    if (last_workgroup(a.ticket, (uint32_t)nblk)) finalize_loss<SEG>(a, nblk, badcu, hglobal, batch, seg_table);
+    if (last_workgroup(a.ticket, (uint32_t)nblk)) finalize_loss<SEG>(a, nblk, badcu, hglobal, batch, seg_table, own, sync_failed);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -150,6 +150,15 @@ def test_epilogue_partitions(lengths, gate):
     assert tt.n_masked > 0
 
 
+@pytest.mark.parametrize("lengths", [[1023], [500, 524], [1024, 1], [500, 524, 1025]])
+def test_epilogue_of_one_workgroup_and_of_several(lengths):
+    """Up to 1024 tokens one workgroup forms the results from its own sums, beyond that the last one from all of them: every
+    token, the loss and the counters against the oracle, with members of the MPT set and clipped tokens."""
+    w = ui.shrink(ui.config(1), lengths, V=64, seg_len=100, name="workgroups_%d" % sum(lengths))
+    res, tt, info = run_full_parity(w, params_for(w, gate_mode=ulorl.GATE_PER_RESPONSE, sigma=1e9, tau=0.3))
+    assert tt.n_masked > 0
+
+
 def test_single_row_single_token_and_empty_response():
     w = ui.shrink(ui.config(1), [1], V=512, seg_len=1, name="one_row")
     run_full_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS))
