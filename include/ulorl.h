@@ -125,8 +125,8 @@ typedef struct ulorl_launch {
                              (ULORL_STATUS_SYNC); 0: the default 2^24; a tiny value lets a test
                              exercise that pass                                                  */
     int32_t gemm_tile;    /* lm_head variant: 0 = chosen by the shape (default): 256 x 256 x 64 block
-                             tiles, eight waves, or 128 x 128 x 64, four waves, for few rows, short rows of
-                             hidden or a d_W of few tiles; 1 = the small ones always.  ulorl_gemm_tn_bf16: 0 = large */
+                             tiles, or 128 x 128 x 64 where those cost less (few rows, short rows of
+                             hidden, few columns); 1 = the small ones always.  ulorl_gemm_tn_bf16: 0 = large */
     int32_t gemm_group_m; /* lm_head variant: block tiles along M that an XCD walks before it moves
                              along N (its L2 then re-serves their operand rows); 0 = default 4;
                              1..64                                                               */

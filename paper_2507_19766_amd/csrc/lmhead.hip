@@ -859,7 +859,8 @@ LmheadLayout lmhead_layout(int64_t N, int64_t Hd, int64_t V, int32_t R, int32_t 
         return off;
     };
 
-    // What more room than the least is used for.  Statistics: 8 to 128 slices.  dHidden (see BwdStepArgs): enough tiles for
+    // What more room than the least is used for.  Statistics: 8 to 128 slices (up to 512 where
+    // the room is there all the same).  dHidden (see BwdStepArgs): enough tiles for
     // every compute unit, at most 8 parts.  dZ: vocab_chunk columns, or what a buffer of 64 to 256 MB (as W and
     // hidden are larger) holds: with few rows a chunk of 8192 columns is too little work for 256 compute
     // units.  777 x 2048 x 151936: 20 steps of 8192 columns 3.3 ms, all columns in one chunk 1.4 ms.  With 16384 rows

@@ -44,7 +44,7 @@ def test_gemm_tn_bf16_against_fp64(M, N, K):
 def test_every_compiled_tile_shape(tile, group_m):
     """Every tile of the plain product (large, small, and the one for a ragged K) and other walks of the tile
     grid give the same answers; the lm_head case is one of few rows and a short hidden size, which takes the
-    small tile whatever is asked for (its large tiles: test_walks_of_large_tiles)."""
+    small tile whatever is asked for (its large tiles: test_walks_of_large_tiles_in_both_calls)."""
     launch = ulorl.Launch(gemm_tile=tile, gemm_group_m=group_m)
     g = torch.Generator(device=DEV).manual_seed(tile)
     for (M, N, K) in ((300, 520, 192), (256, 256, 72), (1300, 700, 128)):     # K = 72 exercises the ragged-K fallback
@@ -64,7 +64,7 @@ def test_tile_edges_of_every_product(tile, n, V, hidden):
     """One to four K tiles of the small tile (all of these shapes take it, by their size or by request), tiles
     one row or one vector past an edge, and shapes whose weight is padded or whose last columns are taken apart
     (hidden or vocabulary no multiple of 64); the tolerances are those of every lm_head case.  The large
-    tile: test_large_tiles_with_half_empty_ones, test_large_tiles_with_few_live_rows."""
+    tile: test_large_tiles_of_every_width and test_large_tiles_of_the_backward."""
     launch = ulorl.Launch(gemm_tile=tile)
     w = ui.shrink(ui.config(5), [n], V=V, hidden=hidden, seg_len=64, name="lmhead_edges")
     for dense in (False, True):
@@ -86,9 +86,9 @@ def test_backward_partitions(n, V, hidden):
 
 @pytest.mark.parametrize("n,V,hidden", [(1300, 64, 320), (1300, 136, 320), (1408, 264, 384), (1409, 1096, 392), (1537, 200, 512)])
 def test_large_tiles_with_half_empty_ones(n, V, hidden):
-    """Shapes that take the large tile, with a last token tile of 20, 128, 129 and 1 rows (last tiles share
-    their columns with the others), hidden sizes whose last tile is half empty too, and contractions of one
-    to four K tiles in the dHidden product."""
+    """More than a thousand rows and few columns, with 20, 128, 129 and 1 rows beyond a multiple of 256, hidden sizes whose last
+    tile is half empty too, and contractions of one to four K tiles in the dHidden product.  (Too few tiles for large ones,
+    which these shapes took once: those are below.)"""
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_halves")
     for dense in (False, True):
         run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(dense_rows=dense))
@@ -142,7 +142,7 @@ def test_chunks_where_the_accumulators_do_not_fit_beside_all_columns(n, V, hidde
         assert float((got.double() - ref).norm() / ref.norm()) <= 4e-3          # bf16 roundings of dz and of the result: 2^-9 each
 
 
-@pytest.mark.parametrize("n", [300, 1300])        # small and large tile
+@pytest.mark.parametrize("n", [300, 1300])
 def test_backward_in_one_chunk_of_eight_parts(n):
     w = ui.shrink(ui.config(5), [n - 1, 1], V=9000, hidden=320, seg_len=64, name="lmhead_eight_parts")
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192)
@@ -167,9 +167,9 @@ def _few_live(w, n_live):
 @pytest.mark.parametrize("n_live", [0, 1, 64, 65, 128, 129, 257])
 @pytest.mark.parametrize("hidden,V", [(320, 328), (512, 256), (392, 1096)])
 def test_large_tiles_with_few_live_rows(n_live, hidden, V):
-    """A large batch (which takes the large tile) with few rows that carry a gradient: the d_W product, both
-    operands transposed, contracts over none, one, two, three and five K tiles (first and last tiles of the
-    loop peeled), in whole and half tiles; against the oracle."""
+    """A batch of 1300 rows with few that carry a gradient: the d_W product, both operands transposed, contracts over none, one,
+    two, three and five K tiles, in whole and half empty tiles; against the oracle.  (Small tiles, by the number of columns; the
+    large ones: test_large_tiles_of_the_backward_with_few_live_rows.)"""
     w = ui.shrink(ui.config(5), [1290, 10], V=V, hidden=hidden, seg_len=64, name="lmhead_large_few")
     d, keep = _few_live(w, n_live)
     p = params_for(w, gate_mode=ulorl.GATE_NEVER, eps_low=10.0, eps_high=10.0)
@@ -182,8 +182,15 @@ def test_large_tiles_with_few_live_rows(n_live, hidden, V):
 
 @pytest.mark.parametrize("group_m", [1, 7, 64])
 def test_walks_of_large_tiles(group_m):
+    """1320 rows and 1544 columns in several chunks.  (Small tiles by now; the large ones in the next test.)"""
     w = ui.shrink(ui.config(5), [1200, 120], V=1544, hidden=320, seg_len=64, name="lmhead_large_walk")
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS, tau=0.05), chunk=512, launch=ulorl.Launch(gemm_group_m=group_m))
+
+
+@pytest.mark.parametrize("group_m", [1, 7, 64])
+def test_walks_of_large_tiles_in_both_calls(group_m):
+    w = ui.shrink(ui.config(5), [500, 45], V=20048, hidden=1024, seg_len=64, name="lmhead_large_walks")
+    run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(gemm_group_m=group_m))
 
 
 def test_lmhead_small_ragged_chunks():
@@ -233,7 +240,7 @@ def test_lmhead_mpt_mask_fires():
 
 @pytest.mark.parametrize("lengths,V,hidden,chunk", [([300, 212], 4096 + 1544, 256, 1024), ([64], 8192 + 8, 64, 64),
                                                     ([1000, 24], 1544, 128, 2048),
-                                                    # several chunks: last columns apart, W padded for V < 2 n, padded along hidden; the last two large tiles
+                                                    # several chunks: last columns apart, W padded for V < 2 n, padded along hidden
                                                     ([693, 7], 8392, 64, 64), ([1500, 1], 3000, 64, 64), ([893, 7], 6000, 72, 64),
                                                     ([1299, 1], 5000, 320, 64), ([1400], 2760, 328, 64)])
 def test_workspace_is_never_overrun(lengths, V, hidden, chunk):
@@ -327,7 +334,7 @@ def test_backward_with_few_or_no_live_rows(n_live):
         _assert_dw_same_up_to_rounding(dW, dW2)
 
 
-@pytest.mark.parametrize("n,Hd", [(200, 320), (300, 320), (300, 2048)])        # the small tile, and the large one
+@pytest.mark.parametrize("n,Hd", [(200, 320), (300, 320), (300, 2048)])        # the small tile twice, and the large one
 def test_forward_statistics_of_large_logits(n, Hd):
     """Logits far beyond the range a model produces still have a log-sum-exp and an entropy: +-2^20 with
     the maxima of one slice's tiles on both sides of it, 1.25 2^28 in steps of 32, 2^29 times small numbers
@@ -381,8 +388,8 @@ def test_forward_of_a_very_wide_vocabulary(V):
     assert float((res.logp - (at - lse)).abs().max()) <= 4e-5
 
 
-@pytest.mark.parametrize("n,V,hidden", [(700, 8392, 64), (1501, 3000, 64), (900, 6000, 72), (90, 56, 64),      # small tile
-                                        (1300, 5000, 320), (1400, 2760, 320), (1300, 5000, 328)])      # large tile
+@pytest.mark.parametrize("n,V,hidden", [(700, 8392, 64), (1501, 3000, 64), (900, 6000, 72), (90, 56, 64),
+                                        (1300, 5000, 320), (1400, 2760, 320), (1300, 5000, 328)])
 @pytest.mark.parametrize("dense", [False, True])
 def test_backward_over_several_ragged_chunks(n, V, hidden, dense):
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_chunks")
