@@ -117,7 +117,7 @@ def test_random_lmhead_case(c):
 
 
 def _lmhead_large_cases():
-    """Shapes that take the large tile in both passes (more than 256 rows and hidden columns, more than 3 * 2^17
+    """Shapes of more than a tile each way (more than 256 rows and hidden columns, more than 3 * 2^17
     elements of hidden), with small chunks and more rows than hidden columns, so that most run over several chunks."""
     rs = np.random.RandomState(20250729)
     out = []
