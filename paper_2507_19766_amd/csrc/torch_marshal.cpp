@@ -303,12 +303,13 @@ std::pair<Tensor, Tensor> lmhead_bwd(const Tensor& h, const Tensor& w, const Opt
 
 // ------------------------------------------------------------------------------------------ autograd
 // The upstream gradient is a 0-dim device tensor; it is multiplied into the saved coefficients on the device (the fp32
-// product that the kernels form with a host scalar), so that nothing waits for the GPU.
+// product that the kernels form with a host scalar), so that nothing waits for the GPU.  The objective's float tensors are
+// arguments of the nodes, so that one of them that requires a gradient makes the loss require one (it gets none).
 using torch::autograd::AutogradContext;
 using torch::autograd::variable_list;
 
 struct TokenLossNode : torch::autograd::Function<TokenLossNode> {
-    static Tensor forward(AutogradContext* ctx, const Tensor& logits, const Objective* o, Fields* f)
+    static Tensor forward(AutogradContext* ctx, const Tensor& logits, const OptTensor&, const OptTensor&, const Objective* o, Fields* f)
     {
         Segments none;
         token_loss_fwd(logits, *o, *f, none, 0, std::nullopt);
@@ -318,12 +319,13 @@ struct TokenLossNode : torch::autograd::Function<TokenLossNode> {
     static variable_list backward(AutogradContext* ctx, const variable_list& grad)
     {
         const variable_list s = ctx->get_saved_variables();
-        return {token_loss_bwd(s[0], s[1], s[2], s[3] * grad[0], 1.0, std::nullopt, false), Tensor(), Tensor()};
+        return {token_loss_bwd(s[0], s[1], s[2], s[3] * grad[0], 1.0, std::nullopt, false), Tensor(), Tensor(), Tensor(), Tensor()};
     }
 };
 
 struct LmheadNode : torch::autograd::Function<LmheadNode> {
-    static Tensor forward(AutogradContext* ctx, const Tensor& hidden, const Tensor& weight, const Objective* o, int64_t chunk, Fields* f)
+    static Tensor forward(AutogradContext* ctx, const Tensor& hidden, const Tensor& weight, const OptTensor&, const OptTensor&, const Objective* o,
+                          int64_t chunk, Fields* f)
     {
         Segments none;
         lmhead_fwd(hidden, weight, *o, chunk, *f, none, 0, std::nullopt);
@@ -347,7 +349,7 @@ struct LmheadNode : torch::autograd::Function<LmheadNode> {
         }
         const auto d = lmhead_bwd(s[0], s[1], s[2], s[3], s[4] * grad[0], 1.0, ctx->saved_data["chunk"].toInt(), std::nullopt, std::nullopt,
                                   std::nullopt, given ? &launch : nullptr);
-        return {d.first, d.second, Tensor(), Tensor(), Tensor()};
+        return {d.first, d.second, Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
     }
 };
 
@@ -441,14 +443,14 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m)
                                     uintptr_t launch, bool want_fields) {
         const Objective o = objective(y, cu, adv, old, ids, params, launch);
         Fields f;
-        const Tensor loss = unlocked([&] { return TokenLossNode::apply(z, &o, &f); });
+        const Tensor loss = unlocked([&] { return TokenLossNode::apply(z, o.advantages, o.old_logp, &o, &f); });
         return py::make_tuple(loss, want_fields ? list_of(f) : py::list());
     });
     m.def("autograd_lmhead", [](const Tensor& h, const Tensor& w, OptTensor y, OptTensor cu, OptTensor adv, OptTensor old, OptTensor ids,
                                 uintptr_t params, uintptr_t launch, int64_t chunk, bool want_fields) {
         const Objective o = objective(y, cu, adv, old, ids, params, launch);
         Fields f;
-        const Tensor loss = unlocked([&] { return LmheadNode::apply(h, w, &o, chunk, &f); });
+        const Tensor loss = unlocked([&] { return LmheadNode::apply(h, w, o.advantages, o.old_logp, &o, chunk, &f); });
         return py::make_tuple(loss, want_fields ? list_of(f) : py::list());
     });
 

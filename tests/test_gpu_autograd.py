@@ -118,3 +118,19 @@ def test_native_nodes_are_autograd_nodes(lmhead):
     with torch.no_grad():
         got = []
         assert call(*leaves, *rest, results=got).grad_fn is None and got[0].lse.shape == (w.N,)
+
+
+@pytest.mark.parametrize("lmhead", [False, True])
+@pytest.mark.parametrize("which", ["advantages", "old_logp"])
+def test_a_loss_of_a_differentiable_objective_input_requires_grad(lmhead, which):
+    """Only logits (hidden, weight) get a gradient; an advantage or behaviour log-prob that requires one makes the loss a node of
+    the graph all the same, and gets none."""
+    w = ui.shrink(ui.config(5) if lmhead else ui.config(2), [20, 13], V=520, seg_len=16, name="marshal_inputs", **({"hidden": 64} if lmhead else {}))
+    d = ui.generate(w, DEV)
+    d[which].requires_grad_(True)
+    leaves = [d[k] for k in (("hidden", "weight") if lmhead else ("logits",))]
+    call = ulorl.autograd.lmhead_token_loss if lmhead else ulorl.autograd.token_loss
+    loss = call(*leaves, d["token_ids"], d["cu_seqlens"], d["advantages"], d["old_logp"], params_for(w, gate_mode=ulorl.GATE_NEVER))
+    assert loss.requires_grad
+    loss.backward()
+    assert d[which].grad is None and all(t.grad is None for t in leaves)
