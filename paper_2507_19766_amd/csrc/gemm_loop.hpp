@@ -67,8 +67,9 @@
 #define UL_READ1_ROWS(DST, OFF) UL_READ_ROWS("y", DST, OFF)
 #define UL_READ1_COLS(DST, OFF) UL_READ_COLS("b", DST, OFF)
 
-// This wave's four instructions of one half tile's copy, J after MFMA 18 + 3 J; another instruction stands between the
-// write of m0 and the copy.
+// This wave's four instructions of one half tile's copy, J after MFMA 18 + 3 J.  gfx9 parts need an instruction between a
+// scalar write of m0 and the copy that takes its LDS address from there, and the compiler looks for that outside of
+// assembly only: whatever expands a copy for n and n + 1 puts one between them.
 #define UL_COPY_AT(J) "(" UL_COPY_FIRST "+3*" J ")"
 #define UL_COPY_ONE(LDS, J, LOAD)                                                                              \
     ".if n==" UL_COPY_AT(J) "\ns_add_u32 m0, %[sw], " LDS "+" J "*4096\n.endif\n"                             \
@@ -119,10 +120,12 @@
     UL_REPEAT(C ".if (n==" UL_COPY_AT("0") ")||(n==" UL_COPY_AT("1") ")||(n==" UL_COPY_AT("2") ")||(n==" UL_COPY_AT("3") ")\ns_nop 0\n.endif\n")
 #define UL_READS_DONE "s_waitcnt lgkmcnt(0)\n"
 #define UL_BARRIER "s_waitcnt vmcnt(16) lgkmcnt(0)\ns_barrier\n"
-// A part over j1 column blocks: it leaves after the last one.  Reads and copies stand in the first block's eight MFMAs.
+// A part over j1 column blocks: it leaves after the last one.  Reads and copies stand in the first block's eight MFMAs, two steps
+// of each after an MFMA.  A read stands between the two steps of the copies (either layout has one at every odd n below
+// 16), so that a write of m0 in the first is not followed at once by its copy.
 #define UL_SHORT_PART(M, RD, CP)                                                                               \
-    ".set n,0\n.rept 8\n" M ".set m,n\n.set n,2*m\n" RD ".set n,2*m+1\n" RD                                      \
-    ".set n," UL_COPY_FIRST "+2*m-2\n" CP ".set n,n+1\n" CP ".set n,m+1\n.endr\n"                                \
+    ".set n,0\n.rept 8\n" M ".set m,n\n.set n,2*m\n" RD ".set n," UL_COPY_FIRST "+2*m-2\n" CP                    \
+    ".set n,2*m+1\n" RD ".set n," UL_COPY_FIRST "+2*m-1\n" CP ".set n,m+1\n.endr\n"                              \
     ".rept 3\ns_cmp_le_u32 %[j1], n/8\ns_cbranch_scc1 5f\n.rept 8\n" M ".set n,n+1\n.endr\n.endr\n5:\n"
 
 // Byte offsets of the halves in LDS: A half h of stage s at 32768 s + 16384 h, B 65536 further (its read addresses include that).
