@@ -201,7 +201,7 @@
         [ry0] "v"(lds_base + 65536u + b.roff[0] + y_shift), [ry1] "v"(lds_base + 65536u + b.roff[1] + y_shift)
 #define UL_IN_READ_COLS_B [rb0] "v"(lds_base + 65536u + b.roff[0]), [rb1] "v"(lds_base + 65536u + b.roff[1]), \
         [rb2] "v"(lds_base + 65536u + b.roff[2]), [rb3] "v"(lds_base + 65536u + b.roff[3])
-#define UL_CLOBBERS "memory", "scc", "vcc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s52", "s53", \
+#define UL_CLOBBERS "memory", "scc", "vcc", "m0", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s52", "s53", \
         "s54", "s55", "s56", "s57", "s58", "s59", "v126", "v127"
 // Accumulator block (i, j) is a[32 i + 4 j : 32 i + 4 j + 3]: X(i, j, first, last).
 #define UL_BLOCKS(X) \

@@ -48,3 +48,22 @@ def test_a_write_of_m0_is_never_followed_at_once_by_a_copy_to_lds(tmp_path):
     large = [k for k in copies if "TileLarge" in k]
     assert len(large) == 3 and all(copies[k] > 100 for k in large), copies
     assert not bad, bad
+
+
+def _loop_source():
+    return open(os.path.join(build.CSRC, "gemm_loop.hpp")).read()
+
+
+def _clobbers(text):
+    return set(re.findall(r'"([a-z0-9]+)"', re.search(r"#define UL_CLOBBERS (.*?)\n#define|#define UL_CLOBBERS (.*?)\n//", text, re.S).group(0)))
+
+
+def test_every_register_that_the_blocks_write_is_named_to_the_compiler():
+    """Scalar registers and m0, and the vector registers of copy offsets; fragments and accumulators are outputs."""
+    text = _loop_source()
+    written = set(re.findall(r"(?:\\n|\")s_(?!cmp|waitcnt|cbranch|branch|barrier|nop)\w+ (m0|s\d+),", text))
+    for first, last in re.findall(r"s_mov_b64 s\[(\d+):(\d+)\],", text):
+        written |= {"s%d" % r for r in range(int(first), int(last) + 1)}
+    written |= set(re.findall(r'#define UL_ROW_\w "(v\d+)"', text))
+    assert {"m0", "s40", "s49"} < written and len(written) == 21, sorted(written)
+    assert written <= _clobbers(text), sorted(written - _clobbers(text))
