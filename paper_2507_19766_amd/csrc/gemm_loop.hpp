@@ -32,7 +32,7 @@
 // Scalar registers of the block: s[40:43], s[44:47] buffer descriptors of A and B, s48 K tiles left to multiply, s49 K tiles
 // left to copy, s52, s53 the offset along k of a K_ROWS operand, s[54:56], s[57:59] the offsets of copy instructions 1 to 3 of
 // a K_COLS one.
-// v126 and v127 are the offsets of a K_ROWS operand's copies.
+// v94 and v95 are the offsets of a K_ROWS operand's copies.
 // Operands: sw = LDS address of the stages + 1024 x wave; r<op>0.. LDS read addresses; v<op>.. byte offsets of a
 // lane's copies; K_ROWS: g<op>, h<op> bytes from one copy instruction to the next and from half 0 to half 1; K_COLS:
 // s<op>1..3 offsets of copy instruction 1..3, t<op>l/h bytes from one K tile to the next.
@@ -85,8 +85,8 @@
 #define UL_COFF_b1 "s57"
 #define UL_COFF_b2 "s58"
 #define UL_COFF_b3 "s59"
-#define UL_ROW_a "v126"
-#define UL_ROW_b "v127"
+#define UL_ROW_a "v94"
+#define UL_ROW_b "v95"
 #define UL_FIRST_ROW_0(XS, X) "v_mov_b32 " UL_ROW_##X ", %[v" XS "]\n"
 #define UL_FIRST_ROW_1(XS, X) "v_add_u32 " UL_ROW_##X ", %[h" XS "], %[v" XS "]\n"
 #define UL_NEXT_ROW(XS, X, J) ".if n==" UL_COPY_AT(J) "\nv_add_u32 " UL_ROW_##X ", %[g" XS "], " UL_ROW_##X "\n.endif\n"
@@ -202,7 +202,11 @@
 #define UL_IN_READ_COLS_B [rb0] "v"(lds_base + 65536u + b.roff[0]), [rb1] "v"(lds_base + 65536u + b.roff[1]), \
         [rb2] "v"(lds_base + 65536u + b.roff[2]), [rb3] "v"(lds_base + 65536u + b.roff[3])
 #define UL_CLOBBERS "memory", "scc", "vcc", "m0", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s52", "s53", \
-        "s54", "s55", "s56", "s57", "s58", "s59", "v126", "v127"
+        "s54", "s55", "s56", "s57", "s58", "s59", "v94", "v95"
+// Eight values of the caller in registers that the block does not write.
+#define UL_KEPT(X, r0, r1, r2, r3, r4, r5, r6, r7)                                                             \
+    "{v" #r0 "}"(X[0]), "{v" #r1 "}"(X[1]), "{v" #r2 "}"(X[2]), "{v" #r3 "}"(X[3]),                              \
+    "{v" #r4 "}"(X[4]), "{v" #r5 "}"(X[5]), "{v" #r6 "}"(X[6]), "{v" #r7 "}"(X[7])
 // Accumulator block (i, j) is a[32 i + 4 j : 32 i + 4 j + 3]: X(i, j, first, last).
 #define UL_BLOCKS(X) \
     X(0, 0, 0, 3) X(0, 1, 4, 7) X(0, 2, 8, 11) X(0, 3, 12, 15) X(0, 4, 16, 19) X(0, 5, 20, 23) X(0, 6, 24, 27) X(0, 7, 28, 31) \

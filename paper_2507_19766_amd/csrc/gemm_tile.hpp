@@ -373,7 +373,9 @@ struct TileLarge {
                          : UL_MAIN_IN, UL_IN_COPY_COLS_A, UL_IN_COPY_COLS_B, UL_IN_READ_COLS_A, UL_IN_READ_COLS_B : UL_CLOBBERS);
     }
     // The same with the caller's 32 running values given to the block, which leaves them alone, in registers of their own: the
-    // compiler would keep some of them in scratch memory around it, and a reload waits for every copy in flight.
+    // compiler would keep some of them in scratch memory around it, and a reload waits for every copy in flight.  Others of the
+    // statistics kernel's values are still there (22 registers spilled, 56 bytes a lane), and some of their reloads stand
+    // in the work on a tile's results, behind the next tile's first copies.
     __device__ __forceinline__ void finish_keep(float (&m)[NJ], float (&S)[NJ], float (&C)[NJ], float (&T)[NJ])
     {
         const int lane = fresh_lane();
@@ -385,7 +387,10 @@ struct TileLarge {
         cursors(pa, pb);
         f32x32 f0, f1, f2, f3;
         asm volatile(UL_MAIN(COLS, ROWS) : UL_BLOCKS(UL_OUT) UL_FRAGMENTS
-                         : UL_MAIN_IN, UL_IN_COPY_COLS_A, UL_IN_COPY_ROWS_B, UL_IN_READ_COLS_A, UL_IN_READ_ROWS_B, "{v96}"(m[0]), "{v97}"(m[1]), "{v98}"(m[2]), "{v99}"(m[3]), "{v100}"(m[4]), "{v101}"(m[5]), "{v102}"(m[6]), "{v103}"(m[7]), "{v104}"(S[0]), "{v105}"(S[1]), "{v106}"(S[2]), "{v107}"(S[3]), "{v108}"(S[4]), "{v109}"(S[5]), "{v110}"(S[6]), "{v111}"(S[7]), "{v112}"(C[0]), "{v113}"(C[1]), "{v114}"(C[2]), "{v115}"(C[3]), "{v116}"(C[4]), "{v117}"(C[5]), "{v118}"(C[6]), "{v119}"(C[7]), "{v120}"(T[0]), "{v121}"(T[1]), "{v122}"(T[2]), "{v123}"(T[3]), "{v124}"(T[4]), "{v125}"(T[5]), "{v126}"(T[6]), "{v127}"(T[7]) : UL_CLOBBERS);
+                     : UL_MAIN_IN, UL_IN_COPY_COLS_A, UL_IN_COPY_ROWS_B, UL_IN_READ_COLS_A, UL_IN_READ_ROWS_B,
+                       UL_KEPT(m, 96, 97, 98, 99, 100, 101, 102, 103), UL_KEPT(S, 104, 105, 106, 107, 108, 109, 110, 111),
+                       UL_KEPT(C, 112, 113, 114, 115, 116, 117, 118, 119), UL_KEPT(T, 120, 121, 122, 123, 124, 125, 126, 127)
+                     : UL_CLOBBERS);
     }
     // x = block (I, J) of the result, taken when it is needed.
     template <int I, int J>

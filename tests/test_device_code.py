@@ -55,7 +55,7 @@ def _loop_source():
 
 
 def _clobbers(text):
-    return set(re.findall(r'"([a-z0-9]+)"', re.search(r"#define UL_CLOBBERS (.*?)\n#define|#define UL_CLOBBERS (.*?)\n//", text, re.S).group(0)))
+    return set(re.findall(r'"([a-z0-9]+)"', re.search(r"#define UL_CLOBBERS (?:.*\\\n)*.*", text).group(0)))
 
 
 def test_every_register_that_the_blocks_write_is_named_to_the_compiler():
@@ -67,3 +67,11 @@ def test_every_register_that_the_blocks_write_is_named_to_the_compiler():
     written |= set(re.findall(r'#define UL_ROW_\w "(v\d+)"', text))
     assert {"m0", "s40", "s49"} < written and len(written) == 21, sorted(written)
     assert written <= _clobbers(text), sorted(written - _clobbers(text))
+
+
+def test_values_kept_over_the_main_loop_are_in_registers_that_it_leaves_alone():
+    kept = re.findall(r"UL_KEPT\(\w, ([0-9, ]+)\)", open(os.path.join(build.CSRC, "gemm_tile.hpp")).read())
+    kept = [int(r) for eight in kept for r in eight.split(",")]
+    assert len(kept) == len(set(kept)) == 32
+    assert max(kept) < 128                                    # the fragments' registers
+    assert not {"v%d" % r for r in kept} & _clobbers(_loop_source())
