@@ -32,7 +32,12 @@ T* as(const X& t)
     return static_cast<T*>(ptr(t));
 }
 
-void* stream_of(const at::Device& dev) { return c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(dev.index()).stream(); }
+// The current stream of a GPU.  (Asked for a device without an index, as the CPU is, torch answers for the current GPU.)
+void* stream_of(const at::Device& dev)
+{
+    TORCH_CHECK_VALUE(dev.is_cuda(), "Expected a cuda device, but got: ", dev.str());
+    return c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(dev.index()).stream();
+}
 
 // The Python class of a failed status; lives as long as the interpreter.
 PyObject* status_error = nullptr;
@@ -63,6 +68,15 @@ void check_vector(const OptTensor& t, at::ScalarType type, int64_t n, const char
     if (!t.has_value()) return;
     TORCH_CHECK_VALUE(t->device() == dev && t->scalar_type() == type && t->dim() == 1 && t->size(0) == n && t->is_contiguous(),
                       name, " must be a contiguous ", type_name(type), "[", n, "] tensor on ", dev.str());
+}
+
+// n elements that a kernel can read one after the other, in whatever shape (a mask of either one-byte type), or nothing.
+void check_elements(const OptTensor& t, at::ScalarType type, int64_t n, const char* name, const at::Device& dev)
+{
+    if (!t.has_value()) return;
+    const bool same = t->scalar_type() == type || (type == at::kByte && t->scalar_type() == at::kBool);
+    TORCH_CHECK_VALUE(t->device() == dev && same && t->numel() >= n && t->is_contiguous(),
+                      name, " must hold ", n, " contiguous elements of ", type_name(type), " on ", dev.str());
 }
 
 struct Logits {
@@ -477,7 +491,15 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m)
                                     const OptTensor& entropy, const OptTensor& mask, const OptTensor& adv, double eps_low, double eps_high) {
         return unlocked([&] {
             const at::Device dev = ids.device();
+            TORCH_CHECK_VALUE(dev.is_cuda(), "Expected a cuda device, but got: ", dev.str());
             const int64_t N = ids.size(0);
+            check_elements(ids, at::kInt, N, "segment_ids", dev);
+            check_elements(ratio, at::kFloat, N, "ratio", dev);
+            check_elements(logp, at::kFloat, N, "logp", dev);
+            check_elements(old, at::kFloat, N, "old_logp", dev);
+            check_elements(entropy, at::kFloat, N, "entropy", dev);
+            check_elements(mask, at::kByte, N, "mpt_mask", dev);
+            check_elements(adv, at::kFloat, N, "advantages", dev);
             Segments s = segment_tensors(K, N, dev);
             check(ulorl_segment_diagnostics(N, (int32_t)K, as<int32_t>(ids), as<float>(ratio), as<float>(logp), as<float>(old), as<float>(entropy),
                                             as<uint8_t>(mask), as<float>(adv), (float)eps_low, (float)eps_high, as<int64_t>(s[0]), as<double>(s[1]),

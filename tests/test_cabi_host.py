@@ -150,6 +150,18 @@ def test_binding_refuses_cpu_tensors():
         ulorl.row_stats(z, torch.zeros(2, dtype=torch.int32))
 
 
+def test_segment_diagnostics_refuses_a_result_on_the_cpu():
+    """Its pointers would be host addresses; refused by the device of the ids, before anything else is looked at."""
+    import torch
+    n = 8
+    f, i, m = torch.zeros(n), torch.zeros(n, dtype=torch.int32), torch.zeros(n, dtype=torch.uint8)
+    res = ulorl.FwdResult(None, f, f, f, ratio=f, segment_out=i, mpt_mask=m)
+    with pytest.raises(ValueError, match="cuda device"):
+        ulorl.segment_diagnostics(res, f, f, 4)
+    with pytest.raises(ValueError, match="cuda device"):
+        ulorl.segment_diagnostics(res, f, None, 4, segment_ids=i)
+
+
 def test_pool_step_rejects_bad_arguments_on_the_host():
     lib = ulorl.load_library()
     vp = ctypes.c_void_p

@@ -129,6 +129,31 @@ def test_segment_diagnostics_match_the_oracle():
     np.testing.assert_array_equal(g3["count"].cpu().numpy(), o["count"][:4])
 
 
+def test_segment_diagnostics_take_what_a_kernel_can_read():
+    """Each tensor where the ids are, of its type and as long; a mask of either one-byte type and a column are as good."""
+    n, K = 70, 3
+    f = torch.rand(n, device=DEV)
+    t = dict(ratio=f + 0.5, logp=-f, old=-f * 1.1, entropy=f, mask=(f > 0.5).to(torch.uint8), adv=f - 0.5,
+             ids=torch.arange(n, device=DEV, dtype=torch.int32) % K)
+
+    def call(**change):
+        x = dict(t, **change)
+        res = ulorl.FwdResult(None, x["logp"], x["entropy"], x["logp"], ratio=x["ratio"], segment_out=x["ids"], mpt_mask=x["mask"])
+        return ulorl.segment_diagnostics(res, x["adv"], x["old"], K)
+    ref = call()
+    for same in (dict(mask=t["mask"].bool()), dict(adv=t["adv"][:, None]), dict(logp=torch.cat([t["logp"], f]))):
+        got = call(**same)
+        assert all(torch.equal(got[k], ref[k]) for k in ref)
+    for name in ("ratio", "logp", "old", "entropy", "mask", "adv"):
+        for bad in (t[name].cpu(), t[name].double(), t[name][:-1], t[name].repeat(2)[::2]):
+            with pytest.raises(ValueError):
+                call(**{name: bad})
+    with pytest.raises(ValueError):
+        call(ids=t["ids"].long())
+    with pytest.raises(ulorl.UlorlError):
+        call(ratio=None)
+
+
 @pytest.mark.parametrize("case", ["logits_two_call", "logits_one_call", "lmhead", "explicit_ids_pois", "many_segments"])
 def test_segment_diagnostics_as_a_by_product_of_the_forward_calls(case):
     """The forward calls hand out the per-segment diagnostics in the same pass as the token terms;
