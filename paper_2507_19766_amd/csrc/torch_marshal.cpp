@@ -12,6 +12,7 @@
 #include <torch/csrc/utils/pybind.h>
 
 #include <array>
+#include <exception>
 #include <optional>
 #include <string>
 #include <vector>
@@ -385,22 +386,17 @@ py::list list_of(const Fields& f)
     return out;
 }
 
-// Runs f without the interpreter's lock; its errors become Python's.
+// Runs f without the interpreter's lock; its errors become the Python classes that torch gives them (OutOfMemoryError, which
+// callers catch, among them).
 template <class F>
 auto unlocked(F f)
 {
     try {
         py::gil_scoped_release no_gil;
         return f();
-    } catch (python_error& e) {
-        e.restore();
+    } catch (const std::exception&) {
+        torch::translate_exception_to_python(std::current_exception());
         throw py::error_already_set();
-    } catch (const c10::ValueError& e) {
-        throw py::value_error(e.what_without_backtrace());
-    } catch (const c10::TypeError& e) {
-        throw py::type_error(e.what_without_backtrace());
-    } catch (const c10::Error& e) {
-        throw std::runtime_error(e.what_without_backtrace());
     }
 }
 

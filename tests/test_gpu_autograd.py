@@ -89,6 +89,25 @@ def test_refusals(change, error):
 
 
 @pytest.mark.parametrize("lmhead", [False, True])
+def test_errors_of_torch_keep_their_classes(lmhead):
+    """A request that no card can hold (8 TB of per-segment counts) raises what a training loop catches to try a smaller batch; an
+    index out of range stays an IndexError."""
+    w = ui.shrink(ui.config(5) if lmhead else ui.config(2), [20, 13], V=520, seg_len=16, name="marshal_classes", **({"hidden": 64} if lmhead else {}))
+    d = ui.generate(w, DEV)
+    p = params_for(w, gate_mode=ulorl.GATE_NEVER)
+    first = [d[k] for k in (("hidden", "weight") if lmhead else ("logits",))]
+    rest = (d["advantages"], d["old_logp"], p)
+    for call in (ulorl.lmhead_token_loss_fwd,) if lmhead else (ulorl.token_loss_fwd, ulorl.token_loss_fwd_bwd):
+        with pytest.raises(torch.OutOfMemoryError):
+            call(*first, d["token_ids"], d["cu_seqlens"], *rest, segments=1 << 40)
+        with pytest.raises(IndexError):
+            call(*first, d["token_ids"], d["cu_seqlens"].sum(dtype=torch.int32), *rest)
+    call = ulorl.autograd.lmhead_token_loss if lmhead else ulorl.autograd.token_loss
+    with pytest.raises(IndexError):
+        call(*[t.requires_grad_(True) for t in first], d["token_ids"], d["cu_seqlens"].sum(dtype=torch.int32), *rest)
+
+
+@pytest.mark.parametrize("lmhead", [False, True])
 def test_native_nodes_are_autograd_nodes(lmhead):
     """Saved tensors pass through saved-tensor hooks, a kept graph runs twice, a changed input is noticed, and no
     graph is kept without grad; on a stream of its own."""
