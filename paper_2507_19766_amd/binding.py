@@ -281,7 +281,7 @@ def token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp=None,
     """ulorl_token_loss_fwd_bwd -> (FwdResult, dlogits).  ``inplace=True`` overwrites ``logits``."""
     with_params, with_launch = _structs(params, launch)
     fields, seg, d = native().token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
-                                                 _addr(with_launch), grad_out, dlogits, inplace, False,
+                                                 _addr(with_launch), float(grad_out), dlogits, bool(inplace), False,
                                                  out._fields() if out is not None else None, workspace, segments)
     return _result(out, fields, seg), d
 
@@ -306,7 +306,7 @@ def token_loss_fwd_bwd_static(logits, token_ids, cu_seqlens, advantages, old_log
     wrapper from allocating outputs either)."""
     with_params, with_launch = _structs(params, launch)
     fields, _, d = native().token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
-                                               _addr(with_launch), grad_out, dlogits, inplace, True,
+                                               _addr(with_launch), float(grad_out), dlogits, bool(inplace), True,
                                                out._fields() if out is not None else None, None, 0)
     return _result(out, fields, None), d
 
@@ -319,7 +319,7 @@ def row_stats(logits, token_ids, out: Optional[FwdResult] = None, launch: Option
 def token_loss_bwd(logits, token_ids, lse, gcoef, grad_out: float = 1.0,
                    dlogits: Optional[torch.Tensor] = None, inplace: bool = False) -> torch.Tensor:
     """ulorl_token_loss_bwd.  ``inplace=True`` overwrites ``logits`` with the gradient."""
-    return native().token_loss_bwd(logits, token_ids, lse, gcoef, grad_out, dlogits, inplace)
+    return native().token_loss_bwd(logits, token_ids, lse, gcoef, float(grad_out), dlogits, bool(inplace))
 
 
 # ------------------------------------------------------------------------------------ lm_head variant
@@ -344,7 +344,7 @@ def lmhead_token_loss_bwd(hidden, weight, token_ids, lse, gcoef, grad_out: float
                           workspace: Optional[torch.Tensor] = None, launch: Optional[Launch] = None):
     """ulorl_lmhead_token_loss_bwd -> (d_hidden [N, Hd] bf16, d_weight [Hd, V] bf16)."""
     with_launch = launch.to_c() if launch is not None else None
-    return native().lmhead_bwd(hidden, weight, token_ids, lse, gcoef, grad_out, vocab_chunk, d_hidden, d_weight, workspace,
+    return native().lmhead_bwd(hidden, weight, token_ids, lse, gcoef, float(grad_out), vocab_chunk, d_hidden, d_weight, workspace,
                                _addr(with_launch))
 
 
@@ -372,7 +372,7 @@ def gemm_tn_bf16(a: torch.Tensor, b: torch.Tensor, out: Optional[torch.Tensor] =
 
 def advantage_prep(rewards, cu_seqlens, group_size: int, truncated=None, eps: float = 1e-6, unbiased: bool = False):
     """ulorl_advantage_prep -> (resp_adv [R], group_keep [R/G], token_adv [N], kept_tokens [1] int64)."""
-    return native().advantage_prep(rewards, truncated, cu_seqlens, group_size, eps, unbiased)
+    return native().advantage_prep(rewards, truncated, cu_seqlens, group_size, float(eps), bool(unbiased))
 
 
 def segment_diagnostics(res: FwdResult, advantages, old_logp, K: int, eps_low: float = 0.2, eps_high: float = 0.2,
@@ -380,7 +380,7 @@ def segment_diagnostics(res: FwdResult, advantages, old_logp, K: int, eps_low: f
     """ulorl_segment_diagnostics on the outputs of a forward call -> dict of per-segment tensors."""
     seg = res.segment_out if segment_ids is None else segment_ids
     return dict(zip(SEGMENT_FIELDS[:-1], native().segment_diagnostics(K, seg, res.ratio, res.logp, old_logp, res.entropy, res.mpt_mask,
-                                                                      advantages, eps_low, eps_high)))
+                                                                      advantages, float(eps_low), float(eps_high))))
 
 
 def segment_pool_step(prev_len, new_len, hit_eos, seg_len: int, max_len: int):
@@ -388,4 +388,4 @@ def segment_pool_step(prev_len, new_len, hit_eos, seg_len: int, max_len: int):
     unfinished_idx, experience_idx, exp_truncated [B] and exp_cu_seqlens [B+1] (only the leading
     counts[0] / counts[1] (+1) entries are meaningful); counts [5] int64."""
     return dict(zip(("state", "total_len", "segments", "unfinished_idx", "experience_idx", "exp_cu_seqlens", "exp_truncated", "counts"),
-                    native().segment_pool_step(prev_len, new_len, hit_eos, seg_len, max_len)))
+                    native().segment_pool_step(prev_len, new_len, hit_eos, int(seg_len), int(max_len))))

@@ -162,6 +162,14 @@ def test_segment_diagnostics_refuses_a_result_on_the_cpu():
         ulorl.segment_diagnostics(res, f, None, 4, segment_ids=i)
 
 
+def test_pool_step_takes_lengths_that_int_takes():
+    """4096.0 (from a configuration file, say) is a length; what is refused here is the device."""
+    import torch
+    i, e = torch.ones(3, dtype=torch.int32), torch.zeros(3, dtype=torch.uint8)
+    with pytest.raises(RuntimeError, match="GPU only"):
+        ulorl.segment_pool_step(i, i, e, 4096.0, 16384.0)
+
+
 def test_pool_step_rejects_bad_arguments_on_the_host():
     lib = ulorl.load_library()
     vp = ctypes.c_void_p

@@ -229,6 +229,14 @@ def test_segment_pool_step_matches_the_oracle(B):
     assert np.array_equal(got["exp_truncated"][:ne], ref["exp_truncated"])
 
 
+def test_segment_pool_step_takes_lengths_that_int_takes():
+    prev, new = (torch.tensor(x, device=DEV, dtype=torch.int32) for x in ([0, 16, 48], [16, 5, 16]))
+    eos = torch.tensor([0, 1, 0], device=DEV, dtype=torch.uint8)
+    a, b = ulorl.segment_pool_step(prev, new, eos, 16, 64), ulorl.segment_pool_step(prev, new, eos, 16.0, np.float32(64))
+    for name in ("state", "total_len", "segments", "counts"):
+        assert torch.equal(a[name], b[name])
+
+
 def test_rollout_model_takes_the_same_path_on_the_gpu():
     """Forty steps of the segment-rollout loop driven by the GPU pool update and by the oracle:
     identical pools at every step."""
