@@ -240,19 +240,25 @@ class FwdResult:
     counters: Optional[torch.Tensor] = None
     segment_stats: Optional[dict] = None      # per-segment diagnostics, when asked for (segments=K)
 
-    def _fields(self):
-        return [self.loss, self.logp, self.entropy, self.lse, self.gcoef, self.mpt_mask, self.ratio, self.segment_out,
-                self.resp_entropy, self.resp_gate, self.counters]
-
 
 SEGMENT_FIELDS = ("count", "ratio_sum", "ratio_max", "clipped", "kl_sum", "ent_sum", "masked", "out_of_range", "_workspace")
 
 
-def _result(out: Optional[FwdResult], fields, segments) -> FwdResult:
+def _fields(out: Optional[FwdResult], stats_only: bool):
+    """A caller's tensors; a stats-only pass looks at the three that it writes."""
+    if out is None:
+        return None
+    if stats_only:
+        return [None, out.logp, out.entropy, out.lse] + [None] * 7
+    return [out.loss, out.logp, out.entropy, out.lse, out.gcoef, out.mpt_mask, out.ratio, out.segment_out, out.resp_entropy,
+            out.resp_gate, out.counters]
+
+
+def _result(out: Optional[FwdResult], fields, segments, stats_only: bool = False) -> FwdResult:
     """The call's tensors as a FwdResult: a new one, or the caller's with what was missing filled in."""
     if out is None:
         out = FwdResult(*fields)
-    else:
+    elif not stats_only:
         (out.loss, out.logp, out.entropy, out.lse, out.gcoef, out.mpt_mask, out.ratio, out.segment_out, out.resp_entropy,
          out.resp_gate, out.counters) = fields
     if segments:
@@ -269,8 +275,8 @@ def token_loss_fwd(logits, token_ids, cu_seqlens, advantages, old_logp=None, par
     ``segments=K`` asks for the per-segment diagnostics of ids 0..K-1 (``out.segment_stats``)."""
     with_params, with_launch = _structs(params, launch)
     fields, seg = native().token_loss_fwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
-                                          _addr(with_launch), out._fields() if out is not None else None, workspace, segments)
-    return _result(out, fields, seg)
+                                          _addr(with_launch), _fields(out, advantages is None), workspace, segments)
+    return _result(out, fields, seg, advantages is None)
 
 
 def token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp=None, params: Params = None,
@@ -282,7 +288,7 @@ def token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp=None,
     with_params, with_launch = _structs(params, launch)
     fields, seg, d = native().token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
                                                  _addr(with_launch), float(grad_out), dlogits, bool(inplace), False,
-                                                 out._fields() if out is not None else None, workspace, segments)
+                                                 _fields(out, False), workspace, segments)
     return _result(out, fields, seg), d
 
 
@@ -307,7 +313,7 @@ def token_loss_fwd_bwd_static(logits, token_ids, cu_seqlens, advantages, old_log
     with_params, with_launch = _structs(params, launch)
     fields, _, d = native().token_loss_fwd_bwd(logits, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
                                                _addr(with_launch), float(grad_out), dlogits, bool(inplace), True,
-                                               out._fields() if out is not None else None, None, 0)
+                                               _fields(out, False), None, 0)
     return _result(out, fields, None), d
 
 
@@ -335,8 +341,8 @@ def lmhead_token_loss_fwd(hidden, weight, token_ids, cu_seqlens, advantages, old
     """ulorl_lmhead_token_loss_fwd."""
     with_params, with_launch = _structs(params, launch)
     fields, seg = native().lmhead_fwd(hidden, weight, token_ids, cu_seqlens, advantages, old_logp, segment_ids, _addr(with_params),
-                                      _addr(with_launch), vocab_chunk, out._fields() if out is not None else None, workspace, segments)
-    return _result(out, fields, seg)
+                                      _addr(with_launch), vocab_chunk, _fields(out, advantages is None), workspace, segments)
+    return _result(out, fields, seg, advantages is None)
 
 
 def lmhead_token_loss_bwd(hidden, weight, token_ids, lse, gcoef, grad_out: float = 1.0, vocab_chunk: int = 8192,

@@ -100,19 +100,23 @@ Tensor empty_rows(int64_t n, at::ScalarType type, const at::Device& dev)
     return n > 0 ? empty(n, type, dev) : empty(1, type, dev).narrow(0, 0, 0);
 }
 
-// The fields of FwdResult, in its order.
+// The fields of FwdResult, in its order.  given: they are the caller's, whose tensors are never replaced; what is missing among them is
+// a null pointer, which the library refuses where it needs one.
 enum { LOSS, LOGP, ENTROPY, LSE, GCOEF, MASK, RATIO, SEGMENT, RESP_ENTROPY, RESP_GATE, COUNTERS, FIELDS };
-using Fields = std::array<Tensor, FIELDS>;
+struct Fields : std::array<Tensor, FIELDS> {
+    bool given = false;
+};
 
 void allocate_rows(Fields& f, int64_t N, const at::Device& dev)
 {
-    if (!f[LOGP].defined())
-        for (int i : {LOGP, ENTROPY, LSE}) f[i] = empty(N, at::kFloat, dev);
+    if (f.given) return;
+    for (int i : {LOGP, ENTROPY, LSE}) f[i] = empty(N, at::kFloat, dev);
 }
-void allocate_objective(Fields& f, int64_t N, int64_t R, const at::Device& dev)
+// complete: a caller's result has to be whole; otherwise one without a loss (that of a stats-only pass) gets the rest.
+void allocate_objective(Fields& f, int64_t N, int64_t R, const at::Device& dev, bool complete)
 {
     allocate_rows(f, N, dev);
-    if (f[LOSS].defined()) return;
+    if (f.given && (complete || f[LOSS].defined())) return;
     f[LOSS] = empty(1, at::kFloat, dev);
     f[GCOEF] = empty(N, at::kFloat, dev);
     f[MASK] = empty(N, at::kByte, dev);
@@ -205,7 +209,7 @@ void token_loss_fwd(const Tensor& z, Objective o, Fields& f, Segments& seg, int6
     }
     o.check_rows(l.N, l.dev);
     o.check_lengths(l.dev);
-    allocate_objective(f, l.N, o.R, l.dev);
+    allocate_objective(f, l.N, o.R, l.dev, false);
     const Tensor ws = workspace_or(workspace, ulorl_token_loss_workspace_bytes(l.N, l.V, (int32_t)o.R), l.dev);
     ulorl_segment_stats st;
     if (K > 0) st = segment_struct(seg = segment_tensors(K, l.N, l.dev), K);
@@ -225,7 +229,7 @@ Tensor token_loss_fwd_bwd(const Tensor& z, Objective o, double grad_out, const O
     o.check_rows(l.N, l.dev);
     o.check_lengths(l.dev);
     TORCH_CHECK_VALUE(o.advantages.has_value(), on_static ? "token_loss_fwd_bwd_static" : "token_loss_fwd_bwd", " needs advantages");
-    allocate_objective(f, l.N, o.R, l.dev);
+    allocate_objective(f, l.N, o.R, l.dev, on_static);
     const Tensor d = gradient_for(z, dlogits, inplace);
     if (on_static) {
         check(ulorl_token_loss_fwd_bwd_static(ptr(z), l.dt, l.N, l.V, l.stride, as<int32_t>(o.token_ids), as<int32_t>(o.cu), (int32_t)o.R,
@@ -284,7 +288,7 @@ void lmhead_fwd(const Tensor& h, const Tensor& w, Objective o, int64_t chunk, Fi
     o.check_rows(l.N, l.dev);
     const bool stats_only = !o.advantages.has_value();
     if (stats_only) allocate_rows(f, l.N, l.dev);
-    else allocate_objective(f, l.N, o.R, l.dev);
+    else allocate_objective(f, l.N, o.R, l.dev, true);
     const Tensor ws = workspace_or(workspace, ulorl_lmhead_workspace_bytes(l.N, l.Hd, l.V, (int32_t)o.R, (int32_t)chunk), l.dev);
     Fields none;
     const Fields& g = stats_only ? none : f;
@@ -374,7 +378,8 @@ using Given = std::optional<std::vector<OptTensor>>;      // a caller's FwdResul
 Fields fields_of(const Given& given)
 {
     Fields f;
-    if (given.has_value())
+    f.given = given.has_value();
+    if (f.given)
         for (int i = 0; i < FIELDS; ++i)
             if ((*given)[i].has_value()) f[i] = *(*given)[i];
     return f;

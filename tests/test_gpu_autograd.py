@@ -1,4 +1,6 @@
 """The torch.autograd entry points hand out exactly what the library calls they forward to produce."""
+import types
+
 import pytest
 import torch
 
@@ -86,6 +88,42 @@ def test_refusals(change, error):
         assert type(e.value) is error
         if error is ulorl.UlorlError:
             assert e.value.status < 0
+
+
+@pytest.mark.parametrize("lmhead", [False, True])
+def test_a_callers_result_is_written_or_refused_never_replaced(lmhead):
+    """``out``: a missing tensor that the library needs is refused with the others left alone; that of a stats-only pass is
+    completed by a logits forward; a stats-only pass looks at its three tensors only."""
+    w = ui.shrink(ui.config(5) if lmhead else ui.config(2), [20, 13], V=520, seg_len=16, name="marshal_out", **({"hidden": 64} if lmhead else {}))
+    d = ui.generate(w, DEV)
+    p = params_for(w, gate_mode=ulorl.GATE_NEVER)
+    first = [d[k] for k in (("hidden", "weight") if lmhead else ("logits",))]
+    rest = (d["cu_seqlens"], d["advantages"], d["old_logp"], p)
+    call = ulorl.lmhead_token_loss_fwd if lmhead else ulorl.token_loss_fwd
+    ref = call(*first, d["token_ids"], *rest)
+    rows = [torch.full((w.N,), 7.0, device=DEV) for _ in range(3)]
+    for hole in range(3):
+        three = [None if i == hole else t for i, t in enumerate(rows)]
+        out = ulorl.FwdResult(None, *three)
+        for cu_and_rest in ((None, None), rest):
+            with pytest.raises(ulorl.UlorlError):
+                call(*first, d["token_ids"], *cu_and_rest, out=out)
+            assert all(a is b for a, b in zip((out.logp, out.entropy, out.lse), three))
+    assert all(bool((t == 7.0).all()) for t in rows)
+    out = types.SimpleNamespace(logp=rows[0], entropy=rows[1], lse=rows[2])
+    assert call(*first, d["token_ids"], None, None, out=out) is out
+    assert torch.equal(_bits(rows[0]), _bits(ref.logp)) and vars(out).keys() == {"logp", "entropy", "lse"}
+    out = ulorl.FwdResult(None, *rows)
+    if lmhead:                                     # its caller's result has to be whole, as that of the static call
+        with pytest.raises(ulorl.UlorlError):
+            call(*first, d["token_ids"], *rest, out=out)
+        return
+    ulorl.init()
+    with pytest.raises(ulorl.UlorlError):
+        ulorl.token_loss_fwd_bwd_static(*first, d["token_ids"], *rest, out=out)
+    assert out.loss is None
+    assert call(*first, d["token_ids"], *rest, out=out) is out and out.logp is rows[0]
+    assert torch.equal(_bits(out.loss), _bits(ref.loss)) and torch.equal(out.mpt_mask, ref.mpt_mask)
 
 
 @pytest.mark.parametrize("lmhead", [False, True])
