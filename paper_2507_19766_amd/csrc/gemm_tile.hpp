@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_limits.hpp"
 #include "gemm_loop.hpp"
 
 namespace ulorl_detail {
@@ -47,19 +48,10 @@ struct Operand {
     int count;
 };
 
-constexpr int kTileK = 64;                       // contraction depth of one LDS stage
 constexpr int kHalf = 128;                       // rows (columns) of one half tile: the unit of copying
 constexpr int kHalfElems = kHalf * kTileK;       // 16 KB
 // Word 3 of a raw (unstructured, stride 0) buffer descriptor on gfx9-family parts: 32-bit data format.
 constexpr int kRawBufferFlags = 0x00020000;
-// Operands are addressed by 32-bit byte offsets: K_ROWS from a tile's first row (up to 256 rows of ld elements), K_COLS from the
-// first of four rows (small tile) or of 52 (large tile).  With at most kMaxLeadingDim elements any stays below 2^31 bytes;
-// larger ones are checked by the caller (k_rows_fit, kMaxColsLeadingDim, kMaxLargeColsLeadingDim).
-constexpr int64_t kMaxLeadingDim = 1 << 22;
-constexpr int64_t kMaxColsLeadingDim = 1 << 29;
-constexpr int64_t kMaxLargeColsLeadingDim = 1 << 25;
-inline bool k_rows_fit(int64_t tile_rows, int64_t ld, int64_t K) { return ((tile_rows - 1) * ld + K) * 2 <= 0xffffffffLL; }
-
 // s_waitcnt immediates: at most n vector memory operations (LDS operations) still outstanding.
 #define ULORL_WAIT_VMEM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 #define ULORL_WAIT_LDS(n) __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | ((n) << 8) | (3 << 14))

@@ -85,28 +85,40 @@ def test_backward_partitions(n, V, hidden):
 
 
 @pytest.mark.parametrize("n,V,hidden", [(1300, 64, 320), (1300, 136, 320), (1408, 264, 384), (1409, 1096, 392), (1537, 200, 512)])
-def test_large_tiles_with_half_empty_ones(n, V, hidden):
+def test_many_rows_and_few_columns(n, V, hidden):
     """More than a thousand rows and few columns, with 20, 128, 129 and 1 rows beyond a multiple of 256, hidden sizes whose last
-    tile is half empty too, and contractions of one to four K tiles in the dHidden product.  (Too few tiles for large ones,
-    which these shapes took once: those are below.)"""
+    tile is half empty too, and contractions of one to four K tiles in the dHidden product.  (Small tiles, too few
+    for large ones, which are below.)"""
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_halves")
     for dense in (False, True):
         run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(dense_rows=dense))
 
 
-@pytest.mark.parametrize("n", [290, 353, 450, 513, 545])
-def test_large_tiles_of_every_width(n):
-    """Large tiles share the tokens evenly, in units of 32 columns: two of 160 (the last with empty columns), of 192, of
-    256 and 224, three of 192 and 160.  The vocabulary (a rest of 80 columns) is wide enough for the large tile
-    in the forward and, from 513 rows on, in the backward."""
-    w = ui.shrink(ui.config(5), [n - 7, 7], V=20048, hidden=1024, seg_len=64, name="lmhead_widths")
+# Large tiles share the tokens evenly, in units of 32 columns.
+LARGE_IN_FORWARD = [(257, 30000, 1024),     # one of 160 and one of 128, whose second half is empty
+                    (288, 30000, 1024),     # the same, full
+                    (290, 30000, 1024),     # two of 160, the last with empty columns
+                    (353, 30000, 1024),     # two of 192
+                    (450, 20048, 1024)]     # 256 and 224
+LARGE_IN_BOTH = [(257, 22008, 2048), (300, 22008, 2048), (353, 22008, 2048),      # the first ones' widths
+                 (513, 20048, 1024),        # 192, 192, 160
+                 (545, 20048, 1024)]        # three of 192
+
+
+@pytest.mark.parametrize("n,V,hidden", LARGE_IN_FORWARD + LARGE_IN_BOTH)
+def test_large_tiles_of_every_width(n, V, hidden):
+    """The vocabularies leave a rest of 48 or 80 columns, or 248."""
+    w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_widths")
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192)
 
 
-@pytest.mark.parametrize("n,V,hidden,chunk", [(1300, 9536, 320, 8192),     # last hidden tile a quarter full
-                                              (1409, 9544, 392, 8192),     # hidden and vocabulary no multiple of 64: padded copies
-                                              (1281, 9480, 448, 1024),     # ten chunks, the last columns apart; a last token in a tile of its own
-                                              (1537, 9472, 512, 8192)])
+LARGE_BACKWARD = [(1300, 9536, 320, 8192),     # last hidden tile a quarter full
+                  (1409, 9544, 392, 8192),     # hidden and vocabulary no multiple of 64: padded copies
+                  (1281, 9480, 448, 1024),     # three chunks, the last columns apart; a last tile of tokens with empty columns
+                  (1537, 9472, 512, 8192)]
+
+
+@pytest.mark.parametrize("n,V,hidden,chunk", LARGE_BACKWARD)
 def test_large_tiles_of_the_backward(n, V, hidden, chunk):
     """Few K tiles of the dz product (5 to 8) and 21 to 25 of the dW product."""
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_large_bwd")
@@ -166,7 +178,7 @@ def _few_live(w, n_live):
 
 @pytest.mark.parametrize("n_live", [0, 1, 64, 65, 128, 129, 257])
 @pytest.mark.parametrize("hidden,V", [(320, 328), (512, 256), (392, 1096)])
-def test_large_tiles_with_few_live_rows(n_live, hidden, V):
+def test_many_rows_with_few_live_ones(n_live, hidden, V):
     """A batch of 1300 rows with few that carry a gradient: the d_W product, both operands transposed, contracts over none, one,
     two, three and five K tiles, in whole and half empty tiles; against the oracle.  (Small tiles, by the number of columns; the
     large ones: test_large_tiles_of_the_backward_with_few_live_rows.)"""
@@ -181,8 +193,8 @@ def test_large_tiles_with_few_live_rows(n_live, hidden, V):
 
 
 @pytest.mark.parametrize("group_m", [1, 7, 64])
-def test_walks_of_large_tiles(group_m):
-    """1320 rows and 1544 columns in several chunks.  (Small tiles by now; the large ones in the next test.)"""
+def test_walks_of_many_rows_and_few_columns(group_m):
+    """1320 rows and 1544 columns in several chunks.  (Small tiles; the large ones in the next test.)"""
     w = ui.shrink(ui.config(5), [1200, 120], V=1544, hidden=320, seg_len=64, name="lmhead_large_walk")
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_ALWAYS, tau=0.05), chunk=512, launch=ulorl.Launch(gemm_group_m=group_m))
 
@@ -365,9 +377,6 @@ def test_forward_statistics_of_large_logits(n, Hd):
     assert torch.all((res.logp.double() - at).abs() <= 1e-6 * at.abs() + 2e-6 + 2e-6 * ent)
 
 
-# The vocabulary in several chunks (vocab_chunk = 64 and more rows than hidden columns, so that the workspace
-# has no room for wide ones), the last one narrower and no multiple of 64; W with its last columns apart
-# (hidden a multiple of 64), padded for having few columns (V < 2 n) and padded along hidden.
 @pytest.mark.parametrize("V", [1 << 25, (1 << 25) + 8])        # the widest weight of the large tile, and the small tile beyond
 def test_forward_of_a_very_wide_vocabulary(V):
     """Offsets into the weight of more than 2^31 bytes.  All columns are zero but for blocks at the start, in the
@@ -388,8 +397,14 @@ def test_forward_of_a_very_wide_vocabulary(V):
     assert float((res.logp - (at - lse)).abs().max()) <= 4e-5
 
 
+# The vocabulary in several chunks (vocab_chunk = 64 and more rows than hidden columns, so that the workspace
+# has no room for wide ones), the last one narrower and no multiple of 64; W with its last columns apart
+# (hidden a multiple of 64), padded for having few columns (V < 2 n) and padded along hidden.
+LARGE_IN_CHUNKS = [(1300, 9480, 320), (3000, 5000, 832), (1404, 9544, 328)]       # the same three with the large tile
+
+
 @pytest.mark.parametrize("n,V,hidden", [(700, 8392, 64), (1501, 3000, 64), (900, 6000, 72), (90, 56, 64),
-                                        (1300, 5000, 320), (1400, 2760, 320), (1300, 5000, 328)])
+                                        (1300, 5000, 320), (1400, 2760, 320), (1300, 5000, 328)] + LARGE_IN_CHUNKS)
 @pytest.mark.parametrize("dense", [False, True])
 def test_backward_over_several_ragged_chunks(n, V, hidden, dense):
     w = ui.shrink(ui.config(5), [n - 7, 7], V=V, hidden=hidden, seg_len=64, name="lmhead_chunks")

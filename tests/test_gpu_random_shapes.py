@@ -116,9 +116,9 @@ def test_random_lmhead_case(c):
         assert bool((res.gcoef[dead] == 0).all()) and bool((res.d_hidden[dead] == 0).all())
 
 
-def _lmhead_large_cases():
-    """Shapes of more than a tile each way (more than 256 rows and hidden columns, more than 3 * 2^17
-    elements of hidden), with small chunks and more rows than hidden columns, so that most run over several chunks."""
+def _lmhead_many_rows_cases():
+    """Shapes of more than 256 rows and hidden columns and more than 3 * 2^17 elements of hidden, with small chunks and more rows
+    than hidden columns, so that most run over several chunks; few columns, so that all take small tiles."""
     rs = np.random.RandomState(20250729)
     out = []
     for i in range(8):
@@ -129,8 +129,20 @@ def _lmhead_large_cases():
     return out
 
 
-@pytest.mark.parametrize("c", _lmhead_large_cases(), ids=lambda c: "%02d_N%d_Hd%d_V%d_c%d" % (c["idx"], sum(c["lengths"]), c["hidden"], c["V"], c["chunk"]))
-def test_random_lmhead_case_of_large_tiles(c):
+def _lmhead_large_cases():
+    """Shapes whose backward takes the large tile, in two to seven chunks, and whose forward does for half of them: last tiles of
+    tokens 192 to 256 wide, hidden sizes that are a multiple of 64 or not, other walks, all rows or the live ones."""
+    rs = np.random.RandomState(20251204)
+    out = []
+    for i in range(8):
+        hidden = 8 * int(rs.randint(49, 110)) if i % 2 else 64 * int(rs.randint(7, 15))
+        n = int(rs.randint(max(hidden, 600), 1900))
+        out.append(dict(idx=i, hidden=hidden, V=8 * int(rs.randint(1250, 2000)), lengths=[n - 9, 9], chunk=64 * int(rs.randint(1, 9)),
+                        group=int(rs.choice([0, 1, 3, 64])), dead_frac=float(rs.choice([0.0, 0.5, 0.98])), dense_rows=bool(i % 3 == 2)))
+    return out
+
+
+def _run_lmhead_case(c):
     from parity import run_lmhead_parity
     w = ui.shrink(ui.config(5), c["lengths"], V=c["V"], hidden=c["hidden"], seg_len=64, name="lmhead_large_%02d" % c["idx"])
     d = ui.generate(w, DEV)
@@ -139,3 +151,13 @@ def test_random_lmhead_case_of_large_tiles(c):
     res, _ = run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=c["chunk"], data=d,
                                launch=ulorl.Launch(gemm_group_m=c["group"], dense_rows=c["dense_rows"]))
     assert bool((res.gcoef[dead] == 0).all()) and bool((res.d_hidden[dead] == 0).all())
+
+
+@pytest.mark.parametrize("c", _lmhead_many_rows_cases(), ids=lambda c: "%02d_N%d_Hd%d_V%d_c%d" % (c["idx"], sum(c["lengths"]), c["hidden"], c["V"], c["chunk"]))
+def test_random_lmhead_case_of_many_rows(c):
+    _run_lmhead_case(c)
+
+
+@pytest.mark.parametrize("c", _lmhead_large_cases(), ids=lambda c: "%02d_N%d_Hd%d_V%d_c%d" % (c["idx"], sum(c["lengths"]), c["hidden"], c["V"], c["chunk"]))
+def test_random_lmhead_case_of_large_tiles(c):
+    _run_lmhead_case(c)
