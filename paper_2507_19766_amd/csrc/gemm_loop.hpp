@@ -17,8 +17,8 @@
 //     3     A1 B1                  A0 of k + 1       B1 of k + 2                        barrier
 // Copies are issued in the order in which they are needed, four instructions per half tile; at either barrier the
 // halves that the next two parts read are those before the last four: at most 16 outstanding.  A barrier after
-// every part (24 outstanding) measured 1.2 % less.  Copies past the last K tile are issued with no lane
-// active, so that the counts stay what they are.
+// every part (24 outstanding) measured 1.2 % less.  Copies past the last K tile are issued all
+// the same, from an empty buffer, so that the counts stay what they are.
 //
 // Measured, TFLOP/s (8192 x 32768 x 2048 and, dHidden, 2048 x 32768 x 8192; no result stored, one card), the loop of eight
 // waves in two groups before it / this one: A transposed 1428 / 1610, both transposed 1395 / 1600, neither 1570 / 1610.

@@ -36,7 +36,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     bf16x2 b = __builtin_convertvector(x, bf16x2);  // round to nearest even
     return __builtin_bit_cast(uint32_t, b);
 }
-__device__ __forceinline__ bf16_t to_bf16(float x) { return (bf16_t)(pack_bf16x2(x, 0.0f) & 0xffffu); }
 
 enum { K_ROWS = 0, K_COLS = 1 };
 
@@ -79,8 +78,11 @@ __device__ __forceinline__ void bare_barrier()
 //   K_COLS   64 rows (k) of 128 m (256 B); vector v of row k in slot v ^ (4 (k mod 4) + 2 ((k / 8) mod 2)).
 //            A ds_read_b64_tr_b16 takes 32 bytes of rows k .. k+3 for each 16 lanes; 32 lanes then cover
 //            the 256-byte bank line once.
-template <int LAYOUT, int NW, int HALVES, int BLOCKS>
+//
+// With HALVES == 2 (the large tile) the copies and reads themselves stand in gemm_loop.hpp; what issues them here serves one half.
+template <int LAYOUT, int NW, int HALVES>
 struct TileOperand {
+    static constexpr int BLOCKS = 4;             // 16-row fragments of a wave
     static constexpr int J = 16 / NW;            // copy instructions per wave and half tile
     static constexpr int NV = HALVES == 2 && LAYOUT == K_ROWS ? 1 : LAYOUT == K_ROWS ? J : HALVES;
     static constexpr int NR = LAYOUT == K_ROWS ? 2 : BLOCKS;
@@ -156,10 +158,11 @@ struct TileOperand {
         }
     }
 
-    // This wave's share of half h of the K tile at the cursor, into stage s; one of its J instructions.
-    __device__ __forceinline__ void copy_part(int j, int h, int s) const
+    // This wave's share of the K tile at the cursor, into stage s; one of its J instructions.
+    __device__ __forceinline__ void copy_part(int j, int s) const
     {
-        bf16_t* dst = lds + (s * HALVES + h) * kHalfElems;
+        static_assert(HALVES == 1, "the large tile's copies are in gemm_loop.hpp");
+        bf16_t* dst = lds + s * kHalfElems;
         if constexpr (LAYOUT == K_ROWS) {
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, (int)extent, kRawBufferFlags);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
@@ -168,13 +171,13 @@ struct TileOperand {
             const __amdgpu_buffer_rsrc_t rs =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src + j * row_step), 0, (int)extent, kRawBufferFlags);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (j * NW + wave) * 512), 16,
-                                                     voff[h], 0, 0, 0);
+                                                     voff[0], 0, 0, 0);
         }
     }
-    __device__ __forceinline__ void copy(int h, int s) const
+    __device__ __forceinline__ void copy(int s) const
     {
 #pragma unroll
-        for (int j = 0; j < J; ++j) copy_part(j, h, s);
+        for (int j = 0; j < J; ++j) copy_part(j, s);
     }
     __device__ __forceinline__ void advance()
     {
@@ -182,13 +185,14 @@ struct TileOperand {
         else src += step;
     }
 
-    // The fragments of half h in stage s: f[ks][b], lane L: row 16 b + L % 16, k = 32 ks + 8 (L / 16) ..+7.
+    // The fragments of stage s: f[ks][b], lane L: row 16 b + L % 16, k = 32 ks + 8 (L / 16) ..+7.
     // K_COLS fragments have arrived on return; K_ROWS ones are waited for by the caller (or their use).
     // The compiler's builtin for the transposing read is taken for a possible LDS write and gets a wait
     // for ALL copies in flight put before it; here the reads are issued and waited for in one block.
-    __device__ __forceinline__ void read(int h, int s, bf16x8 (&f)[2][BLOCKS]) const
+    __device__ __forceinline__ void read(int s, bf16x8 (&f)[2][BLOCKS]) const
     {
-        bf16_t* half = lds + (s * HALVES + h) * kHalfElems;
+        static_assert(HALVES == 1, "the large tile's reads are in gemm_loop.hpp");
+        bf16_t* half = lds + s * kHalfElems;
         if constexpr (LAYOUT == K_ROWS) {
             const char* base = reinterpret_cast<const char*>(half);
 #pragma unroll
@@ -198,10 +202,8 @@ struct TileOperand {
                     f[ks][b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(base + roff[ks] + b * 16 * 128));
         } else {
             const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)half;
-            static_assert(BLOCKS == 2 || BLOCKS == 4, "fragment reads are written out");
             u32x2 r[4 * BLOCKS];          // [ks][block][low / high four k]
-            if constexpr (BLOCKS == 4) {
-                asm volatile(
+            asm volatile(
                 "ds_read_b64_tr_b16 %0, %16\n\t"
                 "ds_read_b64_tr_b16 %1, %16 offset:1024\n\t"
                 "ds_read_b64_tr_b16 %2, %17\n\t"
@@ -218,26 +220,11 @@ struct TileOperand {
                 "ds_read_b64_tr_b16 %13, %18 offset:9216\n\t"
                 "ds_read_b64_tr_b16 %14, %19 offset:8192\n\t"
                 "ds_read_b64_tr_b16 %15, %19 offset:9216\n\t"
-                    "s_waitcnt lgkmcnt(0)"
-                    : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]), 
-              "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(r[12]), "=&v"(r[13]), "=&v"(r[14]), "=&v"(r[15])
-                    : "v"(base + roff[0]), "v"(base + roff[1]), "v"(base + roff[2]), "v"(base + roff[3])
-                    : "memory");
-            } else {
-                asm volatile(
-                "ds_read_b64_tr_b16 %0, %8\n\t"
-                "ds_read_b64_tr_b16 %1, %8 offset:1024\n\t"
-                "ds_read_b64_tr_b16 %2, %9\n\t"
-                "ds_read_b64_tr_b16 %3, %9 offset:1024\n\t"
-                "ds_read_b64_tr_b16 %4, %8 offset:8192\n\t"
-                "ds_read_b64_tr_b16 %5, %8 offset:9216\n\t"
-                "ds_read_b64_tr_b16 %6, %9 offset:8192\n\t"
-                "ds_read_b64_tr_b16 %7, %9 offset:9216\n\t"
-                    "s_waitcnt lgkmcnt(0)"
-                    : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-                    : "v"(base + roff[0]), "v"(base + roff[1])
-                    : "memory");
-            }
+                "s_waitcnt lgkmcnt(0)"
+                : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]),
+                "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(r[12]), "=&v"(r[13]), "=&v"(r[14]), "=&v"(r[15])
+                : "v"(base + roff[0]), "v"(base + roff[1]), "v"(base + roff[2]), "v"(base + roff[3])
+                : "memory");
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -261,7 +248,7 @@ struct ColumnTile {
 // ---------------------------------------------------------------------------------------------
 // Wave (wm, wn) owns the 64-row pieces at rows 128 h + 64 wm, h = 0, 1, and the columns 64 wn ..+63 of half 0 and
 // 16 j1 wn ..+16 j1 - 1 of half 1, where j1 = 1..4 is a quarter of the width of half 1: with B K_ROWS the tile may be 160,
-// 192, 224 or 256 columns wide.  The tiles of a product share its columns evenly, in units of 32 (columns()), so
+// 192, 224 or 256 columns wide, or up to 128 (half 1 is then run as one of 160 and has empty columns only).  The tiles of a product share its columns evenly, in units of 32 (columns()), so
 // that a last tile of a few columns does not cost a whole one: the parts that multiply half 1 leave after j1 of four blocks.
 //
 // begin() issues the first copies, finish() does the rest: a kernel that walks several tiles begins the next one
@@ -274,8 +261,8 @@ struct TileLarge {
     static constexpr int WAVES_M = 2;
     static constexpr size_t LDS_BYTES = 8 * (size_t)kHalfElems * sizeof(bf16_t);
 
-    TileOperand<LA, NW, 2, 4> a;
-    TileOperand<LB, NW, 2, 4> b;
+    TileOperand<LA, NW, 2> a;
+    TileOperand<LB, NW, 2> b;
     f32x4 acc[MI][NJ];
     uint32_t lds_base;
     uint32_t y_shift;         // K_ROWS B: bytes from a half 0 read address to that of half 1
@@ -422,8 +409,8 @@ struct TileSmall {
     static constexpr int WAVES_M = 2;
     static constexpr size_t LDS_BYTES = 4 * (size_t)kHalfElems * sizeof(bf16_t);
 
-    TileOperand<LA, NW, 1, 4> a;
-    TileOperand<LB, NW, 1, 4> b;
+    TileOperand<LA, NW, 1> a;
+    TileOperand<LB, NW, 1> b;
     f32x4 acc[MI][NJ];
     int wave;
 
@@ -448,14 +435,11 @@ struct TileSmall {
     }
     __device__ __forceinline__ void copy_tile(int s)
     {
-        a.copy(0, s);
-        b.copy(0, s);
+        a.copy(s);
+        b.copy(s);
         a.advance();
         b.advance();
     }
-    // Tile k is in stage k & 1.  It is read once this wave's share has landed (the eight copies of tile
-    // k + 1 may be outstanding) and everybody has passed a barrier; after the second barrier every wave
-    // has its fragments in registers and tile k + 2 may overwrite the stage.
     template <int I, int J>
     __device__ __forceinline__ void take(float (&x)[4]) const
     {
@@ -482,6 +466,9 @@ struct TileSmall {
     }
     __device__ __forceinline__ void finish_keep(float (&m)[NJ], float (&S)[NJ], float (&C)[NJ], float (&T)[NJ]) { finish(); }
     __device__ __forceinline__ void finish() { run(*next_a, next_m, *next_b, ColumnTile{next_n, BN}, next_k); }
+    // Tile k is in stage k & 1.  It is read once this wave's share has landed (the eight copies of tile
+    // k + 1 may be outstanding) and everybody has passed a barrier; after the second barrier every wave
+    // has its fragments in registers and tile k + 2 may overwrite the stage.
     __device__ __forceinline__ void run(const Operand& A, int m0, const Operand& B, ColumnTile c, int K)
     {
         clear();
@@ -497,8 +484,8 @@ struct TileSmall {
             else ULORL_WAIT_VMEM(0);
             bare_barrier();
             bf16x8 fa[2][4], fb[2][4];
-            a.read(0, k & 1, fa);
-            b.read(0, k & 1, fb);
+            a.read(k & 1, fa);
+            b.read(k & 1, fb);
             ULORL_WAIT_LDS(0);
             bare_barrier();
             if (k + 2 < KT) copy_tile(k & 1);
