@@ -284,9 +284,10 @@ Lmhead check_lmhead(const Tensor& h, const Tensor& w)
 void lmhead_fwd(const Tensor& h, const Tensor& w, Objective o, int64_t chunk, Fields& f, Segments& seg, int64_t K, const OptTensor& workspace)
 {
     const Lmhead l = check_lmhead(h, w);
-    o.R = o.cu.has_value() ? o.cu->size(0) - 1 : 1;
-    o.check_rows(l.N, l.dev);
     const bool stats_only = !o.advantages.has_value();
+    o.check_rows(l.N, l.dev);
+    if (!stats_only && o.cu.has_value()) o.check_lengths(l.dev);
+    else o.R = o.cu.has_value() ? o.cu->size(0) - 1 : 1;      // a stats-only pass reads none: their number sizes the workspace
     if (stats_only) allocate_rows(f, l.N, l.dev);
     else allocate_objective(f, l.N, o.R, l.dev, true);
     const Tensor ws = workspace_or(workspace, ulorl_lmhead_workspace_bytes(l.N, l.Hd, l.V, (int32_t)o.R, (int32_t)chunk), l.dev);

@@ -205,6 +205,22 @@ def test_walks_of_large_tiles_in_both_calls(group_m):
     run_lmhead_parity(w, params_for(w, gate_mode=ulorl.GATE_NEVER), chunk=8192, launch=ulorl.Launch(gemm_group_m=group_m))
 
 
+def test_lengths_that_a_kernel_cannot_read_are_refused():
+    """As the logits path refuses them; a stats-only pass reads none."""
+    w = ui.shrink(ui.config(5), [20, 13], V=520, hidden=64, seg_len=16, name="lmhead_lengths")
+    d = ui.generate(w, DEV)
+    rest = (d["advantages"], d["old_logp"], params_for(w, gate_mode=ulorl.GATE_NEVER))
+    for cu in (d["cu_seqlens"].cpu(), d["cu_seqlens"].long(), d["cu_seqlens"].repeat_interleave(2)[::2]):
+        for call in (ulorl.lmhead_token_loss_fwd, ulorl.autograd.lmhead_token_loss):
+            with pytest.raises(ValueError, match="cu_seqlens"):
+                call(d["hidden"], d["weight"], d["token_ids"], cu, *rest)
+    with pytest.raises(ulorl.UlorlError):
+        ulorl.lmhead_token_loss_fwd(d["hidden"], d["weight"], d["token_ids"], None, *rest)
+    res = ulorl.lmhead_token_loss_fwd(d["hidden"], d["weight"], d["token_ids"], d["cu_seqlens"].cpu(), None)
+    ref = ulorl.lmhead_token_loss_fwd(d["hidden"], d["weight"], d["token_ids"], None, None)
+    assert torch.equal(res.lse, ref.lse)
+
+
 def test_lmhead_small_ragged_chunks():
     w = ui.shrink(ui.config(5), [120, 83], V=2056, hidden=136, seg_len=32, name="lmhead_small")
     d = ui.generate(w, DEV)
