@@ -57,9 +57,9 @@ PMC = {
 # scaled as above; profiles/lmhead_cfg5_kernel_trace.txt); valid for the lm_head source with this digest and for
 # that workload only.
 PMC_LMHEAD = {
-    "source_sha256": "ab6cbe7a26cea7db2799e29f69e1820846eab0be571cd1c49a31a38fc81578b4",
-    "bwd_bytes": 118549520 * 1024,     # 20 x lmhead_bwd_step_kernel + live rows and their gather, final conversion
-    "fwd_bytes": 60081025 * 1024,      # lmhead_stats_kernel + the small kernels
+    "source_sha256": "b909de1a026704e9600492409677ef176a830ca910410fcc1fb613af7f670dda",
+    "bwd_bytes": 118232695 * 1024,     # 20 x lmhead_bwd_step_kernel + live rows and their gather, final conversion
+    "fwd_bytes": 52962993 * 1024,      # lmhead_stats_kernel + the small kernels
 }
 
 
@@ -323,7 +323,7 @@ def bench_lmhead(args, w, ulorl, ui, torch, dev, as_entry=False):
         e1.record()
         torch.cuda.synchronize()
         dense_ms = e0.elapsed_time(e1) / nd
-    counters_valid = (source_digest("lmhead.hip", "gemm_tile.hpp", "gemm_loop.hpp") == PMC_LMHEAD["source_sha256"] and w.name == "cfg5_lmhead_bf16"
+    counters_valid = (source_digest("lmhead.hip", "lmhead_plan.hpp", "gemm_tile.hpp", "gemm_loop.hpp", "gemm_limits.hpp") == PMC_LMHEAD["source_sha256"] and w.name == "cfg5_lmhead_bf16"
                       and chunk == 8192)
     result = {
         "metric": METRIC,
